@@ -234,7 +234,6 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
         cursor[q] += c->info[i].item_count;
         T.chain_dep_begin = (uint32_t)prev_begin[q];
         T.chain_dep_count = (uint32_t)prev_count[q];
-        T.chain_reserved = 0;
       }
       for (int q = 0; q < c->n_sequences; ++q) {
         if (stage_items[q] > 0) { prev_begin[q] = stage_begin[q]; prev_count[q] = stage_items[q]; }

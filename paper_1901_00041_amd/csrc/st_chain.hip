@@ -91,6 +91,7 @@ __device__ __forceinline__ uint32_t prefetch_filters(ConstOp& T, const st_work_i
   constexpr int kMaxLoads = 12;                       // per thread: 384 KB per workgroup at most
   const int cfg = T.cfg;
   if (cfg >= kNumTileCfgs || cfg == kRowCfg) return 0u;
+  if (T.split_k > 1 && T.k_order == kOrderChannels) return 0u;      // a slice is not one range of the filter rows
   const int NT = kTileShapes[cfg].NT, KB = kTileShapes[cfg].KB;
   const int es = T.in_dtype == ST_DT_F32 ? 4 : 2;
   const int n0 = (int)it.tile_n * NT;

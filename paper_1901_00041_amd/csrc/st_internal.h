@@ -13,8 +13,8 @@ constexpr int kProfSlots = 8;      // 64-bit stamps per work item in a profiled 
 
 // Tile family.  MT = output pixels (rows of the im2col matrix), NT = filters per workgroup tile.
 // The 4 wavefronts form a WPX x WCH grid; MF is the MFMA block edge (32 -> 32x32 blocks,
-// 16 -> 16x16 blocks); KB = bytes of the reduction index staged per row per K step; D = K steps of
-// global loads kept in flight in registers.
+// 16 -> 16x16 blocks); KB = bytes of the reduction index staged per row per K step; D = K steps of operands
+// resident in LDS (as many as fit kSmemBytes; the loads of D - 1 of them are in flight).
 struct TileShape {
   int MT, NT, WPX, WCH, MF, KB, D;
 };
@@ -22,23 +22,23 @@ constexpr int kNumTileCfgs = 7;
 constexpr int kRowCfg = 6;         // the row tile for few-channel layers (conv_tile_rows): 128-pixel segments of
                                    // kRowsPerTile consecutive output rows x 64 filters, one filter row per K step
 constexpr int kChainPoolCfg = 7;   // chain kernel only: TenantDev.cfg of a max-pool op (not a convolution tile shape)
-constexpr int kScalarTapMinItems = 320;   // work items of a launch from which the scalar form of the tap search is used
 constexpr int kRowsPerTile = 4;    // most output rows one row-tile work item may take (the planner picks 1, 2 or 4)
 constexpr TileShape kTileShapes[kNumTileCfgs] = {
     {128, 128, 2, 2, 32, 128, 2},  // 0: wave tile 64x64
-    {128, 64, 2, 2, 32, 128, 2},   // 1: wave tile 64x32
-    {64, 128, 2, 2, 32, 128, 2},   // 2: wave tile 32x64
+    {128, 64, 2, 2, 32, 128, 3},   // 1: wave tile 64x32
+    {64, 128, 2, 2, 32, 128, 3},   // 2: wave tile 32x64
     {64, 64, 2, 2, 32, 128, 4},    // 3: wave tile 32x32
-    {32, 64, 2, 2, 16, 256, 2},    // 4: wave tile 16x32
-    {16, 64, 1, 4, 16, 256, 2},    // 5: wave tile 16x16
+    {32, 64, 2, 2, 16, 256, 3},    // 4: wave tile 16x32
+    {16, 64, 1, 4, 16, 256, 3},    // 5: wave tile 16x16
     {128, 64, 2, 2, 32, 64, 2},    // 6: row tile (few input channels), wave tile 64x32
 };
-constexpr int smem_need(int c) { return 2 * (kTileShapes[c].MT + kTileShapes[c].NT) * (kTileShapes[c].KB + 16); }
 constexpr int kSmemBytes = 73728;  // LDS per workgroup: the largest of the family (checked per tile)
 constexpr int kRowStageBytes = 18432;   // row tile: LDS set aside for the epilogue's transposition buffer
 // tile shapes that also exist as element-wise-gather kernels (channel count not a multiple of the
 // 16-byte vector width); the planner maps such tenants onto one of them
 constexpr bool kGenericCfg[kNumTileCfgs] = {false, true, false, true, false, false, false};
+
+constexpr int kOrderTaps = 0, kOrderChannels = 1, kOrderLinear = 2;   // see conv_tile
 
 // Device-side tenant record, read through scalar loads by every workgroup of that tenant.
 struct TenantDev {
@@ -54,8 +54,10 @@ struct TenantDev {
   int32_t cfg, split_k, k_steps, k_steps_per_split;
   int32_t tiles_m, tiles_n;
   int32_t vec_ok;        // 1: C is a multiple of the 16-byte vector width, gathers use 16-byte loads
-  int32_t tap_uniform;   // 1: each K step lies within one filter tap (C is a multiple of the step) AND the planner
-                         //    wants the tap found with scalar arithmetic (small tiles only; see kScalarTapMinItems)
+  int32_t step_dk, step_dr;   // one K step in the reduction index (r*S + s)*C + c: KT elements = step_dr filter rows of
+                              //    S*C elements and step_dk elements more
+  int32_t k_order;            // kOrder*: how conv_tile walks the reduction index
+  uint32_t tap_rows;          // kOrderChannels: bit r*S for every filter row r
   int32_t shift_c, shift_s;   // floor(n/d) = ((n * magic) >> 31) >> shift, for d = C and d = S
   uint32_t magic_c, magic_s;
   int32_t shift_r, shift_nvp; // same for d = R and d = row_pitch/16 (row tile only)
@@ -66,7 +68,6 @@ struct TenantDev {
   uint32_t y_bytes;           // size of y (and of the residual) in bytes
   int32_t rows_per_tile;      // row tile only: output rows per work item
   int32_t row_pitch;          // row tile only: bytes of one image row in LDS (padding included, multiple of 16)
-  int32_t k_across_waves;     // 1: each wavefront computes the whole tile over a quarter of every K step
   // chain kernel only (st_chain.hip); the per-plan kernel ignores them
   int32_t chain_seq;          // sequence whose completion counter this op's work items wait on and bump
   uint32_t chain_need;        // work items of that sequence that must be complete before this op's may start
@@ -74,7 +75,6 @@ struct TenantDev {
   // chain_flag_base + (tile_m * tiles_n + tile_n) * split_k + slice; the op may start once the flags
   // [chain_dep_begin, chain_dep_begin + chain_dep_count) of the sequence's previous stage all hold the run's number
   uint32_t chain_flag_base, chain_dep_begin, chain_dep_count;
-  uint32_t chain_reserved;
 };
 static_assert(sizeof(TenantDev) % 8 == 0, "TenantDev must keep pointer alignment in arrays");
 

@@ -94,7 +94,6 @@ static const int kSlots = 400;                  // two workgroups resident per c
                                                 // co-resident workgroups share one LDS pipe
 static const double kAloneFactor = 0.77;        // item time of a workgroup that has its compute unit to itself (two that
                                                 // share one each run 20-45 % slower)
-static const int kKAcrossWavesMinSteps = 6;     // shortest K loop for which the 32x64 and 16x64 tiles split K across wavefronts
 static const int kSplitChoices[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 
 struct Option {
@@ -109,6 +108,12 @@ static int row_tile_pitch(const st_conv_desc& d) {
   const int64_t lpad = (int64_t)d.pad * d.C * 2;
   const int64_t pitch = ((lpad + (int64_t)d.W * d.C * 2 + lpad + 15) & ~(int64_t)15) + 64;
   return (int)std::min<int64_t>(pitch, 1 << 24);
+}
+
+// Whether a layer's operands can be fetched as 16-byte vectors: the channel count is a multiple of the vector, and an
+// element position inside a padded image row (conv_tile counts in those) fits 31 bits.
+static bool vector_ok(const st_conv_desc& d) {
+  return d.C % (16 / elem_size(d.in_dtype)) == 0 && ((int64_t)d.W + 2 * (int64_t)d.pad) * d.C < ((int64_t)1 << 31);
 }
 
 // Row tile eligibility (see conv_tile_rows): 16-bit types, 8 <= S*C <= 32, image rows a multiple of 16 bytes,
@@ -454,7 +459,7 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
     std::vector<std::vector<Option>> options(n_tenants);
     for (int t = 0; t < n_tenants; ++t) {
       const st_tenant_info& ti = p->info[t];
-      const bool vec_ok = descs[t].C % (16 / elem_size(descs[t].in_dtype)) == 0;
+      const bool vec_ok = vector_ok(descs[t]);
       options[t] = tenant_options(descs[t], ti.M, ti.Ngemm, ti.Kgemm * elem_size(descs[t].in_dtype), vec_ok, o);
     }
     std::vector<int> pick;
@@ -591,16 +596,14 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       T.in_dtype = d.in_dtype; T.out_dtype = d.out_dtype; T.epilogue = (int32_t)d.epilogue;
       T.cfg = ti.tile_cfg; T.split_k = ti.split_k; T.k_steps = ti.k_steps; T.k_steps_per_split = ti.k_steps_per_split;
       T.tiles_m = ti.tiles_m; T.tiles_n = ti.tiles_n;
-      T.vec_ok = (d.C % (16 / elem_size(d.in_dtype)) == 0) ? 1 : 0;
-      // The filter tap of a K step can be found with scalar arithmetic when C is a multiple of the step.  The small tiles
-      // have that form and a per-lane one (conv_tile, STAP): the scalar form pays when the launch puts two workgroups
-      // on most compute units (configs 2 and 3: 8.8 and 14.4 us against 9.4-9.6 and 15.4-15.5), the per-lane form
-      // when a workgroup is alone on its compute unit (config 1 5.7 -> 5.5 us, the late layers of config 5).
-      T.tap_uniform = (d.C % (kTileShapes[ti.tile_cfg].KB / elem_size(d.in_dtype)) == 0 && fused_total > kScalarTapMinItems) ? 1 : 0;
+      T.vec_ok = vector_ok(d) ? 1 : 0;
+      const int kt = kTileShapes[ti.tile_cfg].KB / elem_size(d.in_dtype);
+      T.step_dr = (int32_t)(kt / ((int64_t)d.S * d.C));
+      T.step_dk = (int32_t)(kt % ((int64_t)d.S * d.C));
+      T.k_order = d.C % kt != 0 || (int64_t)d.R * d.S > 32 ? kOrderTaps : (d.R == 1 && d.S == 1 && d.pad == 0) ? kOrderLinear : kOrderChannels;
+      for (int r = 0; T.k_order == kOrderChannels && r < d.R; ++r) T.tap_rows |= 1u << (r * d.S);
       magic_for(d.C, &T.magic_c, &T.shift_c);
       magic_for(d.S, &T.magic_s, &T.shift_s);
-      // the sum of the four partial tiles costs about as much as the LDS reads saved over a few K steps
-      T.k_across_waves = (T.vec_ok && (ti.tile_cfg == 4 || ti.tile_cfg == 5) && ti.k_steps_per_split >= kKAcrossWavesMinSteps) ? 1 : 0;
       T.row_pitch = row_tile_pitch(d);
       magic_for(T.row_pitch / 16, &T.magic_nvp, &T.shift_nvp);
       magic_for(d.R, &T.magic_r, &T.shift_r);

@@ -429,20 +429,427 @@ _Pragma("unroll")
   }
 }
 
+// ---- split-K hand-off ----------------------------------------------------------------------------
+// Publishes this workgroup's partial tile; the last workgroup to arrive sums all slices in index order into acc and
+// returns true (it goes on to the epilogue), the others return false.
+template <int MT, int NT, int BM, int BN, int MF, class Acc, class TD>
+__device__ __forceinline__ bool split_k_reduce(const TD& T, const st_work_item it, Acc (&acc)[BM][BN], int tid, char* smem, uint64_t* prof) {
+  constexpr int NG = (MF == 32) ? 4 : 1;      // groups of 4 consecutive filters per block per lane
+  {
+    const int tile_id = (int)it.tile_m * T.tiles_n + (int)it.tile_n;
+    constexpr uint32_t kTileBytes = MT * NT * 4;
+    const __amdgpu_buffer_rsrc_t rs =
+        make_rsrc(T.ws + (int64_t)tile_id * T.split_k * (MT * NT), (uint32_t)T.split_k * kTileBytes);
+    const uint32_t my = (uint32_t)it.k_split_idx * kTileBytes;
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+#pragma unroll
+      for (int j = 0; j < BN; ++j)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+          f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs,
+                                                 (((i * BN + j) * NG + g) * kThreads + tid) * 16, my, kAuxDeviceCoherent);
+        }
+    __builtin_amdgcn_s_waitcnt(0);       // every store of this thread has completed (written through)
+    __syncthreads();
+    uint32_t* flag = (uint32_t*)smem;
+    if (tid == 0) {
+      const uint32_t old = __hip_atomic_fetch_add(&T.counters[tile_id], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t last = (old == (uint32_t)(T.split_k - 1));
+      if (last) __hip_atomic_store(&T.counters[tile_id], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next run
+      *flag = last;
+    }
+    __syncthreads();
+    if (*flag == 0u) {
+      if (prof && tid == 0) prof[6] = wall_clock64();
+      return false;
+    }
+    // Sum the slices in index order.  Loads are issued in batches (GB groups x SB slices) so that the
+    // device-coherent reads, each a trip to memory, overlap; slices past split_k read as zero.
+    constexpr int NGRP = BM * BN * NG;
+    constexpr int GB = NGRP < 4 ? NGRP : 4;
+    constexpr int SB = (NGRP > 4) ? 4 : 8;   // at most 32 partial vectors (128 registers) in flight
+    static_assert(NGRP % GB == 0, "group batching");
+    const int split = T.split_k;
+#pragma unroll
+    for (int g0 = 0; g0 < NGRP; g0 += GB) {
+      f32x4 sum[GB];
+#pragma unroll
+      for (int gg = 0; gg < GB; ++gg) sum[gg] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int s0 = 0; s0 < split; s0 += SB) {
+        u32x4 part[SB][GB];
+#pragma unroll
+        for (int ss = 0; ss < SB; ++ss)
+#pragma unroll
+          for (int gg = 0; gg < GB; ++gg) {
+            const uint32_t voff = (s0 + ss < split) ? (uint32_t)(((g0 + gg) * kThreads + tid) * 16) : kInvalidOffset;
+            part[ss][gg] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (s0 + ss) * (int)kTileBytes, kAuxDeviceCoherent);
+          }
+#pragma unroll
+        for (int ss = 0; ss < SB; ++ss)
+#pragma unroll
+          for (int gg = 0; gg < GB; ++gg) sum[gg] += __builtin_bit_cast(f32x4, part[ss][gg]);
+      }
+#pragma unroll
+      for (int gg = 0; gg < GB; ++gg) {
+        constexpr int dummy = 0; (void)dummy;
+        const int grp = g0 + gg;
+        const int i = grp / (BN * NG), j = (grp / NG) % BN, g = grp % NG;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][j][4 * g + e] = sum[gg][e];
+      }
+    }
+  }
+  return true;
+}
+
+// ---- memory to LDS without registers -------------------------------------------------------------
+// One instruction moves 16 bytes per lane from a buffer straight into LDS: lane l's bytes land at lds_base + 16 * l
+// (lds_base is wave-uniform), lanes whose offset is out of range write zeros.  The compiler is not told about the LDS
+// write: whoever reads the data first waits for the vector-memory counter (wait_loads) and for a barrier.
+template <int AUX, int OFF>
+__device__ __forceinline__ void load_to_lds(const u32x4& rsrc, uint32_t voff, uint32_t soff, uint32_t lds_base) {   // to lds_base + OFF
+  static_assert(AUX == 0 || AUX == kAuxDeviceCoherent, "cache policy");
+  if constexpr (AUX == 0)
+    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "i"(OFF) : "memory", "scc");
+  else
+    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen sc1 lds" ::"s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "i"(OFF) : "memory", "scc");
+}
+// Waits until at most N of this wavefront's loads are outstanding and all its LDS reads are done, then for the other
+// wavefronts to get there.
+template <int N>
+__device__ __forceinline__ void wait_loads_barrier() {
+  static_assert(N >= 0 && N < 64, "the vector-memory counter has six bits");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(N) : "memory");
+}
+template <int MAXS, int PER>
+__device__ __forceinline__ void wait_steps_barrier(int steps) {   // all but the `steps` most recent K steps have arrived
+  if constexpr (MAXS <= 0) wait_loads_barrier<0>();
+  else {
+    if (steps >= MAXS) wait_loads_barrier<MAXS * PER>();
+    else wait_steps_barrier<MAXS - 1, PER>(steps);
+  }
+}
+__device__ __forceinline__ u32x4 rsrc_words(const void* base, uint32_t bytes) {
+  const uint64_t a = (uint64_t)(uintptr_t)base;
+  return u32x4{(uint32_t)a, (uint32_t)(a >> 32), bytes, 0x00020000u};
+}
+
 // ---- one workgroup tile --------------------------------------------------------------------------
-// MT x NT output tile, 4 wavefronts as WPX x WCH, MFMA block edge MF, KB bytes of the reduction index
-// staged per row per step, D steps of global loads kept in flight in registers ahead of the LDS
-// double buffer.  All global loads are buffer loads whose out-of-range lanes return zero, so padding,
-// ragged tiles and the end of the K range cost no branches.  GENERIC selects element-wise gathers for
-// tensors whose channel count is not a multiple of the 16-byte vector width (e.g. C = 3).
-// KW ("K across wavefronts"): instead of dividing the tile's pixels and filters among the four wavefronts (each
-// operand row is then read from LDS by WCH resp. WPX of them), every wavefront computes the WHOLE tile over one
-// quarter of each K step (sub-step = wavefront index), so every staged byte is read from LDS exactly once.  After
-// the K loop the four partial tiles are summed through LDS, in wavefront order, into the accumulators the
-// pixel/filter division would have produced, and everything downstream (split-K, epilogue) is unchanged.
-template <int MT, int NT, int WPX, int WCH, int MF, int KB, int D, int DT, bool GENERIC, bool KW = false, class POL = PlainActs,
-          bool STAP = false, class TD>
+// MT x NT output tile, 4 wavefronts as WPX x WCH, MFMA block edge MF, KB bytes of the reduction index staged per row
+// per K step, ST steps of operands resident in LDS.  Operands go from memory to LDS directly (load_to_lds), so no
+// register and no LDS-write instruction is spent on staging; the loads of ST - 1 further steps are in flight while one
+// step's MFMAs run, and the MFMA operands of the next step are read from LDS during them.  A K step is one barrier.
+// Out-of-range lanes load zeros, so padding, ragged tiles and the end of the K range need no branches.
+// LDS rows are KB bytes without padding: 16-byte chunk c of row r sits at position c ^ swz(r), so that the 16 rows an
+// MFMA operand read touches at a time fall into 16 different 16-byte bank groups; the swizzle is applied by choosing
+// which chunk each lane fetches (a lane's LDS position is fixed).
+template <int MT, int NT, int WPX, int WCH, int MF, int KB, int ST, int DT, class POL = PlainActs, class TD>
 __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+  constexpr int ES = ElemOf<DT>::ES;
+  constexpr int VEC = 16 / ES;          // elements per 16-byte vector
+  constexpr int KT = KB / ES;           // elements of K per step
+  constexpr int CH = KB / 16;           // 16-byte chunks per row
+  constexpr int RPI = 64 / CH;          // rows one load instruction of a wavefront covers
+  constexpr int AW = MT / (4 * RPI), BW = NT / (4 * RPI);   // load instructions per wavefront and step
+  constexpr int kStage = (MT + NT) * KB;
+  constexpr int WM = MT / WPX, WN = NT / WCH;
+  constexpr int BM = WM / MF, BN = WN / MF;
+  constexpr int SUBB = (MF == 32) ? 32 : 64;   // row bytes one MFMA sub-step consumes
+  constexpr int NSUB = KB / SUBB;
+  typedef Mma<DT, MF> MMA;
+  typedef typename MMA::Acc Acc;
+  static_assert(WPX * WCH == 4 && WM % MF == 0 && WN % MF == 0, "bad tile shape");
+  static_assert(MT % (4 * RPI) == 0 && NT % (4 * RPI) == 0, "every wavefront stages whole instructions");
+  static_assert(ST >= 2 && ST * kStage <= kSmemBytes, "tile does not fit the LDS allocation");
+  static_assert(KB == 64 || KB == 128 || KB == 256, "swizzles exist for these row lengths");
+  static_assert(MF == 32 || KB >= 128, "the 64-byte swizzle is for 32x32 blocks");
+
+  const int tid = work_thread_id();
+  if (prof && tid == 0) {
+    prof[0] = __builtin_readcyclecounter();
+    prof[4] = wall_clock64();
+    prof[5] = ((uint64_t)__builtin_amdgcn_s_getreg(0x1814) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(0xF804);
+  }
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = (int)it.tile_m * MT;
+  const int n0 = (int)it.tile_n * NT;
+  // everything the K loop needs of the record, read once (the loads to LDS count as writes to any memory)
+  const int C = T.C, W = T.W, WC = W * C, H = T.H, R = T.R, S = T.S, SC = S * C, step_dk = T.step_dk, step_dr = T.step_dr;
+  const u32x4 rx = rsrc_words(T.x, T.x_bytes), rw = rsrc_words(T.w, T.w_bytes);
+
+  // K-step range of this work item
+  const int ks_begin = (int)it.k_split_idx * T.k_steps_per_split;
+  int ks_end = ks_begin + T.k_steps_per_split;
+  if (ks_end > T.k_steps) ks_end = T.k_steps;
+  const int nsteps = ks_end - ks_begin;
+
+  // staging: which row of an instruction's block of RPI rows, and which 16-byte chunk of it, this lane fetches
+  const int lr = lane / CH;
+  const int swz = (KB == 256) ? ((4 * wave + lr) & 15) : (KB == 128) ? ((4 * (wave & 1) + (lr >> 1)) & 7) : ((lr >> 2) & 3);
+  const int chunk = (lane % CH) ^ swz;
+  // per-thread patch rows: first image row and column, and element offset of the patch
+  int a_h0[AW], a_w0[AW], a_base[AW];
+#pragma unroll
+  for (int i = 0; i < AW; ++i) {
+    const int m = m0 + (i * 4 + wave) * RPI + lr;
+    const bool ok = m < T.M;
+    const int mm = ok ? m : 0;
+    const int n = fast_div(mm, T.magic_pq, T.shift_pq);
+    const int pq = mm - n * T.PQ;
+    const int p = fast_div(pq, T.magic_q, T.shift_q);
+    const int q = pq - p * T.Q;
+    const int h0 = p * T.stride - T.pad;
+    a_w0[i] = q * T.stride - T.pad;
+    a_base[i] = (n * H + h0) * WC + a_w0[i] * C;
+    a_h0[i] = ok ? h0 : -(1 << 24);     // a dead row fails every bounds check
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + (uint32_t)wave * 1024u;
+
+  // wavefront / lane geometry of the MFMA operands
+  const int wm0 = (wave % WPX) * WM;
+  const int wn0 = (wave / WPX) * WN;
+  const int lrow = lane & (MF - 1);
+  const int lk = lane / MF;          // 0..1 for 32x32 blocks, 0..3 for 16x16 blocks
+  const int rsw = (KB == 256) ? (lrow & 15) : (KB == 128) ? ((lrow >> 1) & 7) : ((lrow >> 2) & 3);
+  const int rbase = lrow * KB + (lk ^ rsw) * 16;          // sub-step 0; sub-step u is this ^ (u * SUBB)
+  uint32_t a_lds[NSUB], b_lds[NSUB];     // LDS offset of this lane's first pixel and first filter fragment in stage 0, per sub-step
+#pragma unroll
+  for (int u = 0; u < NSUB; ++u) {
+    a_lds[u] = (uint32_t)((rbase ^ (u * SUBB)) + wm0 * KB);
+    b_lds[u] = (uint32_t)((rbase ^ (u * SUBB)) + MT * KB + wn0 * KB);
+  }
+
+  Acc acc[BM][BN];
+#pragma unroll
+  for (int i = 0; i < BM; ++i)
+#pragma unroll
+    for (int j = 0; j < BN; ++j)
+#pragma unroll
+      for (int v = 0; v < (int)(sizeof(Acc) / 4); ++v) acc[i][j][v] = 0.f;
+  struct Frags { u32x4 w[NSUB][BN], x[NSUB][BM]; };
+  auto read_one = [&](auto I, auto stage_off, Frags& f) {     // operand fragment I of the step: per sub-step filters, then pixels
+    constexpr int u = decltype(I)::value / (BN + BM), q = decltype(I)::value % (BN + BM);
+    if constexpr (q < BN) f.w[u][q] = *(const u32x4*)(smem + b_lds[u] + (stage_off + q * MF * KB));
+    else f.x[u][q - BN] = *(const u32x4*)(smem + a_lds[u] + (stage_off + (q - BN) * MF * KB));
+  };
+  auto read_frags = [&](auto stage_off, Frags& f) { static_for<NSUB*(BN + BM)>([&](auto I) { read_one(I, stage_off, f); }); };
+  constexpr int NMMA = NSUB * BM * BN;
+  auto mma_one = [&](auto I, const Frags& f) {
+    constexpr int u = decltype(I)::value / (BM * BN), i = decltype(I)::value / BN % BM, j = decltype(I)::value % BN;
+    acc[i][j] = MMA::run(f.w[u][j], f.x[u][i], acc[i][j]);
+  };
+  auto mma = [&](const Frags& f) { static_for<NMMA>([&](auto I) { mma_one(I, f); }); };
+
+  // The reduction index k = (r*S + s)*C + c is walked in one of three orders (planner's k_order):
+  //   kOrderTaps      ascending k; any C.  Every lane keeps the position of its own vector: filter row kr and element
+  //                   kk = s*C + c inside it, which is also the element offset inside the image row, from the patch.
+  //   kOrderChannels  C a multiple of the step, at most 32 taps: channel blocks outermost, the R*S taps of a block one
+  //                   after another.  Tap and block are uniform, a row's valid taps are bits of one register.
+  //   kOrderLinear    1x1 layers without padding: nothing changes from step to step but the scalar offset.
+  // What bounds a step: 16 clocks of the vector-memory unit per load instruction (a 64x64 step is 256), MFMA time, and,
+  // for a wavefront that has its SIMD to itself, four clocks or so per instruction of any kind.  Hence tap masks, immediate
+  // LDS offsets and as little scalar arithmetic as possible.  Clocks per 64x64 step alone on a compute unit, 3x3 layers:
+  // 634 staged through registers, 608 with loads straight to LDS, 500 with loads, LDS reads and MFMAs taking turns, 350
+  // with masks and immediates, 295 with the MFMAs spread evenly (1x1 layers: 320).  128x128, two workgroups per unit: 1932
+  // -> 1300 (777 -> 1040 TFLOP/s); rows of 64 bytes instead of 128 take 1830, half of every cache line fetched twice.
+  auto k_loop = [&](auto ORDER) {
+    constexpr int order = decltype(ORDER)::value;
+    constexpr uint32_t kTop = 0x80000000u;
+    int kr = 0, kk = 0, koff = 0;          // kOrderTaps: per lane
+    int s_left = 0, r_left = 0;            // kOrderChannels: taps left in this filter row, rows left after it
+    uint32_t a_soff = 0u, b_soff;          // byte offsets of the step; kOrderChannels: a_soff is added per lane (it may be negative)
+    uint32_t va[AW], vb[BW], b_off[BW];    // byte offsets of the next step's vectors
+    uint32_t bad[AW], bad0[AW];            // kOrderChannels: bit 31 - t: tap t of this row lies outside; bad: shifted to the next tap
+    const uint32_t c_bytes = (uint32_t)(C * ES), wrap_row = (uint32_t)((WC - SC) * ES);
+    const uint32_t wrap_a = (uint32_t)(KB - R * WC * ES), wrap_b = (uint32_t)(KB - R * SC * ES);
+    if constexpr (order == kOrderTaps) {
+      const int k = ks_begin * KT + chunk * VEC;
+      kr = fast_div(fast_div(k, T.magic_c, T.shift_c), T.magic_s, T.shift_s);
+      kk = k - kr * SC;
+      koff = kr * WC + kk;
+      b_soff = (uint32_t)(ks_begin * KB);
+    } else {
+      int block = ks_begin, tap = 0, r = 0, sx = 0;
+      if constexpr (order == kOrderChannels) {
+        if (ks_begin != 0) {
+          const int taps = R * S;
+          block = ks_begin / taps;
+          tap = ks_begin - block * taps;
+          r = tap / S;
+          sx = tap - r * S;
+        }
+        s_left = S - 1 - sx;
+        r_left = R - 1 - r;
+      }
+      a_soff = (uint32_t)((r * WC + sx * C) * ES + block * KB);
+      b_soff = (uint32_t)(tap * C * ES + block * KB);
+#pragma unroll
+      for (int i = 0; i < AW; ++i) {
+        a_base[i] = (a_base[i] + chunk * VEC) * ES;
+        if constexpr (order == kOrderLinear) {
+          va[i] = a_h0[i] >= 0 ? (uint32_t)a_base[i] : kInvalidOffset;
+        } else {
+          // filter rows and columns that lie inside: [h_lo, h_hi) and [w_lo, w_hi)
+          const int h_lo = a_h0[i] < 0 ? -a_h0[i] : 0, h_hi = H - a_h0[i] < R ? H - a_h0[i] : R;
+          const int w_lo = a_w0[i] < 0 ? -a_w0[i] : 0, w_hi = W - a_w0[i] < S ? W - a_w0[i] : S;
+          const uint32_t cols = w_hi > w_lo ? ((w_hi < 32 ? (1u << w_hi) : 0u) - (1u << w_lo)) : 0u;
+          const int b_lo = h_lo * S, b_hi = h_hi * S;
+          const uint32_t rows = h_hi > h_lo && h_lo < R ? (((b_hi < 32 ? (1u << b_hi) : 0u) - (1u << b_lo)) & T.tap_rows) : 0u;
+          bad0[i] = ~__builtin_bitreverse32(cols * rows);
+          bad[i] = bad0[i] << tap;
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < BW; ++i) {
+      const int row = n0 + (i * 4 + wave) * RPI + lr;
+      vb[i] = b_off[i] = row < T.K ? (uint32_t)(row * T.Kg + chunk * VEC) * ES : kInvalidOffset;
+    }
+    auto addresses = [&]() {
+      if constexpr (order == kOrderChannels) {
+#pragma unroll
+        for (int i = 0; i < AW; ++i) va[i] = (bad[i] & kTop) | ((uint32_t)a_base[i] + a_soff);
+      } else if constexpr (order == kOrderTaps) {
+        const bool kin = kr < R;        // past the end of the reduction index nothing is loaded
+        const int hr = kin ? kr : (1 << 28);
+        const uint32_t kmask = kin ? 0u : kInvalidOffset;
+#pragma unroll
+        for (int i = 0; i < AW; ++i) {
+          const bool ok = ((unsigned)(a_h0[i] + hr) < (unsigned)H) & ((unsigned)(a_w0[i] * C + kk) < (unsigned)WC);
+          va[i] = ok ? (uint32_t)(a_base[i] + koff) * ES : kInvalidOffset;
+        }
+#pragma unroll
+        for (int i = 0; i < BW; ++i) vb[i] = b_off[i] | kmask;
+      }
+    };
+    addresses();
+    // one step on, after a step's loads were issued
+    auto advance = [&]() {
+      if constexpr (order == kOrderLinear) {
+        a_soff += KB;
+        b_soff += KB;
+      } else if constexpr (order == kOrderChannels) {
+        a_soff += c_bytes;
+        b_soff += c_bytes;
+#pragma unroll
+        for (int i = 0; i < AW; ++i) bad[i] <<= 1;
+        if (__builtin_expect(--s_left < 0, 0)) {
+          s_left = S - 1;
+          a_soff += wrap_row;
+          if (--r_left < 0) {
+            r_left = R - 1;
+            a_soff += wrap_a;
+            b_soff += wrap_b;
+#pragma unroll
+            for (int i = 0; i < AW; ++i) bad[i] = bad0[i];
+          }
+        }
+      } else {
+        const bool wrap = kk + step_dk >= SC;
+        kk += step_dk - (wrap ? SC : 0);
+        kr += step_dr + (wrap ? 1 : 0);
+        koff += step_dr * WC + step_dk + (wrap ? WC - SC : 0);
+        b_soff += KB;
+      }
+      addresses();
+    };
+    auto issue_one = [&](auto I, auto stage_off) {     // load instruction I of the step
+      constexpr int i = decltype(I)::value, off = i < AW ? i * 4096 : MT * KB + (i - AW) * 4096;
+      if constexpr (i < AW) load_to_lds<POL::kActAux, off>(rx, va[i], order == kOrderLinear ? a_soff : 0u, lds0 + (uint32_t)stage_off);
+      else load_to_lds<0, off>(rw, vb[i - AW], b_soff, lds0 + (uint32_t)stage_off);
+    };
+
+    // step s lives in stage s % ST.  The first ST steps go in flight at once.
+    const int in_flight = nsteps < ST ? nsteps : ST;
+    for (int s = 0; s < in_flight; ++s) {
+      static_for<AW + BW>([&](auto I) { issue_one(I, s * kStage); });
+      advance();
+    }
+    wait_steps_barrier<ST - 1, AW + BW>(in_flight - 1);
+    if (prof && tid == 0) prof[1] = __builtin_readcyclecounter();
+    Frags f0, f1;
+    read_frags(0, f0);
+    // One K step: wait until step k + 1 has arrived and everyone has read step k's operands, read step k + 1's operands
+    // and compute step k meanwhile, refill step k's stage with step k + ST.  The vector-memory unit takes 16 clocks
+    // per load instruction (64 bytes per clock) and a wavefront stands still while the unit is busy, so loads, LDS reads
+    // and MFMAs take turns.
+    auto step = [&](const Frags& fc, Frags& fn, auto cur, auto nxt) {
+      wait_loads_barrier<(ST - 2) * (AW + BW)>();
+      constexpr int NL = AW + BW, NR = NSUB * (BN + BM);
+      static_for<NL>([&](auto L) {
+        constexpr int l = decltype(L)::value, b = l * NR / NL, e = (l + 1) * NR / NL, mb = l * NMMA / NL, me = (l + 1) * NMMA / NL;
+        issue_one(L, cur);
+        static_for<e - b>([&](auto I) { read_one(std::integral_constant<int, b + decltype(I)::value>{}, nxt, fn); });
+        static_for<me - mb>([&](auto I) { mma_one(std::integral_constant<int, mb + decltype(I)::value>{}, fc); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      advance();
+    };
+    // the last ST steps of the range (and short ranges): nothing is left to refill
+    auto last_step = [&](const Frags& fc, Frags& fn, int nxt, int left) {     // left = steps after this one
+      if (left > 0) {
+        wait_steps_barrier<ST - 2, AW + BW>(left - 1);
+        read_frags(nxt, fn);
+      }
+      mma(fc);
+    };
+    int k = 0, cur = 0;              // cur: LDS offset of step k's stage
+    auto after = [&](int off) { return off + kStage < ST * kStage ? off + kStage : 0; };
+    constexpr int U = ST % 2 == 0 ? ST : 2 * ST;
+    for (; k + U + ST <= nsteps; k += U)       // whole turns of the stages: their LDS offsets are immediates
+      static_for<U>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        const std::integral_constant<int, j % ST * kStage> c{};
+        const std::integral_constant<int, (j + 1) % ST * kStage> n{};
+        if constexpr (j % 2 == 0) step(f0, f1, c, n);
+        else step(f1, f0, c, n);
+      });
+    for (; k + 1 + ST < nsteps; k += 2) {
+      const int n1 = after(cur), n2 = after(n1);
+      step(f0, f1, cur, n1);
+      step(f1, f0, n1, n2);
+      cur = n2;
+    }
+    if (k + ST < nsteps) {
+      const int n1 = after(cur);
+      step(f0, f1, cur, n1);
+      f0 = f1;
+      cur = n1;
+      ++k;
+    }
+    for (;; k += 2) {
+      const int n1 = after(cur), n2 = after(n1);
+      last_step(f0, f1, n1, nsteps - 1 - k);
+      if (k + 1 >= nsteps) break;
+      last_step(f1, f0, n2, nsteps - 2 - k);
+      if (k + 2 >= nsteps) break;
+      cur = n2;
+    }
+  };
+  switch (T.k_order) {
+    case kOrderLinear: k_loop(std::integral_constant<int, kOrderLinear>{}); break;
+    case kOrderChannels: k_loop(std::integral_constant<int, kOrderChannels>{}); break;
+    default: k_loop(std::integral_constant<int, kOrderTaps>{}); break;
+  }
+
+  if (prof && tid == 0) prof[2] = __builtin_readcyclecounter();
+  if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
+
+  // ---- epilogue: (+ residual) -> ReLU -> cast -> store ---------------------------------------------
+  tile_epilogue<MT, NT, BM, BN, MF, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, prof);
+  if (prof && tid == 0) {
+    prof[3] = __builtin_readcyclecounter();
+    prof[6] = wall_clock64();
+  }
+}
+
+// ---- gather tile for channel counts that are not a multiple of the 16-byte vector -------------------
+// The same implicit GEMM with element-wise gathers (e.g. C = 3), D steps of loads kept in flight in registers ahead of
+// an LDS double buffer with rows padded by 16 bytes.
+template <int MT, int NT, int WPX, int WCH, int MF, int KB, int D, int DT, class POL = PlainActs, class TD>
+__device__ __forceinline__ void conv_tile_gather(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr int ES = ElemOf<DT>::ES;
   constexpr int VEC = 16 / ES;          // elements per 16-byte vector
   constexpr int KT = KB / ES;           // elements of K per step
@@ -459,8 +866,6 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
   typedef typename MMA::Acc Acc;
   static_assert(WPX * WCH == 4 && WM % MF == 0 && WN % MF == 0, "bad tile shape");
   static_assert(2 * (MT + NT) * ROWB <= kSmemBytes, "tile does not fit the LDS allocation");
-  constexpr int TBM = MT / MF, TBN = NT / MF;       // MFMA blocks of the whole tile
-  static_assert(!KW || (NSUB == 4 && 4 * TBM * TBN * (MF * MF / 64) * 4 * 64 <= kSmemBytes), "KW needs four sub-steps per K step and room for four partial tiles");
 
   char* sA = smem;                          // [2][MT][ROWB]  patches
   char* sB = smem + 2 * MT * ROWB;          // [2][NT][ROWB]  filters
@@ -513,85 +918,47 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
 
   // position of the next vector this thread will fetch, in the reduction index k = (r*S + s)*C + c
   int k_elem = ks_begin * KT + chunk * VEC;
-  int k_step0 = ks_begin * KT;   // first element of the step, uniform over the workgroup
 
   u32x4 ra[D][A_IT], rb[D][B_IT];
 
   // Issue the global loads of the next K step into one register slot, then advance the K position.
   auto issue = [&](u32x4 (&qa)[A_IT], u32x4 (&qb)[B_IT]) {
-    if constexpr (!GENERIC) {
-      const bool kin = k_elem < klimit;
-      // filter tap (kr, ksx) and offset of this thread's vector
-      int kr, ksx, koff;
-      if (!STAP || !T.tap_uniform) {
-        // per-lane form.  Without STAP this is the only form and a K step is a single basic block: the compiler then
-        // overlaps the address arithmetic, the loads and the LDS writes with the MFMAs, which is what a workgroup
-        // alone on its compute unit needs (a 128x128 workgroup steps 18 % faster, config 5's late layers 3 %).
-        const int rs = fast_div(k_elem, T.magic_c, T.shift_c);
-        kr = fast_div(rs, T.magic_s, T.shift_s);
-        ksx = rs - kr * S;
-        koff = (kr * W + ksx) * C + (k_elem - rs * C);
-      } else {
-        // C is a multiple of the K step: the whole step lies in one filter tap, found with scalar math.  The small
-        // tiles of a launch that puts two workgroups on most compute units are instantiated with STAP and take this
-        // path (the planner sets tap_uniform for them; the run-time test keeps the step in several basic blocks, and
-        // with a second workgroup to fill the gaps that, with the cheaper arithmetic, is the faster arrangement:
-        // configs 2 and 3 lose 6-8 % with either form as a single block).
-        const int rs = fast_div(k_step0, T.magic_c, T.shift_c);
-        kr = fast_div(rs, T.magic_s, T.shift_s);
-        ksx = rs - kr * S;
-        koff = (kr * W + ksx) * C + (k_step0 - rs * C) + chunk * VEC;
-      }
+    // element-wise gather: every element of the vector has its own (r, s, c)
+    uint32_t ea[A_IT][VEC], eb[B_IT][VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      const int ke = k_elem + e;
+      const bool kin = ke < klimit;
+      const int rs = fast_div(ke, T.magic_c, T.shift_c);
+      const int kc = ke - rs * C;
+      const int kr = fast_div(rs, T.magic_s, T.shift_s);
+      const int ksx = rs - kr * S;
+      const int koff = (kr * W + ksx) * C + kc;
 #pragma unroll
       for (int i = 0; i < A_IT; ++i) {
         const bool ok = kin & ((unsigned)(a_h0[i] + kr) < (unsigned)H) & ((unsigned)(a_w0[i] + ksx) < (unsigned)W);
         const uint32_t off = ok ? (uint32_t)(a_base[i] + koff) * ES : kInvalidOffset;
-        qa[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, POL::kActAux);
+        if constexpr (ES == 4) ea[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, (int)off, 0, POL::kActAux);
+        else ea[i][e] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rx, (int)off, 0, POL::kActAux);
       }
 #pragma unroll
       for (int i = 0; i < B_IT; ++i) {
-        const uint32_t off = (b_ok[i] & kin) ? (uint32_t)(b_off[i] + k_elem) * ES : kInvalidOffset;
-        qb[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)off, 0, 0);
-      }
-    } else {
-      // element-wise gather: every element of the vector has its own (r, s, c)
-      uint32_t ea[A_IT][VEC], eb[B_IT][VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        const int ke = k_elem + e;
-        const bool kin = ke < klimit;
-        const int rs = fast_div(ke, T.magic_c, T.shift_c);
-        const int kc = ke - rs * C;
-        const int kr = fast_div(rs, T.magic_s, T.shift_s);
-        const int ksx = rs - kr * S;
-        const int koff = (kr * W + ksx) * C + kc;
-#pragma unroll
-        for (int i = 0; i < A_IT; ++i) {
-          const bool ok = kin & ((unsigned)(a_h0[i] + kr) < (unsigned)H) & ((unsigned)(a_w0[i] + ksx) < (unsigned)W);
-          const uint32_t off = ok ? (uint32_t)(a_base[i] + koff) * ES : kInvalidOffset;
-          if constexpr (ES == 4) ea[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, (int)off, 0, POL::kActAux);
-          else ea[i][e] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rx, (int)off, 0, POL::kActAux);
-        }
-#pragma unroll
-        for (int i = 0; i < B_IT; ++i) {
-          const uint32_t off = (b_ok[i] & kin) ? (uint32_t)(b_off[i] + ke) * ES : kInvalidOffset;
-          if constexpr (ES == 4) eb[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rw, (int)off, 0, 0);
-          else eb[i][e] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (int)off, 0, 0);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < A_IT; ++i) {
-        if constexpr (ES == 4) qa[i] = u32x4{ea[i][0], ea[i][1], ea[i][2], ea[i][3]};
-        else qa[i] = u32x4{ea[i][0] | (ea[i][1] << 16), ea[i][2] | (ea[i][3] << 16), ea[i][4] | (ea[i][5] << 16), ea[i][6] | (ea[i][7] << 16)};
-      }
-#pragma unroll
-      for (int i = 0; i < B_IT; ++i) {
-        if constexpr (ES == 4) qb[i] = u32x4{eb[i][0], eb[i][1], eb[i][2], eb[i][3]};
-        else qb[i] = u32x4{eb[i][0] | (eb[i][1] << 16), eb[i][2] | (eb[i][3] << 16), eb[i][4] | (eb[i][5] << 16), eb[i][6] | (eb[i][7] << 16)};
+        const uint32_t off = (b_ok[i] & kin) ? (uint32_t)(b_off[i] + ke) * ES : kInvalidOffset;
+        if constexpr (ES == 4) eb[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rw, (int)off, 0, 0);
+        else eb[i][e] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (int)off, 0, 0);
       }
     }
+#pragma unroll
+    for (int i = 0; i < A_IT; ++i) {
+      if constexpr (ES == 4) qa[i] = u32x4{ea[i][0], ea[i][1], ea[i][2], ea[i][3]};
+      else qa[i] = u32x4{ea[i][0] | (ea[i][1] << 16), ea[i][2] | (ea[i][3] << 16), ea[i][4] | (ea[i][5] << 16), ea[i][6] | (ea[i][7] << 16)};
+    }
+#pragma unroll
+    for (int i = 0; i < B_IT; ++i) {
+      if constexpr (ES == 4) qb[i] = u32x4{eb[i][0], eb[i][1], eb[i][2], eb[i][3]};
+      else qb[i] = u32x4{eb[i][0] | (eb[i][1] << 16), eb[i][2] | (eb[i][3] << 16), eb[i][4] | (eb[i][5] << 16), eb[i][6] | (eb[i][7] << 16)};
+    }
     k_elem += KT;
-    k_step0 += KT;
   };
   auto store_lds = [&](const u32x4 (&qa)[A_IT], const u32x4 (&qb)[B_IT], int buf) {
 #pragma unroll
@@ -620,32 +987,8 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
     for (int j = 0; j < BN; ++j)
 #pragma unroll
       for (int v = 0; v < (int)(sizeof(Acc) / 4); ++v) acc[i][j][v] = 0.f;
-  // KW: this wavefront's partial sums of the whole tile
-  Acc part[KW ? TBM : 1][KW ? TBN : 1];
-  if constexpr (KW) {
-#pragma unroll
-    for (int i = 0; i < TBM; ++i)
-#pragma unroll
-      for (int j = 0; j < TBN; ++j)
-#pragma unroll
-        for (int v = 0; v < (int)(sizeof(Acc) / 4); ++v) part[i][j][v] = 0.f;
-  }
 
   auto compute = [&](int buf) {
-    if constexpr (KW) {
-      const char* pa = sA + (buf * MT + lrow) * ROWB + lk * 16 + wave * SUBB;
-      const char* pb = sB + (buf * NT + lrow) * ROWB + lk * 16 + wave * SUBB;
-      u32x4 wf[TBN], xf[TBM];
-#pragma unroll
-      for (int j = 0; j < TBN; ++j) wf[j] = *(const u32x4*)(pb + j * MF * ROWB);
-#pragma unroll
-      for (int i = 0; i < TBM; ++i) xf[i] = *(const u32x4*)(pa + i * MF * ROWB);
-#pragma unroll
-      for (int i = 0; i < TBM; ++i)
-#pragma unroll
-        for (int j = 0; j < TBN; ++j) part[i][j] = MMA::run(wf[j], xf[i], part[i][j]);
-      return;
-    }
     const char* pa = sA + (buf * MT + wm0 + lrow) * ROWB + lk * 16;
     const char* pb = sB + (buf * NT + wn0 + lrow) * ROWB + lk * 16;
 #pragma unroll
@@ -687,107 +1030,9 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
     static_nest<D - 1>(rem, step);
   }
 
-  if constexpr (KW) {
-    // sum the four wavefronts' partial tiles: each writes all its blocks ([wavefront][block][lane], 16-byte
-    // groups), then takes the blocks of its own share of the tile and adds the four copies in wavefront order
-    constexpr int VPB = (int)(sizeof(Acc) / 16);           // 16-byte groups per block per lane
-    f32x4* red = (f32x4*)smem;
-#pragma unroll
-    for (int i = 0; i < TBM; ++i)
-#pragma unroll
-      for (int j = 0; j < TBN; ++j)
-#pragma unroll
-        for (int g = 0; g < VPB; ++g)
-          red[((wave * TBM * TBN + i * TBN + j) * VPB + g) * 64 + lane] =
-              f32x4{part[i][j][4 * g], part[i][j][4 * g + 1], part[i][j][4 * g + 2], part[i][j][4 * g + 3]};
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < BM; ++i)
-#pragma unroll
-      for (int j = 0; j < BN; ++j) {
-        const int bi = wm0 / MF + i, bj = wn0 / MF + j;
-#pragma unroll
-        for (int g = 0; g < VPB; ++g) {
-          f32x4 sum = red[((0 * TBM * TBN + bi * TBN + bj) * VPB + g) * 64 + lane];
-#pragma unroll
-          for (int w = 1; w < 4; ++w) sum += red[((w * TBM * TBN + bi * TBN + bj) * VPB + g) * 64 + lane];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[i][j][4 * g + e] = sum[e];
-        }
-      }
-    __syncthreads();      // the partial tiles are consumed before the epilogue reuses the buffer
-  }
-
   if (prof && tid == 0) prof[2] = __builtin_readcyclecounter();
 
-  // ---- split-K: publish the partial tile; the last workgroup to arrive sums all slices in order --
-  constexpr int NG = (MF == 32) ? 4 : 1;      // groups of 4 consecutive filters per block per lane
-  if (T.split_k > 1) {
-    const int tile_id = (int)it.tile_m * T.tiles_n + (int)it.tile_n;
-    constexpr uint32_t kTileBytes = MT * NT * 4;
-    const __amdgpu_buffer_rsrc_t rs =
-        make_rsrc(T.ws + (int64_t)tile_id * T.split_k * (MT * NT), (uint32_t)T.split_k * kTileBytes);
-    const uint32_t my = (uint32_t)it.k_split_idx * kTileBytes;
-#pragma unroll
-    for (int i = 0; i < BM; ++i)
-#pragma unroll
-      for (int j = 0; j < BN; ++j)
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs,
-                                                 (((i * BN + j) * NG + g) * kThreads + tid) * 16, my, kAuxDeviceCoherent);
-        }
-    __builtin_amdgcn_s_waitcnt(0);       // every store of this thread has completed (written through)
-    __syncthreads();
-    uint32_t* flag = (uint32_t*)smem;
-    if (tid == 0) {
-      const uint32_t old = __hip_atomic_fetch_add(&T.counters[tile_id], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const uint32_t last = (old == (uint32_t)(T.split_k - 1));
-      if (last) __hip_atomic_store(&T.counters[tile_id], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next run
-      *flag = last;
-    }
-    __syncthreads();
-    if (*flag == 0u) {
-      if (prof && tid == 0) prof[6] = wall_clock64();
-      return;
-    }
-    // Sum the slices in index order.  Loads are issued in batches (GB groups x SB slices) so that the
-    // device-coherent reads, each a trip to memory, overlap; slices past split_k read as zero.
-    constexpr int NGRP = BM * BN * NG;
-    constexpr int GB = NGRP < 4 ? NGRP : 4;
-    constexpr int SB = (NGRP > 4) ? 4 : 8;   // at most 32 partial vectors (128 registers) in flight
-    static_assert(NGRP % GB == 0, "group batching");
-    const int split = T.split_k;
-#pragma unroll
-    for (int g0 = 0; g0 < NGRP; g0 += GB) {
-      f32x4 sum[GB];
-#pragma unroll
-      for (int gg = 0; gg < GB; ++gg) sum[gg] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int s0 = 0; s0 < split; s0 += SB) {
-        u32x4 part[SB][GB];
-#pragma unroll
-        for (int ss = 0; ss < SB; ++ss)
-#pragma unroll
-          for (int gg = 0; gg < GB; ++gg) {
-            const uint32_t voff = (s0 + ss < split) ? (uint32_t)(((g0 + gg) * kThreads + tid) * 16) : kInvalidOffset;
-            part[ss][gg] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (s0 + ss) * (int)kTileBytes, kAuxDeviceCoherent);
-          }
-#pragma unroll
-        for (int ss = 0; ss < SB; ++ss)
-#pragma unroll
-          for (int gg = 0; gg < GB; ++gg) sum[gg] += __builtin_bit_cast(f32x4, part[ss][gg]);
-      }
-#pragma unroll
-      for (int gg = 0; gg < GB; ++gg) {
-        constexpr int dummy = 0; (void)dummy;
-        const int grp = g0 + gg;
-        const int i = grp / (BN * NG), j = (grp / NG) % BN, g = grp % NG;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[i][j][4 * g + e] = sum[gg][e];
-      }
-    }
-  }
+  if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
 
   // ---- epilogue: (+ residual) -> ReLU -> cast -> store ---------------------------------------------
   tile_epilogue<MT, NT, BM, BN, MF, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, prof);
@@ -1016,10 +1261,15 @@ __device__ __forceinline__ void conv_tile_rows(const TD& T, const st_work_item i
   }
 }
 
-template <int CFG, int DT, bool GENERIC, bool KW = false, class POL = PlainActs, bool STAP = false, class TD>
+template <int CFG, int DT, class POL = PlainActs, class TD>
 __device__ __forceinline__ void run_cfg(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr TileShape s = kTileShapes[CFG];
-  conv_tile<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, s.D, DT, GENERIC, KW, POL, STAP>(T, it, smem, prof);
+  conv_tile<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, s.D, DT, POL>(T, it, smem, prof);
+}
+template <int CFG, int DT, class POL = PlainActs, class TD>
+__device__ __forceinline__ void run_gather(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+  constexpr TileShape s = kTileShapes[CFG];
+  conv_tile_gather<s.MT, s.NT, s.WPX, s.WCH, s.MF, 128, CFG == 1 ? 2 : 4, DT, POL>(T, it, smem, prof);
 }
 
 // TD is TenantDev, or TenantDev qualified with the constant address space (records that no launch in flight
@@ -1028,34 +1278,12 @@ template <int DT, class POL = PlainActs, class TD>
 __device__ __forceinline__ void run_dtype(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
   if (T.vec_ok) {
     switch (T.cfg) {
-      case 0: run_cfg<0, DT, false, false, POL>(T, it, smem, prof); break;
-      case 1: run_cfg<1, DT, false, false, POL>(T, it, smem, prof); break;
-      case 2: run_cfg<2, DT, false, false, POL>(T, it, smem, prof); break;
-      // the three smallest tiles exist with either form of the tap search (see conv_tile)
-      case 3:
-        if (T.tap_uniform) run_cfg<3, DT, false, false, POL, true>(T, it, smem, prof);
-        else run_cfg<3, DT, false, false, POL>(T, it, smem, prof);
-        break;
-      // the two smallest tiles split each K step across the wavefronts (see KW above) when the planner found
-      // the K loop long enough to repay the final sum of the four partial tiles
-      case 4:
-        if (T.k_across_waves) {
-          if (T.tap_uniform) run_cfg<4, DT, false, true, POL, true>(T, it, smem, prof);
-          else run_cfg<4, DT, false, true, POL>(T, it, smem, prof);
-        } else {
-          if (T.tap_uniform) run_cfg<4, DT, false, false, POL, true>(T, it, smem, prof);
-          else run_cfg<4, DT, false, false, POL>(T, it, smem, prof);
-        }
-        break;
-      default:
-        if (T.k_across_waves) {
-          if (T.tap_uniform) run_cfg<5, DT, false, true, POL, true>(T, it, smem, prof);
-          else run_cfg<5, DT, false, true, POL>(T, it, smem, prof);
-        } else {
-          if (T.tap_uniform) run_cfg<5, DT, false, false, POL, true>(T, it, smem, prof);
-          else run_cfg<5, DT, false, false, POL>(T, it, smem, prof);
-        }
-        break;
+      case 0: run_cfg<0, DT, POL>(T, it, smem, prof); break;
+      case 1: run_cfg<1, DT, POL>(T, it, smem, prof); break;
+      case 2: run_cfg<2, DT, POL>(T, it, smem, prof); break;
+      case 3: run_cfg<3, DT, POL>(T, it, smem, prof); break;
+      case 4: run_cfg<4, DT, POL>(T, it, smem, prof); break;
+      default: run_cfg<5, DT, POL>(T, it, smem, prof); break;
     }
   } else {
     // few-channel layers: the row tile when the planner found it eligible, else element-wise gathers
@@ -1063,8 +1291,8 @@ __device__ __forceinline__ void run_dtype(const TD& T, const st_work_item it, ch
     if constexpr (DT != ST_DT_F32) {
       if (T.cfg == kRowCfg) { conv_tile_rows<DT, POL>(T, it, smem, prof); return; }
     }
-    if (T.cfg == 1) run_cfg<1, DT, true, false, POL>(T, it, smem, prof);
-    else run_cfg<3, DT, true, false, POL>(T, it, smem, prof);
+    if (T.cfg == 1) run_gather<1, DT, POL>(T, it, smem, prof);
+    else run_gather<3, DT, POL>(T, it, smem, prof);
   }
 }
 
