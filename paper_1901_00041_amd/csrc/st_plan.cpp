@@ -148,11 +148,10 @@ static int xcd_block_of(const st_work_item& it, const st_tenant_info& ti) {
   return (int)(bm * ti.xcd_blocks_n + bn);
 }
 
-static void xcd_arrange(st_work_item* items, int64_t n, int phase, const st_tenant_info& ti) {
-  if (ti.xcd_blocks_m * ti.xcd_blocks_n <= 1 || n < 2) return;
-  std::vector<st_work_item> bucket[kNumXCDs];
+// Fills n positions from the XCDs' own lists: position q (XCD (phase + q) mod 8) takes the next item of its XCD, or, when
+// none is left, of the XCD with the most items left (lowest XCD on ties).
+static void deal(const std::vector<st_work_item> (&bucket)[kNumXCDs], st_work_item* out, int64_t n, int phase) {
   size_t head[kNumXCDs] = {};
-  for (int64_t i = 0; i < n; ++i) bucket[xcd_block_of(items[i], ti) % kNumXCDs].push_back(items[i]);
   for (int64_t q = 0; q < n; ++q) {
     int x = (int)((phase + q) % kNumXCDs);
     if (head[x] == bucket[x].size()) {
@@ -160,28 +159,78 @@ static void xcd_arrange(st_work_item* items, int64_t n, int phase, const st_tena
       for (int c = 0; c < kNumXCDs; ++c)
         if (bucket[c].size() - head[c] > best) { best = bucket[c].size() - head[c]; x = c; }
     }
-    items[q] = bucket[x][head[x]++];
+    out[q] = bucket[x][head[x]++];
   }
 }
 
-// The block grid of a tenant: among the grids a x b with a, b in {1, 2, 4, 8}, a * b <= 8, a <= tiles_m, b <= tiles_n,
+static void xcd_arrange(st_work_item* items, int64_t n, int phase, const st_tenant_info& ti) {
+  if (ti.xcd_blocks_m * ti.xcd_blocks_n <= 1 || n < 2) return;
+  std::vector<st_work_item> bucket[kNumXCDs];
+  for (int64_t i = 0; i < n; ++i) bucket[xcd_block_of(items[i], ti) % kNumXCDs].push_back(items[i]);
+  deal(bucket, items, n, phase);
+}
+
+// The block grid of a tenant: among the grids a x b with a, b in {1, 2, 4, 8}, a * b <= blocks, a <= tiles_m, b <= tiles_n,
 // the one with the most blocks, then the fewest bytes fetched over all XCDs (b times the activations plus a times the
 // filters), then the smallest a.
-static void xcd_block_choice(const st_conv_desc& d, st_tenant_info* ti) {
+static void xcd_block_choice(const st_conv_desc& d, const st_tenant_info& ti, int blocks, int* out_a, int* out_b) {
   const int64_t es = elem_size(d.in_dtype);
-  const int64_t w_bytes = ti->Ngemm * ti->Kgemm * es, x_bytes = (int64_t)d.N * d.C * d.H * d.W * es;
+  const int64_t w_bytes = ti.Ngemm * ti.Kgemm * es, x_bytes = (int64_t)d.N * d.C * d.H * d.W * es;
   int best_a = 1, best_b = 1;
   int64_t best_cost = x_bytes + w_bytes;
-  for (int a = 1; a <= kNumXCDs; a *= 2)
-    for (int b = 1; a * b <= kNumXCDs; b *= 2) {
-      if (a > ti->tiles_m || b > ti->tiles_n) continue;
+  for (int a = 1; a <= blocks; a *= 2)
+    for (int b = 1; a * b <= blocks; b *= 2) {
+      if (a > ti.tiles_m || b > ti.tiles_n) continue;
       const int64_t cost = b * x_bytes + a * w_bytes;
       if (a * b > best_a * best_b || (a * b == best_a * best_b && cost < best_cost)) {
         best_a = a; best_b = b; best_cost = cost;
       }
     }
-  ti->xcd_blocks_m = best_a;
-  ti->xcd_blocks_n = best_b;
+  *out_a = best_a;
+  *out_b = best_b;
+}
+
+// Placement of a stretch of the fused list that holds several tenants' items of about the same cost.  Cutting every
+// tenant into 8 blocks would have every XCD fetch some of every tenant (for 120 tenants of 8 tiles each, 157 MB
+// instead of 43 MB, and the fills of the L2s, at about 7 TB/s, then bound the launch); here a tenant is cut into as
+// few blocks as fit an XCD's share of the stretch, and the blocks are dealt to the XCDs, largest first, each to the XCD
+// with the fewest items.  Positions then take their own XCD's items in order; where the shares are uneven, the XCD with
+// the most items left gives one away, as in xcd_arrange.  [begin, end) are the stretch's runs of one tenant's items each.
+struct ItemRun { int tenant; int64_t begin, end; };
+
+static void xcd_arrange_tenants(st_work_item* items, const std::vector<ItemRun>& runs, const std::vector<st_conv_desc>& descs,
+                                const std::vector<st_tenant_info>& info) {
+  const int64_t first = runs.front().begin, total = runs.back().end - first;
+  const int64_t share = (total + kNumXCDs - 1) / kNumXCDs;
+  struct Block { size_t run; int index; int64_t count; };
+  std::vector<Block> blocks;
+  std::vector<int> grid_a(runs.size()), grid_b(runs.size()), block_base(runs.size());
+  auto block_of = [&](size_t r, const st_work_item& it) {
+    const st_tenant_info& ti = info[runs[r].tenant];
+    return (int)((int64_t)it.tile_m * grid_a[r] / ti.tiles_m) * grid_b[r] + (int)((int64_t)it.tile_n * grid_b[r] / ti.tiles_n);
+  };
+  for (size_t r = 0; r < runs.size(); ++r) {
+    int nb = 1;
+    while (nb < kNumXCDs && (runs[r].end - runs[r].begin) > share * nb) nb *= 2;
+    xcd_block_choice(descs[runs[r].tenant], info[runs[r].tenant], nb, &grid_a[r], &grid_b[r]);
+    block_base[r] = (int)blocks.size();
+    for (int g = 0; g < grid_a[r] * grid_b[r]; ++g) blocks.push_back({r, g, 0});
+    for (int64_t i = runs[r].begin; i < runs[r].end; ++i) ++blocks[block_base[r] + block_of(r, items[i])].count;
+  }
+  std::vector<size_t> order(blocks.size());
+  for (size_t i = 0; i < order.size(); ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return blocks[a].count > blocks[b].count; });
+  int64_t load[kNumXCDs] = {};
+  std::vector<int> xcd(blocks.size());
+  for (size_t i : order) {
+    const int x = (int)(std::min_element(load, load + kNumXCDs) - load);
+    xcd[i] = x;
+    load[x] += blocks[i].count;
+  }
+  std::vector<st_work_item> bucket[kNumXCDs];
+  for (size_t r = 0; r < runs.size(); ++r)
+    for (int64_t i = runs[r].begin; i < runs[r].end; ++i) bucket[xcd[block_base[r] + block_of(r, items[i])]].push_back(items[i]);
+  deal(bucket, items + first, total, (int)(first % kNumXCDs));
 }
 
 static Option make_row_option(const st_conv_desc& d, int rows_per_tile) {
@@ -494,7 +543,7 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       ti.k_steps_per_split = op.steps_per_split;
       ti.item_begin = fused_total;
       ti.item_count = (int64_t)ti.tiles_m * ti.tiles_n * op.split;
-      xcd_block_choice(descs[t], &ti);
+      xcd_block_choice(descs[t], ti, kNumXCDs, &ti.xcd_blocks_m, &ti.xcd_blocks_n);
       fused_total += ti.item_count;
     }
     if (fused_total >= ((int64_t)1 << 31)) {
@@ -545,7 +594,7 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
     if (o.order == 0) {
       // All items of a tenant cost the same except those of a shorter last K slice, so sorting the items by cost
       // (stably, from the nested tenant-major order) is sorting at most two runs per tenant.
-      struct Run { int tenant; int which; int64_t cost; };     // which: -1 all items, 0 full slices, 1 the last slice
+      struct Run { int tenant; int which; int64_t cost, count; };     // which: -1 all items, 0 full slices, 1 the last slice
       std::vector<Run> runs;
       runs.reserve((size_t)n_tenants * 2);
       for (int t = 0; t < n_tenants; ++t) {
@@ -553,10 +602,11 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
         const int last_steps = ti.k_steps - (ti.split_k - 1) * ti.k_steps_per_split;
         auto cost = [&](int steps) { return (int64_t)(steps * kStepCost[ti.tile_cfg] + kEpiCost[ti.tile_cfg]); };
         if (ti.split_k == 1 || last_steps == ti.k_steps_per_split) {
-          runs.push_back({t, -1, cost(ti.split_k == 1 ? ti.k_steps : ti.k_steps_per_split)});
+          runs.push_back({t, -1, cost(ti.split_k == 1 ? ti.k_steps : ti.k_steps_per_split), ti.item_count});
         } else {
-          runs.push_back({t, 0, cost(ti.k_steps_per_split)});
-          runs.push_back({t, 1, cost(last_steps)});
+          const int64_t tiles = ti.item_count / ti.split_k;
+          runs.push_back({t, 0, cost(ti.k_steps_per_split), ti.item_count - tiles});
+          runs.push_back({t, 1, cost(last_steps), tiles});
         }
       }
       std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.cost > b.cost; });
@@ -576,12 +626,25 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
               p->items_fused.push_back(it);
             }
       }
-      // within every run of one tenant's items, place the items that read the same operand slice on one XCD
-      for (size_t b = 0; b < p->items_fused.size();) {
-        size_t e = b + 1;
-        while (e < p->items_fused.size() && p->items_fused[e].tenant == p->items_fused[b].tenant) ++e;
-        xcd_arrange(p->items_fused.data() + b, (int64_t)(e - b), (int)(b % kNumXCDs), p->info[p->items_fused[b].tenant]);
-        b = e;
+      // Placement: a stretch of at least 8 runs whose items cost about the same (within a fifth) is shared out tenant by
+      // tenant; otherwise every run is cut into 8 blocks, each kept on one XCD.
+      size_t r0 = 0;
+      int64_t at = 0;
+      while (r0 < runs.size()) {
+        size_t r1 = r0;
+        std::vector<ItemRun> stretch;
+        for (int64_t b = at; r1 < runs.size() && runs[r1].cost * 5 >= runs[r0].cost * 4; ++r1) {
+          stretch.push_back({runs[r1].tenant, b, b + runs[r1].count});
+          b += runs[r1].count;
+        }
+        if (stretch.size() >= (size_t)kNumXCDs) {
+          xcd_arrange_tenants(p->items_fused.data(), stretch, p->descs, p->info);
+        } else {
+          for (const ItemRun& r : stretch)
+            xcd_arrange(p->items_fused.data() + r.begin, r.end - r.begin, (int)(r.begin % kNumXCDs), p->info[r.tenant]);
+        }
+        at = stretch.back().end;
+        r0 = r1;
       }
     }
     // device records
