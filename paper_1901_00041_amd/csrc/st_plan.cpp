@@ -80,20 +80,26 @@ static void magic_for(int d, uint32_t* m, int32_t* L) {
 // ---------------------------------------------------------------------------------------------------
 // Cost of one work item in shader clocks, from in-kernel time stamps on an MI355X (st_conv_run_profiled):
 //   first operands staged | one K step | epilogue | split-K hand-off (write-through, counter, read back).
-// The launch is modelled as list scheduling of the items on kSlots workgroup slots: its duration is about
-// max(longest item, sum of item times / kSlots).  The planner picks, per tenant, the (tile, split) option
-// that minimises that maximum over the whole launch.
-static const double kFirstCost = 3000.0;
-static const double kStepCost[kNumTileCfgs] = {1770.0, 1240.0, 1180.0, 750.0, 1180.0, 890.0, 520.0};
-static const double kEpiCost[kNumTileCfgs] = {5200.0, 3000.0, 3100.0, 2000.0, 1200.0, 1100.0, 2800.0};
+// A workgroup that has its compute unit to itself and two that share one behave differently (the shared step is bound by
+// the compute unit's 64 bytes per clock from the L2, the lone one by latency and instruction issue), and fp32 MFMAs take
+// eight times as long as 16-bit ones, so there are four tables.
+// The launch is modelled as list scheduling of the items on workgroup slots: its duration is about max(longest item, sum
+// of item times / slots).  The planner picks, per tenant, the (tile, split) option that minimises that maximum over
+// the whole launch: once for kSlots slots of shared compute units, once for one workgroup on each.
+struct ItemCosts { double first[kNumTileCfgs], step[kNumTileCfgs], epi[kNumTileCfgs]; };
+// [fp32 operands][alone on the compute unit]
+static const ItemCosts kCosts[2][2] = {
+    {{{4800, 4500, 4500, 3800, 4200, 3250, 3000}, {1250, 740, 740, 430, 650, 560, 520}, {4700, 2500, 2600, 1800, 1400, 1230, 2800}},
+     {{2700, 2500, 2500, 2300, 2600, 2200, 3000}, {820, 470, 470, 305, 450, 375, 520}, {3900, 2070, 2080, 1500, 1240, 1120, 2800}}},
+    {{{5200, 5500, 5500, 4300, 4300, 3250, 0}, {7200, 3600, 3600, 1850, 1850, 1060, 0}, {8000, 4500, 4000, 3000, 1800, 1330, 0}},
+     {{3500, 3000, 3000, 2500, 2700, 2300, 0}, {4350, 2260, 2240, 1200, 1300, 740, 0}, {4300, 2200, 2200, 1670, 1430, 1180, 0}}}};
 static const double kRowStageCost = 6500.0;     // row tile: copying image rows and filters into LDS
-static const double kGenericStepFactor = 2.8;   // element-wise gathers are bound by the texture addresser
-static const double kGenericFirstCost = 19000.0;
-static const double kSplitCost = 5000.0, kSplitPerElem = 1.0, kSplitRoundCost = 2700.0;   // hand-off grows with the tile
-static const int kSlots = 400;                  // two workgroups resident per compute unit (512), derated because
-                                                // co-resident workgroups share one LDS pipe
-static const double kAloneFactor = 0.77;        // item time of a workgroup that has its compute unit to itself (two that
-                                                // share one each run 20-45 % slower)
+static const double kGatherStepCost[kNumTileCfgs] = {0, 3470.0, 0, 2100.0, 0, 0, 0};   // element-wise gathers: bound by the texture addresser
+static const double kGatherFirstCost = 19000.0;
+static const double kSplitCost = 3600.0, kSplitPerElem = 0.6;               // hand-off, grows with the tile
+static const double kSplitRoundCost = 2000.0, kSplitRoundPerElem = 0.25;    // per further batch of slices read back
+static const int kSlots = 400;                  // two workgroups resident per compute unit (512), derated: the launch's
+                                                // tail and the dispatch ramp leave some of them empty
 static const int kSplitChoices[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 
 struct Option {
@@ -233,7 +239,7 @@ static void xcd_arrange_tenants(st_work_item* items, const std::vector<ItemRun>&
   deal(bucket, items + first, total, (int)(first % kNumXCDs));
 }
 
-static Option make_row_option(const st_conv_desc& d, int rows_per_tile) {
+static Option make_row_option(const st_conv_desc& d, int rows_per_tile, bool alone) {
   Option o;
   o.rows_per_tile = rows_per_tile;
   const int P = (d.H + 2 * d.pad - d.R) / d.stride + 1, Q = (d.W + 2 * d.pad - d.S) / d.stride + 1;
@@ -241,12 +247,13 @@ static Option make_row_option(const st_conv_desc& d, int rows_per_tile) {
   o.split = 1;
   o.steps_per_split = d.R;
   o.items = (int64_t)d.N * cdiv(P, rows_per_tile) * cdiv(Q, kTileShapes[kRowCfg].MT) * cdiv(d.K, kTileShapes[kRowCfg].NT);
-  o.item_time = kFirstCost + kRowStageCost + 500.0 * rows_per_tile + rows_per_tile * (d.R * kStepCost[kRowCfg] + kEpiCost[kRowCfg]);
+  const ItemCosts& c = kCosts[0][alone ? 1 : 0];
+  o.item_time = c.first[kRowCfg] + kRowStageCost + 500.0 * rows_per_tile + rows_per_tile * (d.R * c.step[kRowCfg] + c.epi[kRowCfg]);
   o.area = o.item_time * (double)o.items;
   return o;
 }
 
-static Option make_option(int64_t M, int64_t Ng, int64_t kbytes, bool vec_ok, int cfg, int split) {
+static Option make_option(int64_t M, int64_t Ng, int64_t kbytes, bool vec_ok, bool f32, bool alone, int cfg, int split) {
   Option o;
   o.rows_per_tile = 0;
   const int k_steps = cdiv(kbytes, kTileShapes[cfg].KB);
@@ -257,21 +264,22 @@ static Option make_option(int64_t M, int64_t Ng, int64_t kbytes, bool vec_ok, in
   o.split = split;
   o.steps_per_split = per;
   o.items = (int64_t)cdiv(M, kTileShapes[cfg].MT) * cdiv(Ng, kTileShapes[cfg].NT) * split;
-  const double step = kStepCost[cfg] * (vec_ok ? 1.0 : kGenericStepFactor);
-  o.item_time = (vec_ok ? kFirstCost : kGenericFirstCost) + per * step + kEpiCost[cfg] +
-                (split > 1 ? kSplitCost + kSplitPerElem * kTileShapes[cfg].MT * kTileShapes[cfg].NT +
-                                 kSplitRoundCost * ((split - 1) / 8) : 0.0);
+  const ItemCosts& c = kCosts[f32 ? 1 : 0][alone ? 1 : 0];
+  const double elems = (double)kTileShapes[cfg].MT * kTileShapes[cfg].NT;
+  const int batch = elems > 4096 ? 4 : 8;      // slices read back at a time
+  o.item_time = (vec_ok ? c.first[cfg] : kGatherFirstCost) + per * (vec_ok ? c.step[cfg] : kGatherStepCost[cfg]) + c.epi[cfg] +
+                (split > 1 ? kSplitCost + kSplitPerElem * elems + (kSplitRoundCost + kSplitRoundPerElem * elems) * ((split - 1) / batch) : 0.0);
   o.area = o.item_time * (double)o.items;
   return o;
 }
 
-static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int64_t Ng, int64_t kbytes, bool vec_ok,
+static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int64_t Ng, int64_t kbytes, bool vec_ok, bool alone,
                                           const st_plan_opts& o) {
   std::vector<Option> out;
-  const bool row_ok = row_tile_ok(d);
+  const bool row_ok = row_tile_ok(d), f32 = d.in_dtype == ST_DT_F32;
   if (row_ok && (o.tile_cfg == 0 || o.tile_cfg - 1 == kRowCfg) && o.split_k <= 1) {
     for (int rt = 1; rt <= kRowsPerTile; rt *= 2)
-      if (o.rows_per_tile == 0 || o.rows_per_tile == rt) out.push_back(make_row_option(d, rt));
+      if (o.rows_per_tile == 0 || o.rows_per_tile == rt) out.push_back(make_row_option(d, rt, alone));
     if (o.tile_cfg - 1 == kRowCfg) return out;
   }
   for (int c = 0; c < kNumTileCfgs; ++c) {
@@ -284,12 +292,12 @@ static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int6
       if (c != forced) continue;
     }
     if (o.split_k >= 1) {
-      out.push_back(make_option(M, Ng, kbytes, vec_ok, c, o.split_k));
+      out.push_back(make_option(M, Ng, kbytes, vec_ok, f32, alone, c, o.split_k));
       continue;
     }
     int last_split = 0;
     for (int sp : kSplitChoices) {
-      Option op = make_option(M, Ng, kbytes, vec_ok, c, sp);
+      Option op = make_option(M, Ng, kbytes, vec_ok, f32, alone, c, sp);
       if (op.split == last_split) continue;             // clamped to the same factor as before
       if (op.split > 1 && op.steps_per_split < 2) continue;
       last_split = op.split;
@@ -505,23 +513,30 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       p->bytes += ti.bytes;
     }
     // tile shape and split-K per tenant, chosen jointly from the cost model
-    std::vector<std::vector<Option>> options(n_tenants);
-    for (int t = 0; t < n_tenants; ++t) {
-      const st_tenant_info& ti = p->info[t];
-      const bool vec_ok = vector_ok(descs[t]);
-      options[t] = tenant_options(descs[t], ti.M, ti.Ngemm, ti.Kgemm * elem_size(descs[t].in_dtype), vec_ok, o);
-    }
+    auto all_options = [&](bool alone) {
+      std::vector<std::vector<Option>> options(n_tenants);
+      for (int t = 0; t < n_tenants; ++t) {
+        const st_tenant_info& ti = p->info[t];
+        options[t] = tenant_options(descs[t], ti.M, ti.Ngemm, ti.Kgemm * elem_size(descs[t].in_dtype), vector_ok(descs[t]), alone, o);
+      }
+      return options;
+    };
+    std::vector<std::vector<Option>> options = all_options(false);
     std::vector<int> pick;
     choose_all(options, o.target_items > 0 ? o.target_items : kSlots, &pick);
     if (o.target_items == 0) {
-      // A launch of no more work items than compute units puts every workgroup on a compute unit of its own, where
-      // it runs faster than beside a second one (kAloneFactor).  Plan for that too, and take it if the model says
-      // it is the shorter launch (config 3: 224 tiles of 64x64 in 13.3 us against 416 of 32x64 in 14.5).
+      // A launch of no more work items than compute units puts every workgroup on a compute unit of its own.  Plan for
+      // that too, and take it if the model says it is the shorter launch (config 3: 224 tiles of 64x64 instead of 416 of
+      // 32x64).
+      std::vector<std::vector<Option>> lone = all_options(true);
       std::vector<int> alone;
-      choose_all(options, kNumCUs, &alone);
+      choose_all(lone, kNumCUs, &alone);
       int64_t n_alone = 0;
-      for (int t = 0; t < n_tenants; ++t) n_alone += options[t][alone[t]].items;
-      if (n_alone <= kNumCUs && kAloneFactor * modelled(options, alone, kNumCUs) < modelled(options, pick, kSlots)) pick = alone;
+      for (int t = 0; t < n_tenants; ++t) n_alone += lone[t][alone[t]].items;
+      if (n_alone <= kNumCUs && modelled(lone, alone, kNumCUs) < modelled(options, pick, 2 * kNumCUs)) {
+        options.swap(lone);
+        pick = alone;
+      }
     }
     int64_t fused_total = 0;
     for (int t = 0; t < n_tenants; ++t) {
@@ -600,7 +615,9 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       for (int t = 0; t < n_tenants; ++t) {
         const st_tenant_info& ti = p->info[t];
         const int last_steps = ti.k_steps - (ti.split_k - 1) * ti.k_steps_per_split;
-        auto cost = [&](int steps) { return (int64_t)(steps * kStepCost[ti.tile_cfg] + kEpiCost[ti.tile_cfg]); };
+        const ItemCosts& c = kCosts[descs[t].in_dtype == ST_DT_F32 ? 1 : 0][0];
+        const double step = vector_ok(descs[t]) || ti.row_tiled ? c.step[ti.tile_cfg] : kGatherStepCost[ti.tile_cfg];
+        auto cost = [&](int steps) { return (int64_t)(steps * step + c.epi[ti.tile_cfg]) * std::max(1, ti.rows_per_tile); };
         if (ti.split_k == 1 || last_steps == ti.k_steps_per_split) {
           runs.push_back({t, -1, cost(ti.split_k == 1 ? ti.k_steps : ti.k_steps_per_split), ti.item_count});
         } else {
