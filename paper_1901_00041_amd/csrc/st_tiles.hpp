@@ -138,6 +138,23 @@ __device__ __forceinline__ float f16_bits_to_f32(uint16_t b) {
   return (float)__builtin_bit_cast(_Float16, b);
 }
 
+// two fp32 values rounded to nearest even, packed; DT is one of the 16-bit types
+template <int DT>
+__device__ __forceinline__ uint32_t pack16(float a, float b) {
+  if constexpr (DT == ST_DT_BF16) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+  } else {
+    return (uint32_t)f32_to_f16_bits(a) | ((uint32_t)f32_to_f16_bits(b) << 16);
+  }
+}
+template <int DT>
+__device__ __forceinline__ float unpack16(uint32_t pair, int which) {
+  const uint16_t h = (uint16_t)(pair >> (16 * which));
+  if constexpr (DT == ST_DT_BF16) return bf16_bits_to_f32(h);
+  else return f16_bits_to_f32(h);
+}
+
 // ---- cache-coherent partial-tile traffic for split-K -------------------------------------------------
 // Split-K partial tiles travel between workgroups that may sit on different XCDs, whose L2 caches are
 // not coherent with each other.  Instead of fences that write back and invalidate a whole L2, the
@@ -163,6 +180,62 @@ __device__ __forceinline__ int fast_div(int n, uint32_t m, int L) {
 
 constexpr uint32_t kInvalidOffset = 0x80000000u;   // >= num_records of every buffer: the load returns 0
 
+// ---- memory to LDS without registers -------------------------------------------------------------
+// One instruction moves 16 bytes per lane from a buffer straight into LDS: lane l's bytes land at lds_base + 16 * l
+// (lds_base is wave-uniform), lanes whose offset is out of range write zeros.  The compiler is not told about the LDS
+// write: whoever reads the data first waits for the vector-memory counter (wait_loads) and for a barrier.
+template <int AUX, int OFF>
+__device__ __forceinline__ void load_to_lds(const u32x4& rsrc, uint32_t voff, uint32_t soff, uint32_t lds_base) {   // to lds_base + OFF
+  static_assert(AUX == 0 || AUX == kAuxDeviceCoherent, "cache policy");
+  if constexpr (AUX == 0)
+    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "i"(OFF) : "memory", "scc");
+  else
+    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen sc1 lds" ::"s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "i"(OFF) : "memory", "scc");
+}
+// Waits until at most N of this wavefront's loads are outstanding and all its LDS reads are done, then for the other
+// wavefronts to get there.
+template <int N>
+__device__ __forceinline__ void wait_loads_barrier() {
+  static_assert(N >= 0 && N < 64, "the vector-memory counter has six bits");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(N) : "memory");
+}
+template <int MAXS, int PER>
+__device__ __forceinline__ void wait_steps_barrier(int steps) {   // all but the `steps` most recent K steps have arrived
+  if constexpr (MAXS <= 0) wait_loads_barrier<0>();
+  else {
+    if (steps >= MAXS) wait_loads_barrier<MAXS * PER>();
+    else wait_steps_barrier<MAXS - 1, PER>(steps);
+  }
+}
+__device__ __forceinline__ u32x4 rsrc_words(const void* base, uint32_t bytes) {
+  const uint64_t a = (uint64_t)(uintptr_t)base;
+  return u32x4{(uint32_t)a, (uint32_t)(a >> 32), bytes, 0x00020000u};
+}
+
+// LDS copy of a 16-bit residual tile, [pixel][filter] in rows of NT * 2 bytes: 16-byte chunk c of row r sits at position
+// c ^ residual_swizzle(r), which spreads the 8-byte reads of 16 pixels over the banks.
+template <int NT>
+__device__ __forceinline__ int residual_swizzle(int row) {
+  static_assert(NT == 64 || NT == 128, "residual rows of 128 or 256 bytes");
+  return NT == 128 ? (row & 15) : ((row >> 1) & 7);
+}
+// Load instructions per wavefront that stage_residual issues.
+template <int MT, int NT> constexpr int kResidualLoads = (MT * NT * 2 + 4095) / 4096;
+// Puts the residual tile's loads in flight, to LDS offset lds_base (of this wavefront: + 1024 * wave); needs
+// kResidualLoads * 4096 bytes there.
+template <int MT, int NT, class POL, class TD>
+__device__ __forceinline__ void stage_residual(const TD& T, int m0, int n0, int wave, int lane, uint32_t lds_base) {
+  constexpr int CH = NT / 8, RPI = 64 / CH;
+  const u32x4 rr = rsrc_words(T.res, T.y_bytes);
+  static_for<kResidualLoads<MT, NT>>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    const int row = (i * 4 + wave) * RPI + lane / CH;
+    const int ch = n0 + ((lane % CH) ^ residual_swizzle<NT>(row)) * 8;
+    const bool ok = (row < MT) & (m0 + row < T.M) & (ch < T.K);
+    load_to_lds<POL::kActAux, i * 4096>(rr, ok ? ((uint32_t)(m0 + row) * (uint32_t)T.K + (uint32_t)ch) * 2u : kInvalidOffset, 0u, lds_base);
+  });
+}
+
 // ---- epilogue shared by all tile kernels: (+ residual) -> ReLU -> cast -> store ---------------------
 // The transposed output rows are stored write-through (sc1), so they leave the L2 while the kernel still runs
 // instead of waiting in it for the write-back at the end of the kernel, which the next launch on the stream
@@ -171,23 +244,47 @@ constexpr uint32_t kInvalidOffset = 0x80000000u;   // >= num_records of every bu
 // im2col row m0 and first filter n0; rows at or past m_end are not stored.
 // The transposition buffer `smem` holds MT/PASSES pixel rows; with PASSES > 1 the tile is written out in
 // that many slices of consecutive pixel rows.
-template <int MT, int NT, int BM, int BN, int MF, int PASSES = 1, int CAP = kSmemBytes, class POL = PlainActs, class Acc, class TD>
+// DT is the operands' type: 16-bit outputs have the operands' type (out_dtype is fp32 or in_dtype).
+// res_lds >= 0: the tile of a 16-bit residual is on its way to smem + res_lds (stage_residual); else a residual is loaded
+// here, where its latency is in the open (128x128 tile, bf16, alone on its compute unit: 7900 clocks from the last MFMA to
+// the last store with the residual loaded here, 4500 with it staged; without a residual 5700 -> 3400 with packed conversions).
+template <int MT, int NT, int BM, int BN, int MF, int DT, int PASSES = 1, int CAP = kSmemBytes, class POL = PlainActs, class Acc, class TD>
 __device__ __forceinline__ void tile_epilogue(const TD& T, Acc (&acc)[BM][BN], int m0, int m_end, int n0, int wm0,
-                                              int wn0, int lrow, int lk, int tid, char* smem, uint64_t* prof = nullptr) {
+                                              int wn0, int lrow, int lk, int tid, char* smem, uint64_t* prof = nullptr, int res_lds = -1) {
   constexpr int NG = (MF == 32) ? 4 : 1;
   const bool relu = (T.epilogue & ST_EPI_RELU) != 0u;
   const bool has_res = (T.epilogue & ST_EPI_RESIDUAL) != 0u;
   const int Kf = T.K;
   const bool vec4 = (Kf & 3) == 0;
-  if ((Kf & 7) == 0 && T.out_dtype != ST_DT_F32 && !has_res) {
-    // 16-bit output without a residual: ReLU and the rounding are applied to the accumulators, and the
-    // transposition buffer holds the finished 16-bit values, [pixel][filter], the whole tile at once.  Every
-    // lane then moves 16 bytes of one output row from LDS to memory.
+  bool done16 = false;
+  if constexpr (DT != ST_DT_F32) {
+   if ((Kf & 7) == 0 && T.out_dtype != ST_DT_F32 && (!has_res || res_lds >= 0)) {
+    // 16-bit output: the residual (if any, staged in LDS) is added to the accumulators, ReLU and the rounding are applied
+    // to them, and the transposition buffer holds the finished 16-bit values, [pixel][filter], the whole tile at once.
+    // Every lane then moves 16 bytes of one output row from LDS to memory.
+    done16 = true;
     constexpr int PITCHB = NT * 2 + 16;   // bytes per pixel row; the pad spreads the 8-byte writes of 8 pixels over the banks
     static_assert(MT * PITCHB <= CAP, "16-bit output tile does not fit the transposition buffer");
-    const bool isbf = (T.out_dtype == ST_DT_BF16);
     const __amdgpu_buffer_rsrc_t ry = make_rsrc(T.y, T.y_bytes);
-    __syncthreads();                // the buffer (operands, split-K flag, or the previous tile) is no longer read
+    if (has_res) {
+      wait_loads_barrier<0>();
+      const char* rs = smem + res_lds;
+#pragma unroll
+      for (int i = 0; i < BM; ++i)
+#pragma unroll
+        for (int j = 0; j < BN; ++j)
+#pragma unroll
+          for (int g = 0; g < NG; ++g) {
+            const int row = wm0 + i * MF + lrow;
+            const int chl = wn0 + j * MF + ((MF == 32) ? (8 * g + 4 * lk) : (4 * lk));
+            const uint2 r = *(const uint2*)(rs + row * (NT * 2) + (((chl >> 3) ^ residual_swizzle<NT>(row)) << 4) + (chl & 4) * 2);
+            acc[i][j][4 * g + 0] += unpack16<DT>(r.x, 0);
+            acc[i][j][4 * g + 1] += unpack16<DT>(r.x, 1);
+            acc[i][j][4 * g + 2] += unpack16<DT>(r.y, 0);
+            acc[i][j][4 * g + 3] += unpack16<DT>(r.y, 1);
+          }
+    }
+    __syncthreads();                // the buffer (operands, residual, or the previous tile) is no longer read
 #pragma unroll
     for (int i = 0; i < BM; ++i)
 #pragma unroll
@@ -203,10 +300,8 @@ __device__ __forceinline__ void tile_epilogue(const TD& T, Acc (&acc)[BM][BN], i
             if (relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
           }
           uint2 pk;
-          pk.x = isbf ? ((uint32_t)f32_to_bf16_rne(v[0]) | ((uint32_t)f32_to_bf16_rne(v[1]) << 16))
-                      : ((uint32_t)f32_to_f16_bits(v[0]) | ((uint32_t)f32_to_f16_bits(v[1]) << 16));
-          pk.y = isbf ? ((uint32_t)f32_to_bf16_rne(v[2]) | ((uint32_t)f32_to_bf16_rne(v[3]) << 16))
-                      : ((uint32_t)f32_to_f16_bits(v[2]) | ((uint32_t)f32_to_f16_bits(v[3]) << 16));
+          pk.x = pack16<DT>(v[0], v[1]);
+          pk.y = pack16<DT>(v[2], v[3]);
           *(uint2*)(smem + row * PITCHB + chl * 2) = pk;
         }
     __syncthreads();
@@ -223,7 +318,10 @@ __device__ __forceinline__ void tile_epilogue(const TD& T, Acc (&acc)[BM][BN], i
       const u32x4 d = *(const u32x4*)(smem + (row < MT ? row : 0) * PITCHB + cv * 16);
       __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off, 0, kAuxDeviceCoherent);
     }
-  } else if ((Kf & 7) == 0) {
+   }
+  }
+  if (done16) return;
+  if ((Kf & 7) == 0) {
     // Transpose through LDS: accumulators go to an fp32 [pixel][filter] tile, then every lane handles 16
     // bytes of one output row, so residual loads and output stores are whole contiguous rows.
     constexpr int PITCH = NT + 4;   // floats; the pad keeps the 16-byte writes of 16 pixels on distinct banks
@@ -247,7 +345,7 @@ __device__ __forceinline__ void tile_epilogue(const TD& T, Acc (&acc)[BM][BN], i
           const bool ok = (MP * (NT / 4) % kThreads == 0 || v < MP * (NT / 4)) & (m < m_end) & (ch < Kf);
           rpre[u] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)(ok ? ((uint32_t)m * (uint32_t)Kf + (uint32_t)ch) * 4u : kInvalidOffset), 0, POL::kActAux);
         }
-      } else {
+      } else if constexpr (DT != ST_DT_F32) {
 #pragma unroll
         for (int u = 0; u < IT16; ++u) {
           const int v = u * kThreads + tid;
@@ -307,11 +405,10 @@ __device__ __forceinline__ void tile_epilogue(const TD& T, Acc (&acc)[BM][BN], i
           __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a[u]), ry, (int)off[u], 0, kAuxDeviceCoherent);
         }
       }
-    } else {
+    } else if constexpr (DT != ST_DT_F32) {
       constexpr int NV = NT / 8;
       constexpr int IT = (MP * NV + kThreads - 1) / kThreads;
       constexpr int UB = IT < 4 ? IT : 4;
-      const bool isbf = (T.out_dtype == ST_DT_BF16);
 #pragma unroll
       for (int u0 = 0; u0 < IT; u0 += UB) {
         f32x4 lo[UB], hi[UB];
@@ -333,9 +430,8 @@ __device__ __forceinline__ void tile_epilogue(const TD& T, Acc (&acc)[BM][BN], i
             const u32x4 r = kPrefetchRes ? rpre[u0 + u] : __builtin_amdgcn_raw_buffer_load_b128(rr, (int)off[u], 0, POL::kActAux);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const uint16_t h0 = (uint16_t)(r[e >> 1] >> (16 * (e & 1))), h1 = (uint16_t)(r[2 + (e >> 1)] >> (16 * (e & 1)));
-              lo[u][e] += isbf ? bf16_bits_to_f32(h0) : f16_bits_to_f32(h0);
-              hi[u][e] += isbf ? bf16_bits_to_f32(h1) : f16_bits_to_f32(h1);
+              lo[u][e] += unpack16<DT>(r[e >> 1], e & 1);
+              hi[u][e] += unpack16<DT>(r[2 + (e >> 1)], e & 1);
             }
           }
         }
@@ -351,10 +447,8 @@ __device__ __forceinline__ void tile_epilogue(const TD& T, Acc (&acc)[BM][BN], i
           u32x4 pk;
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
-            pk[e] = isbf ? ((uint32_t)f32_to_bf16_rne(lo[u][2 * e]) | ((uint32_t)f32_to_bf16_rne(lo[u][2 * e + 1]) << 16))
-                         : ((uint32_t)f32_to_f16_bits(lo[u][2 * e]) | ((uint32_t)f32_to_f16_bits(lo[u][2 * e + 1]) << 16));
-            pk[2 + e] = isbf ? ((uint32_t)f32_to_bf16_rne(hi[u][2 * e]) | ((uint32_t)f32_to_bf16_rne(hi[u][2 * e + 1]) << 16))
-                             : ((uint32_t)f32_to_f16_bits(hi[u][2 * e]) | ((uint32_t)f32_to_f16_bits(hi[u][2 * e + 1]) << 16));
+            pk[e] = pack16<DT>(lo[u][2 * e], lo[u][2 * e + 1]);
+            pk[2 + e] = pack16<DT>(hi[u][2 * e], hi[u][2 * e + 1]);
           }
           __builtin_amdgcn_raw_buffer_store_b128(pk, ry, (int)off[u], 0, kAuxDeviceCoherent);
         }
@@ -394,9 +488,8 @@ _Pragma("unroll")
 _Pragma("unroll")
               for (int e = 0; e < 4; ++e) if (e < nv) y[e] = v[e];
             }
-          } else {
+          } else if constexpr (DT != ST_DT_F32) {
             uint16_t* y = (uint16_t*)T.y + o;
-            const bool isbf = (T.out_dtype == ST_DT_BF16);
             if (has_res) {
               const uint16_t* rp = (const uint16_t*)T.res + o;
 _Pragma("unroll")
@@ -405,23 +498,20 @@ _Pragma("unroll")
                   uint16_t rb;
                   if constexpr (POL::kActAux == 0) rb = rp[e];
                   else rb = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(make_rsrc(T.res, T.y_bytes), (int)((uint32_t)(o + e) * 2u), 0, POL::kActAux);
-                  v[e] += isbf ? bf16_bits_to_f32(rb) : f16_bits_to_f32(rb);
+                  v[e] += unpack16<DT>(rb, 0);
                 }
             }
             if (relu)
 _Pragma("unroll")
               for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-            uint16_t hbits[4];
-_Pragma("unroll")
-            for (int e = 0; e < 4; ++e) hbits[e] = isbf ? f32_to_bf16_rne(v[e]) : f32_to_f16_bits(v[e]);
+            uint2 pk;
+            pk.x = pack16<DT>(v[0], v[1]);
+            pk.y = pack16<DT>(v[2], v[3]);
             if (vec4) {
-              uint2 pk;
-              pk.x = (uint32_t)hbits[0] | ((uint32_t)hbits[1] << 16);
-              pk.y = (uint32_t)hbits[2] | ((uint32_t)hbits[3] << 16);
               *(uint2*)y = pk;
             } else {
 _Pragma("unroll")
-              for (int e = 0; e < 4; ++e) if (e < nv) y[e] = hbits[e];
+              for (int e = 0; e < 4; ++e) if (e < nv) y[e] = (uint16_t)((e < 2 ? pk.x : pk.y) >> (16 * (e & 1)));
             }
           }
         }
@@ -504,38 +594,6 @@ __device__ __forceinline__ bool split_k_reduce(const TD& T, const st_work_item i
   return true;
 }
 
-// ---- memory to LDS without registers -------------------------------------------------------------
-// One instruction moves 16 bytes per lane from a buffer straight into LDS: lane l's bytes land at lds_base + 16 * l
-// (lds_base is wave-uniform), lanes whose offset is out of range write zeros.  The compiler is not told about the LDS
-// write: whoever reads the data first waits for the vector-memory counter (wait_loads) and for a barrier.
-template <int AUX, int OFF>
-__device__ __forceinline__ void load_to_lds(const u32x4& rsrc, uint32_t voff, uint32_t soff, uint32_t lds_base) {   // to lds_base + OFF
-  static_assert(AUX == 0 || AUX == kAuxDeviceCoherent, "cache policy");
-  if constexpr (AUX == 0)
-    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "i"(OFF) : "memory", "scc");
-  else
-    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen sc1 lds" ::"s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "i"(OFF) : "memory", "scc");
-}
-// Waits until at most N of this wavefront's loads are outstanding and all its LDS reads are done, then for the other
-// wavefronts to get there.
-template <int N>
-__device__ __forceinline__ void wait_loads_barrier() {
-  static_assert(N >= 0 && N < 64, "the vector-memory counter has six bits");
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(N) : "memory");
-}
-template <int MAXS, int PER>
-__device__ __forceinline__ void wait_steps_barrier(int steps) {   // all but the `steps` most recent K steps have arrived
-  if constexpr (MAXS <= 0) wait_loads_barrier<0>();
-  else {
-    if (steps >= MAXS) wait_loads_barrier<MAXS * PER>();
-    else wait_steps_barrier<MAXS - 1, PER>(steps);
-  }
-}
-__device__ __forceinline__ u32x4 rsrc_words(const void* base, uint32_t bytes) {
-  const uint64_t a = (uint64_t)(uintptr_t)base;
-  return u32x4{(uint32_t)a, (uint32_t)(a >> 32), bytes, 0x00020000u};
-}
-
 // ---- one workgroup tile --------------------------------------------------------------------------
 // MT x NT output tile, 4 wavefronts as WPX x WCH, MFMA block edge MF, KB bytes of the reduction index staged per row
 // per K step, ST steps of operands resident in LDS.  Operands go from memory to LDS directly (load_to_lds), so no
@@ -563,6 +621,7 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
   static_assert(WPX * WCH == 4 && WM % MF == 0 && WN % MF == 0, "bad tile shape");
   static_assert(MT % (4 * RPI) == 0 && NT % (4 * RPI) == 0, "every wavefront stages whole instructions");
   static_assert(ST >= 2 && ST * kStage <= kSmemBytes, "tile does not fit the LDS allocation");
+  static_assert(kResidualLoads<MT, NT> * 4096 <= kStage, "a 16-bit residual tile must fit a stage");
   static_assert(KB == 64 || KB == 128 || KB == 256, "swizzles exist for these row lengths");
   static_assert(MF == 32 || KB >= 128, "the 64-byte swizzle is for 32x32 blocks");
 
@@ -642,6 +701,13 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
   };
   auto mma = [&](const Frags& f) { static_for<NMMA>([&](auto I) { mma_one(I, f); }); };
 
+  // A 16-bit residual tile is loaded into the stage of the last step but one as soon as that is free (no later loads
+  // are waited for by count), and added in the epilogue.
+  int res_lds = -1;
+  if constexpr (DT != ST_DT_F32) {
+    if ((T.epilogue & ST_EPI_RESIDUAL) != 0u && T.out_dtype != ST_DT_F32 && (T.K & 7) == 0 && T.split_k == 1)
+      res_lds = (nsteps == 1 ? 1 : (nsteps - 2) % ST) * kStage;
+  }
   // The reduction index k = (r*S + s)*C + c is walked in one of three orders (planner's k_order):
   //   kOrderTaps      ascending k; any C.  Every lane keeps the position of its own vector: filter row kr and element
   //                   kk = s*C + c inside it, which is also the element offset inside the image row, from the patch.
@@ -767,7 +833,12 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
       static_for<AW + BW>([&](auto I) { issue_one(I, s * kStage); });
       advance();
     }
-    wait_steps_barrier<ST - 1, AW + BW>(in_flight - 1);
+    if (res_lds >= 0 && nsteps == 1) {          // a one-step K loop: the residual follows the operands at once
+      stage_residual<MT, NT, POL>(T, m0, n0, wave, lane, lds0 + (uint32_t)res_lds);
+      wait_loads_barrier<kResidualLoads<MT, NT>>();
+    } else {
+      wait_steps_barrier<ST - 1, AW + BW>(in_flight - 1);
+    }
     if (prof && tid == 0) prof[1] = __builtin_readcyclecounter();
     Frags f0, f1;
     read_frags(0, f0);
@@ -791,6 +862,7 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
     auto last_step = [&](const Frags& fc, Frags& fn, int nxt, int left) {     // left = steps after this one
       if (left > 0) {
         wait_steps_barrier<ST - 2, AW + BW>(left - 1);
+        if (left == 1 && res_lds >= 0) stage_residual<MT, NT, POL>(T, m0, n0, wave, lane, lds0 + (uint32_t)res_lds);
         read_frags(nxt, fn);
       }
       mma(fc);
@@ -838,7 +910,7 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
   if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
 
   // ---- epilogue: (+ residual) -> ReLU -> cast -> store ---------------------------------------------
-  tile_epilogue<MT, NT, BM, BN, MF, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, prof);
+  tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, prof, res_lds);
   if (prof && tid == 0) {
     prof[3] = __builtin_readcyclecounter();
     prof[6] = wall_clock64();
@@ -1035,7 +1107,7 @@ __device__ __forceinline__ void conv_tile_gather(const TD& T, const st_work_item
   if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
 
   // ---- epilogue: (+ residual) -> ReLU -> cast -> store ---------------------------------------------
-  tile_epilogue<MT, NT, BM, BN, MF, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, prof);
+  tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, prof);
   if (prof && tid == 0) {
     prof[3] = __builtin_readcyclecounter();
     prof[6] = wall_clock64();
@@ -1253,7 +1325,7 @@ __device__ __forceinline__ void conv_tile_rows(const TD& T, const st_work_item i
     };
     if (nh > 1) k_loop(std::integral_constant<int, 2>{}); else k_loop(std::integral_constant<int, 1>{});
     const int mrow = (n * P + p0 + rt) * Q;
-    tile_epilogue<MT, NT, BM, BN, MF, EPI_PASSES, kStageBytes, POL>(T, acc, mrow + q0, mrow + q_end, n0, wm0, wn0, lrow, lk, tid, smem);
+    tile_epilogue<MT, NT, BM, BN, MF, DT, EPI_PASSES, kStageBytes, POL>(T, acc, mrow + q0, mrow + q_end, n0, wm0, wn0, lrow, lk, tid, smem);
   }
   if (prof && tid == 0) {
     prof[2] = prof[3] = __builtin_readcyclecounter();
