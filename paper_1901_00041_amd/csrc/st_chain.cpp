@@ -29,6 +29,9 @@ struct st_chain {
   // colbegin[.. + j + 1]), the kChainColumns exclusive columns first, then the shared ones
   std::vector<uint32_t> colbegin;
   uint32_t* d_colbegin = nullptr;
+  std::vector<ChainPrefetch> prefetch;       // queues per XCD: XCD x's filters in stage order, [prefetch_begin[x], prefetch_begin[x + 1])
+  uint32_t prefetch_begin[kNumXCDs + 1] = {};
+  ChainPrefetch* d_prefetch = nullptr;
   int workgroups = 0;                        // planned size of the launch
   int launch_workgroups = 0;                 // 0 = workgroups; else a smaller size asked for by the caller
   unsigned run_parity = 0;                   // control block the next run uses
@@ -136,6 +139,9 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
     // completion flags: one per work item; a sequence's items of one stage are contiguous, op after op
     int64_t flag_total = 0;
     std::vector<int64_t> prev_begin((size_t)c->n_sequences, 0), prev_count((size_t)c->n_sequences, 0);
+    // ... and of the stage before that one: what a stage's filters wait for before they are prefetched
+    std::vector<int64_t> prev2_begin((size_t)c->n_sequences, 0), prev2_count((size_t)c->n_sequences, 0);
+    std::vector<ChainPrefetch> ahead[kNumXCDs];
     // split-K workspace of a sequence: the largest need of any of its stages (its stages never overlap in time)
     std::vector<int64_t> seq_ws((size_t)c->n_sequences, 0), seq_ct((size_t)c->n_sequences, 0);
     struct Use { int op; int64_t ws_off, ct_off; };
@@ -234,9 +240,14 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
         cursor[q] += c->info[i].item_count;
         T.chain_dep_begin = (uint32_t)prev_begin[q];
         T.chain_dep_count = (uint32_t)prev_count[q];
+        if (ops[i].kind == ST_OP_CONV)
+          ahead[q % kNumXCDs].push_back({(uint32_t)i, T.chain_flag_base, (uint32_t)prev2_begin[q], (uint32_t)prev2_count[q]});
       }
       for (int q = 0; q < c->n_sequences; ++q) {
-        if (stage_items[q] > 0) { prev_begin[q] = stage_begin[q]; prev_count[q] = stage_items[q]; }
+        if (stage_items[q] > 0) {
+          prev2_begin[q] = prev_begin[q]; prev2_count[q] = prev_count[q];
+          prev_begin[q] = stage_begin[q]; prev_count[q] = stage_items[q];
+        }
         done[q] += stage_items[q];
         seq_ws[q] = std::max(seq_ws[q], stage_ws[q]);
         seq_ct[q] = std::max(seq_ct[q], stage_ct[q]);
@@ -253,10 +264,17 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
         if (c->n_queues > 1) c->colbegin[(size_t)qi] = (uint32_t)c->items.size();
         c->items.insert(c->items.end(), queues[(size_t)qi].begin(), queues[(size_t)qi].end());
       }
-      if (c->n_queues > 1) c->colbegin[(size_t)n_sub] = (uint32_t)c->items.size();
+      if (c->n_queues > 1) {
+        c->colbegin[(size_t)n_sub] = (uint32_t)c->items.size();
+        for (int x = 0; x < kNumXCDs; ++x) {
+          c->prefetch_begin[x] = (uint32_t)c->prefetch.size();
+          c->prefetch.insert(c->prefetch.end(), ahead[x].begin(), ahead[x].end());
+        }
+        c->prefetch_begin[kNumXCDs] = (uint32_t)c->prefetch.size();
+      }
     }
     if (status == ST_OK) {
-      // arena: [op table][queue][control block x2][split-K counters][completion flags][column boundaries][split-K partial tiles]
+      // arena: [op table][queue][control block x2][split-K counters][completion flags][column boundaries][prefetch list][split-K partial tiles]
       auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
       c->ctl_slots = (uint32_t)(kChainCtlSeq + c->n_sequences);
       int64_t ws_total = 0, ct_total = 0;
@@ -272,7 +290,8 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
       const size_t off_ct = off_ctl + up(ctl_words * 4 * 2);
       const size_t off_flags = off_ct + up((size_t)ct_total * 4);
       const size_t off_cols = off_flags + up(c->n_queues > 1 ? c->items.size() * 4 : 0);
-      const size_t off_ws = off_cols + up(c->colbegin.size() * 4);
+      const size_t off_pf = off_cols + up(c->colbegin.size() * 4);
+      const size_t off_ws = off_pf + up(c->prefetch.size() * sizeof(ChainPrefetch));
       const size_t total = off_ws + (size_t)ws_total * 4;
       if (!host_only && n_ops > 0) {
         hipError_t e = hipMalloc((void**)&c->d_arena, total);
@@ -287,6 +306,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
           std::memcpy(host.data(), c->table.data(), (size_t)n_ops * sizeof(TenantDev));
           std::memcpy(host.data() + off_items, c->items.data(), c->items.size() * sizeof(st_work_item));
           if (!c->colbegin.empty()) std::memcpy(host.data() + off_cols, c->colbegin.data(), c->colbegin.size() * 4);
+          if (!c->prefetch.empty()) std::memcpy(host.data() + off_pf, c->prefetch.data(), c->prefetch.size() * sizeof(ChainPrefetch));
           e = hipMemcpy(c->d_arena, host.data(), off_ws, hipMemcpyHostToDevice);
           if (e != hipSuccess) status = hip_fail(e, "hipMemcpy (chain tables)");
           c->d_ops = (TenantDev*)c->d_arena;
@@ -299,6 +319,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
             c->d_item_flags = (uint32_t*)(c->d_arena + off_flags);
             c->item_flags_bytes = c->items.size() * 4;
             c->d_colbegin = (uint32_t*)(c->d_arena + off_cols);
+            c->d_prefetch = (ChainPrefetch*)(c->d_arena + off_pf);
           }
         }
       }
@@ -328,7 +349,7 @@ static st_status chain_launch(st_chain* c, void* stream, uint64_t* prof_dev) {
     if (c->d_item_flags) ST_HIP((hipError_t)launch_zero(c->d_item_flags, (int64_t)((c->item_flags_bytes + 15) & ~(size_t)15), stream));
     c->run_number = 1u;
   }
-  ST_HIP((hipError_t)launch_chain(c->d_ops, c->d_items, (uint32_t)c->items.size(), c->d_colbegin, (uint32_t)c->n_queues, c->d_ctl[p],
+  ST_HIP((hipError_t)launch_chain(c->d_ops, c->d_items, (uint32_t)c->items.size(), c->d_colbegin, (uint32_t)c->n_queues, c->d_prefetch, c->prefetch_begin, c->d_ctl[p],
                                   c->d_ctl[p ^ 1u], c->ctl_slots, c->d_item_flags, c->run_number, c->spin_limit_ticks, c->flags,
                                   c->launch_workgroups > 0 ? c->launch_workgroups : c->workgroups, stream, prof_dev));
   c->run_parity = p ^ 1u;

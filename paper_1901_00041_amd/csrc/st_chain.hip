@@ -44,11 +44,12 @@ struct ChainArgs {
   uint32_t flags;         // kChainFlag*
   uint32_t n_queues;      // 1: one queue for the whole chip, entries claimed one by one; kNumXCDs: columns (see st_chain_kernel)
   uint32_t q_end;         // one queue: it is items[0 .. q_end)
+  const ChainPrefetch* prefetch;      // columns: XCD x's filters in stage order are prefetch[prefetch_begin[x] .. prefetch_begin[x + 1])
+  uint32_t prefetch_begin[kNumXCDs + 1];
   const uint32_t* colbegin;   // columns: column j of XCD x is items[colbegin[x * 2 * kChainColumns + j] .. colbegin[.. + j + 1])
 };
 
-constexpr int kChainGraceLooks = 24;             // looks at a dependency (0.3 us each) before the filter touches are issued
-                                                 // (per pass of the 8 x 53-layer chain: 6 looks 459 us, 12: 456, 24 and 48: 454, never touching: 456)
+constexpr int kChainGraceLooks = 24;             // looks at a dependency (0.3 us each) before the abort flag and the clock are looked at
 constexpr uint32_t kChainMaxPolls = 1u << 22;   // a poll takes a microsecond or so: seconds, far beyond any real wait
 
 // The op table and the queue never change while a launch runs: they are read through the constant address space, so
@@ -57,6 +58,7 @@ constexpr uint32_t kChainMaxPolls = 1u << 22;   // a poll takes a microsecond or
 // re-loads of the op record.)
 typedef __attribute__((address_space(4))) const st_work_item ConstItem;
 typedef __attribute__((address_space(4))) const TenantDev ConstOp;
+typedef __attribute__((address_space(4))) const ChainPrefetch ConstPrefetch;
 
 template <int DT>
 __device__ __forceinline__ void pool_item(ConstOp& T, const st_work_item it) {
@@ -83,36 +85,54 @@ __device__ __forceinline__ void chain_item(ConstOp& T, const st_work_item it, ch
   }
 }
 
-// While a work item waits for its sequence's previous stage, its filter slab is pulled towards the compute unit: the
-// filters do not depend on any earlier layer, they are read from memory exactly once per pass, and a cold first touch
-// from HBM is the longest single latency of a small item.  One 4-byte load per 128-byte line of the rows
-// [n0, n0 + NT) x this item's K range; nothing waits for the loads here (the value is consumed after the wait).
-__device__ __forceinline__ uint32_t prefetch_filters(ConstOp& T, const st_work_item it, int tid) {
-  constexpr int kMaxLoads = 12;                       // per thread: 384 KB per workgroup at most
-  const int cfg = T.cfg;
-  if (cfg >= kNumTileCfgs || cfg == kRowCfg) return 0u;
-  if (T.split_k > 1 && T.k_order == kOrderChannels) return 0u;      // a slice is not one range of the filter rows
-  const int NT = kTileShapes[cfg].NT, KB = kTileShapes[cfg].KB;
-  const int es = T.in_dtype == ST_DT_F32 ? 4 : 2;
-  const int n0 = (int)it.tile_n * NT;
-  const int rows = (T.K - n0 < NT) ? (T.K - n0) : NT;
-  const int row_bytes = T.Kg * es;
-  int kb0 = (int)it.k_split_idx * T.k_steps_per_split * KB;
-  int kb1 = kb0 + T.k_steps_per_split * KB;
-  if (kb1 > row_bytes) kb1 = row_bytes;
-  if (rows <= 0 || kb1 <= kb0) return 0u;
-  const int lines_per_row = (kb1 - kb0 + 127) >> 7;
-  const int total = rows * lines_per_row;
+// Filters are read from memory exactly once per pass (376 MB for eight 53-layer networks: more than the memory-side cache
+// holds) and do not depend on any earlier layer, and a small stage's tiles wait for them more than for anything else.  So
+// workgroups that wait with nothing to do pull a stage's filters into their XCD's L2 while the stage before it runs: each
+// of the kChainColumns workgroups with a shared column touches its share of the 128-byte lines of w.  The touches are
+// spread out on purpose, one line per lane and round trip: in one burst they delay the running stage's own loads.
+// Eight networks of batch 1, us per pass: no prefetch 411, 256 threads with four lines each in flight 394, with one line
+// 388, 128 threads 378, 64 threads 380; batch 8: 1333, 1255, 1249, 1246, 1273.
+__device__ __forceinline__ void prefetch_filters(ConstOp& T, uint32_t rank, int tid) {
+  constexpr uint32_t kLanes = 128u;
+  if ((uint32_t)tid >= kLanes) return;
   const __amdgpu_buffer_rsrc_t rw = make_rsrc(T.w, T.w_bytes);
-  uint32_t acc = 0u;
-#pragma unroll
-  for (int u = 0; u < kMaxLoads; ++u) {
-    const int l = u * kThreads + tid;
-    const int r = l / lines_per_row, c = l - r * lines_per_row;
-    const uint32_t off = (l < total) ? (uint32_t)((n0 + r) * row_bytes + kb0 + (c << 7)) : kInvalidOffset;
-    acc |= (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rw, (int)off, 0, 0);
+  const uint32_t w_bytes = T.w_bytes;
+  for (uint32_t off = (rank * kLanes + (uint32_t)tid) * 128u; off < w_bytes; off += (uint32_t)kChainColumns * kLanes * 128u) {
+    const uint32_t v = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rw, (int)off, 0, 0);
+    asm volatile("" ::"v"(v));
   }
-  return acc;
+}
+
+// Whether flags [c0, n) all hold the run's number (one wavefront, uniform); c0 moves past those found set.  64 flags at a
+// time, or 256 while that many are left.
+__device__ __forceinline__ bool flags_set(const uint32_t* f, uint32_t n, uint32_t run, uint32_t lane, uint32_t& c0) {
+  while (c0 + 64u < n) {
+    constexpr int G = 4;
+    uint32_t v[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const uint32_t c = c0 + 64u * g + lane;
+      v[g] = __hip_atomic_load(f + (c < n ? c : n - 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (__builtin_amdgcn_ballot_w64(v[g] != run) != 0ull) return false;
+      c0 += 64u;
+    }
+  }
+  if (c0 < n) {
+    const uint32_t c = c0 + lane;
+    const bool unset = (c < n) && __hip_atomic_load(f + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != run;
+    if (__builtin_amdgcn_ballot_w64(unset) != 0ull) return false;
+    c0 = n;
+  }
+  return true;
+}
+
+// Whether the stage before prefetch entry pf's has started, i.e. the stage before that one is complete.
+__device__ __forceinline__ bool prefetch_due(const ChainArgs& a, uint32_t pf, uint32_t lane, uint32_t& c0) {
+  ConstPrefetch& p = ((ConstPrefetch*)a.prefetch)[pf];
+  return flags_set(a.item_flags + p.gate_begin, p.gate_count, a.run_number, lane, c0);
 }
 
 // Next position of queue q for this workgroup (thread 0 only); past the end once the pass has been abandoned.
@@ -147,6 +167,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
   // the entries of this workgroup: [qb, qe) of the work list; one queue: claimed one by one from all of it
   const bool claiming = a.n_queues == 1u;
   uint32_t qb = 0u, qe = a.q_end;
+  uint32_t pf = 0u, pf_end = 0u, rank = 0u;     // filters still to prefetch (shared columns only), and this workgroup's share
   if (!claiming) {
     const uint32_t xcc = (uint32_t)__builtin_amdgcn_s_getreg(0x1814) & 15u;       // XCC_ID
     if (xcc >= a.n_queues) {
@@ -170,8 +191,16 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
     const __attribute__((address_space(4))) uint32_t* cb = (const __attribute__((address_space(4))) uint32_t*)(a.colbegin + col);
     qb = cb[0];
     qe = cb[1];
+    const uint32_t in_xcd = col - xcc * 2u * kChainColumns;
+    if (in_xcd >= (uint32_t)kChainColumns) {
+      rank = in_xcd - (uint32_t)kChainColumns;
+      pf = a.prefetch_begin[xcc];
+      pf_end = a.prefetch_begin[xcc + 1u];
+    }
   }
   uint32_t n_done = 0u;
+  bool gave_up = false;
+  uint32_t seen_key = 0xffffffffu, seen_need = 0u;      // the dependency this workgroup last saw complete
   {
     uint32_t next = 0xffffffffu;            // one queue, thread 0: the entry claimed ahead
     if (claiming && tid == 0) next = chain_claim(a, 0u, qb, qe);
@@ -196,68 +225,62 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
       // one word of every 64-byte line of the op record, requested before the dependency wait and used after it, so
       // that the record sits in the scalar cache when the tile code reads its fields
       const uint32_t rec_touch = (uint32_t)(uintptr_t)T.x ^ (uint32_t)T.R ^ (uint32_t)T.tiles_m ^ T.x_bytes ^ T.chain_flag_base;
-      if (T.chain_need != 0u) {
+      // A workgroup's further entries of a stage need not look again: one look at the flags of a stage of hundreds of items
+      // is microseconds.
+      const bool by_flags = (a.flags & kChainFlagLocalFlags) != 0u;
+      const uint32_t key = by_flags ? T.chain_dep_begin : (uint32_t)T.chain_seq;
+      if (T.chain_need != 0u && !(key == seen_key && T.chain_need <= seen_need)) {
         // Wavefront 0 looks at the dependency: with flags, at those of the sequence's previous stage, 64 at a time from
         // the first that was not yet set (they were stored by workgroups of this XCD and sit, newer than memory, in
         // its L2, where a device-scope load finds them; such a load never stops at the vector cache); with a
         // counter, at the sequence's count of finished entries (bumped by device-scope atomics, carried out at the
         // memory side; a workgroup-scope load would stop at the vector cache and never see it move).
-        const bool by_flags = (a.flags & kChainFlagLocalFlags) != 0u;
         const uint32_t* f = a.item_flags + T.chain_dep_begin;
         const uint32_t n = T.chain_dep_count, run = a.run_number, need = T.chain_need;
         const uint32_t* ctr = a.ctl + (kChainCtlSeq + T.chain_seq) * kChainCtlStride;
         uint32_t c0 = 0u;                     // flags before c0 are known to be set
         auto satisfied = [&]() -> bool {      // wavefront 0 only, uniform
           if (!by_flags) return (int32_t)(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - need) >= 0;
-          while (c0 < n) {
-            const uint32_t c = c0 + (uint32_t)tid;
-            const bool unset = (c < n) && __hip_atomic_load(f + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != run;
-            if (__builtin_amdgcn_ballot_w64(unset) != 0ull) return false;
-            c0 += 64u;
-          }
-          return true;
+          return flags_set(f, n, run, (uint32_t)tid, c0);
         };
-        // first looks: an entry whose dependency is complete, or completes within a couple of microseconds (the
-        // workgroups of a stage finish within about one of each other), starts at once
-        if (tid < 64) {
-          bool ready = satisfied();
-          for (int g = 0; g < kChainGraceLooks && !ready; ++g) {
-            __builtin_amdgcn_s_sleep(2);
-            ready = satisfied();
-          }
-          if (tid == 0) s_msg[1] = ready ? 1u : 2u;
-        }
-        __syncthreads();
-        const uint32_t first = s_msg[1];
-        if (first == 2u) {
-          __syncthreads();                    // s_msg[1] has been read by everyone
-          // a longer wait: pull the filter slab closer meanwhile (the touches must have returned before the entry
-          // starts, which is why an entry that is about to become ready does not issue them)
-          const uint32_t touched = prefetch_filters(T, it, tid);
+        // Wait.  In between, filters of coming stages may be due (pf): wavefront 0 says what happens next, 1 = the entry
+        // starts, 2 = prefetch, 0 = the pass is abandoned.
+        const uint64_t t0 = wall_clock64();
+        uint32_t polls = 0u, p0 = 0u, msg;
+        do {
           if (tid < 64) {
-            const uint64_t t0 = wall_clock64();
-            uint32_t ok = 1u, polls = 0u;
+            msg = 1u;
             while (!satisfied()) {
-              // the abort flag and the clock are looked at on every 16th poll (every few microseconds)
-              if ((++polls & 15u) != 0u) { __builtin_amdgcn_s_sleep(2); continue; }
-              if (__hip_atomic_load(&a.ctl[kChainCtlAbort * kChainCtlStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) { ok = 0u; break; }
+              if (pf < pf_end && prefetch_due(a, pf, (uint32_t)tid, p0)) { msg = 2u; break; }
+              // the abort flag and the clock are looked at on every 16th poll (every few microseconds) after the first looks
+              if ((++polls & 15u) != 0u || polls <= (uint32_t)kChainGraceLooks) { __builtin_amdgcn_s_sleep(2); continue; }
+              if (__hip_atomic_load(&a.ctl[kChainCtlAbort * kChainCtlStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) { msg = 0u; break; }
               if (wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls) {
                 if (tid == 0) __hip_atomic_store(&a.ctl[kChainCtlAbort * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ok = 0u;
+                msg = 0u;
                 break;
               }
               __builtin_amdgcn_s_sleep(2);
             }
-            waited = wall_clock64() - t0;
-            if (tid == 0) s_msg[1] = ok;
+            if (tid == 0) s_msg[1] = msg;
           }
-          // No cache is invalidated here: everything an entry reads that this launch wrote (activations, residuals,
-          // split-K partial tiles) is read with device-scope loads, and everything else did not change.
           __syncthreads();
-          asm volatile("" ::"v"(touched));      // the prefetch loads are complete (and not optimised away)
-          if (s_msg[1] == 0u) break;
-        }
+          msg = __builtin_amdgcn_readfirstlane(s_msg[1]);
+          if (msg == 2u) {
+            __syncthreads();                  // s_msg[1] has been read by everyone
+            prefetch_filters(*(ConstOp*)(a.ops + ((ConstPrefetch*)a.prefetch)[pf].op), rank, tid);
+            ++pf;
+            p0 = 0u;
+          }
+        } while (msg == 2u);
+        waited = wall_clock64() - t0;
+        // No cache is invalidated here: everything an entry reads that this launch wrote (activations, residuals,
+        // split-K partial tiles) is read with device-scope loads, and everything else did not change.
+        if (msg == 0u) { gave_up = true; break; }
+        seen_key = key;
+        seen_need = T.chain_need;
       }
+      while (pf < pf_end && ((ConstPrefetch*)a.prefetch)[pf].flag_base <= T.chain_flag_base) ++pf;      // too late to prefetch these
       asm volatile("" ::"s"(rec_touch));
       if (T.cfg == kChainPoolCfg && prof && tid == 0) prof[4] = wall_clock64();
       chain_item(T, it, smem, prof);
@@ -285,6 +308,29 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
       }
     }
   }
+  // a shared column is often done long before the pass is: go on prefetching
+  if (pf < pf_end && !gave_up) {
+    const uint64_t t0 = wall_clock64();
+    uint32_t polls = 0u;
+    while (pf < pf_end) {
+      if (tid < 64) {
+        uint32_t p0 = 0u, msg = 2u;
+        while (!prefetch_due(a, pf, (uint32_t)tid, p0)) {
+          __builtin_amdgcn_s_sleep(8);
+          if ((++polls & 15u) != 0u) continue;
+          if (wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls ||
+              __hip_atomic_load(&a.ctl[kChainCtlAbort * kChainCtlStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) { msg = 0u; break; }
+        }
+        if (tid == 0) s_msg[1] = msg;
+      }
+      __syncthreads();
+      const uint32_t msg = __builtin_amdgcn_readfirstlane(s_msg[1]);
+      __syncthreads();
+      if (msg == 0u) break;                   // a prefetch is only a favour: nothing to report
+      prefetch_filters(*(ConstOp*)(a.ops + ((ConstPrefetch*)a.prefetch)[pf].op), rank, tid);
+      ++pf;
+    }
+  }
   if (tid == 0 && n_done != 0u) __hip_atomic_fetch_add(&a.ctl[kChainCtlDone * kChainCtlStride], n_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -304,8 +350,8 @@ int chain_max_workgroups(int* out_workgroups, int* out_xcds) {
   return 0;
 }
 
-int launch_chain(const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, uint32_t n_queues,
-                 uint32_t* ctl, uint32_t* ctl_other, uint32_t ctl_slots, uint32_t* item_flags, uint32_t run_number,
+int launch_chain(const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, uint32_t n_queues, const ChainPrefetch* prefetch_dev,
+                 const uint32_t* prefetch_begin, uint32_t* ctl, uint32_t* ctl_other, uint32_t ctl_slots, uint32_t* item_flags, uint32_t run_number,
                  uint32_t spin_limit_ticks, uint32_t flags, int grid, void* stream, uint64_t* prof_dev) {
   if (n_queues != 1u && n_queues != (uint32_t)kNumXCDs) return (int)hipErrorInvalidValue;
   if (grid <= 0 || n_items == 0u) return 0;
@@ -325,6 +371,8 @@ int launch_chain(const TenantDev* ops_dev, const st_work_item* items_dev, uint32
   a.n_queues = n_queues;
   a.q_end = n_items;
   a.colbegin = colbegin_dev;
+  a.prefetch = prefetch_dev;
+  for (int x = 0; x <= kNumXCDs; ++x) a.prefetch_begin[x] = prefetch_dev ? prefetch_begin[x] : 0u;
   hipLaunchKernelGGL(st_chain_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, a);
   return (int)hipGetLastError();
 }

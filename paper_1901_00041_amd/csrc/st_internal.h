@@ -96,9 +96,12 @@ constexpr int kChainCtlAbort = 1, kChainCtlDone = 2, kChainCtlHead = 4, kChainCt
 constexpr int kChainRankWords = kNumXCDs * 256;   // arrival counts per (XCD, compute unit key), dense, after the slots
 constexpr int kChainColumns = kNumCUs / kNumXCDs; // exclusive columns per XCD (one per compute unit), and as many shared
 constexpr uint32_t kChainFlagLocalFlags = 4u;     // completion travels through per-item flags in the XCD's own L2
+// Filters to pull into an XCD's L2 ahead of their stage: op's w, once the flags [gate_begin, gate_begin + gate_count) are
+// set (those of the stage two before; none for the first two stages); flag_base is the op's own.
+struct ChainPrefetch { uint32_t op, flag_base, gate_begin, gate_count; };
 int chain_max_workgroups(int* out_workgroups, int* out_xcds);
-int launch_chain(const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, uint32_t n_queues,
-                 uint32_t* ctl, uint32_t* ctl_other, uint32_t ctl_slots, uint32_t* item_flags, uint32_t run_number,
+int launch_chain(const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, uint32_t n_queues, const ChainPrefetch* prefetch_dev,
+                 const uint32_t* prefetch_begin, uint32_t* ctl, uint32_t* ctl_other, uint32_t ctl_slots, uint32_t* item_flags, uint32_t run_number,
                  uint32_t spin_limit_ticks, uint32_t flags, int grid, void* stream, uint64_t* prof_dev);
 int launch_empty(void* stream);
 // Allocation-free path: device address of the current GPU's fixed scratch array (looked up on first use per device),
