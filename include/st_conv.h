@@ -77,7 +77,7 @@ typedef struct st_plan_opts {
   int32_t target_items;  /* 0 = default; else the workgroup slots the planner's cost model fills      */
   int32_t rows_per_tile; /* 0 = choose; 1, 2 or 4 forces the output rows per work item of row-tiled   */
                          /* tenants (ignored for the others)                                         */
-  int32_t chain_queues;  /* st_chain_plan only: 0 = choose; 1 = one work queue for the whole chip; 2 = the  */
+  int32_t chain_queues;  /* st_chain_plan only: 0 = choose; 1 = one persistent launch with one work queue; 2 = the */
                          /* per-XCD layout, each sequence bound to one XCD (needs a whole 8-XCD device)     */
   int32_t reserved;      /* must be 0                                                                */
 } st_plan_opts;
@@ -267,8 +267,9 @@ void st_pipeline_destroy(st_pipeline* pipeline);
  * ops of a sequence, and that sequences share no written tensor.
  *
  * Tiles are chosen per stage (all ops of that stage, over all sequences, planned together as st_conv_plan would).
- * Within a stage the longest work items come first.  There is either one queue for the whole chip, whose entries
- * the resident workgroups claim one by one in stage order, or (the default from 8 sequences on, on a whole 8-XCD
+ * Within a stage the longest work items come first.  There is either one queue for the whole chip, worked through one
+ * launch per stage by default (with chain_queues = 1 as one persistent launch whose resident workgroups claim the entries
+ * one by one in stage order), or (the default from 8 sequences on, on a whole 8-XCD
  * device) the work is laid out per XCD, sequence s on XCD s mod 8, served only by the workgroups that run on that
  * XCD: a sequence's activations then stay in one XCD's L2, and a finished work item is announced through that L2 (a
  * flag per work item) instead of through memory.  An XCD's entries are dealt into COLUMNS, each a list of entries in
@@ -326,7 +327,7 @@ typedef struct st_chain st_chain; /* opaque */
  * queue, control blocks, split-K workspace) unless opts->host_only.  n_ops == 0 gives an empty chain.  opts as for
  * st_conv_plan (order is ignored: the queue order is fixed). */
 st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const st_plan_opts* opts, st_chain** out_chain);
-/* One pass: one launch on hip_stream.  Asynchronous, allocation-free.  Two runs of one chain must not overlap in
+/* One pass: one launch on hip_stream (one per stage with fewer than 8 sequences and chain_queues = 0).  Asynchronous, allocation-free.  Two runs of one chain must not overlap in
  * time (queue them on one stream). */
 st_status st_chain_run(st_chain* chain, void* hip_stream);
 /* The same with in-kernel time stamps per queue entry (HOST buffer of 8 uint64 per entry, as st_conv_run_profiled;

@@ -1,5 +1,5 @@
 // Host side of the chain (st_chain_*): validation, per-stage planning through st_conv_plan, the queue, the dependency
-// thresholds, the device arena and the persistent launch.
+// thresholds, the device arena and the launches.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -25,6 +25,8 @@ struct st_chain {
   uint32_t spin_limit_ticks = 10000000u;     // 100 ms of the 100 MHz constant clock
   uint32_t flags = 0;
   int n_queues = 1;                          // 1, or kNumXCDs
+  bool stage_launches = false;               // one launch per stage instead of the persistent one (one queue, unless asked for it)
+  std::vector<int64_t> stage_begin;          // one queue: stage s (in order) is items[stage_begin[s] .. stage_begin[s + 1])
   // one queue: all of items.  Queues per XCD: column j of XCD x is items[colbegin[x * 2 * kChainColumns + j] ..
   // colbegin[.. + j + 1]), the kChainColumns exclusive columns first, then the shared ones
   std::vector<uint32_t> colbegin;
@@ -125,6 +127,10 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
       return fail(ST_ERR_UNSUPPORTED, "the per-XCD layout needs a device with %d XCDs, this one shows %d", kNumXCDs, n_xcd);
     }
     c->n_queues = (want_queues == 2 || (want_queues == 0 && n_xcd == kNumXCDs && c->n_sequences >= kNumXCDs)) ? kNumXCDs : 1;
+    // With one queue a pass is a launch per stage, unless the caller asked for the persistent one: entries claimed one by
+    // one and completions counted at the memory side cost more than the launches (4 networks of batch 4: 927 us as one
+    // launch, 597 as 50; one network of batch 8: 1085 and 421).
+    c->stage_launches = c->n_queues == 1 && want_queues == 0;
     // per XCD: producer and consumer of a sequence share that XCD's L2, and completion travels through it
     c->flags = c->n_queues > 1 ? kChainFlagLocalFlags : 0u;
     // The shared columns are only used when a compute unit holds two workgroups (the per-XCD layout exists on a whole
@@ -219,6 +225,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
         }
         stage_items[q] += n_it;
       }
+      if (c->n_queues == 1) c->stage_begin.push_back((int64_t)queues[0].size());
       // one queue: as is.  Queues per XCD: the stage's entries (longest first) are dealt to the XCD's columns, to the
       // exclusive ones first, to the shared ones only beyond one per compute unit, then round again; so a stage with
       // no more entries than compute units never shares one, and every column is in stage order
@@ -253,6 +260,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
         seq_ct[q] = std::max(seq_ct[q], stage_ct[q]);
       }
     }
+    if (c->n_queues == 1) c->stage_begin.push_back((int64_t)queues[0].size());
     if (status == ST_OK) {
       int64_t total_items = 0;
       for (const auto& qv : queues) total_items += (int64_t)qv.size();
@@ -343,6 +351,13 @@ static st_status chain_launch(st_chain* c, void* stream, uint64_t* prof_dev) {
   if (!c) return fail(ST_ERR_INVALID_ARG, "chain is NULL");
   if (c->host_only) return fail(ST_ERR_UNSUPPORTED, "chain was built host-only and cannot run");
   if (c->items.empty()) return ST_OK;
+  if (c->stage_launches) {
+    for (size_t g = 0; g + 1 < c->stage_begin.size(); ++g) {
+      const int64_t b = c->stage_begin[g], n = c->stage_begin[g + 1] - b;
+      ST_HIP((hipError_t)launch_conv(c->d_ops, c->d_items + b, n, stream, prof_dev ? prof_dev + b * kProfSlots : nullptr));
+    }
+    return ST_OK;
+  }
   const unsigned p = c->run_parity;
   if (++c->run_number == 0u) {
     // the run numbers have wrapped: forget every flag of the old numbering (a fill kernel, so a capture may hold it)
@@ -383,6 +398,7 @@ extern "C" st_status st_chain_aborted(st_chain* chain, int32_t* aborted) {
   *aborted = 0;
   if (chain->host_only || chain->items.empty()) return ST_OK;
   ST_HIP(hipDeviceSynchronize());
+  if (chain->stage_launches) return ST_OK;           // nothing waits inside a launch, nothing can give up
   uint32_t flag[2] = {0u, 0u}, done = 0u;
   for (int b = 0; b < 2; ++b) ST_HIP(hipMemcpy(&flag[b], chain->d_ctl[b] + kChainCtlAbort * kChainCtlStride, 4, hipMemcpyDeviceToHost));
   // the block of the most recent run still holds its count of completed work items (the other one was cleared by it)

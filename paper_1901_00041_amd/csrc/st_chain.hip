@@ -60,31 +60,6 @@ typedef __attribute__((address_space(4))) const st_work_item ConstItem;
 typedef __attribute__((address_space(4))) const TenantDev ConstOp;
 typedef __attribute__((address_space(4))) const ChainPrefetch ConstPrefetch;
 
-template <int DT>
-__device__ __forceinline__ void pool_item(ConstOp& T, const st_work_item it) {
-  const int64_t idx = (int64_t)it.tile_m * kThreads + work_thread_id();
-  if (idx >= (int64_t)T.M) return;
-  const u32x4 v = maxpool_vector<DT, kAuxDeviceCoherent>(T.x, T.x_bytes, idx, T.H, T.W, T.C, T.P, T.Q, T.R, T.stride, T.pad);
-  __builtin_amdgcn_raw_buffer_store_b128(v, make_rsrc(T.y, T.y_bytes), (int)((uint32_t)idx * 16u), 0, kAuxDeviceCoherent);
-}
-
-// One queue entry's work.
-__device__ __forceinline__ void chain_item(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
-  if (T.cfg == kChainPoolCfg) {
-    switch (T.in_dtype) {
-      case ST_DT_BF16: pool_item<ST_DT_BF16>(T, it); break;
-      case ST_DT_F16: pool_item<ST_DT_F16>(T, it); break;
-      default: pool_item<ST_DT_F32>(T, it); break;
-    }
-  } else {
-    switch (T.in_dtype) {
-      case ST_DT_BF16: run_dtype<ST_DT_BF16, CoherentActs>(T, it, smem, prof); break;
-      case ST_DT_F16: run_dtype<ST_DT_F16, CoherentActs>(T, it, smem, prof); break;
-      default: run_dtype<ST_DT_F32, CoherentActs>(T, it, smem, prof); break;
-    }
-  }
-}
-
 // Filters are read from memory exactly once per pass (376 MB for eight 53-layer networks: more than the memory-side cache
 // holds) and do not depend on any earlier layer, and a small stage's tiles wait for them more than for anything else.  So
 // workgroups that wait with nothing to do pull a stage's filters into their XCD's L2 while the stage before it runs: each
@@ -283,7 +258,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
       while (pf < pf_end && ((ConstPrefetch*)a.prefetch)[pf].flag_base <= T.chain_flag_base) ++pf;      // too late to prefetch these
       asm volatile("" ::"s"(rec_touch));
       if (T.cfg == kChainPoolCfg && prof && tid == 0) prof[4] = wall_clock64();
-      chain_item(T, it, smem, prof);
+      run_item<CoherentActs>(T, it, smem, prof);
       // Completion.  Outputs were stored write-through; channel counts that are not a multiple of 8 take an epilogue
       // with plain stores and need the release fence (write-back of the L2).
       if (T.cfg != kChainPoolCfg && (T.K & 7) != 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");

@@ -27,11 +27,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_conv_kernel(const TenantDev* _
   const st_work_item it = items[blockIdx.x];
   const TenantDev& T = tenants[it.tenant];
   uint64_t* prof = prof_base ? prof_base + (size_t)blockIdx.x * kProfSlots : nullptr;
-  switch (T.in_dtype) {
-    case ST_DT_BF16: run_dtype<ST_DT_BF16>(T, it, smem, prof); break;
-    case ST_DT_F16: run_dtype<ST_DT_F16>(T, it, smem, prof); break;
-    default: run_dtype<ST_DT_F32>(T, it, smem, prof); break;
-  }
+  run_item<PlainActs>(T, it, smem, prof);
 }
 
 __global__ void st_empty_kernel() {}

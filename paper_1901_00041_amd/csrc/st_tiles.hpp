@@ -1430,4 +1430,31 @@ __device__ __forceinline__ u32x4 maxpool_vector(const void* __restrict__ xv, uin
   else return u32x4{bits[0] | (bits[1] << 16), bits[2] | (bits[3] << 16), bits[4] | (bits[5] << 16), bits[6] | (bits[7] << 16)};
 }
 
+// One max-pool work item: kThreads output vectors, stored write-through.
+template <int DT, int AUX, class TD>
+__device__ __forceinline__ void pool_item(const TD& T, const st_work_item it) {
+  const int64_t idx = (int64_t)it.tile_m * kThreads + work_thread_id();
+  if (idx >= (int64_t)T.M) return;
+  const u32x4 v = maxpool_vector<DT, AUX>(T.x, T.x_bytes, idx, T.H, T.W, T.C, T.P, T.Q, T.R, T.stride, T.pad);
+  __builtin_amdgcn_raw_buffer_store_b128(v, make_rsrc(T.y, T.y_bytes), (int)((uint32_t)idx * 16u), 0, kAuxDeviceCoherent);
+}
+
+// One work item of a plan or chain: a tile of a convolution, or (chains only) a max-pool item.
+template <class POL, class TD>
+__device__ __forceinline__ void run_item(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+  if (T.cfg == kChainPoolCfg) {
+    switch (T.in_dtype) {
+      case ST_DT_BF16: pool_item<ST_DT_BF16, POL::kActAux>(T, it); break;
+      case ST_DT_F16: pool_item<ST_DT_F16, POL::kActAux>(T, it); break;
+      default: pool_item<ST_DT_F32, POL::kActAux>(T, it); break;
+    }
+    return;
+  }
+  switch (T.in_dtype) {
+    case ST_DT_BF16: run_dtype<ST_DT_BF16, POL>(T, it, smem, prof); break;
+    case ST_DT_F16: run_dtype<ST_DT_F16, POL>(T, it, smem, prof); break;
+    default: run_dtype<ST_DT_F32, POL>(T, it, smem, prof); break;
+  }
+}
+
 }  // namespace st
