@@ -130,7 +130,7 @@ __device__ __forceinline__ uint32_t chain_claim(const ChainArgs& a, uint32_t q, 
 // any number of resident workgroups.)
 __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[kSmemBytes];
-  __shared__ uint32_t s_msg[2];
+  uint32_t* s_msg = (uint32_t*)smem;      // between work items only: read, then a barrier, before a tile or the next message
   const int tid = threadIdx.x;
   if (blockIdx.x == 0) {
     // the control block of the NEXT run (runs alternate between two blocks; the stream orders them)
@@ -185,6 +185,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
         if (tid == 0) s_msg[0] = next;
         __syncthreads();
         idx = __builtin_amdgcn_readfirstlane(s_msg[0]);
+        __syncthreads();
       }
       if (idx >= qe) break;
       ConstItem* ip = (ConstItem*)(a.items + idx);
@@ -241,8 +242,8 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
           }
           __syncthreads();
           msg = __builtin_amdgcn_readfirstlane(s_msg[1]);
+          __syncthreads();                    // s_msg[1] has been read by everyone
           if (msg == 2u) {
-            __syncthreads();                  // s_msg[1] has been read by everyone
             prefetch_filters(*(ConstOp*)(a.ops + ((ConstPrefetch*)a.prefetch)[pf].op), rank, tid);
             ++pf;
             p0 = 0u;

@@ -32,13 +32,20 @@ constexpr TileShape kTileShapes[kNumTileCfgs] = {
     {16, 64, 1, 4, 16, 256, 3},    // 5: wave tile 16x16
     {128, 64, 2, 2, 32, 64, 2},    // 6: row tile (few input channels), wave tile 64x32
 };
-constexpr int kSmemBytes = 73728;  // LDS per workgroup: the largest of the family (checked per tile)
+constexpr int kSmemBytes = 81920;  // LDS per workgroup: half a compute unit's 160 KiB
 constexpr int kRowStageBytes = 18432;   // row tile: LDS set aside for the epilogue's transposition buffer
 // tile shapes that also exist as element-wise-gather kernels (channel count not a multiple of the
 // 16-byte vector width); the planner maps such tenants onto one of them
 constexpr bool kGenericCfg[kNumTileCfgs] = {false, true, false, true, false, false, false};
 
 constexpr int kOrderTaps = 0, kOrderChannels = 1, kOrderLinear = 2;   // see conv_tile
+constexpr int kOrderPatch = 3;     // see conv_tile_patch
+// filter steps resident in LDS when a tile shape keeps its input patch there (0: the shape has no such form; two patches and
+// two 16 KiB steps of a 128x128 tile would leave no room for a third).  Filters from beyond the L2 need the fourth step
+// where a step is short: eight tenants of 3x3 on 64x64 tiles 11.1 us with three, 9.1 with four.
+constexpr int kPatchStages[kNumTileCfgs] = {0, 4, 3, 4, 3, 0, 0};
+constexpr int kPatchTaps = 9;
+constexpr int kPatchMin = 4;       // load instructions per wavefront and channel block: at least (some twice, if fewer would do)
 
 // Device-side tenant record, read through scalar loads by every workgroup of that tenant.
 struct TenantDev {
@@ -57,7 +64,10 @@ struct TenantDev {
   int32_t step_dk, step_dr;   // one K step in the reduction index (r*S + s)*C + c: KT elements = step_dr filter rows of
                               //    S*C elements and step_dk elements more
   int32_t k_order;            // kOrder*: how conv_tile walks the reduction index
-  uint32_t tap_rows;          // kOrderChannels: bit r*S for every filter row r
+  uint32_t tap_rows;          // kOrderChannels, kOrderPatch: bit r*S for every filter row r
+  int32_t patch_rows;         // kOrderPatch: most input pixels a tile's taps touch
+  int32_t patch_loads;        // load instructions per wavefront and channel block
+  int32_t patch_blocks;       // channel blocks per K slice
   int32_t shift_c, shift_s;   // floor(n/d) = ((n * magic) >> 31) >> shift, for d = C and d = S
   uint32_t magic_c, magic_s;
   int32_t shift_r, shift_nvp; // same for d = R and d = row_pitch/16 (row tile only)

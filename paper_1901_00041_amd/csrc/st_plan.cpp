@@ -82,17 +82,21 @@ static void magic_for(int d, uint32_t* m, int32_t* L) {
 //   first operands staged | one K step | epilogue | split-K hand-off (write-through, counter, read back).
 // A workgroup that has its compute unit to itself and two that share one behave differently (the shared step is bound by
 // the compute unit's 64 bytes per clock from the L2, the lone one by latency and instruction issue), and fp32 MFMAs take
-// eight times as long as 16-bit ones, so there are four tables.
+// eight times as long as 16-bit ones, so there are four tables, and two more for 16-bit 3x3 layers whose input patch stays
+// in LDS (a shape without that form costs there what it costs in the first table).
 // The launch is modelled as list scheduling of the items on workgroup slots: its duration is about max(longest item, sum
 // of item times / slots).  The planner picks, per tenant, the (tile, split) option that minimises that maximum over
 // the whole launch: once for kSlots slots of shared compute units, once for one workgroup on each.
 struct ItemCosts { double first[kNumTileCfgs], step[kNumTileCfgs], epi[kNumTileCfgs]; };
-// [fp32 operands][alone on the compute unit]
-static const ItemCosts kCosts[2][2] = {
+enum { kCosts16 = 0, kCosts32 = 1, kCostsPatch = 2 };
+// [kCosts*][alone on the compute unit]
+static const ItemCosts kCosts[3][2] = {
     {{{4800, 4500, 4500, 3800, 4200, 3250, 3000}, {1250, 740, 740, 430, 650, 560, 520}, {4700, 2500, 2600, 1800, 1400, 1230, 2800}},
      {{2700, 2500, 2500, 2300, 2600, 2200, 3000}, {820, 470, 470, 305, 450, 375, 520}, {3900, 2070, 2080, 1500, 1240, 1120, 2800}}},
     {{{5200, 5500, 5500, 4300, 4300, 3250, 0}, {7200, 3600, 3600, 1850, 1850, 1060, 0}, {8000, 4500, 4000, 3000, 1800, 1330, 0}},
-     {{3500, 3000, 3000, 2500, 2700, 2300, 0}, {4350, 2260, 2240, 1200, 1300, 740, 0}, {4300, 2200, 2200, 1670, 1430, 1180, 0}}}};
+     {{3500, 3000, 3000, 2500, 2700, 2300, 0}, {4350, 2260, 2240, 1200, 1300, 740, 0}, {4300, 2200, 2200, 1670, 1430, 1180, 0}}},
+    {{{4800, 2300, 2400, 2000, 2300, 3250, 0}, {1250, 620, 680, 380, 590, 560, 0}, {4700, 2400, 2500, 1700, 1400, 1230, 0}},
+     {{2700, 1500, 1550, 1300, 1600, 2200, 0}, {820, 465, 445, 310, 410, 375, 0}, {3900, 2060, 2030, 1500, 1240, 1120, 0}}}};
 static const double kRowStageCost = 6500.0;     // row tile: copying image rows and filters into LDS
 static const double kGatherStepCost[kNumTileCfgs] = {0, 3470.0, 0, 2100.0, 0, 0, 0};   // element-wise gathers: bound by the texture addresser
 static const double kGatherFirstCost = 19000.0;
@@ -120,6 +124,27 @@ static int row_tile_pitch(const st_conv_desc& d) {
 // element position inside a padded image row (conv_tile counts in those) fits 31 bits.
 static bool vector_ok(const st_conv_desc& d) {
   return d.C % (16 / elem_size(d.in_dtype)) == 0 && ((int64_t)d.W + 2 * (int64_t)d.pad) * d.C < ((int64_t)1 << 31);
+}
+
+// Whether a tile shape can keep the layer's input patch in LDS (see conv_tile_patch), and the patch's size: 16-bit types,
+// 3x3, stride 1, no more output columns and rows than input ones (then the input pixels under a tile's pixels ascend),
+// channels a multiple of the step, and LDS room for the patch (twice when there is more than one channel block) beside
+// the filter stages.
+static bool patch_geometry(const st_conv_desc& d, int cfg, int32_t* rows, int32_t* loads) {
+  if (d.in_dtype == ST_DT_F32 || kPatchStages[cfg] == 0 || d.stride != 1 || d.R != 3 || d.S != 3 || d.pad > 1) return false;
+  const int64_t kb = kTileShapes[cfg].KB, mt = kTileShapes[cfg].MT, blocks = (int64_t)d.C * 2 / kb;
+  const int64_t P = (int64_t)d.H + 2 * d.pad - 2, Q = (int64_t)d.W + 2 * d.pad - 2;
+  if ((int64_t)d.C * 2 % kb != 0) return false;
+  // from a tile's first pixel to its last: one input pixel per pixel, W - Q more per row begun, (H - P) * W more per image
+  const int64_t span = (mt - 1) + (mt - 1 + Q - 1) / Q * (d.W - Q) + (mt - 1 + P * Q - 1) / (P * Q) * (d.H - P) * d.W;
+  const int64_t n = span + 2 * (int64_t)d.W + 3;
+  const int64_t per_turn = 4 * 64 / (kb / 16);                       // rows the four wavefronts load with one instruction each
+  const int64_t turns = (n + 1 + per_turn - 1) / per_turn;           // the row after the last is the zero row
+  const int64_t lds = turns * per_turn * kb * (blocks > 1 ? 2 : 1) + (int64_t)kPatchStages[cfg] * kTileShapes[cfg].NT * kb;
+  if (lds > kSmemBytes) return false;
+  *rows = (int32_t)n;
+  *loads = (int32_t)turns;
+  return true;
 }
 
 // Row tile eligibility (see conv_tile_rows): 16-bit types, 8 <= S*C <= 32, image rows a multiple of 16 bytes,
@@ -253,7 +278,7 @@ static Option make_row_option(const st_conv_desc& d, int rows_per_tile, bool alo
   return o;
 }
 
-static Option make_option(int64_t M, int64_t Ng, int64_t kbytes, bool vec_ok, bool f32, bool alone, int cfg, int split) {
+static Option make_option(const st_conv_desc& d, int64_t M, int64_t Ng, int64_t kbytes, bool vec_ok, bool alone, int cfg, int split) {
   Option o;
   o.rows_per_tile = 0;
   const int k_steps = cdiv(kbytes, kTileShapes[cfg].KB);
@@ -264,7 +289,9 @@ static Option make_option(int64_t M, int64_t Ng, int64_t kbytes, bool vec_ok, bo
   o.split = split;
   o.steps_per_split = per;
   o.items = (int64_t)cdiv(M, kTileShapes[cfg].MT) * cdiv(Ng, kTileShapes[cfg].NT) * split;
-  const ItemCosts& c = kCosts[f32 ? 1 : 0][alone ? 1 : 0];
+  int32_t rows, loads;
+  const bool patch = per % kPatchTaps == 0 && patch_geometry(d, cfg, &rows, &loads);
+  const ItemCosts& c = kCosts[d.in_dtype == ST_DT_F32 ? kCosts32 : patch ? kCostsPatch : kCosts16][alone ? 1 : 0];
   const double elems = (double)kTileShapes[cfg].MT * kTileShapes[cfg].NT;
   const int batch = elems > 4096 ? 4 : 8;      // slices read back at a time
   o.item_time = (vec_ok ? c.first[cfg] : kGatherFirstCost) + per * (vec_ok ? c.step[cfg] : kGatherStepCost[cfg]) + c.epi[cfg] +
@@ -276,7 +303,7 @@ static Option make_option(int64_t M, int64_t Ng, int64_t kbytes, bool vec_ok, bo
 static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int64_t Ng, int64_t kbytes, bool vec_ok, bool alone,
                                           const st_plan_opts& o) {
   std::vector<Option> out;
-  const bool row_ok = row_tile_ok(d), f32 = d.in_dtype == ST_DT_F32;
+  const bool row_ok = row_tile_ok(d);
   if (row_ok && (o.tile_cfg == 0 || o.tile_cfg - 1 == kRowCfg) && o.split_k <= 1) {
     for (int rt = 1; rt <= kRowsPerTile; rt *= 2)
       if (o.rows_per_tile == 0 || o.rows_per_tile == rt) out.push_back(make_row_option(d, rt, alone));
@@ -292,12 +319,12 @@ static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int6
       if (c != forced) continue;
     }
     if (o.split_k >= 1) {
-      out.push_back(make_option(M, Ng, kbytes, vec_ok, f32, alone, c, o.split_k));
+      out.push_back(make_option(d, M, Ng, kbytes, vec_ok, alone, c, o.split_k));
       continue;
     }
     int last_split = 0;
     for (int sp : kSplitChoices) {
-      Option op = make_option(M, Ng, kbytes, vec_ok, f32, alone, c, sp);
+      Option op = make_option(d, M, Ng, kbytes, vec_ok, alone, c, sp);
       if (op.split == last_split) continue;             // clamped to the same factor as before
       if (op.split > 1 && op.steps_per_split < 2) continue;
       last_split = op.split;
@@ -376,6 +403,39 @@ static void choose_all(const std::vector<std::vector<Option>>& opts, int slots, 
     best = d;
     *pick = cur;
   }
+}
+
+// For a launch that is to give every item a compute unit of its own: the smallest bound on the item time that at most
+// `cus` items can meet, every tenant taking its option of fewest items within the bound.  Returns the longest item's time,
+// or a negative number if no bound does.
+static double choose_alone(const std::vector<std::vector<Option>>& opts, int cus, std::vector<int>* pick) {
+  std::vector<double> limits;
+  for (const auto& v : opts)
+    for (const Option& op : v) limits.push_back(op.item_time);
+  std::sort(limits.begin(), limits.end());
+  auto fits = [&](double limit) {
+    int64_t items = 0;
+    pick->assign(opts.size(), 0);
+    for (size_t t = 0; t < opts.size(); ++t) {
+      int best = -1;
+      for (size_t i = 0; i < opts[t].size(); ++i) {
+        const Option& op = opts[t][i];
+        if (op.item_time > limit) continue;
+        if (best < 0 || op.items < opts[t][best].items || (op.items == opts[t][best].items && op.item_time < opts[t][best].item_time)) best = (int)i;
+      }
+      if (best < 0) return false;
+      (*pick)[t] = best;
+      items += opts[t][best].items;
+    }
+    return items <= cus;
+  };
+  size_t lo = 0, hi = limits.size();
+  while (lo < hi) {
+    const size_t mid = (lo + hi) / 2;
+    if (fits(limits[mid])) hi = mid; else lo = mid + 1;
+  }
+  if (lo == limits.size() || !fits(limits[lo])) return -1.0;
+  return limits[lo];
 }
 
 // The model's duration of a launch with the given choice per tenant.
@@ -530,10 +590,8 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       // 32x64).
       std::vector<std::vector<Option>> lone = all_options(true);
       std::vector<int> alone;
-      choose_all(lone, kNumCUs, &alone);
-      int64_t n_alone = 0;
-      for (int t = 0; t < n_tenants; ++t) n_alone += lone[t][alone[t]].items;
-      if (n_alone <= kNumCUs && modelled(lone, alone, kNumCUs) < modelled(options, pick, 2 * kNumCUs)) {
+      const double longest = choose_alone(lone, kNumCUs, &alone);
+      if (longest >= 0.0 && longest < modelled(options, pick, 2 * kNumCUs)) {
         options.swap(lone);
         pick = alone;
       }
@@ -682,6 +740,10 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       T.step_dk = (int32_t)(kt % ((int64_t)d.S * d.C));
       T.k_order = d.C % kt != 0 || (int64_t)d.R * d.S > 32 ? kOrderTaps : (d.R == 1 && d.S == 1 && d.pad == 0) ? kOrderLinear : kOrderChannels;
       for (int r = 0; T.k_order == kOrderChannels && r < d.R; ++r) T.tap_rows |= 1u << (r * d.S);
+      if (patch_geometry(d, ti.tile_cfg, &T.patch_rows, &T.patch_loads) && ti.k_steps_per_split % kPatchTaps == 0) {
+        T.k_order = kOrderPatch;
+        T.patch_blocks = ti.k_steps_per_split / kPatchTaps;
+      }
       magic_for(d.C, &T.magic_c, &T.shift_c);
       magic_for(d.S, &T.magic_s, &T.shift_s);
       T.row_pitch = row_tile_pitch(d);

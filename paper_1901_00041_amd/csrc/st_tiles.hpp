@@ -917,6 +917,204 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
   }
 }
 
+// ---- workgroup tile with the input patch resident in LDS ---------------------------------------------
+// For 3x3 stride-1 layers in 16-bit types.  conv_tile stages a pixel row once per tap; here the run of input pixels that
+// the tile's taps touch (MT + 2 * W + 2 of them for a same-size layer: the output's linear order is the input's) is loaded
+// once per block of KT channels, into one of two buffers, while the previous block's taps are computed, and only filters
+// are staged per step.  A tap is an offset in LDS rows, its addresses computed once; a pixel whose tap lies outside the
+// image reads the row after the last, which is zero.
+// What it takes away: a good part of the 64 bytes per clock a compute unit can load, and half of the load instructions a
+// lone workgroup issues.  A K step at 256 channels of 14x14, data not in the L2: 64x64 tile 335 -> 312 clocks alone and
+// 444 -> 368 beside a second workgroup, 128x64 702 -> 550, 64x128 695 -> 625; first operands 3700 -> 2370.  What bounds it now:
+// alone the LDS reads and the barrier, beside a second one the MFMAs (512 of 550 clocks at 128x64).
+// LDS: [patch][patch, when there is more than one channel block][ST filter steps][NT][KB].
+template <int MT, int NT, int WPX, int WCH, int MF, int KB, int ST, int DT, class POL = PlainActs, class TD>
+__device__ __forceinline__ void conv_tile_patch(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+  constexpr int ES = ElemOf<DT>::ES;
+  constexpr int VEC = 16 / ES;
+  constexpr int CH = KB / 16;
+  constexpr int RPI = 64 / CH;          // LDS rows one load instruction of a wavefront covers
+  constexpr int BW = NT / (4 * RPI);    // filter load instructions per wavefront and step
+  constexpr int kStage = NT * KB;
+  constexpr int WM = MT / WPX, WN = NT / WCH;
+  constexpr int BM = WM / MF, BN = WN / MF;
+  constexpr int SUBB = (MF == 32) ? 32 : 64;
+  constexpr int NSUB = KB / SUBB;
+  constexpr int kTaps = kPatchTaps;
+  typedef Mma<DT, MF> MMA;
+  typedef typename MMA::Acc Acc;
+  static_assert(ES == 2 && (KB == 128 || KB == 256) && NT % (4 * RPI) == 0 && kTaps == 9 && ST < kTaps, "patch tile shape");
+
+  const int tid = work_thread_id();
+  if (prof && tid == 0) {
+    prof[0] = __builtin_readcyclecounter();
+    prof[4] = wall_clock64();
+    prof[5] = ((uint64_t)__builtin_amdgcn_s_getreg(0x1814) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(0xF804);
+  }
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = (int)it.tile_m * MT;
+  const int n0 = (int)it.tile_n * NT;
+  const int W = T.W, H = T.H, pad = T.pad;
+  const uint32_t c_bytes = (uint32_t)(T.C * ES);
+  const int p_rows = T.patch_rows, p_loads = T.patch_loads;
+  const uint32_t p_bytes = (uint32_t)(p_loads * 4 * RPI * KB);      // one patch buffer
+  const u32x4 rx = rsrc_words(T.x, T.x_bytes), rw = rsrc_words(T.w, T.w_bytes);
+
+  // channel blocks of this K slice
+  const int block0 = (int)it.k_split_idx * T.patch_blocks;
+  const int all_blocks = (int)(c_bytes / KB);
+  const int blocks = all_blocks - block0 < T.patch_blocks ? all_blocks - block0 : T.patch_blocks;
+
+  // linear input pixel under tap (0, 0) of output pixel m (may lie outside the image, or before its start)
+  auto locate = [&](int m, int& h0, int& w0) -> int {
+    const int n = fast_div(m, T.magic_pq, T.shift_pq);
+    const int pq = m - n * T.PQ;
+    const int p = fast_div(pq, T.magic_q, T.shift_q);
+    h0 = p - pad;
+    w0 = pq - p * T.Q - pad;
+    return (n * H + h0) * W + w0;
+  };
+  int h0, w0;
+  const int lo = __builtin_amdgcn_readfirstlane(locate(m0, h0, w0));
+
+  // staging geometry (see conv_tile): the row of an instruction's block this lane fetches, and which chunk of it
+  const int lr = lane / CH;
+  const int swz = (KB == 256) ? ((4 * wave + lr) & 15) : ((4 * (wave & 1) + (lr >> 1)) & 7);
+  const int chunk = (lane % CH) ^ swz;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + (uint32_t)wave * 1024u;
+  const uint32_t b_lds0 = __builtin_amdgcn_readfirstlane((all_blocks > 1 ? 2u : 1u) * p_bytes);
+  const int pr0 = wave * RPI + lr;
+  const uint32_t pv0 = (uint32_t)((lo + pr0) * (int)c_bytes + chunk * 16);
+  const int p_left = p_rows - pr0;
+  const uint32_t turn_bytes = (uint32_t)(4 * RPI) * c_bytes;
+  auto issue_patch = [&](int j, uint32_t soff, uint32_t lds) {      // load instruction j of a channel block's patch
+    const uint32_t v = j * 4 * RPI < p_left ? pv0 + (uint32_t)j * turn_bytes : kInvalidOffset;
+    load_to_lds<POL::kActAux, 0>(rx, v, soff, __builtin_amdgcn_readfirstlane(lds + (uint32_t)j * 4096u));
+  };
+  uint32_t b_off[BW];
+#pragma unroll
+  for (int i = 0; i < BW; ++i) {
+    const int row = n0 + (i * 4 + wave) * RPI + lr;
+    b_off[i] = row < T.K ? (uint32_t)(row * T.Kg + chunk * VEC) * ES : kInvalidOffset;
+  }
+  uint32_t b_soff = __builtin_amdgcn_readfirstlane((uint32_t)(block0 * KB));      // of the step to be staged next
+  const uint32_t wrap_b = (uint32_t)KB - (uint32_t)(kTaps - 1) * c_bytes;
+  const uint32_t b_base = lds0 + b_lds0;
+  auto issue_filter = [&](auto I, uint32_t stage_off) {
+    constexpr int i = decltype(I)::value;
+    load_to_lds<0, i * 4096>(rw, b_off[i], b_soff, __builtin_amdgcn_readfirstlane(b_base + stage_off));
+  };
+  {
+    const uint32_t soff = b_soff;
+    for (int j = 0; j < p_loads; ++j) issue_patch(j, soff, lds0);
+  }
+  static_for<ST>([&](auto S) {
+    static_for<BW>([&](auto I) { issue_filter(I, decltype(S)::value * kStage); });
+    b_soff += c_bytes;
+  });
+
+  // MFMA operands: filters as in conv_tile; for a pixel its LDS address per tap, in the patch being read
+  const int wm0 = (wave % WPX) * WM;
+  const int wn0 = (wave / WPX) * WN;
+  const int lrow = lane & (MF - 1);
+  const int lk = lane / MF;
+  const int rsw = (KB == 256) ? (lrow & 15) : ((lrow >> 1) & 7);
+  const int rbase = lrow * KB + (lk ^ rsw) * 16;
+  uint32_t a_tap[kTaps][BM];
+  const uint32_t b_lds = (uint32_t)(rbase + wn0 * KB) + b_lds0;
+#pragma unroll
+  for (int i = 0; i < BM; ++i) {
+    const int m = m0 + wm0 + i * MF + lrow;
+    const int row0 = locate(m < T.M ? m : m0, h0, w0) - lo;
+#pragma unroll
+    for (int t = 0; t < kTaps; ++t) {
+      const int r = t / 3, s = t % 3;
+      const bool in = m < T.M && (uint32_t)(h0 + r) < (uint32_t)H && (uint32_t)(w0 + s) < (uint32_t)W;
+      const int row = in ? row0 + r * W + s : p_rows;
+      a_tap[t][i] = (uint32_t)(row * KB + lk * 16) ^ (KB == 256 ? ((uint32_t)row << 4) & 0xf0u : ((uint32_t)row << 3) & 0x70u);
+    }
+  }
+
+  Acc acc[BM][BN];
+#pragma unroll
+  for (int i = 0; i < BM; ++i)
+#pragma unroll
+    for (int j = 0; j < BN; ++j)
+#pragma unroll
+      for (int v = 0; v < (int)(sizeof(Acc) / 4); ++v) acc[i][j][v] = 0.f;
+  struct Frags { u32x4 w[NSUB][BN], x[NSUB][BM]; };
+  auto read_one = [&](auto I, auto N, uint32_t b_addr, Frags& f) {      // operand I of tap N, its filters at b_addr
+    constexpr int u = decltype(I)::value / (BN + BM), q = decltype(I)::value % (BN + BM), n = decltype(N)::value;
+    if constexpr (q < BN) f.w[u][q] = *(const u32x4*)(smem + (b_addr ^ (uint32_t)(u * SUBB)) + q * MF * KB);
+    else f.x[u][q - BN] = *(const u32x4*)(smem + (a_tap[n][q - BN] ^ (uint32_t)(u * SUBB)));
+  };
+  constexpr int NR = NSUB * (BN + BM), NMMA = NSUB * BM * BN;
+  auto mma_one = [&](auto I, const Frags& f) {
+    constexpr int u = decltype(I)::value / (BM * BN), i = decltype(I)::value / BN % BM, j = decltype(I)::value % BN;
+    acc[i][j] = MMA::run(f.w[u][j], f.x[u][i], acc[i][j]);
+  };
+
+  wait_loads_barrier<(ST - 1) * BW>();
+  if (prof && tid == 0) prof[1] = __builtin_readcyclecounter();
+  Frags f0, f1;
+  static_for<NR>([&](auto I) { read_one(I, std::integral_constant<int, 0>{}, b_lds, f0); });
+  uint32_t cur = 0;      // the stage the step being computed was read from
+  // One channel block.  Step t computes tap t, reads the operands of the next one and issues the filters ST steps ahead
+  // into the stage tap t was read from.  MORE blocks to come: the next one's patch is loaded in one go behind step 0's filters,
+  // since loads return in order: filters issued behind it arrive no earlier, and the patch often comes from far away.
+  uint32_t delta = p_bytes, next_lds = lds0 + p_bytes, p_soff = (uint32_t)((block0 + 1) * KB);
+  auto block = [&](auto MORE) {
+    constexpr bool more = decltype(MORE)::value;
+    static_for<kTaps>([&](auto TT) {
+      constexpr int t = decltype(TT)::value, n = (t + 1) % kTaps;
+      constexpr bool read = more || t + 1 < kTaps, load = more || t + ST < kTaps;
+      // loads younger than tap t + 1's filters: those of the taps up to t + ST - 1, and the patch loads (at least kPatchMin)
+      constexpr int younger = (more ? ST - 2 : (kTaps - 2 - t < ST - 2 ? (kTaps - 2 - t > 0 ? kTaps - 2 - t : 0) : ST - 2)) * BW + (more && t >= 1 && t <= ST - 1 ? kPatchMin : 0);
+      const Frags& fc = t % 2 == 0 ? f0 : f1;
+      Frags& fn = t % 2 == 0 ? f1 : f0;
+      const uint32_t nxt = cur + kStage < (uint32_t)(ST * kStage) ? cur + kStage : 0u, b_addr = b_lds + nxt;
+      if constexpr (read) wait_loads_barrier<younger>();
+      static_for<BW>([&](auto L) {
+        constexpr int l = decltype(L)::value, b = l * NR / BW, e = (l + 1) * NR / BW, mb = l * NMMA / BW, me = (l + 1) * NMMA / BW;
+        if constexpr (load) issue_filter(L, cur);
+        if constexpr (read)
+          static_for<e - b>([&](auto I) { read_one(std::integral_constant<int, b + decltype(I)::value>{}, std::integral_constant<int, n>{}, b_addr, fn); });
+        static_for<me - mb>([&](auto I) { mma_one(std::integral_constant<int, mb + decltype(I)::value>{}, fc); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if constexpr (more && t == 0) {
+        static_for<kPatchMin>([&](auto J) {
+          constexpr int j = decltype(J)::value;
+          issue_patch(j < p_loads - 1 ? j : p_loads - 1, p_soff, next_lds);
+        });
+        for (int j = kPatchMin; j < p_loads; ++j) issue_patch(j, p_soff, next_lds);
+      }
+      if constexpr (load) b_soff += (t + ST) % kTaps == kTaps - 1 ? wrap_b : c_bytes;
+      cur = nxt;
+      if constexpr (more) {
+#pragma unroll
+        for (int i = 0; i < BM; ++i) a_tap[t][i] += delta;
+      }
+    });
+    if constexpr (more) {
+      f0 = f1;
+      next_lds -= delta;
+      delta = 0u - delta;
+      p_soff += KB;
+    }
+  };
+  for (int b = 1; b < blocks; ++b) block(std::true_type{});
+  block(std::false_type{});
+
+  if (prof && tid == 0) prof[2] = __builtin_readcyclecounter();
+  if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
+  tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, prof);
+  if (prof && tid == 0) {
+    prof[3] = __builtin_readcyclecounter();
+    prof[6] = wall_clock64();
+  }
+}
+
 // ---- gather tile for channel counts that are not a multiple of the 16-byte vector -------------------
 // The same implicit GEMM with element-wise gathers (e.g. C = 3), D steps of loads kept in flight in registers ahead of
 // an LDS double buffer with rows padded by 16 bytes.
@@ -1336,6 +1534,12 @@ __device__ __forceinline__ void conv_tile_rows(const TD& T, const st_work_item i
 template <int CFG, int DT, class POL = PlainActs, class TD>
 __device__ __forceinline__ void run_cfg(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr TileShape s = kTileShapes[CFG];
+  if constexpr (DT != ST_DT_F32 && kPatchStages[CFG] > 0) {
+    if (T.k_order == kOrderPatch) {
+      conv_tile_patch<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, kPatchStages[CFG], DT, POL>(T, it, smem, prof);
+      return;
+    }
+  }
   conv_tile<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, s.D, DT, POL>(T, it, smem, prof);
 }
 template <int CFG, int DT, class POL = PlainActs, class TD>
