@@ -23,6 +23,7 @@ PROBE_SOURCES = ["st_bench_probe.hip"]
 # packed fp32 instructions are switched off for all device code (they are not needed here)
 CFLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-pthread", "-x", "hip",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          "-mllvm", "-amdgpu-kernarg-preload-count=8",      # kernel arguments arrive in registers: 0.3 us off every launch
           "-Wall", "-Wno-unused-command-line-argument"]
 NOISE = "is not a recognized feature for this target"
 

@@ -52,12 +52,8 @@ struct ChainArgs {
 constexpr int kChainGraceLooks = 24;             // looks at a dependency (0.3 us each) before the abort flag and the clock are looked at
 constexpr uint32_t kChainMaxPolls = 1u << 22;   // a poll takes a microsecond or so: seconds, far beyond any real wait
 
-// The op table and the queue never change while a launch runs: they are read through the constant address space, so
-// that every field is a scalar load.  (Through plain global pointers nothing counts as invariant inside the loop
-// over work items, which has stores, atomics and barriers in it, and every barrier of the tile code forces vector
-// re-loads of the op record.)
-typedef __attribute__((address_space(4))) const st_work_item ConstItem;
-typedef __attribute__((address_space(4))) const TenantDev ConstOp;
+// Nothing counts as invariant inside the loop over work items, which has stores, atomics and barriers in it: what never
+// changes while a launch runs is read through the constant address space.
 typedef __attribute__((address_space(4))) const ChainPrefetch ConstPrefetch;
 
 // Filters are read from memory exactly once per pass (376 MB for eight 53-layer networks: more than the memory-side cache

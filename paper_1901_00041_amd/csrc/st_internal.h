@@ -1,5 +1,6 @@
 // Internal types shared by the host planner and the device kernels (not part of the C ABI).
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 #include "st_conv.h"
@@ -49,35 +50,39 @@ constexpr int kPatchMin = 4;       // load instructions per wavefront and channe
 
 // Device-side tenant record, read through scalar loads by every workgroup of that tenant.
 struct TenantDev {
+  // read by every tile, most of it at once (tile_fields_loaded): three 64-byte lines
   const void* x;
   const void* w;
   void* y;
   const void* res;
-  float* ws;             // split-K partial tiles (nullptr when split_k == 1)
-  uint32_t* counters;    // one arrival counter per output tile (split-K only), zero between runs
   int32_t C, H, W, K, R, S, stride, pad;
-  int32_t P, Q, PQ, M, Kg;
+  int32_t Q, PQ, M, Kg;
   int32_t in_dtype, out_dtype, epilogue;
   int32_t cfg, split_k, k_steps, k_steps_per_split;
-  int32_t tiles_m, tiles_n;
   int32_t vec_ok;        // 1: C is a multiple of the 16-byte vector width, gathers use 16-byte loads
   int32_t step_dk, step_dr;   // one K step in the reduction index (r*S + s)*C + c: KT elements = step_dr filter rows of
                               //    S*C elements and step_dk elements more
   int32_t k_order;            // kOrder*: how conv_tile walks the reduction index
-  uint32_t tap_rows;          // kOrderChannels, kOrderPatch: bit r*S for every filter row r
+  uint32_t tap_rows;          // kOrderChannels: bit r*S for every filter row r
   int32_t patch_rows;         // kOrderPatch: most input pixels a tile's taps touch
   int32_t patch_loads;        // load instructions per wavefront and channel block
   int32_t patch_blocks;       // channel blocks per K slice
-  int32_t shift_c, shift_s;   // floor(n/d) = ((n * magic) >> 31) >> shift, for d = C and d = S
-  uint32_t magic_c, magic_s;
-  int32_t shift_r, shift_nvp; // same for d = R and d = row_pitch/16 (row tile only)
-  uint32_t magic_r, magic_nvp;
-  int32_t shift_pq, shift_q;  // same for d = P*Q and d = Q (pixel index -> image, row, column)
+  int32_t tiles_n;
+  int32_t shift_pq, shift_q;  // floor(n/d) = ((n * magic) >> 31) >> shift, for d = P*Q and d = Q (pixel index -> image, row, column)
   uint32_t magic_pq, magic_q;
   uint32_t x_bytes, w_bytes;  // buffer sizes for bounds-checked loads
   uint32_t y_bytes;           // size of y (and of the residual) in bytes
+  int32_t shift_c, shift_s;   // the same division for d = C and d = S
+  uint32_t magic_c, magic_s;
+  int32_t P;
+  // read by some
+  float* ws;             // split-K partial tiles (nullptr when split_k == 1)
+  uint32_t* counters;    // one arrival counter per output tile (split-K only), zero between runs
+  int32_t shift_r, shift_nvp; // same for d = R and d = row_pitch/16 (row tile only)
+  uint32_t magic_r, magic_nvp;
   int32_t rows_per_tile;      // row tile only: output rows per work item
   int32_t row_pitch;          // row tile only: bytes of one image row in LDS (padding included, multiple of 16)
+  int32_t tiles_m;
   // chain kernel only (st_chain.hip); the per-plan kernel ignores them
   int32_t chain_seq;          // sequence whose completion counter this op's work items wait on and bump
   uint32_t chain_need;        // work items of that sequence that must be complete before this op's may start
@@ -86,6 +91,7 @@ struct TenantDev {
   // [chain_dep_begin, chain_dep_begin + chain_dep_count) of the sequence's previous stage all hold the run's number
   uint32_t chain_flag_base, chain_dep_begin, chain_dep_count;
 };
+static_assert(offsetof(TenantDev, ws) == 192 && sizeof(TenantDev) == 256, "lines of the scalar cache");
 static_assert(sizeof(TenantDev) % 8 == 0, "TenantDev must keep pointer alignment in arrays");
 
 // Launchers implemented in st_kernels.hip.  All asynchronous; return the hipError_t as int.

@@ -24,8 +24,14 @@ __global__ __launch_bounds__(kThreads, 2) void st_conv_kernel(const TenantDev* _
                                                           const st_work_item* __restrict__ items,
                                                           uint64_t* __restrict__ prof_base) {
   __shared__ __attribute__((aligned(16))) char smem[kSmemBytes];
-  const st_work_item it = items[blockIdx.x];
-  const TenantDev& T = tenants[it.tenant];
+  ConstItem* ip = (ConstItem*)(items + blockIdx.x);
+  st_work_item it;
+  it.tenant = ip->tenant;
+  it.k_split_idx = ip->k_split_idx;
+  it.tile_m = ip->tile_m;
+  it.tile_n = ip->tile_n;
+  it.reserved = 0u;
+  ConstOp& T = *(ConstOp*)(tenants + it.tenant);
   uint64_t* prof = prof_base ? prof_base + (size_t)blockIdx.x * kProfSlots : nullptr;
   run_item<PlainActs>(T, it, smem, prof);
 }

@@ -26,7 +26,18 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// Records and work items that no launch in flight modifies: the constant address space makes every read a scalar load,
+// however many stores, atomics and barriers surround it.
+typedef __attribute__((address_space(4))) const st_work_item ConstItem;
+typedef __attribute__((address_space(4))) const TenantDev ConstOp;
 
+// Has the fields of a record that the start of a tile needs loaded by here, together.  Read one by one where they are first
+// needed, they cost a tile eight round trips of 75 ns, most of the 1300 clocks before its first load.
+__device__ __forceinline__ void tile_fields_loaded(ConstOp& T) {
+  asm volatile("" ::"s"(T.x), "s"(T.w), "s"(T.x_bytes), "s"(T.w_bytes), "s"(T.C), "s"(T.H), "s"(T.W), "s"(T.K), "s"(T.R), "s"(T.S), "s"(T.stride), "s"(T.pad),
+               "s"(T.Q), "s"(T.PQ), "s"(T.M), "s"(T.Kg), "s"(T.shift_pq), "s"(T.shift_q), "s"(T.magic_pq), "s"(T.magic_q), "s"(T.k_steps),
+               "s"(T.k_steps_per_split), "s"(T.k_order), "s"(T.epilogue), "s"(T.out_dtype), "s"(T.split_k));
+}
 
 // The thread's index in its workgroup, read afresh wherever a work item starts.  Inside a loop over work items the
 // compiler would otherwise compute everything that depends only on the thread index (lane geometry, staging rows of
@@ -223,8 +234,8 @@ __device__ __forceinline__ int residual_swizzle(int row) {
 template <int MT, int NT> constexpr int kResidualLoads = (MT * NT * 2 + 4095) / 4096;
 // Puts the residual tile's loads in flight, to LDS offset lds_base (of this wavefront: + 1024 * wave); needs
 // kResidualLoads * 4096 bytes there.
-template <int MT, int NT, class POL, class TD>
-__device__ __forceinline__ void stage_residual(const TD& T, int m0, int n0, int wave, int lane, uint32_t lds_base) {
+template <int MT, int NT, class POL>
+__device__ __forceinline__ void stage_residual(ConstOp& T, int m0, int n0, int wave, int lane, uint32_t lds_base) {
   constexpr int CH = NT / 8, RPI = 64 / CH;
   const u32x4 rr = rsrc_words(T.res, T.y_bytes);
   static_for<kResidualLoads<MT, NT>>([&](auto I) {
@@ -248,8 +259,8 @@ __device__ __forceinline__ void stage_residual(const TD& T, int m0, int n0, int 
 // res_lds >= 0: the tile of a 16-bit residual is on its way to smem + res_lds (stage_residual); else a residual is loaded
 // here, where its latency is in the open (128x128 tile, bf16, alone on its compute unit: 7900 clocks from the last MFMA to
 // the last store with the residual loaded here, 4500 with it staged; without a residual 5700 -> 3400 with packed conversions).
-template <int MT, int NT, int BM, int BN, int MF, int DT, int PASSES = 1, int CAP = kSmemBytes, class POL = PlainActs, class Acc, class TD>
-__device__ __forceinline__ void tile_epilogue(const TD& T, Acc (&acc)[BM][BN], int m0, int m_end, int n0, int wm0,
+template <int MT, int NT, int BM, int BN, int MF, int DT, int PASSES = 1, int CAP = kSmemBytes, class POL = PlainActs, class Acc>
+__device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], int m0, int m_end, int n0, int wm0,
                                               int wn0, int lrow, int lk, int tid, char* smem, uint64_t* prof = nullptr, int res_lds = -1) {
   constexpr int NG = (MF == 32) ? 4 : 1;
   const bool relu = (T.epilogue & ST_EPI_RELU) != 0u;
@@ -522,8 +533,8 @@ _Pragma("unroll")
 // ---- split-K hand-off ----------------------------------------------------------------------------
 // Publishes this workgroup's partial tile; the last workgroup to arrive sums all slices in index order into acc and
 // returns true (it goes on to the epilogue), the others return false.
-template <int MT, int NT, int BM, int BN, int MF, class Acc, class TD>
-__device__ __forceinline__ bool split_k_reduce(const TD& T, const st_work_item it, Acc (&acc)[BM][BN], int tid, char* smem, uint64_t* prof) {
+template <int MT, int NT, int BM, int BN, int MF, class Acc>
+__device__ __forceinline__ bool split_k_reduce(ConstOp& T, const st_work_item it, Acc (&acc)[BM][BN], int tid, char* smem, uint64_t* prof) {
   constexpr int NG = (MF == 32) ? 4 : 1;      // groups of 4 consecutive filters per block per lane
   {
     const int tile_id = (int)it.tile_m * T.tiles_n + (int)it.tile_n;
@@ -603,8 +614,8 @@ __device__ __forceinline__ bool split_k_reduce(const TD& T, const st_work_item i
 // LDS rows are KB bytes without padding: 16-byte chunk c of row r sits at position c ^ swz(r), so that the 16 rows an
 // MFMA operand read touches at a time fall into 16 different 16-byte bank groups; the swizzle is applied by choosing
 // which chunk each lane fetches (a lane's LDS position is fixed).
-template <int MT, int NT, int WPX, int WCH, int MF, int KB, int ST, int DT, class POL = PlainActs, class TD>
-__device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+template <int MT, int NT, int WPX, int WCH, int MF, int KB, int ST, int DT, class POL = PlainActs>
+__device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr int ES = ElemOf<DT>::ES;
   constexpr int VEC = 16 / ES;          // elements per 16-byte vector
   constexpr int KT = KB / ES;           // elements of K per step
@@ -625,6 +636,7 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
   static_assert(KB == 64 || KB == 128 || KB == 256, "swizzles exist for these row lengths");
   static_assert(MF == 32 || KB >= 128, "the 64-byte swizzle is for 32x32 blocks");
 
+  tile_fields_loaded(T);
   const int tid = work_thread_id();
   if (prof && tid == 0) {
     prof[0] = __builtin_readcyclecounter();
@@ -648,21 +660,33 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
   const int lr = lane / CH;
   const int swz = (KB == 256) ? ((4 * wave + lr) & 15) : (KB == 128) ? ((4 * (wave & 1) + (lr >> 1)) & 7) : ((lr >> 2) & 3);
   const int chunk = (lane % CH) ^ swz;
-  // per-thread patch rows: first image row and column, and element offset of the patch
+  // per-thread patch rows: first image row and column, and element offset of the patch (a 1x1 layer of stride 1 without
+  // padding needs no position in the image: output pixel m is input pixel m)
   int a_h0[AW], a_w0[AW], a_base[AW];
+  const bool same_pixels = T.k_order == kOrderLinear && T.stride == 1;
+  if (!same_pixels) {
 #pragma unroll
-  for (int i = 0; i < AW; ++i) {
-    const int m = m0 + (i * 4 + wave) * RPI + lr;
-    const bool ok = m < T.M;
-    const int mm = ok ? m : 0;
-    const int n = fast_div(mm, T.magic_pq, T.shift_pq);
-    const int pq = mm - n * T.PQ;
-    const int p = fast_div(pq, T.magic_q, T.shift_q);
-    const int q = pq - p * T.Q;
-    const int h0 = p * T.stride - T.pad;
-    a_w0[i] = q * T.stride - T.pad;
-    a_base[i] = (n * H + h0) * WC + a_w0[i] * C;
-    a_h0[i] = ok ? h0 : -(1 << 24);     // a dead row fails every bounds check
+    for (int i = 0; i < AW; ++i) {
+      const int m = m0 + (i * 4 + wave) * RPI + lr;
+      const bool ok = m < T.M;
+      const int mm = ok ? m : 0;
+      const int n = fast_div(mm, T.magic_pq, T.shift_pq);
+      const int pq = mm - n * T.PQ;
+      const int p = fast_div(pq, T.magic_q, T.shift_q);
+      const int q = pq - p * T.Q;
+      const int h0 = p * T.stride - T.pad;
+      a_w0[i] = q * T.stride - T.pad;
+      a_base[i] = (n * H + h0) * WC + a_w0[i] * C;
+      a_h0[i] = ok ? h0 : -(1 << 24);     // a dead row fails every bounds check
+    }
+  } else {
+    const int m = m0 + wave * RPI + lr;
+#pragma unroll
+    for (int i = 0; i < AW; ++i) {
+      a_w0[i] = 0;
+      a_base[i] = i == 0 ? m * C : a_base[i - 1] + 4 * RPI * C;
+      a_h0[i] = m + i * 4 * RPI < T.M ? 0 : -1;
+    }
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + (uint32_t)wave * 1024u;
 
@@ -928,8 +952,8 @@ __device__ __forceinline__ void conv_tile(const TD& T, const st_work_item it, ch
 // 444 -> 368 beside a second workgroup, 128x64 702 -> 550, 64x128 695 -> 625; first operands 3700 -> 2370.  What bounds it now:
 // alone the LDS reads and the barrier, beside a second one the MFMAs (512 of 550 clocks at 128x64).
 // LDS: [patch][patch, when there is more than one channel block][ST filter steps][NT][KB].
-template <int MT, int NT, int WPX, int WCH, int MF, int KB, int ST, int DT, class POL = PlainActs, class TD>
-__device__ __forceinline__ void conv_tile_patch(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+template <int MT, int NT, int WPX, int WCH, int MF, int KB, int ST, int DT, class POL = PlainActs>
+__device__ __forceinline__ void conv_tile_patch(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr int ES = ElemOf<DT>::ES;
   constexpr int VEC = 16 / ES;
   constexpr int CH = KB / 16;
@@ -945,6 +969,7 @@ __device__ __forceinline__ void conv_tile_patch(const TD& T, const st_work_item 
   typedef typename MMA::Acc Acc;
   static_assert(ES == 2 && (KB == 128 || KB == 256) && NT % (4 * RPI) == 0 && kTaps == 9 && ST < kTaps, "patch tile shape");
 
+  tile_fields_loaded(T);
   const int tid = work_thread_id();
   if (prof && tid == 0) {
     prof[0] = __builtin_readcyclecounter();
@@ -1118,8 +1143,8 @@ __device__ __forceinline__ void conv_tile_patch(const TD& T, const st_work_item 
 // ---- gather tile for channel counts that are not a multiple of the 16-byte vector -------------------
 // The same implicit GEMM with element-wise gathers (e.g. C = 3), D steps of loads kept in flight in registers ahead of
 // an LDS double buffer with rows padded by 16 bytes.
-template <int MT, int NT, int WPX, int WCH, int MF, int KB, int D, int DT, class POL = PlainActs, class TD>
-__device__ __forceinline__ void conv_tile_gather(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+template <int MT, int NT, int WPX, int WCH, int MF, int KB, int D, int DT, class POL = PlainActs>
+__device__ __forceinline__ void conv_tile_gather(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr int ES = ElemOf<DT>::ES;
   constexpr int VEC = 16 / ES;          // elements per 16-byte vector
   constexpr int KT = KB / ES;           // elements of K per step
@@ -1336,8 +1361,8 @@ __device__ __forceinline__ u32x4 window128(const u32x4& lo, const u32x4& hi, int
 // 64 filters are copied once into an LDS array [filter][r][32] padded with zeros, and the MFMA operands
 // are assembled from LDS.  K is laid out as r*32 + (s*C + c).  Eligibility is decided by the planner:
 // 16-bit types, 8 <= S*C <= 32, W*C*2 a multiple of 16, stride*C even, LDS footprint.
-template <int DT, class POL = PlainActs, class TD>
-__device__ __forceinline__ void conv_tile_rows(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+template <int DT, class POL = PlainActs>
+__device__ __forceinline__ void conv_tile_rows(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr int MT = 128, NT = 64, MF = 32, WM = 64, WN = 32, BM = 2, BN = 1, KR = 32;
   const int RT = T.rows_per_tile;                    // output rows per work item (1..kRowsPerTile)
   constexpr int EPI_PASSES = 2;
@@ -1531,8 +1556,8 @@ __device__ __forceinline__ void conv_tile_rows(const TD& T, const st_work_item i
   }
 }
 
-template <int CFG, int DT, class POL = PlainActs, class TD>
-__device__ __forceinline__ void run_cfg(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+template <int CFG, int DT, class POL = PlainActs>
+__device__ __forceinline__ void run_cfg(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr TileShape s = kTileShapes[CFG];
   if constexpr (DT != ST_DT_F32 && kPatchStages[CFG] > 0) {
     if (T.k_order == kOrderPatch) {
@@ -1542,16 +1567,14 @@ __device__ __forceinline__ void run_cfg(const TD& T, const st_work_item it, char
   }
   conv_tile<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, s.D, DT, POL>(T, it, smem, prof);
 }
-template <int CFG, int DT, class POL = PlainActs, class TD>
-__device__ __forceinline__ void run_gather(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+template <int CFG, int DT, class POL = PlainActs>
+__device__ __forceinline__ void run_gather(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr TileShape s = kTileShapes[CFG];
   conv_tile_gather<s.MT, s.NT, s.WPX, s.WCH, s.MF, 128, CFG == 1 ? 2 : 4, DT, POL>(T, it, smem, prof);
 }
 
-// TD is TenantDev, or TenantDev qualified with the constant address space (records that no launch in flight
-// modifies: every field read is then a scalar load, however many stores, atomics and barriers surround it).
-template <int DT, class POL = PlainActs, class TD>
-__device__ __forceinline__ void run_dtype(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+template <int DT, class POL = PlainActs>
+__device__ __forceinline__ void run_dtype(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   if (T.vec_ok) {
     switch (T.cfg) {
       case 0: run_cfg<0, DT, POL>(T, it, smem, prof); break;
@@ -1635,8 +1658,8 @@ __device__ __forceinline__ u32x4 maxpool_vector(const void* __restrict__ xv, uin
 }
 
 // One max-pool work item: kThreads output vectors, stored write-through.
-template <int DT, int AUX, class TD>
-__device__ __forceinline__ void pool_item(const TD& T, const st_work_item it) {
+template <int DT, int AUX>
+__device__ __forceinline__ void pool_item(ConstOp& T, const st_work_item it) {
   const int64_t idx = (int64_t)it.tile_m * kThreads + work_thread_id();
   if (idx >= (int64_t)T.M) return;
   const u32x4 v = maxpool_vector<DT, AUX>(T.x, T.x_bytes, idx, T.H, T.W, T.C, T.P, T.Q, T.R, T.stride, T.pad);
@@ -1644,8 +1667,8 @@ __device__ __forceinline__ void pool_item(const TD& T, const st_work_item it) {
 }
 
 // One work item of a plan or chain: a tile of a convolution, or (chains only) a max-pool item.
-template <class POL, class TD>
-__device__ __forceinline__ void run_item(const TD& T, const st_work_item it, char* smem, uint64_t* prof) {
+template <class POL>
+__device__ __forceinline__ void run_item(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   if (T.cfg == kChainPoolCfg) {
     switch (T.in_dtype) {
       case ST_DT_BF16: pool_item<ST_DT_BF16, POL::kActAux>(T, it); break;
