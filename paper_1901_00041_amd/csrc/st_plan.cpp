@@ -98,13 +98,21 @@ static const ItemCosts kCosts[3][2] = {
     {{{4800, 2300, 2400, 2000, 2300, 3250, 0}, {1250, 620, 680, 380, 590, 560, 0}, {4700, 2400, 2500, 1700, 1400, 1230, 0}},
      {{2700, 1500, 1550, 1300, 1600, 2200, 0}, {820, 465, 445, 310, 410, 375, 0}, {3900, 2060, 2030, 1500, 1240, 1120, 0}}}};
 static const double kRowStageCost = 6500.0;     // row tile: copying image rows and filters into LDS
-static const double kGatherStepCost[kNumTileCfgs] = {0, 3470.0, 0, 2100.0, 0, 0, 0};   // element-wise gathers: bound by the texture addresser
-static const double kGatherFirstCost = 19000.0;
+// any channel count (conv_tile_gather) [fp32 operands]: bound by the texture addresser, which takes unaligned vectors apart
+static const double kGatherStepCost[2][kNumTileCfgs] = {{0, 2600.0, 0, 1550.0, 0, 0, 0}, {0, 3600.0, 0, 2000.0, 0, 0, 0}};
+static const double kGatherPartCost[kNumTileCfgs] = {0, 4000.0, 0, 1900.0, 0, 0, 0};   // more if the step crosses a filter row
+static const double kGatherFirstCost = 7000.0;
 static const double kSplitCost = 3600.0, kSplitPerElem = 0.6;               // hand-off, grows with the tile
 static const double kSplitRoundCost = 2000.0, kSplitRoundPerElem = 0.25;    // per further batch of slices read back
 static const int kSlots = 400;                  // two workgroups resident per compute unit (512), derated: the launch's
                                                 // tail and the dispatch ramp leave some of them empty
 static const int kSplitChoices[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+
+// One K step of conv_tile_gather; the share of steps that cross a filter row grows as filter rows get shorter.
+static double gather_step_cost(const st_conv_desc& d, int cfg) {
+  const double kt = 128.0 / elem_size(d.in_dtype), crossing = d.R == 1 ? 0.0 : std::min(1.0, kt / ((double)d.S * d.C));
+  return kGatherStepCost[d.in_dtype == ST_DT_F32 ? 1 : 0][cfg] + crossing * kGatherPartCost[cfg];
+}
 
 struct Option {
   int cfg, split, steps_per_split, rows_per_tile;
@@ -294,7 +302,7 @@ static Option make_option(const st_conv_desc& d, int64_t M, int64_t Ng, int64_t 
   const ItemCosts& c = kCosts[d.in_dtype == ST_DT_F32 ? kCosts32 : patch ? kCostsPatch : kCosts16][alone ? 1 : 0];
   const double elems = (double)kTileShapes[cfg].MT * kTileShapes[cfg].NT;
   const int batch = elems > 4096 ? 4 : 8;      // slices read back at a time
-  o.item_time = (vec_ok ? c.first[cfg] : kGatherFirstCost) + per * (vec_ok ? c.step[cfg] : kGatherStepCost[cfg]) + c.epi[cfg] +
+  o.item_time = (vec_ok ? c.first[cfg] : kGatherFirstCost) + per * (vec_ok ? c.step[cfg] : gather_step_cost(d, cfg)) + c.epi[cfg] +
                 (split > 1 ? kSplitCost + kSplitPerElem * elems + (kSplitRoundCost + kSplitRoundPerElem * elems) * ((split - 1) / batch) : 0.0);
   o.area = o.item_time * (double)o.items;
   return o;
@@ -674,7 +682,7 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
         const st_tenant_info& ti = p->info[t];
         const int last_steps = ti.k_steps - (ti.split_k - 1) * ti.k_steps_per_split;
         const ItemCosts& c = kCosts[descs[t].in_dtype == ST_DT_F32 ? 1 : 0][0];
-        const double step = vector_ok(descs[t]) || ti.row_tiled ? c.step[ti.tile_cfg] : kGatherStepCost[ti.tile_cfg];
+        const double step = vector_ok(descs[t]) || ti.row_tiled ? c.step[ti.tile_cfg] : gather_step_cost(descs[t], ti.tile_cfg);
         auto cost = [&](int steps) { return (int64_t)(steps * step + c.epi[ti.tile_cfg]) * std::max(1, ti.rows_per_tile); };
         if (ti.split_k == 1 || last_steps == ti.k_steps_per_split) {
           runs.push_back({t, -1, cost(ti.split_k == 1 ? ti.k_steps : ti.k_steps_per_split), ti.item_count});

@@ -1141,8 +1141,12 @@ __device__ __forceinline__ void conv_tile_patch(ConstOp& T, const st_work_item i
 }
 
 // ---- gather tile for channel counts that are not a multiple of the 16-byte vector -------------------
-// The same implicit GEMM with element-wise gathers (e.g. C = 3), D steps of loads kept in flight in registers ahead of
-// an LDS double buffer with rows padded by 16 bytes.
+// The same implicit GEMM for any C, D steps of loads kept in flight in registers ahead of an LDS double buffer with rows
+// padded by 16 bytes.  A vector of the reduction index is contiguous in memory as long as it stays inside one filter row,
+// and is then one 16-byte load from an element-aligned address; only vectors that cross into the next filter row, into the
+// padding or past the end are put together element by element, by the wavefronts that have any.
+// Bound by the texture addresser either way: a 64x64 bf16 step of C = 1023 takes 1140 clocks (3530 with every element loaded
+// by itself), of 5x5 with C = 239 1490 (3460), of 3x3 with C = 67, where a third of the steps cross a row, 1940 (2560).
 template <int MT, int NT, int WPX, int WCH, int MF, int KB, int D, int DT, class POL = PlainActs>
 __device__ __forceinline__ void conv_tile_gather(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr int ES = ElemOf<DT>::ES;
@@ -1175,7 +1179,7 @@ __device__ __forceinline__ void conv_tile_gather(ConstOp& T, const st_work_item 
   const int row0 = tid / CH;
   const int m0 = (int)it.tile_m * MT;
   const int n0 = (int)it.tile_n * NT;
-  const int C = T.C, H = T.H, W = T.W, S = T.S, Kg = T.Kg;
+  const int C = T.C, H = T.H, W = T.W, R = T.R, S = T.S, Kg = T.Kg;
   const __amdgpu_buffer_rsrc_t rx = make_rsrc(T.x, T.x_bytes);
   const __amdgpu_buffer_rsrc_t rw = make_rsrc(T.w, T.w_bytes);
 
@@ -1211,6 +1215,16 @@ __device__ __forceinline__ void conv_tile_gather(ConstOp& T, const st_work_item 
     b_off[i] = b_ok[i] ? (n0 + row) * Kg : 0;
   }
 
+  // elements of a filter row (s*C + c) that lie inside the image: [a_lo, a_hi)
+  const int SC = S * C, WC = W * C;
+  int a_lo[A_IT], a_hi[A_IT];
+#pragma unroll
+  for (int i = 0; i < A_IT; ++i) {
+    const int s_lo = a_w0[i] < 0 ? -a_w0[i] : 0, s_hi = W - a_w0[i];
+    a_lo[i] = (s_lo < S ? s_lo : S) * C;
+    a_hi[i] = (s_hi < 0 ? 0 : s_hi < S ? s_hi : S) * C;
+  }
+
   // position of the next vector this thread will fetch, in the reduction index k = (r*S + s)*C + c
   int k_elem = ks_begin * KT + chunk * VEC;
 
@@ -1218,40 +1232,55 @@ __device__ __forceinline__ void conv_tile_gather(ConstOp& T, const st_work_item 
 
   // Issue the global loads of the next K step into one register slot, then advance the K position.
   auto issue = [&](u32x4 (&qa)[A_IT], u32x4 (&qb)[B_IT]) {
-    // element-wise gather: every element of the vector has its own (r, s, c)
-    uint32_t ea[A_IT][VEC], eb[B_IT][VEC];
+    const int kr = fast_div(fast_div(k_elem, T.magic_c, T.shift_c), T.magic_s, T.shift_s);
+    const int kk = k_elem - kr * SC, koff = kr * WC + kk;
+    const bool whole_k = k_elem + VEC <= klimit, one_row = whole_k & (kk + VEC <= SC);
+    bool a_part[A_IT], b_part = !whole_k & (k_elem < klimit), any = b_part;
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const int ke = k_elem + e;
-      const bool kin = ke < klimit;
-      const int rs = fast_div(ke, T.magic_c, T.shift_c);
-      const int kc = ke - rs * C;
-      const int kr = fast_div(rs, T.magic_s, T.shift_s);
-      const int ksx = rs - kr * S;
-      const int koff = (kr * W + ksx) * C + kc;
+    for (int i = 0; i < A_IT; ++i) {
+      const bool in = one_row & ((unsigned)(a_h0[i] + kr) < (unsigned)H) & (kk >= a_lo[i]) & (kk + VEC <= a_hi[i]);
+      // anything of it inside, though not all as one piece
+      a_part[i] = !in & (k_elem < klimit) & (a_h0[i] + R > 0) & (!one_row | (((unsigned)(a_h0[i] + kr) < (unsigned)H) & (kk < a_hi[i]) & (kk + VEC > a_lo[i])));
+      any |= a_part[i];
+      qa[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(in ? (uint32_t)(a_base[i] + koff) * ES : kInvalidOffset), 0, POL::kActAux);
+    }
+#pragma unroll
+    for (int i = 0; i < B_IT; ++i)
+      qb[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(b_ok[i] & whole_k ? (uint32_t)(b_off[i] + k_elem) * ES : kInvalidOffset), 0, 0);
+    if (__builtin_expect(__ballot(any) != 0, 0)) {
+      uint32_t ea[A_IT][VEC], eb[B_IT][VEC];
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        const int ke = k_elem + e;
+        const bool kin = ke < klimit;
+        const bool next = kk + e >= SC;                   // in a later filter row
+        const int er = next ? fast_div(fast_div(ke, T.magic_c, T.shift_c), T.magic_s, T.shift_s) : kr;
+        const int ek = ke - er * SC;
+#pragma unroll
+        for (int i = 0; i < A_IT; ++i) {
+          const bool ok = a_part[i] & kin & ((unsigned)(a_h0[i] + er) < (unsigned)H) & (ek >= a_lo[i]) & (ek < a_hi[i]);
+          const uint32_t off = ok ? (uint32_t)(a_base[i] + er * WC + ek) * ES : kInvalidOffset;
+          if constexpr (ES == 4) ea[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, (int)off, 0, POL::kActAux);
+          else ea[i][e] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rx, (int)off, 0, POL::kActAux);
+        }
+#pragma unroll
+        for (int i = 0; i < B_IT; ++i) {
+          const uint32_t off = (b_ok[i] & b_part & kin) ? (uint32_t)(b_off[i] + ke) * ES : kInvalidOffset;
+          if constexpr (ES == 4) eb[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rw, (int)off, 0, 0);
+          else eb[i][e] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (int)off, 0, 0);
+        }
+      }
+      // a vector is either whole or gathered; the other kind's loads were out of range and gave zeros
 #pragma unroll
       for (int i = 0; i < A_IT; ++i) {
-        const bool ok = kin & ((unsigned)(a_h0[i] + kr) < (unsigned)H) & ((unsigned)(a_w0[i] + ksx) < (unsigned)W);
-        const uint32_t off = ok ? (uint32_t)(a_base[i] + koff) * ES : kInvalidOffset;
-        if constexpr (ES == 4) ea[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, (int)off, 0, POL::kActAux);
-        else ea[i][e] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rx, (int)off, 0, POL::kActAux);
+        if constexpr (ES == 4) qa[i] |= u32x4{ea[i][0], ea[i][1], ea[i][2], ea[i][3]};
+        else qa[i] |= u32x4{ea[i][0] | (ea[i][1] << 16), ea[i][2] | (ea[i][3] << 16), ea[i][4] | (ea[i][5] << 16), ea[i][6] | (ea[i][7] << 16)};
       }
 #pragma unroll
       for (int i = 0; i < B_IT; ++i) {
-        const uint32_t off = (b_ok[i] & kin) ? (uint32_t)(b_off[i] + ke) * ES : kInvalidOffset;
-        if constexpr (ES == 4) eb[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rw, (int)off, 0, 0);
-        else eb[i][e] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (int)off, 0, 0);
+        if constexpr (ES == 4) qb[i] |= u32x4{eb[i][0], eb[i][1], eb[i][2], eb[i][3]};
+        else qb[i] |= u32x4{eb[i][0] | (eb[i][1] << 16), eb[i][2] | (eb[i][3] << 16), eb[i][4] | (eb[i][5] << 16), eb[i][6] | (eb[i][7] << 16)};
       }
-    }
-#pragma unroll
-    for (int i = 0; i < A_IT; ++i) {
-      if constexpr (ES == 4) qa[i] = u32x4{ea[i][0], ea[i][1], ea[i][2], ea[i][3]};
-      else qa[i] = u32x4{ea[i][0] | (ea[i][1] << 16), ea[i][2] | (ea[i][3] << 16), ea[i][4] | (ea[i][5] << 16), ea[i][6] | (ea[i][7] << 16)};
-    }
-#pragma unroll
-    for (int i = 0; i < B_IT; ++i) {
-      if constexpr (ES == 4) qb[i] = u32x4{eb[i][0], eb[i][1], eb[i][2], eb[i][3]};
-      else qb[i] = u32x4{eb[i][0] | (eb[i][1] << 16), eb[i][2] | (eb[i][3] << 16), eb[i][4] | (eb[i][5] << 16), eb[i][6] | (eb[i][7] << 16)};
     }
     k_elem += KT;
   };
