@@ -205,9 +205,8 @@ st_status st_conv_plan_rebind(st_plan* plan, int32_t tenant, const void* x, cons
 
 /* All tenants' pointers at once, from descs[t].x/w/y/residual (everything else in descs is ignored; the
  * plan keeps its shapes).  Nothing happens when no pointer differs from the plan's current ones.
- * Otherwise the device table is updated by one copy ordered on hip_stream, from pinned memory the plan
- * owns: runs queued on that stream before the call still see the old pointers, runs queued after it the
- * new ones.  Runs of this plan on other streams must not overlap the call. */
+ * Otherwise the device table is updated by one small launch on hip_stream: runs queued on that stream
+ * before the call still see the old pointers, runs queued after it the new ones.  Runs of this plan on other streams must not overlap the call. */
 st_status st_conv_plan_rebind_all(st_plan* plan, const st_conv_desc* descs, int32_t n_tenants, void* hip_stream);
 
 /* Plan cache for dynamically arriving work (Section 4: the scheduler merges whichever kernels are ready,

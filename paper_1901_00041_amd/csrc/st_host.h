@@ -42,10 +42,4 @@ struct st_plan {
   char* d_workspace = nullptr;              // split-K counters, then all tenants' partial tiles
   hipEvent_t ev_fork = nullptr;
   std::vector<hipEvent_t> ev_join;          // one per stream slot used by space-only
-  // pinned staging slots for stream-ordered uploads of the tenant table (st_conv_plan_rebind_all)
-  static constexpr int kStageSlots = 4;
-  st::TenantDev* h_stage[kStageSlots] = {nullptr, nullptr, nullptr, nullptr};
-  hipEvent_t ev_stage[kStageSlots] = {nullptr, nullptr, nullptr, nullptr};
-  bool stage_used[kStageSlots] = {false, false, false, false};
-  int stage_next = 0;
 };

@@ -125,6 +125,8 @@ int launch_empty(void* stream);
 constexpr int64_t kNoallocScratchBytes = (int64_t)32 << 20;
 int noalloc_scratch(void** out_ptr);
 int launch_poke(const void* host_src, int64_t bytes, void* dst_dev, void* stream);
+// the four tensor pointers of n records -> device table, through kernel arguments
+int launch_bind(const TenantDev* host, int n, TenantDev* table_dev, void* stream);
 int launch_zero(void* dst_dev, int64_t bytes, void* stream);
 int launch_copy(const void* src, void* dst, int64_t bytes, void* stream);
 int launch_maxpool(const void* x, void* y, int N, int H, int W, int C, int P, int Q, int win, int stride,

@@ -110,9 +110,8 @@ __global__ __launch_bounds__(256) void st_maxpool_kernel(const void* __restrict_
 int launch_conv(const TenantDev* tenants_dev, const st_work_item* items_dev, int64_t n_items, void* stream,
                 uint64_t* prof_dev) {
   if (n_items <= 0) return 0;
-  hipLaunchKernelGGL(st_conv_kernel, dim3((unsigned)n_items), dim3(kThreads), 0, (hipStream_t)stream, tenants_dev, items_dev,
-                     prof_dev);
-  return (int)hipGetLastError();
+  void* args[] = {&tenants_dev, &items_dev, &prof_dev};
+  return (int)hipLaunchKernel((const void*)st_conv_kernel, dim3((unsigned)n_items), dim3(kThreads), args, 0, (hipStream_t)stream);
 }
 
 // Plain 16-byte-per-lane copy: the reference kernel for scaling hardware traffic counters.
@@ -143,6 +142,39 @@ struct PokePayload { u32x4 v[kPokeVecs]; };
 __global__ __launch_bounds__(256) void st_poke_kernel(PokePayload p, u32x4* __restrict__ dst, int nvec) {
   const int i = threadIdx.x;
   if (i < nvec) dst[i] = p.v[i];
+}
+
+// New tensor pointers for a plan's tenants, in stream order.  As a launch the update costs about what any launch costs;
+// as a copy from pinned memory it took a copy routine with its barriers, and an event for every reuse of the memory (a
+// step of 8 arriving tenants 13.4 -> 9.7 us).  The payload is copied with the arguments, so there is a small form too.
+constexpr int kBindSmall = 16, kBindLarge = 112;
+template <int N>
+struct BindPayload { u32x4 v[2 * N]; };
+static_assert(offsetof(TenantDev, x) == 0 && offsetof(TenantDev, res) == 24, "the pointers are a record's first 32 bytes");
+
+template <int N>
+__global__ __launch_bounds__(256) void st_bind_kernel(BindPayload<N> p, TenantDev* __restrict__ table, int n) {
+  const int i = threadIdx.x;
+  if (i < 2 * n) ((u32x4*)(table + (i >> 1)))[i & 1] = p.v[i];
+}
+
+template <int N>
+static hipError_t bind(const TenantDev* host, int n, TenantDev* table, hipStream_t stream) {
+  BindPayload<N> p;
+  for (int i = 0; i < n; ++i) std::memcpy(&p.v[2 * i], host + i, 32);
+  std::memset(&p.v[2 * n], 0, (size_t)(N - n) * 32);
+  void* args[] = {&p, &table, &n};
+  return hipLaunchKernel((const void*)st_bind_kernel<N>, dim3(1), dim3(256), args, 0, stream);
+}
+
+int launch_bind(const TenantDev* host, int n, TenantDev* table_dev, void* stream) {
+  for (int done = 0; done < n; done += kBindLarge) {
+    const int m = n - done < kBindLarge ? n - done : kBindLarge;
+    const hipError_t e = m <= kBindSmall ? bind<kBindSmall>(host + done, m, table_dev + done, (hipStream_t)stream)
+                                         : bind<kBindLarge>(host + done, m, table_dev + done, (hipStream_t)stream);
+    if (e != hipSuccess) return (int)e;
+  }
+  return 0;
 }
 
 __global__ __launch_bounds__(256) void st_zero_kernel(u32x4* __restrict__ dst, int64_t nvec) {

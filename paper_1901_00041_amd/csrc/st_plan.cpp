@@ -459,12 +459,6 @@ static double modelled(const std::vector<std::vector<Option>>& opts, const std::
 static void destroy_device(st_plan* p) {
   if (p->d_arena) (void)hipFree(p->d_arena);
   p->d_arena = nullptr;
-  for (int i = 0; i < st_plan::kStageSlots; ++i) {
-    if (p->h_stage[i]) (void)hipHostFree(p->h_stage[i]);
-    if (p->ev_stage[i]) (void)hipEventDestroy(p->ev_stage[i]);
-    p->h_stage[i] = nullptr;
-    p->ev_stage[i] = nullptr;
-  }
   if (p->ev_fork) (void)hipEventDestroy(p->ev_fork);
   for (hipEvent_t e : p->ev_join)
     if (e) (void)hipEventDestroy(e);
@@ -1127,26 +1121,7 @@ extern "C" st_status st_conv_plan_rebind_all(st_plan* plan, const st_conv_desc* 
     T.x = d.x; T.w = d.w; T.y = d.y;
     if (T.epilogue & ST_EPI_RESIDUAL) T.res = d.residual;
   }
-  if (!plan->host_only && n_tenants > 0) {
-    // stream-ordered upload from a pinned slot; a slot is reused only after the copy that read it has finished
-    const int slot = plan->stage_next;
-    const size_t bytes = next.size() * sizeof(TenantDev);
-    if (!plan->h_stage[slot]) ST_HIP(hipHostMalloc((void**)&plan->h_stage[slot], bytes, hipHostMallocDefault));
-    if (!plan->ev_stage[slot]) ST_HIP(hipEventCreateWithFlags(&plan->ev_stage[slot], hipEventDisableTiming));
-    if (plan->stage_used[slot]) ST_HIP(hipEventSynchronize(plan->ev_stage[slot]));
-    std::memcpy(plan->h_stage[slot], next.data(), bytes);
-    ST_HIP(hipMemcpyAsync(plan->d_tenants, plan->h_stage[slot], bytes, hipMemcpyHostToDevice, (hipStream_t)hip_stream));
-    plan->stage_next = (slot + 1) % st_plan::kStageSlots;
-    plan->stage_used[slot] = true;      // the copy is queued: from here on the slot must not be rewritten before it ran
-    plan->tenants.swap(next);
-    for (int t = 0; t < n_tenants; ++t) {
-      const TenantDev& T = plan->tenants[t];
-      st_conv_desc& mine = plan->descs[t];
-      mine.x = T.x; mine.w = T.w; mine.y = T.y; mine.residual = T.res;
-    }
-    ST_HIP(hipEventRecord(plan->ev_stage[slot], (hipStream_t)hip_stream));
-    return ST_OK;
-  }
+  if (!plan->host_only) ST_HIP((hipError_t)launch_bind(next.data(), n_tenants, plan->d_tenants, hip_stream));
   plan->tenants.swap(next);
   for (int t = 0; t < n_tenants; ++t) {
     const TenantDev& T = plan->tenants[t];

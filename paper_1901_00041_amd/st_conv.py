@@ -268,7 +268,10 @@ def _check(st, where):
 
 
 def st_conv_run(plan: Plan, stream=None) -> None:
-    _check(lib().st_conv_run(plan.handle, _stream(stream)), "st_conv_run")
+    # spelled out: a small launch takes the host about three microseconds, and calls and type checks here are tenths of one
+    st = (_lib or lib()).st_conv_run(plan.handle, stream if stream is None or type(stream) is int else stream.cuda_stream)
+    if st != ST_OK:
+        raise StError(st, "st_conv_run")
 
 
 def st_conv_run_noalloc(plan: Plan, stream=None) -> None:
