@@ -154,7 +154,7 @@ int64_t st_conv_noalloc_max_bytes(void);
  * fused work-list order: [0] shader-clock at start, [1] first operands staged, [2] K loop done,
  * [3] tile stored (0 for split-K slices that did not do the final reduction), [4] 100 MHz wall clock
  * at start, [5] hardware id (XCC id << 32 | HW_ID register), [6] 100 MHz wall clock at the end,
- * [7] unused. */
+ * [7] unused (0). */
 st_status st_conv_run_profiled(const st_plan* plan, void* hip_stream, uint64_t* stamps, int64_t capacity);
 
 /* Per-tenant timing of one fused launch (the per-kernel monitoring Section 4 asks of the scheduler; the
@@ -330,7 +330,8 @@ st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const st_plan_opt
  * time (queue them on one stream). */
 st_status st_chain_run(st_chain* chain, void* hip_stream);
 /* The same with in-kernel time stamps per queue entry (HOST buffer of 8 uint64 per entry, as st_conv_run_profiled;
- * slot [7] = ticks of the 100 MHz clock the entry waited for its dependency).  Synchronous diagnostic. */
+ * a max-pool entry leaves [1] and [2] at 0; slot [7] = ticks of the 100 MHz clock the entry waited for its dependency,
+ * 0 where a launch holds one stage).  Synchronous diagnostic. */
 st_status st_chain_run_profiled(st_chain* chain, void* hip_stream, uint64_t* stamps, int64_t capacity);
 /* Waits for the device, then *aborted = 1 if any run since the last call gave up on a dependency wait, or if the
  * last run did not complete every work item (an XCD that received no workgroups); the chain is reset. */

@@ -254,7 +254,6 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
       }
       while (pf < pf_end && ((ConstPrefetch*)a.prefetch)[pf].flag_base <= T.chain_flag_base) ++pf;      // too late to prefetch these
       asm volatile("" ::"s"(rec_touch));
-      if (T.cfg == kChainPoolCfg && prof && tid == 0) prof[4] = wall_clock64();
       run_item<CoherentActs>(T, it, smem, prof);
       // Completion.  Outputs were stored write-through; channel counts that are not a multiple of 8 take an epilogue
       // with plain stores and need the release fence (write-back of the L2).
@@ -273,10 +272,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
         // entry's work it sits in front of the first operand loads in the in-order memory counter; issued before the
         // completion signal (even as early as the end of the K loop: measured) it delays every dependant.
         if (claiming) next = chain_claim(a, 0u, qb, qe);
-        if (prof) {
-          prof[7] = waited;
-          if (T.cfg == kChainPoolCfg) prof[6] = wall_clock64();
-        }
+        if (prof) prof[7] = waited;
       }
     }
   }

@@ -49,6 +49,17 @@ __device__ __forceinline__ int work_thread_id() {
   return t;
 }
 
+// The stamps every work item of a profiled launch leaves (one thread calls; slots as st_conv_run_profiled documents them).
+__device__ __forceinline__ void stamp_start(uint64_t* prof) {
+  prof[0] = __builtin_readcyclecounter();
+  prof[4] = wall_clock64();
+  prof[5] = ((uint64_t)__builtin_amdgcn_s_getreg(0x1814) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(0xF804);
+}
+__device__ __forceinline__ void stamp_end(uint64_t* prof) {
+  prof[3] = __builtin_readcyclecounter();
+  prof[6] = wall_clock64();
+}
+
 template <int DT> struct ElemOf;
 template <> struct ElemOf<ST_DT_F32> { static constexpr int ES = 4; };
 template <> struct ElemOf<ST_DT_BF16> { static constexpr int ES = 2; };
@@ -261,7 +272,7 @@ __device__ __forceinline__ void stage_residual(ConstOp& T, int m0, int n0, int w
 // the last store with the residual loaded here, 4500 with it staged; without a residual 5700 -> 3400 with packed conversions).
 template <int MT, int NT, int BM, int BN, int MF, int DT, int PASSES = 1, int CAP = kSmemBytes, class POL = PlainActs, class Acc>
 __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], int m0, int m_end, int n0, int wm0,
-                                              int wn0, int lrow, int lk, int tid, char* smem, uint64_t* prof = nullptr, int res_lds = -1) {
+                                              int wn0, int lrow, int lk, int tid, char* smem, int res_lds = -1) {
   constexpr int NG = (MF == 32) ? 4 : 1;
   const bool relu = (T.epilogue & ST_EPI_RELU) != 0u;
   const bool has_res = (T.epilogue & ST_EPI_RESIDUAL) != 0u;
@@ -316,7 +327,6 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
           *(uint2*)(smem + row * PITCHB + chl * 2) = pk;
         }
     __syncthreads();
-    if (prof && tid == 0) prof[7] = __builtin_readcyclecounter();
     constexpr int NV = NT / 8;
     constexpr int IT = (MT * NV + kThreads - 1) / kThreads;
 #pragma unroll
@@ -382,7 +392,6 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
             *(f32x4*)(sC + row * PITCH + chl) = f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
         }
     __syncthreads();
-    if (prof && tid == 0) prof[7] = __builtin_readcyclecounter();
     // Branch-free read-back: rows past the tile end or filters past K get an out-of-range offset, which
     // drops the store (and makes the residual load return zero).
     if (T.out_dtype == ST_DT_F32) {
@@ -638,11 +647,7 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
 
   tile_fields_loaded(T);
   const int tid = work_thread_id();
-  if (prof && tid == 0) {
-    prof[0] = __builtin_readcyclecounter();
-    prof[4] = wall_clock64();
-    prof[5] = ((uint64_t)__builtin_amdgcn_s_getreg(0x1814) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(0xF804);
-  }
+  if (prof && tid == 0) stamp_start(prof);
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = (int)it.tile_m * MT;
   const int n0 = (int)it.tile_n * NT;
@@ -934,11 +939,8 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
   if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
 
   // ---- epilogue: (+ residual) -> ReLU -> cast -> store ---------------------------------------------
-  tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, prof, res_lds);
-  if (prof && tid == 0) {
-    prof[3] = __builtin_readcyclecounter();
-    prof[6] = wall_clock64();
-  }
+  tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, res_lds);
+  if (prof && tid == 0) stamp_end(prof);
 }
 
 // ---- workgroup tile with the input patch resident in LDS ---------------------------------------------
@@ -971,11 +973,7 @@ __device__ __forceinline__ void conv_tile_patch(ConstOp& T, const st_work_item i
 
   tile_fields_loaded(T);
   const int tid = work_thread_id();
-  if (prof && tid == 0) {
-    prof[0] = __builtin_readcyclecounter();
-    prof[4] = wall_clock64();
-    prof[5] = ((uint64_t)__builtin_amdgcn_s_getreg(0x1814) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(0xF804);
-  }
+  if (prof && tid == 0) stamp_start(prof);
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = (int)it.tile_m * MT;
   const int n0 = (int)it.tile_n * NT;
@@ -1133,11 +1131,8 @@ __device__ __forceinline__ void conv_tile_patch(ConstOp& T, const st_work_item i
 
   if (prof && tid == 0) prof[2] = __builtin_readcyclecounter();
   if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
-  tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, prof);
-  if (prof && tid == 0) {
-    prof[3] = __builtin_readcyclecounter();
-    prof[6] = wall_clock64();
-  }
+  tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem);
+  if (prof && tid == 0) stamp_end(prof);
 }
 
 // ---- gather tile for channel counts that are not a multiple of the 16-byte vector -------------------
@@ -1170,11 +1165,7 @@ __device__ __forceinline__ void conv_tile_gather(ConstOp& T, const st_work_item 
   char* sB = smem + 2 * MT * ROWB;          // [2][NT][ROWB]  filters
 
   const int tid = work_thread_id();
-  if (prof && tid == 0) {
-    prof[0] = __builtin_readcyclecounter();
-    prof[4] = wall_clock64();
-    prof[5] = ((uint64_t)__builtin_amdgcn_s_getreg(0x1814) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(0xF804);
-  }
+  if (prof && tid == 0) stamp_start(prof);
   const int chunk = tid % CH;    // which 16 bytes of the row slab this thread stages
   const int row0 = tid / CH;
   const int m0 = (int)it.tile_m * MT;
@@ -1359,11 +1350,8 @@ __device__ __forceinline__ void conv_tile_gather(ConstOp& T, const st_work_item 
   if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
 
   // ---- epilogue: (+ residual) -> ReLU -> cast -> store ---------------------------------------------
-  tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, prof);
-  if (prof && tid == 0) {
-    prof[3] = __builtin_readcyclecounter();
-    prof[6] = wall_clock64();
-  }
+  tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem);
+  if (prof && tid == 0) stamp_end(prof);
 }
 
 // The 128 bits that start kk 16-bit elements into the 256-bit value hi:lo (kk wave-uniform, 0..8).
@@ -1401,11 +1389,7 @@ __device__ __forceinline__ void conv_tile_rows(ConstOp& T, const st_work_item it
   typedef Mma<DT, MF> MMA;
   typedef typename MMA::Acc Acc;
   const int tid = work_thread_id();
-  if (prof && tid == 0) {
-    prof[0] = __builtin_readcyclecounter();
-    prof[4] = wall_clock64();
-    prof[5] = ((uint64_t)__builtin_amdgcn_s_getreg(0x1814) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(0xF804);
-  }
+  if (prof && tid == 0) stamp_start(prof);
   const int lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
   const int lrow = lane & 31, lk = lane >> 5;
@@ -1580,8 +1564,8 @@ __device__ __forceinline__ void conv_tile_rows(ConstOp& T, const st_work_item it
     tile_epilogue<MT, NT, BM, BN, MF, DT, EPI_PASSES, kStageBytes, POL>(T, acc, mrow + q0, mrow + q_end, n0, wm0, wn0, lrow, lk, tid, smem);
   }
   if (prof && tid == 0) {
-    prof[2] = prof[3] = __builtin_readcyclecounter();
-    prof[6] = wall_clock64();
+    prof[2] = __builtin_readcyclecounter();
+    stamp_end(prof);
   }
 }
 
@@ -1699,11 +1683,13 @@ __device__ __forceinline__ void pool_item(ConstOp& T, const st_work_item it) {
 template <class POL>
 __device__ __forceinline__ void run_item(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   if (T.cfg == kChainPoolCfg) {
+    if (prof && threadIdx.x == 0) stamp_start(prof);
     switch (T.in_dtype) {
       case ST_DT_BF16: pool_item<ST_DT_BF16, POL::kActAux>(T, it); break;
       case ST_DT_F16: pool_item<ST_DT_F16, POL::kActAux>(T, it); break;
       default: pool_item<ST_DT_F32, POL::kActAux>(T, it); break;
     }
+    if (prof && threadIdx.x == 0) stamp_end(prof);
     return;
   }
   switch (T.in_dtype) {
