@@ -27,6 +27,7 @@
 #include <utility>
 
 #include "st_internal.h"
+#include "st_launch.h"
 #include "st_tiles.hpp"
 
 namespace st {
@@ -341,8 +342,7 @@ int launch_chain(const TenantDev* ops_dev, const st_work_item* items_dev, uint32
   a.colbegin = colbegin_dev;
   a.prefetch = prefetch_dev;
   for (int x = 0; x <= kNumXCDs; ++x) a.prefetch_begin[x] = prefetch_dev ? prefetch_begin[x] : 0u;
-  hipLaunchKernelGGL(st_chain_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, a);
-  return (int)hipGetLastError();
+  return (int)launch(st_chain_kernel, (unsigned)grid, kThreads, stream, a);
 }
 
 }  // namespace st

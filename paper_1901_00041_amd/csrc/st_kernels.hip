@@ -11,6 +11,7 @@
 #include <utility>
 
 #include "st_internal.h"
+#include "st_launch.h"
 #include "st_tiles.hpp"
 
 // Fixed scratch memory for the entry point that allocates nothing (st_conv_run_noalloc).  One array per GPU, held
@@ -110,8 +111,7 @@ __global__ __launch_bounds__(256) void st_maxpool_kernel(const void* __restrict_
 int launch_conv(const TenantDev* tenants_dev, const st_work_item* items_dev, int64_t n_items, void* stream,
                 uint64_t* prof_dev) {
   if (n_items <= 0) return 0;
-  void* args[] = {&tenants_dev, &items_dev, &prof_dev};
-  return (int)hipLaunchKernel((const void*)st_conv_kernel, dim3((unsigned)n_items), dim3(kThreads), args, 0, (hipStream_t)stream);
+  return (int)launch(st_conv_kernel, (unsigned)n_items, kThreads, stream, tenants_dev, items_dev, prof_dev);
 }
 
 // Plain 16-byte-per-lane copy: the reference kernel for scaling hardware traffic counters.
@@ -123,8 +123,7 @@ int launch_copy(const void* src, void* dst, int64_t bytes, void* stream) {
   const int64_t n16 = bytes / 16;
   if (n16 <= 0) return 0;
   const unsigned blocks = (unsigned)((n16 + 255) / 256 < 8192 ? (n16 + 255) / 256 : 8192);
-  hipLaunchKernelGGL(st_copy_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, (const u32x4*)src, (u32x4*)dst, n16);
-  return (int)hipGetLastError();
+  return (int)launch(st_copy_kernel, blocks, 256, stream, (const u32x4*)src, (u32x4*)dst, n16);
 }
 
 // ---- the entry point that allocates nothing: tables and split-K workspace in the fixed array `scratch` -------
@@ -159,19 +158,17 @@ __global__ __launch_bounds__(256) void st_bind_kernel(BindPayload<N> p, TenantDe
 }
 
 template <int N>
-static hipError_t bind(const TenantDev* host, int n, TenantDev* table, hipStream_t stream) {
+static hipError_t bind(const TenantDev* host, int n, TenantDev* table, void* stream) {
   BindPayload<N> p;
   for (int i = 0; i < n; ++i) std::memcpy(&p.v[2 * i], host + i, 32);
   std::memset(&p.v[2 * n], 0, (size_t)(N - n) * 32);
-  void* args[] = {&p, &table, &n};
-  return hipLaunchKernel((const void*)st_bind_kernel<N>, dim3(1), dim3(256), args, 0, stream);
+  return launch(st_bind_kernel<N>, 1, 256, stream, p, table, n);
 }
 
 int launch_bind(const TenantDev* host, int n, TenantDev* table_dev, void* stream) {
   for (int done = 0; done < n; done += kBindLarge) {
     const int m = n - done < kBindLarge ? n - done : kBindLarge;
-    const hipError_t e = m <= kBindSmall ? bind<kBindSmall>(host + done, m, table_dev + done, (hipStream_t)stream)
-                                         : bind<kBindLarge>(host + done, m, table_dev + done, (hipStream_t)stream);
+    const hipError_t e = m <= kBindSmall ? bind<kBindSmall>(host + done, m, table_dev + done, stream) : bind<kBindLarge>(host + done, m, table_dev + done, stream);
     if (e != hipSuccess) return (int)e;
   }
   return 0;
@@ -207,8 +204,7 @@ int launch_poke(const void* host_src, int64_t bytes, void* dst_dev, void* stream
     const int64_t n = bytes - done < (int64_t)sizeof(PokePayload) ? bytes - done : (int64_t)sizeof(PokePayload);
     std::memset(&p, 0, sizeof(p));
     std::memcpy(&p, src + done, (size_t)n);
-    hipLaunchKernelGGL(st_poke_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, p, (u32x4*)(dst + done), (int)((n + 15) / 16));
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch(st_poke_kernel, 1, 256, stream, p, (u32x4*)(dst + done), (int)((n + 15) / 16));
     if (e != hipSuccess) return (int)e;
   }
   return 0;
@@ -218,30 +214,24 @@ int launch_zero(void* dst_dev, int64_t bytes, void* stream) {
   const int64_t nvec = (bytes + 15) / 16;
   if (nvec <= 0) return 0;
   const unsigned blocks = (unsigned)((nvec + 255) / 256 < 1024 ? (nvec + 255) / 256 : 1024);
-  hipLaunchKernelGGL(st_zero_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, (u32x4*)dst_dev, nvec);
-  return (int)hipGetLastError();
+  return (int)launch(st_zero_kernel, blocks, 256, stream, (u32x4*)dst_dev, nvec);
 }
 
 int launch_empty(void* stream) {
-  hipLaunchKernelGGL(st_empty_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream);
-  return (int)hipGetLastError();
+  return (int)launch(st_empty_kernel, 1, 64, stream);
 }
 
 int launch_maxpool(const void* x, void* y, int N, int H, int W, int C, int P, int Q, int win, int stride, int pad,
                    int dtype, void* stream) {
-  hipStream_t s = (hipStream_t)stream;
   const int es = dtype == ST_DT_F32 ? 4 : 2;
   const int vec = (C % (16 / es) == 0) ? 16 / es : 1;
   const int64_t total = (int64_t)N * P * Q * (C / vec);
   if (total <= 0) return 0;
   const unsigned blocks = (unsigned)((total + 255) / 256);
-#define ST_POOL(DT, V) \
-  hipLaunchKernelGGL((st_maxpool_kernel<DT, V>), dim3(blocks), dim3(256), 0, s, x, y, N, H, W, C, P, Q, win, stride, pad)
-  if (dtype == ST_DT_F32) { if (vec == 4) ST_POOL(ST_DT_F32, 4); else ST_POOL(ST_DT_F32, 1); }
-  else if (dtype == ST_DT_BF16) { if (vec == 8) ST_POOL(ST_DT_BF16, 8); else ST_POOL(ST_DT_BF16, 1); }
-  else { if (vec == 8) ST_POOL(ST_DT_F16, 8); else ST_POOL(ST_DT_F16, 1); }
-#undef ST_POOL
-  return (int)hipGetLastError();
+  auto kernel = dtype == ST_DT_F32    ? (vec == 4 ? st_maxpool_kernel<ST_DT_F32, 4> : st_maxpool_kernel<ST_DT_F32, 1>)
+                : dtype == ST_DT_BF16 ? (vec == 8 ? st_maxpool_kernel<ST_DT_BF16, 8> : st_maxpool_kernel<ST_DT_BF16, 1>)
+                                      : (vec == 8 ? st_maxpool_kernel<ST_DT_F16, 8> : st_maxpool_kernel<ST_DT_F16, 1>);
+  return (int)launch(kernel, blocks, 256, stream, x, y, N, H, W, C, P, Q, win, stride, pad);
 }
 
 }  // namespace st

@@ -30,6 +30,7 @@ st_status st::fail(st_status s, const char* fmt, ...) {
   return s;
 }
 st_status st::hip_fail(hipError_t e, const char* what) {
+  (void)hipGetLastError();      // reported here: the runtime must not report it again to whoever asks next on this thread
   return fail(e == hipErrorOutOfMemory ? ST_ERR_OUT_OF_MEMORY : ST_ERR_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
