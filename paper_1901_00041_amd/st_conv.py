@@ -268,8 +268,8 @@ def _check(st, where):
 
 
 def st_conv_run(plan: Plan, stream=None) -> None:
-    # spelled out: a small launch takes the host about three microseconds, and calls and type checks here are tenths of one
-    st = (_lib or lib()).st_conv_run(plan.handle, stream if stream is None or type(stream) is int else stream.cuda_stream)
+    # _stream() and _check() spelled out: a small launch takes the host about three microseconds, and calls here are tenths of one
+    st = (_lib or lib()).st_conv_run(plan.handle, stream if stream is None or isinstance(stream, int) else int(stream.cuda_stream))
     if st != ST_OK:
         raise StError(st, "st_conv_run")
 
