@@ -77,8 +77,9 @@ typedef struct st_plan_opts {
   int32_t target_items;  /* 0 = default; else the workgroup slots the planner's cost model fills      */
   int32_t rows_per_tile; /* 0 = choose; 1, 2 or 4 forces the output rows per work item of row-tiled   */
                          /* tenants (ignored for the others)                                         */
-  int32_t chain_queues;  /* st_chain_plan only: 0 = choose; 1 = one persistent launch with one work queue; 2 = the */
-                         /* per-XCD layout, each sequence bound to one XCD (needs a whole 8-XCD device)     */
+  int32_t chain_queues;  /* st_chain_plan only: 0 = choose (the per-XCD layout from 8 sequences on, else a launch per */
+                         /* stage); 1 = one persistent launch with one work queue; 2 = the per-XCD layout, each      */
+                         /* sequence bound to one XCD (needs a whole 8-XCD device)                                   */
   int32_t reserved;      /* must be 0                                                                */
 } st_plan_opts;
 
@@ -258,18 +259,17 @@ void st_pipeline_destroy(st_pipeline* pipeline);
 /* ---- A whole chain of dependent layers as ONE launch -------------------------------------------------------
  * The space-time policy of Section 4 applied across layers as well as across tenants: the work items of every
  * op (a convolution layer, or a max-pool) of every tenant go into one queue, and one persistent launch works
- * through it.  Ops are grouped into SEQUENCES (one per tenant network: Section 4's disjoint graphs) and, within a
+ * through it (or, with few sequences, a launch per stage: see below).  Ops are grouped into SEQUENCES (one per tenant network: Section 4's disjoint graphs) and, within a
  * sequence, ordered by STAGE: an op's work items start once every work item of its sequence's ops with a smaller
  * stage is complete; ops of one sequence with equal stage are independent of each other (a block's projection
- * convolution and its first 1x1 convolution, say); different sequences never wait for each other.  The caller
- * guarantees that this order covers every read-after-write, write-after-read and write-after-write between the
+ * convolution and its first 1x1 convolution, say); different sequences never wait for each other inside a persistent
+ * launch, and are in lock-step where a pass is a launch per stage.  The caller guarantees that this order covers every read-after-write, write-after-read and write-after-write between the
  * ops of a sequence, and that sequences share no written tensor.
  *
  * Tiles are chosen per stage (all ops of that stage, over all sequences, planned together as st_conv_plan would).
  * Within a stage the longest work items come first.  There is either one queue for the whole chip, worked through one
  * launch per stage by default (with chain_queues = 1 as one persistent launch whose resident workgroups claim the entries
- * one by one in stage order), or (the default from 8 sequences on, on a whole 8-XCD
- * device) the work is laid out per XCD, sequence s on XCD s mod 8, served only by the workgroups that run on that
+ * one by one in stage order), or (the default from 8 sequences on, on a whole 8-XCD device) the work is laid out per XCD, sequence s on XCD s mod 8, served only by the workgroups that run on that
  * XCD: a sequence's activations then stay in one XCD's L2, and a finished work item is announced through that L2 (a
  * flag per work item) instead of through memory.  An XCD's entries are dealt into COLUMNS, each a list of entries in
  * stage order that ONE workgroup works through (it draws its column when it starts; nothing is claimed per entry):
@@ -300,7 +300,9 @@ typedef struct st_chain_op {
 
 typedef struct st_chain_info {
   int32_t n_ops, n_sequences, n_stages;
-  int32_t workgroups;        /* size of the persistent launch (resident workgroup slots, or fewer)    */
+  int32_t workgroups;        /* size of the persistent launch (resident workgroup slots, or fewer); where a   */
+                             /* pass is a launch per stage: what that size would be (a stage's launch has one */
+                             /* workgroup per work item)                                               */
   int64_t n_items;           /* queue entries                                                         */
   int64_t flops, bytes;      /* sums over the convolution ops (as st_plan_info)                       */
   int64_t workspace_bytes;   /* split-K partial tiles and counters (shared by a sequence's stages)    */
@@ -326,8 +328,9 @@ typedef struct st_chain st_chain; /* opaque */
  * queue, control blocks, split-K workspace) unless opts->host_only.  n_ops == 0 gives an empty chain.  opts as for
  * st_conv_plan (order is ignored: the queue order is fixed). */
 st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const st_plan_opts* opts, st_chain** out_chain);
-/* One pass: one launch on hip_stream (one per stage with fewer than 8 sequences and chain_queues = 0).  Asynchronous, allocation-free.  Two runs of one chain must not overlap in
- * time (queue them on one stream). */
+/* One pass: one launch on hip_stream, or one per stage (chain_queues = 0 with fewer than 8 sequences, or on a device that
+ * is not a whole 8-XCD one).  Asynchronous, allocation-free.  Two runs of one chain must not overlap in time (queue them
+ * on one stream). */
 st_status st_chain_run(st_chain* chain, void* hip_stream);
 /* The same with in-kernel time stamps per queue entry (HOST buffer of 8 uint64 per entry, as st_conv_run_profiled;
  * a max-pool entry leaves [1] and [2] at 0; slot [7] = ticks of the 100 MHz clock the entry waited for its dependency,
@@ -337,11 +340,13 @@ st_status st_chain_run_profiled(st_chain* chain, void* hip_stream, uint64_t* sta
  * last run did not complete every work item (an XCD that received no workgroups); the chain is reset. */
 st_status st_chain_aborted(st_chain* chain, int32_t* aborted);
 /* The wall-clock limit of a dependency wait in microseconds (0 = give up at once unless already satisfied: a test
- * hook that makes every kernel still exit normally). */
+ * hook that makes every kernel still exit normally).  No effect where a pass is a launch per stage: nothing waits
+ * inside a launch, and no pass is ever abandoned. */
 st_status st_chain_set_wait_limit_us(st_chain* chain, int64_t microseconds);
 /* Size of the launch in workgroups (0 = the planned size, st_chain_info.workgroups; at most that).  A test hook
  * too: with fewer workgroups than the column form needs, the undrawn columns' dependants give up after the wait
- * limit and the pass is reported as abandoned, every kernel still exiting normally. */
+ * limit and the pass is reported as abandoned, every kernel still exiting normally.  No effect on the launches of a
+ * pass that is a launch per stage (the value is checked all the same). */
 st_status st_chain_set_workgroups(st_chain* chain, int32_t workgroups);
 st_status st_chain_get_info(const st_chain* chain, st_chain_info* out);
 st_status st_chain_get_op_info(const st_chain* chain, int32_t op, st_chain_op_info* out);

@@ -34,7 +34,7 @@ struct st_chain {
   std::vector<ChainPrefetch> prefetch;       // queues per XCD: XCD x's filters in stage order, [prefetch_begin[x], prefetch_begin[x + 1])
   uint32_t prefetch_begin[kNumXCDs + 1] = {};
   ChainPrefetch* d_prefetch = nullptr;
-  int workgroups = 0;                        // planned size of the launch
+  int workgroups = 0;                        // planned size of the persistent launch (what it would be, with a launch per stage)
   int launch_workgroups = 0;                 // 0 = workgroups; else a smaller size asked for by the caller
   unsigned run_parity = 0;                   // control block the next run uses
   int64_t runs = 0;
@@ -128,8 +128,8 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
     }
     c->n_queues = (want_queues == 2 || (want_queues == 0 && n_xcd == kNumXCDs && c->n_sequences >= kNumXCDs)) ? kNumXCDs : 1;
     // With one queue a pass is a launch per stage, unless the caller asked for the persistent one: entries claimed one by
-    // one and completions counted at the memory side cost more than the launches (4 networks of batch 4: 927 us as one
-    // launch, 597 as 50; one network of batch 8: 1085 and 421).
+    // one and completions counted at the memory side cost more than the launches (4 networks of batch 4: 879 us as one
+    // launch, 524 as 50; one network of batch 8: 969 and 359; 7 of batch 1: 617 and 436).
     c->stage_launches = c->n_queues == 1 && want_queues == 0;
     // per XCD: producer and consumer of a sequence share that XCD's L2, and completion travels through it
     c->flags = c->n_queues > 1 ? kChainFlagLocalFlags : 0u;
@@ -282,7 +282,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
       }
     }
     if (status == ST_OK) {
-      // arena: [op table][queue][control block x2][split-K counters][completion flags][column boundaries][prefetch list][split-K partial tiles]
+      // arena: [op table][queue][control block x2, persistent launch only][split-K counters][completion flags][column boundaries][prefetch list][split-K partial tiles]
       auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
       c->ctl_slots = (uint32_t)(kChainCtlSeq + c->n_sequences);
       int64_t ws_total = 0, ct_total = 0;
@@ -294,7 +294,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
       c->workspace_bytes = ws_total * 4 + ct_total * 4;
       const size_t off_items = up((size_t)n_ops * sizeof(TenantDev));
       const size_t off_ctl = off_items + up(c->items.size() * sizeof(st_work_item));
-      const size_t ctl_words = (size_t)c->ctl_slots * kChainCtlStride + kChainRankWords;   // one control block
+      const size_t ctl_words = c->stage_launches ? 0 : (size_t)c->ctl_slots * kChainCtlStride + kChainRankWords;   // one control block
       const size_t off_ct = off_ctl + up(ctl_words * 4 * 2);
       const size_t off_flags = off_ct + up((size_t)ct_total * 4);
       const size_t off_cols = off_flags + up(c->n_queues > 1 ? c->items.size() * 4 : 0);
@@ -319,8 +319,10 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
           if (e != hipSuccess) status = hip_fail(e, "hipMemcpy (chain tables)");
           c->d_ops = (TenantDev*)c->d_arena;
           c->d_items = (st_work_item*)(c->d_arena + off_items);
-          c->d_ctl[0] = (uint32_t*)(c->d_arena + off_ctl);
-          c->d_ctl[1] = c->d_ctl[0] + ctl_words;
+          if (!c->stage_launches) {
+            c->d_ctl[0] = (uint32_t*)(c->d_arena + off_ctl);
+            c->d_ctl[1] = c->d_ctl[0] + ctl_words;
+          }
           c->d_counters = c->d_arena + off_ct;
           c->counters_bytes = (size_t)ct_total * 4;
           if (c->n_queues > 1) {

@@ -2,16 +2,19 @@
 //
 // Section 4 merges the ready kernels of disjoint DNN graphs into super-kernels; a launch per layer still pays, per
 // layer, the launch gap, the ramp of a fresh grid and the drain of its slowest tile.  Here every tenant's whole
-// sequence of layers sits in one work queue in (stage, cost) order.  A fixed set of resident workgroups claims
-// queue entries in order with one atomic each; an entry of sequence q and stage s may start once every work item of
-// q's earlier stages is complete (one completion counter per sequence), so a tenant's next layer starts the moment
-// its own previous layer is done, while other tenants' tiles fill the slots that its stragglers leave idle.
+// sequence of layers is worked through by a fixed set of resident workgroups; an entry of sequence q and stage s may
+// start once every work item of q's earlier stages is complete, so a tenant's next layer starts the moment its own
+// previous layer is done, while other tenants' tiles fill the slots that its stragglers leave idle.  The entries lie
+// either in columns per XCD (8 sequences or more: see st_chain_kernel) or, on request, in one queue in (stage, cost)
+// order that the workgroups claim entry by entry with one atomic each.  (The default with fewer than 8 sequences is
+// neither: a launch of st_conv_kernel per stage, in which the sequences are in lock-step.)
 //
-// Progress: entries are claimed strictly in queue order and every entry depends only on entries before it, so the
+// Progress: an entry depends only on earlier stages.  One queue: entries are claimed strictly in stage order, so the
 // lowest unfinished entry is always held by a running workgroup whose dependencies are complete; no co-residency of
-// all workgroups is needed.  Every wait is bounded twice over: by a wall-clock limit and by a count of polls; when
+// all workgroups is needed.  Columns: each is worked through in stage order, and every column in use needs its
+// workgroup.  Every wait is bounded twice over: by a wall-clock limit and by a count of polls; when
 // either expires the waiter raises the abort flag, and every workgroup leaves at its next claim or wait.  A workgroup
-// also claims at most n_items + 1 times.  So the kernel always exits, whatever the clock or the counters do.
+// also takes at most n_items + 1 entries.  So the kernel always exits, whatever the clock or the counters do.
 //
 // Memory: producers write their outputs through to memory (device-scope stores) and wait for them before they
 // signal; consumers read activations, residuals and partial tiles with device-scope loads (CoherentActs), which

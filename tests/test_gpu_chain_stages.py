@@ -54,3 +54,29 @@ def test_stamps_of_every_entry(n_tenants, chain_queues):
     else:
         assert (waited >= 0).all() and (waited <= end.max() - start.min()).all() and waited.max() > 0
     assert not chain.aborted()
+
+
+def test_persistent_launch_hooks_do_nothing_to_stage_launches():
+    """The wait limit and the size of the launch are accepted and checked, and leave a pass that is a launch per stage alone."""
+    import torch
+    from paper_1901_00041_amd import st_conv as sc
+    from paper_1901_00041_amd.stack import ResNetStack
+    stack = ResNetStack(n_tenants=2, image=64, seeded_weights=False)
+    last = stack.steps[-1]
+    stack.run("fused")
+    torch.cuda.synchronize()
+    want = stack.buf[last.dst].clone()
+    stack.build_chain(0)
+    chain = stack.chain
+    with pytest.raises(sc.StError):
+        chain.set_workgroups(chain.info().workgroups + 1)
+    chain.set_workgroups(1)
+    chain.set_wait_limit_us(0)
+    for i, b in stack.buf.items():
+        if i != 0:
+            b.zero_()
+    stack.run("fused_chain")
+    torch.cuda.synchronize()
+    n = last.shape.N * last.shape.P * last.shape.Q * last.shape.K
+    assert torch.equal(stack.buf[last.dst][:, :n], want[:, :n])
+    assert not chain.aborted()
