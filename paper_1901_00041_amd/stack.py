@@ -25,8 +25,10 @@ from . import synth
 
 # Workgroup slots the planner fills per launch when the caller gives no options.  Every launch of the stack is followed
 # by one that depends on it, so a launch's slowest work item and its tail count for more than in a launch that stands
-# alone, and somewhat fewer, larger work items than the planner's default (400) do better: measured per pass of 8
-# tenants, 200 slots 560 us, 250 555, 300 545, 350 572, 400 578, 450 581.
+# alone, and somewhat fewer, larger work items than the planner's default (400) do better.  us per pass with 200, 250, 300,
+# 350, 400, 450 slots: 8 tenants of batch 1 as layer launches 445, 443, 437, 438, 442, 448 and as a chain 372, 372, 368, 378,
+# 390, 407; 4 tenants of batch 4 as layer launches 545, 549, 541, 563, 566, 566; 8 of batch 8 as a chain 1176, 1164, 1181,
+# 1191, 1187, 1183.
 STACK_SLOTS = 300
 
 
