@@ -206,6 +206,9 @@ constexpr uint32_t kInvalidOffset = 0x80000000u;   // >= num_records of every bu
 // One instruction moves 16 bytes per lane from a buffer straight into LDS: lane l's bytes land at lds_base + 16 * l
 // (lds_base is wave-uniform), lanes whose offset is out of range write zeros.  The compiler is not told about the LDS
 // write: whoever reads the data first waits for the vector-memory counter (wait_loads_barrier) and for a barrier.
+// (M0 is reserved: the compiler sets it right before each use of its own, and warns that an asm statement writes it.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int AUX, int OFF>
 __device__ __forceinline__ void load_to_lds(const u32x4& rsrc, uint32_t voff, uint32_t soff, uint32_t lds_base) {   // to lds_base + OFF
   static_assert(AUX == 0 || AUX == kAuxDeviceCoherent, "cache policy");
@@ -214,6 +217,7 @@ __device__ __forceinline__ void load_to_lds(const u32x4& rsrc, uint32_t voff, ui
   else
     asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen sc1 lds" ::"s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "i"(OFF) : "memory", "scc", "m0");
 }
+#pragma clang diagnostic pop
 // Waits until at most N of this wavefront's loads are outstanding and all its LDS reads are done, then for the other
 // wavefronts to get there.
 template <int N>
