@@ -120,16 +120,6 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(std::make_integer_sequence<int, N>{}, static_cast<F&&>(f));
 }
 
-// short-circuit "any": f(0) || f(1) || ... || f(N-1), each f called with an integral_constant
-template <int... Is, class F>
-__device__ __forceinline__ bool static_any_impl(std::integer_sequence<int, Is...>, F&& f) {
-  return (f(std::integral_constant<int, Is>{}) || ...);
-}
-template <int N, class F>
-__device__ __forceinline__ bool static_any(F&& f) {
-  return static_any_impl(std::make_integer_sequence<int, N>{}, static_cast<F&&>(f));
-}
-
 // nested conditionals: if (n > 0) { f(0); if (n > 1) { f(1); ... } } up to N levels
 template <int I, int N, class F>
 __device__ __forceinline__ void static_nest_impl(int n, F&& f) {
@@ -145,10 +135,7 @@ __device__ __forceinline__ void static_nest(int n, F&& f) {
   static_nest_impl<0, N>(n, static_cast<F&&>(f));
 }
 
-// ---- output conversion ---------------------------------------------------------------------------
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-  return __builtin_bit_cast(uint16_t, (__bf16)f);     // v_cvt_pk_bf16_f32: round to nearest even
-}
+// ---- output conversion (fp32 to 16 bits rounds to nearest even: v_cvt_pk_bf16_f32, v_cvt_f16_f32) ----
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) {
   return __builtin_bit_cast(float, (uint32_t)b << 16);
 }
@@ -607,7 +594,6 @@ __device__ __forceinline__ bool split_k_reduce(ConstOp& T, const st_work_item it
       }
 #pragma unroll
       for (int gg = 0; gg < GB; ++gg) {
-        constexpr int dummy = 0; (void)dummy;
         const int grp = g0 + gg;
         const int i = grp / (BN * NG), j = (grp / NG) % BN, g = grp % NG;
 #pragma unroll
@@ -1241,7 +1227,7 @@ __device__ __forceinline__ void conv_tile_gather(ConstOp& T, const st_work_item 
     }
 #pragma unroll
     for (int i = 0; i < B_IT; ++i)
-      qb[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(b_ok[i] & whole_k ? (uint32_t)(b_off[i] + k_elem) * ES : kInvalidOffset), 0, 0);
+      qb[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)((b_ok[i] & whole_k) ? (uint32_t)(b_off[i] + k_elem) * ES : kInvalidOffset), 0, 0);
     if (__builtin_expect(__ballot(any) != 0, 0)) {
       uint32_t ea[A_IT][VEC], eb[B_IT][VEC];
 #pragma unroll
