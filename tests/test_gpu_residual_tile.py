@@ -32,6 +32,18 @@ def _check(shapes, key, what, **opts):
         torch.cuda.synchronize()
         for i, t in enumerate(tenants):
             helpers.check_tenant(t, f"{what}[{i}] {t.shape} {opts}")
+    # the same tiles in the persistent kernel, which reads activations and residuals past the caches
+    want = [t.dy.clone() for t in tenants]
+    ops = [sc.make_chain_op(sc.ST_OP_CONV, i, 0, t.desc()) for i, t in enumerate(tenants)]
+    for queues in (1, 2):
+        chain = sc.Chain(ops, sc.plan_opts(chain_queues=queues, **opts), keep=tenants)
+        for t in tenants:
+            t.clear()
+        chain.run()
+        torch.cuda.synchronize()
+        assert not chain.aborted()
+        for i, t in enumerate(tenants):
+            assert torch.equal(t.dy, want[i]), f"{what}[{i}] {t.shape} {opts} chain_queues={queues}"
 
 
 @pytest.mark.parametrize("split_k", [1, 3])
