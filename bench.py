@@ -10,7 +10,8 @@ every tenant's 53-layer stack (configuration 5), through cached plans, tensors r
 10-20 ms and a handful of steps is a stable measurement.  Exactly K steps are timed between two device
 synchronisations; every step is also bracketed by HIP events on the launch stream (median, p10, p90).
 
-Prints ONE JSON line.  `value` is the aggregate conv TFLOP/s of the fused (space-time) policy on the headline
+Prints ONE JSON line, kept below MAX_LINE characters; --details FILE also writes the full record it was shortened from.
+`value` is the aggregate conv TFLOP/s of the fused (space-time) policy on the headline
 workload, one batch at a time on one stream, in the form named by `config.policy` (a fixed choice, not a minimum
 over forms).  The time-only and space-only baselines are timed the same way (one batch at a time, per-tenant
 launches joined at every layer), once with the fused plan's tiles and once with each tenant planned alone; the
@@ -693,6 +694,55 @@ def probes():
 
 
 # ----------------------------------------------------------------------------------------------------------------
+# the printed line
+# ----------------------------------------------------------------------------------------------------------------
+MAX_LINE = 6000       # readers keep the last several thousand characters of the output: a longer line would lose its start
+
+
+def _short(v):
+    """Numbers to six significant digits, through dicts and lists."""
+    if isinstance(v, float):
+        return float(f"{v:.6g}")
+    if isinstance(v, dict):
+        return {k: _short(x) for k, x in v.items()}
+    return [_short(x) for x in v] if isinstance(v, (list, tuple)) else v
+
+
+def _us(forms: dict) -> dict:
+    return {f: r["us_per_pass"] if "us_per_pass" in r else r["error"][:100] for f, r in forms.items()}
+
+
+def printed(line: dict) -> dict:
+    """The full record without its repetitions: of every form timed beside the headline only us per pass, of every
+    configuration its headline form, speed-ups and roofline fractions; figures to six digits, but for the headline's own."""
+    exact = {k: line[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                                  "vs_baseline", "dtype", "data", "config", "timed_region_s")}
+    rest = {k: v for k, v in line.items() if k not in exact and k not in ("policies", "rooflines", "extras", "per_config", "cpu_baseline")}
+    rest["policies_us_per_pass"] = _us(line["policies"])
+    if "extras" in line:
+        rest["extras_us_per_pass"] = _us(line["extras"])
+    if "cpu_baseline" in line:
+        cb = rest["cpu_baseline"] = dict(line["cpu_baseline"])
+        if "end_to_end_drift" in cb:
+            tenants = cb.pop("end_to_end_drift")["tenants"]
+            cb["end_to_end_drift"] = {k: max(t[k] for t in tenants) for k in ("max_abs_err_over_max_abs_ref", "rel_l2")}
+        if "whole_configs" in cb:
+            cb["whole_configs_gflops"] = {c: {leg: r.get("gflops", "failed") for leg, r in legs.items()} for c, legs in cb.pop("whole_configs").items()}
+    if "per_config" in line:
+        rest["per_config"] = {}
+        for c, r in line["per_config"].items():
+            if not isinstance(r, dict):
+                rest["per_config"][c] = r
+            elif "error" in r:
+                rest["per_config"][c] = {"error": r["error"][:100]}
+            else:
+                rest["per_config"][c] = {"form": r["headline_form"], "us_per_pass": r["policies"][r["headline_form"]]["us_per_pass"], "tflops": r["value_tflops"],
+                                         **{k: r[k] for k in ("speedup_vs_time_only", "speedup_vs_space_only", "plan_build_us", "work_items") if k in r},
+                                         **{k: r["roofline"][k] for k in ("bound", "frac", "bound_us_per_pass", "frac_of_own_bound", "traffic")}}
+    return {**exact, **_short(rest)}
+
+
+# ----------------------------------------------------------------------------------------------------------------
 def measure(cfg: int, steps: int, warmup: int, policies, extras: bool, extra_steps: int = 4):
     passes = PASSES_PER_STEP[cfg]
     copies = 1
@@ -755,6 +805,7 @@ def main():
     ap.add_argument("--isolation", action="store_true", help="per-tenant completion spread of identical tenants: fused launch vs space-only")
     ap.add_argument("--occupancy", action="store_true", help="per-tenant occupancy table of one fused launch of --config (1-4), as markdown")
     ap.add_argument("--probes", action="store_true", help="achievable copy bandwidth and MFMA rates of this chip")
+    ap.add_argument("--details", default="", help="file for the full record of the run")
     ap.add_argument("--form", default="", help="with --counters: the form to run (default: the headline form of --config)")
     ap.add_argument("--counters", action="store_true",
                     help="counter-collection mode for rocprofv3 --pmc: only K passes of the headline form of --config and K launches "
@@ -858,7 +909,10 @@ def main():
         line["per_config"] = per_config
         if not args.no_cpu:
             line["cpu_baseline"]["whole_configs"] = oracle_legs()
-    print(json.dumps(line))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(line, f, indent=1)
+    print(json.dumps(printed(line)))
     if failed:
         print(f"bench.py: configurations {failed} failed", file=sys.stderr)
         sys.exit(1)
