@@ -16,16 +16,18 @@ workload, one batch at a time on one stream, in the form named by `config.policy
 over forms).  The time-only and space-only baselines are timed the same way (one batch at a time, per-tenant
 launches joined at every layer), once with the fused plan's tiles and once with each tenant planned alone; the
 speed-ups are against the FASTER of the two.  Forms with several batches in flight, free-running streams and
-cold caches are under `extras` and never enter `value`.  `roofline` describes the launches `value` timed;
+cold caches are under `extras_us_per_pass` and never enter `value`.  `roofline` describes the launches `value` timed;
 `per_config` carries the same measurement for every configuration with its own roofline bound; `cpu_baseline`
 is the fp64 oracle timed on this host.
 """
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import math
 import os
+import re
 import statistics
 import subprocess
 import sys
@@ -278,15 +280,27 @@ def launch_floor_us(n: int = 2000) -> float:
 # ----------------------------------------------------------------------------------------------------------------
 # roofline
 # ----------------------------------------------------------------------------------------------------------------
-def measured_traffic(cfg: int, form: str):
-    """HBM bytes per launch of the dominant kernel from the committed counter summary (profiles/hbm_traffic.txt:
-    config, form, bytes read, bytes written), or None."""
-    path = os.path.join(ROOT, "profiles", "hbm_traffic.txt")
+KERNEL_SOURCES = ("st_internal.h", "st_tiles.hpp", "st_kernels.hip", "st_chain.hip", "st_plan.cpp", "st_chain.cpp")
+
+
+def kernel_sources_id() -> str:
+    """Identifies what the kernels and planners do: a hash over their sources without comments and white space."""
+    h = hashlib.sha256()
+    for name in KERNEL_SOURCES:
+        text = open(os.path.join(ROOT, "paper_1901_00041_amd", "csrc", name)).read()
+        h.update("".join(re.sub(r"//[^\n]*", "", text).split()).encode())
+    return h.hexdigest()[:12]
+
+
+def measured_traffic(cfg: int, form: str, path: str = os.path.join(ROOT, "profiles", "hbm_traffic.txt")):
+    """HBM bytes per launch of the dominant kernel from the committed counter summary (config, form, bytes read, bytes
+    written, kernel_sources_id of the code they were counted on), or None if there is none for the present code."""
     try:
-        for line in open(path):
-            f = line.split()
-            if len(f) >= 4 and f[0] == str(cfg) and f[1] == form:
-                return float(f[2]) + float(f[3])
+        with open(path) as lines:
+            for line in lines:
+                f = line.split()
+                if len(f) >= 5 and f[0] == str(cfg) and f[1] == form and f[4] == kernel_sources_id():
+                    return float(f[2]) + float(f[3])
     except OSError:
         pass
     return None

@@ -86,3 +86,17 @@ def test_printed_line_is_short_and_whole():
         assert out[k] == line[k], k
     assert out["roofline"]["frac"] == float(f"{roof['frac']:.6g}") and out["cpu_baseline"]["end_to_end_drift"]["rel_l2"] == float(f"{7 / 300:.6g}")
     assert set(out["per_config"]) == set(line["per_config"]) and out["per_config"]["2"]["tflops"] == 333.333
+
+
+def test_traffic_is_reported_only_for_the_code_it_was_counted_on(tmp_path):
+    sys.path.insert(0, ROOT)
+    import bench
+    path = tmp_path / "traffic.txt"
+    path.write_text(f"# comment\n5 fused 10 5 {bench.kernel_sources_id()}\n4 fused 10 5 0123456789ab\n3 fused 10 5\n")
+    assert bench.measured_traffic(5, "fused", str(path)) == 15.0
+    assert bench.measured_traffic(5, "fused_chain", str(path)) is None      # not counted
+    assert bench.measured_traffic(4, "fused", str(path)) is None            # counted on other code
+    assert bench.measured_traffic(3, "fused", str(path)) is None            # on nobody knows what
+    assert bench.measured_traffic(5, "fused", str(tmp_path / "none")) is None
+    before = bench.kernel_sources_id()
+    assert before == bench.kernel_sources_id() and len(before) == 12
