@@ -74,7 +74,8 @@ typedef struct st_plan_opts {
   int32_t order;         /* 0 = longest work item first (default); 1 = tenant-major; 2 = equal        */
                          /* progress: tenants interleaved in proportion to their item counts         */
   int32_t host_only;     /* 1 = build the tables on the host only (no device calls); run => error    */
-  int32_t target_items;  /* 0 = default; else the workgroup slots the planner's cost model fills      */
+  int32_t target_items;  /* 0 = default; else the workgroup slots the planner's cost model fills (two */
+                         /* to a compute unit; the default also considers one workgroup on each)      */
   int32_t rows_per_tile; /* 0 = choose; 1, 2 or 4 forces the output rows per work item of row-tiled   */
                          /* tenants (ignored for the others)                                         */
   int32_t chain_queues;  /* st_chain_plan only: 0 = choose (the per-XCD layout from 8 sequences on, else a launch per */

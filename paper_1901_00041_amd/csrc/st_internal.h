@@ -35,8 +35,8 @@ constexpr TileShape kTileShapes[kNumTileCfgs] = {
 };
 constexpr int kSmemBytes = 81920;  // LDS per workgroup: half a compute unit's 160 KiB
 constexpr int kRowStageBytes = 18432;   // row tile: LDS set aside for the epilogue's transposition buffer
-// tile shapes that also exist as element-wise-gather kernels (channel count not a multiple of the
-// 16-byte vector width); the planner maps such tenants onto one of them
+// tile shapes that also exist for any channel count (conv_tile_gather: not a multiple of the 16-byte vector
+// width); the planner maps such tenants onto one of them
 constexpr bool kGenericCfg[kNumTileCfgs] = {false, true, false, true, false, false, false};
 
 constexpr int kOrderTaps = 0, kOrderChannels = 1, kOrderLinear = 2;   // see conv_tile
@@ -59,7 +59,7 @@ struct TenantDev {
   int32_t Q, PQ, M, Kg;
   int32_t in_dtype, out_dtype, epilogue;
   int32_t cfg, split_k, k_steps, k_steps_per_split;
-  int32_t vec_ok;        // 1: C is a multiple of the 16-byte vector width, gathers use 16-byte loads
+  int32_t vec_ok;        // 1: C is a multiple of the 16-byte vector width (conv_tile), 0: any channel count or row tile
   int32_t step_dk, step_dr;   // one K step in the reduction index (r*S + s)*C + c: KT elements = step_dr filter rows of
                               //    S*C elements and step_dk elements more
   int32_t k_order;            // kOrder*: how conv_tile walks the reduction index

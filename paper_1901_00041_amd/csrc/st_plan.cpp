@@ -87,7 +87,9 @@ static void magic_for(int d, uint32_t* m, int32_t* L) {
 // in LDS (a shape without that form costs there what it costs in the first table).
 // The launch is modelled as list scheduling of the items on workgroup slots: its duration is about max(longest item, sum
 // of item times / slots).  The planner picks, per tenant, the (tile, split) option that minimises that maximum over
-// the whole launch: once for kSlots slots of shared compute units, once for one workgroup on each.
+// the whole launch: once for kSlots slots of shared compute units and, if the caller names no number of slots, once for
+// one workgroup on each.  (So a plan with target_items, which every stack and chain has, is priced by the shared tables
+// throughout; and the order of the fused list goes by the shared tables without the patch form, whatever was planned.)
 struct ItemCosts { double first[kNumTileCfgs], step[kNumTileCfgs], epi[kNumTileCfgs]; };
 enum { kCosts16 = 0, kCosts32 = 1, kCostsPatch = 2 };
 // [kCosts*][alone on the compute unit]
@@ -589,8 +591,9 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
     choose_all(options, o.target_items > 0 ? o.target_items : kSlots, &pick);
     if (o.target_items == 0) {
       // A launch of no more work items than compute units puts every workgroup on a compute unit of its own.  Plan for
-      // that too, and take it if the model says it is the shorter launch (config 3: 224 tiles of 64x64 instead of 416 of
-      // 32x64).
+      // that too, and take it if the model says it is the shorter launch (one 3x3 layer of each of a ResNet's four stages,
+      // batch 1: 207 items 6.7 us, the shared plan's 399 7.5; eight 3x3 layers 256->256 at 14x14: 224 tiles of 64x64 8.1 us,
+      // 416 of 32x64 8.25).
       std::vector<std::vector<Option>> lone = all_options(true);
       std::vector<int> alone;
       const double longest = choose_alone(lone, kNumCUs, &alone);
@@ -1269,8 +1272,11 @@ extern "C" st_status st_pipeline_create(int32_t depth, st_pipeline** out_pipelin
 }
 
 extern "C" int32_t st_pipeline_slots(int32_t depth) {
-  // measured on configs 2-4: one launch in flight fills the planner's default; two share the chip as 256 slots
-  // each, four and more as 128 each (smaller shares lose to the fixed cost per work item)
+  // One launch in flight fills the planner's default; two share the chip as 256 slots each, four and more as 128 each
+  // (smaller shares lose to the fixed cost per work item, larger ones to launches that queue behind one another).  us per
+  // batch with 64, 128, 192, 256, 320, 400 slots, two in flight: one 3x3 layer of each of a ResNet's four stages 4.3, 3.8,
+  // 4.0, 4.0, 4.0, 4.4, eight 3x3 layers 256->256 at 14x14 6.4, 6.1, 5.2, 5.5, 5.5, 6.5; four: 4.5, 4.1, 4.4, 4.3, 4.4, 5.1 and
+  // 6.7, 6.5, 6.1, 6.1, 6.1, 7.1 (sixteen unlike tenants do not care).
   if (depth <= 1) return 0;
   return depth == 2 ? 256 : 128;
 }

@@ -1362,7 +1362,7 @@ __device__ __forceinline__ u32x4 window128(const u32x4& lo, const u32x4& hi, int
 // ---- row tile for layers with very few input channels ---------------------------------------------
 // For the 7x7 / stride-2 / 3-channel stem the im2col row of one (pixel, filter row r) is S*C = 21
 // contiguous elements of the NHWC image, at an odd element offset, so neither 16-byte gathers nor the
-// element-wise gather variant are efficient.  This kernel gives one workgroup kRowsPerTile consecutive
+// any-channel tile are efficient.  This kernel gives one workgroup up to kRowsPerTile consecutive
 // output rows (a segment of up to 128 pixels of each) x 64 filters: the input rows they need are copied
 // whole into LDS with 16-byte loads (rows outside the image and the left/right padding are zeros), the
 // 64 filters are copied once into an LDS array [filter][r][32] padded with zeros, and the MFMA operands
@@ -1588,8 +1588,8 @@ __device__ __forceinline__ void run_dtype(ConstOp& T, const st_work_item it, cha
       default: run_cfg<5, DT, POL>(T, it, smem, prof); break;
     }
   } else {
-    // few-channel layers: the row tile when the planner found it eligible, else element-wise gathers
-    // (which exist for the two tile shapes marked in kGenericCfg)
+    // the row tile for few-channel layers that the planner found eligible, else the any-channel tile (which exists for
+    // the two tile shapes marked in kGenericCfg)
     if constexpr (DT != ST_DT_F32) {
       if (T.cfg == kRowCfg) { conv_tile_rows<DT, POL>(T, it, smem, prof); return; }
     }
