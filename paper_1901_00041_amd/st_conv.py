@@ -269,7 +269,10 @@ def _check(st, where):
 
 def st_conv_run(plan: Plan, stream=None) -> None:
     # _stream() and _check() spelled out: a small launch takes the host about three microseconds, and calls here are tenths of one
-    st = (_lib or lib()).st_conv_run(plan.handle, stream if stream is None or isinstance(stream, int) else int(stream.cuda_stream))
+    try:
+        st = (_lib or lib()).st_conv_run(plan.handle, stream if stream is None or type(stream) is int else stream.cuda_stream)
+    except (AttributeError, ctypes.ArgumentError):      # an int subclass, or a handle held as another kind of integer
+        st = lib().st_conv_run(plan.handle, _stream(stream))
     if st != ST_OK:
         raise StError(st, "st_conv_run")
 
