@@ -28,7 +28,7 @@ SMALL = [
     ConvShape(3, 64, 7, 7, 136, 1, 1, 1, 0, "bf16", "f32"),
     ConvShape(1, 16, 13, 13, 24, 5, 5, 1, 2, "bf16", "f32"),
     ConvShape(2, 8, 10, 9, 16, 3, 2, 1, 0, "bf16", "f32"),
-    ConvShape(1, 3, 30, 26, 64, 7, 7, 2, 3, "bf16", "f32"),     # C=3: element-wise gather
+    ConvShape(1, 3, 30, 26, 64, 7, 7, 2, 3, "bf16", "f32"),     # C=3: any-channel tile
     ConvShape(1, 24, 8, 8, 20, 3, 3, 1, 1, "f16", "f32"),
     ConvShape(2, 12, 9, 9, 36, 3, 3, 1, 1, "f32", "f32"),
     ConvShape(1, 5, 8, 9, 7, 3, 3, 2, 2, "f32", "f32"),          # odd everything, scalar stores
@@ -36,8 +36,8 @@ SMALL = [
     ConvShape(2, 3, 20, 32, 40, 7, 7, 2, 3, "bf16", "f32"),     # row tile (few channels), ragged filters
     ConvShape(1, 3, 9, 272, 72, 7, 7, 2, 3, "bf16", "bf16"),    # row tile, two pixel tiles per output row
     ConvShape(1, 4, 9, 16, 24, 3, 7, 1, 3, "f16", "f32"),       # row tile, stride 1, C = 4
-    ConvShape(1, 96, 9, 9, 40, 3, 3, 1, 1, "bf16", "f32"),      # K = 864: seven 256-byte steps, so the two smallest
-    ConvShape(1, 48, 6, 6, 24, 3, 3, 1, 1, "f32", "f32"),       #   tiles split K across wavefronts (bf16 and fp32)
+    ConvShape(1, 96, 9, 9, 40, 3, 3, 1, 1, "bf16", "f32"),      # K = 864: seven steps of 256 bytes, the last one short
+    ConvShape(1, 48, 6, 6, 24, 3, 3, 1, 1, "f32", "f32"),       # the same in bytes for fp32
 ]
 
 
