@@ -16,7 +16,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJDIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libst_conv.so")
-SOURCES = ["st_kernels.hip", "st_chain.hip", "st_plan.cpp", "st_chain.cpp"]
+SOURCES = ["st_conv_all.hip", "st_chain_all.hip", "st_conv_bf16_rows.hip", "st_chain_bf16.hip", "st_conv_bf16.hip", "st_conv_f16.hip", "st_conv_f32.hip",
+           "st_kernels.hip", "st_chain.hip", "st_plan.cpp", "st_chain.cpp"]
 # the benchmark's achievable-roof probe: its own small library, not part of the convolution library's ABI
 PROBE_LIB = os.path.join(PKG, "libst_bench_probe.so")
 PROBE_SOURCES = ["st_bench_probe.hip"]
@@ -55,7 +56,7 @@ def _objects(sources, verbose, extra, incremental):
         if incremental and os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(src), hm):
             continue
         jobs.append([hipcc] + CFLAGS + list(extra) + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", src, "-o", obj])
-    with ThreadPoolExecutor(max_workers=max(1, len(jobs))) as pool:
+    with ThreadPoolExecutor(max_workers=max(1, min(len(jobs), os.cpu_count() or 1))) as pool:
         list(pool.map(lambda c: _run(c, verbose), jobs))
     return objs
 

@@ -20,6 +20,8 @@ struct st_chain {
   std::vector<st_work_item> items;           // the queue; item.tenant = op index
   int n_sequences = 0, n_stages = 0;
   bool host_only = false;
+  uint32_t kernel_needs = 0;
+  std::vector<uint32_t> stage_needs;         // one queue: of every stage's launch
   int64_t flops = 0, bytes = 0, workspace_bytes = 0;
   uint32_t ctl_slots = 0;                    // slots of one control block (kChainCtlStride words each)
   uint32_t spin_limit_ticks = 10000000u;     // 100 ms of the 100 MHz constant clock
@@ -225,6 +227,10 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
         }
         stage_items[q] += n_it;
       }
+      uint32_t needs = 0u;
+      for (int i : kv.second) needs |= kernel_needs(c->table[i]);
+      c->kernel_needs |= needs;
+      c->stage_needs.push_back(needs);
       if (c->n_queues == 1) c->stage_begin.push_back((int64_t)queues[0].size());
       // one queue: as is.  Queues per XCD: the stage's entries (longest first) are dealt to the XCD's columns, to the
       // exclusive ones first, to the shared ones only beyond one per compute unit, then round again; so a stage with
@@ -312,7 +318,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
           }
           std::vector<char> host(off_ws, 0);
           std::memcpy(host.data(), c->table.data(), (size_t)n_ops * sizeof(TenantDev));
-          std::memcpy(host.data() + off_items, c->items.data(), c->items.size() * sizeof(st_work_item));
+          coded_items(c->table, c->items, (st_work_item*)(host.data() + off_items));
           if (!c->colbegin.empty()) std::memcpy(host.data() + off_cols, c->colbegin.data(), c->colbegin.size() * 4);
           if (!c->prefetch.empty()) std::memcpy(host.data() + off_pf, c->prefetch.data(), c->prefetch.size() * sizeof(ChainPrefetch));
           e = hipMemcpy(c->d_arena, host.data(), off_ws, hipMemcpyHostToDevice);
@@ -356,7 +362,7 @@ static st_status chain_launch(st_chain* c, void* stream, uint64_t* prof_dev) {
   if (c->stage_launches) {
     for (size_t g = 0; g + 1 < c->stage_begin.size(); ++g) {
       const int64_t b = c->stage_begin[g], n = c->stage_begin[g + 1] - b;
-      ST_HIP((hipError_t)launch_conv(c->d_ops, c->d_items + b, n, stream, prof_dev ? prof_dev + b * kProfSlots : nullptr));
+      ST_HIP((hipError_t)launch_conv(c->stage_needs[g], c->d_ops, c->d_items + b, n, stream, prof_dev ? prof_dev + b * kProfSlots : nullptr));
     }
     return ST_OK;
   }
@@ -366,7 +372,7 @@ static st_status chain_launch(st_chain* c, void* stream, uint64_t* prof_dev) {
     if (c->d_item_flags) ST_HIP((hipError_t)launch_zero(c->d_item_flags, (int64_t)((c->item_flags_bytes + 15) & ~(size_t)15), stream));
     c->run_number = 1u;
   }
-  ST_HIP((hipError_t)launch_chain(c->d_ops, c->d_items, (uint32_t)c->items.size(), c->d_colbegin, (uint32_t)c->n_queues, c->d_prefetch, c->prefetch_begin, c->d_ctl[p],
+  ST_HIP((hipError_t)launch_chain(c->kernel_needs, c->d_ops, c->d_items, (uint32_t)c->items.size(), c->d_colbegin, (uint32_t)c->n_queues, c->d_prefetch, c->prefetch_begin, c->d_ctl[p],
                                   c->d_ctl[p ^ 1u], c->ctl_slots, c->d_item_flags, c->run_number, c->spin_limit_ticks, c->flags,
                                   c->launch_workgroups > 0 ? c->launch_workgroups : c->workgroups, stream, prof_dev));
   c->run_parity = p ^ 1u;

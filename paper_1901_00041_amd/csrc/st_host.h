@@ -15,6 +15,13 @@ st_status fail(st_status s, const char* fmt, ...);
 st_status hip_fail(hipError_t e, const char* what);
 
 inline int elem_size(int dt) { return dt == ST_DT_F32 ? 4 : 2; }
+// The device's copy of a work list: every item with its code word.
+inline void coded_items(const std::vector<TenantDev>& ops, const std::vector<st_work_item>& items, st_work_item* out) {
+  for (size_t i = 0; i < items.size(); ++i) {
+    out[i] = items[i];
+    out[i].reserved = tile_code(ops[items[i].tenant]);
+  }
+}
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 }  // namespace st
@@ -32,6 +39,7 @@ struct st_plan {
   std::vector<st_work_item> items_fused;    // order of the fused launch
   std::vector<st_work_item> items_tenant;   // tenant-major, sliced by the baselines
   bool host_only = false;
+  uint32_t kernel_needs = 0;                // what the launch's kernel must have been compiled for
   int64_t flops = 0, bytes = 0, workspace_bytes = 0;
   int64_t ws_floats = 0, n_counters = 0;    // split-K: fp32 elements of all partial tiles, arrival counters
   // device

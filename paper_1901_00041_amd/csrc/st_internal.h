@@ -39,6 +39,19 @@ constexpr int kRowStageBytes = 18432;   // row tile: LDS set aside for the epilo
 // width); the planner maps such tenants onto one of them
 constexpr bool kGenericCfg[kNumTileCfgs] = {false, true, false, true, false, false, false};
 
+// What a workgroup runs, in the `reserved` word of the device's copy of a work item: a tile form (vector and any-channel forms
+// of a shape, its form with the input patch resident, the row tile, a chain's max-pool) and the operands' type.  A workgroup
+// then needs nothing but its work item to find its code, and the tenant's record is fetched once, by the tile that runs.
+constexpr uint32_t kFormVector = 0, kFormPatch = 8, kFormGather = 16, kFormRows = 24, kFormPool = 25;     // + the tile shape for the first three
+constexpr uint32_t kFormTypeShift = 8, kFormMask = (1u << kFormTypeShift) - 1u;
+// What a kernel was compiled for: bit `type` for every operand type, and the forms beyond vector and patch tiles.  All tile
+// code in one kernel costs every launch: a tile is reached over several far jumps through instructions that no other
+// workgroup has fetched, and registers are allotted for the largest.  A launch takes the smallest kernel that has its forms
+// (one kernel with nested switches over the record -> these, us per pass: four 3x3 layers of batch 1 7.47 -> 7.13, eight
+// 256->256 at 14x14 8.33 -> 8.20, 20 fp32 layers 20.0 -> 19.4, eight 53-layer networks of batch 1 as a chain 369 -> 357, four of
+// batch 4 as 49 launches 543 -> 535).
+constexpr uint32_t kHasRows = 8u, kHasGather = 16u, kHasPools = 32u, kHasEverything = 63u;
+
 constexpr int kOrderTaps = 0, kOrderChannels = 1, kOrderLinear = 2;   // see conv_tile
 constexpr int kOrderPatch = 3;     // see conv_tile_patch
 // filter steps resident in LDS when a tile shape keeps its input patch there (0: the shape has no such form; two patches and
@@ -94,9 +107,25 @@ struct TenantDev {
 static_assert(offsetof(TenantDev, ws) == 192 && sizeof(TenantDev) == 256, "lines of the scalar cache");
 static_assert(sizeof(TenantDev) % 8 == 0, "TenantDev must keep pointer alignment in arrays");
 
-// Launchers implemented in st_kernels.hip.  All asynchronous; return the hipError_t as int.
-int launch_conv(const TenantDev* tenants_dev, const st_work_item* items_dev, int64_t n_items, void* stream,
+// The work item's code word for an op, and what its kernel must have been compiled for.
+inline uint32_t tile_code(const TenantDev& T) {
+  const uint32_t form = T.cfg == kChainPoolCfg ? kFormPool
+                        : T.vec_ok             ? (T.k_order == kOrderPatch ? kFormPatch : kFormVector) + (uint32_t)T.cfg
+                        : T.cfg == kRowCfg     ? kFormRows
+                                               : kFormGather + (T.cfg == 1 ? 1u : 3u);
+  return form | ((uint32_t)T.in_dtype << kFormTypeShift);
+}
+inline uint32_t kernel_needs(const TenantDev& T) {
+  const uint32_t form = tile_code(T) & kFormMask;
+  return (1u << T.in_dtype) | (form == kFormPool ? kHasPools : form == kFormRows ? kHasRows : form >= kFormGather ? kHasGather : 0u);
+}
+
+// Launchers.  All asynchronous; return the hipError_t as int.  `needs`: kernel_needs of every tenant in the list.
+int launch_conv(uint32_t needs, const TenantDev* tenants_dev, const st_work_item* items_dev, int64_t n_items, void* stream,
                 uint64_t* prof_dev);
+// ... of one kernel (st_conv_kernel.hpp)
+template <uint32_t HAS>
+int launch_conv_kernel(const TenantDev* tenants_dev, const st_work_item* items_dev, int64_t n_items, void* stream, uint64_t* prof_dev);
 // Persistent chain launch (st_chain.hip).  ctl / ctl_other: this run's and the next run's control block.  A block is
 // ctl_slots slots of kChainCtlStride 32-bit words (256 bytes) with one live word each, so that the words hundreds of
 // workgroups poll and bump sit in different cache lines and memory channels: slot kChainCtlAbort the abort flag,
@@ -116,7 +145,7 @@ constexpr uint32_t kChainFlagLocalFlags = 4u;     // completion travels through 
 // set (those of the stage two before; none for the first two stages); flag_base is the op's own.
 struct ChainPrefetch { uint32_t op, flag_base, gate_begin, gate_count; };
 int chain_max_workgroups(int* out_workgroups, int* out_xcds);
-int launch_chain(const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, uint32_t n_queues, const ChainPrefetch* prefetch_dev,
+int launch_chain(uint32_t needs, const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, uint32_t n_queues, const ChainPrefetch* prefetch_dev,
                  const uint32_t* prefetch_begin, uint32_t* ctl, uint32_t* ctl_other, uint32_t ctl_slots, uint32_t* item_flags, uint32_t run_number,
                  uint32_t spin_limit_ticks, uint32_t flags, int grid, void* stream, uint64_t* prof_dev);
 int launch_empty(void* stream);

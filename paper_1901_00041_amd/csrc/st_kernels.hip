@@ -21,22 +21,6 @@ static __device__ __align__(256) unsigned char scratch[st::kNoallocScratchBytes]
 
 namespace st {
 
-__global__ __launch_bounds__(kThreads, 2) void st_conv_kernel(const TenantDev* __restrict__ tenants,
-                                                          const st_work_item* __restrict__ items,
-                                                          uint64_t* __restrict__ prof_base) {
-  __shared__ __attribute__((aligned(16))) char smem[kSmemBytes];
-  ConstItem* ip = (ConstItem*)(items + blockIdx.x);
-  st_work_item it;
-  it.tenant = ip->tenant;
-  it.k_split_idx = ip->k_split_idx;
-  it.tile_m = ip->tile_m;
-  it.tile_n = ip->tile_n;
-  it.reserved = 0u;
-  ConstOp& T = *(ConstOp*)(tenants + it.tenant);
-  uint64_t* prof = prof_base ? prof_base + (size_t)blockIdx.x * kProfSlots : nullptr;
-  run_item<PlainActs>(T, it, smem, prof);
-}
-
 __global__ void st_empty_kernel() {}
 
 // NHWC max-pool; padding never wins.  One thread per (output pixel, group of VEC channels): the window's
@@ -108,10 +92,24 @@ __global__ __launch_bounds__(256) void st_maxpool_kernel(const void* __restrict_
   }
 }
 
-int launch_conv(const TenantDev* tenants_dev, const st_work_item* items_dev, int64_t n_items, void* stream,
+// Each kernel is instantiated in a source file of its own (st_conv_*.hip).
+extern template int launch_conv_kernel<1u << ST_DT_BF16>(const TenantDev*, const st_work_item*, int64_t, void*, uint64_t*);
+extern template int launch_conv_kernel<1u << ST_DT_F16>(const TenantDev*, const st_work_item*, int64_t, void*, uint64_t*);
+extern template int launch_conv_kernel<1u << ST_DT_F32>(const TenantDev*, const st_work_item*, int64_t, void*, uint64_t*);
+extern template int launch_conv_kernel<(1u << ST_DT_BF16) | kHasRows | kHasPools>(const TenantDev*, const st_work_item*, int64_t, void*, uint64_t*);
+extern template int launch_conv_kernel<kHasEverything>(const TenantDev*, const st_work_item*, int64_t, void*, uint64_t*);
+
+int launch_conv(uint32_t needs, const TenantDev* tenants_dev, const st_work_item* items_dev, int64_t n_items, void* stream,
                 uint64_t* prof_dev) {
   if (n_items <= 0) return 0;
-  return (int)launch(st_conv_kernel, (unsigned)n_items, kThreads, stream, tenants_dev, items_dev, prof_dev);
+  const auto fits = [=](uint32_t has) { return (needs & ~has) == 0u; };
+  constexpr uint32_t kBf16 = 1u << ST_DT_BF16, kF16 = 1u << ST_DT_F16, kF32 = 1u << ST_DT_F32, kBf16Rows = kBf16 | kHasRows | kHasPools;
+  const auto run = fits(kBf16)       ? launch_conv_kernel<kBf16>
+                   : fits(kF16)      ? launch_conv_kernel<kF16>
+                   : fits(kF32)      ? launch_conv_kernel<kF32>
+                   : fits(kBf16Rows) ? launch_conv_kernel<kBf16Rows>
+                                     : launch_conv_kernel<kHasEverything>;
+  return run(tenants_dev, items_dev, n_items, stream, prof_dev);
 }
 
 // Plain 16-byte-per-lane copy: the reference kernel for scaling hardware traffic counters.

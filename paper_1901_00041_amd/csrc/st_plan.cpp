@@ -519,8 +519,8 @@ static st_status upload(st_plan* p) {
     return fail(ST_ERR_OUT_OF_MEMORY, "host allocation failed");
   }
   std::memcpy(host.data(), p->tenants.data(), n * sizeof(TenantDev));
-  std::memcpy(host.data() + off_fused, p->items_fused.data(), ib);
-  std::memcpy(host.data() + off_tenant, p->items_tenant.data(), ib);
+  coded_items(p->tenants, p->items_fused, (st_work_item*)(host.data() + off_fused));
+  coded_items(p->tenants, p->items_tenant, (st_work_item*)(host.data() + off_tenant));
   ST_HIP(hipMemcpy(p->d_arena, host.data(), off_ws, hipMemcpyHostToDevice));
   return ST_OK;
 }
@@ -761,6 +761,7 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       T.w_bytes = (uint32_t)(ti.Ngemm * ti.Kgemm * elem_size(d.in_dtype));
       T.y_bytes = (uint32_t)(ti.M * ti.Ngemm * elem_size(d.out_dtype));
       T.rows_per_tile = ti.rows_per_tile;
+      p->kernel_needs |= kernel_needs(T);
     }
   } catch (const std::bad_alloc&) {
     delete p;
@@ -786,7 +787,7 @@ extern "C" st_status st_conv_run(const st_plan* plan, void* hip_stream) {
   st_status s = check_runnable(plan);
   if (s != ST_OK) return s;
   if (plan->items_fused.empty()) return ST_OK;
-  ST_HIP((hipError_t)launch_conv(plan->d_tenants, plan->d_items_fused, (int64_t)plan->items_fused.size(), hip_stream, nullptr));
+  ST_HIP((hipError_t)launch_conv(plan->kernel_needs, plan->d_tenants, plan->d_items_fused, (int64_t)plan->items_fused.size(), hip_stream, nullptr));
   return ST_OK;
 }
 
@@ -830,11 +831,11 @@ extern "C" st_status st_conv_run_noalloc(const st_plan* plan, void* hip_stream) 
       ct += (size_t)ti.tiles_m * ti.tiles_n;
     }
   }
-  std::memcpy(host.data() + off_items, plan->items_fused.data(), ib);
+  coded_items(plan->tenants, plan->items_fused, (st_work_item*)(host.data() + off_items));
   ST_HIP((hipError_t)launch_poke(host.data(), (int64_t)off_counters, dev, hip_stream));
   // the array keeps the last call's contents: the arrival counters must start at zero (the partial tiles need not)
   if (plan->n_counters > 0) ST_HIP((hipError_t)launch_zero(dev + off_counters, (int64_t)up((size_t)plan->n_counters * 4), hip_stream));
-  ST_HIP((hipError_t)launch_conv((const TenantDev*)dev, (const st_work_item*)(dev + off_items), (int64_t)plan->items_fused.size(),
+  ST_HIP((hipError_t)launch_conv(plan->kernel_needs, (const TenantDev*)dev, (const st_work_item*)(dev + off_items), (int64_t)plan->items_fused.size(),
                                  hip_stream, nullptr));
   return ST_OK;
 }
@@ -848,7 +849,7 @@ extern "C" st_status st_conv_run_profiled(const st_plan* plan, void* hip_stream,
   uint64_t* d = nullptr;
   ST_HIP(hipMalloc((void**)&d, (size_t)n * kProfSlots * 8));
   hipError_t e = hipMemsetAsync(d, 0, (size_t)n * kProfSlots * 8, (hipStream_t)hip_stream);   // ordered before the launch
-  if (e == hipSuccess) e = (hipError_t)launch_conv(plan->d_tenants, plan->d_items_fused, n, hip_stream, d);
+  if (e == hipSuccess) e = (hipError_t)launch_conv(plan->kernel_needs, plan->d_tenants, plan->d_items_fused, n, hip_stream, d);
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)hip_stream);
   if (e == hipSuccess) e = hipMemcpy(stamps, d, (size_t)n * kProfSlots * 8, hipMemcpyDeviceToHost);
   (void)hipFree(d);
@@ -888,7 +889,7 @@ extern "C" st_status st_conv_run_time_only(const st_plan* plan, void* hip_stream
   if (s != ST_OK) return s;
   for (size_t t = 0; t < plan->info.size(); ++t) {
     const st_tenant_info& ti = plan->info[t];
-    ST_HIP((hipError_t)launch_conv(plan->d_tenants, plan->d_items_tenant + ti.item_begin, ti.item_count, hip_stream, nullptr));
+    ST_HIP((hipError_t)launch_conv(plan->kernel_needs, plan->d_tenants, plan->d_items_tenant + ti.item_begin, ti.item_count, hip_stream, nullptr));
   }
   return ST_OK;
 }
@@ -909,7 +910,7 @@ extern "C" st_status st_conv_run_space_only(const st_plan* plan, void* const* hi
   }
   for (size_t t = 0; t < n; ++t) {
     const st_tenant_info& ti = plan->info[t];
-    ST_HIP((hipError_t)launch_conv(plan->d_tenants, plan->d_items_tenant + ti.item_begin, ti.item_count,
+    ST_HIP((hipError_t)launch_conv(plan->kernel_needs, plan->d_tenants, plan->d_items_tenant + ti.item_begin, ti.item_count,
                                    hip_streams[t % (size_t)n_streams], nullptr));
   }
   for (size_t i = 1; i < used; ++i) {
@@ -1009,7 +1010,7 @@ static st_status issue_threaded(const st_plan* const* plans, int32_t n_plans, co
       const size_t si = stream_of(L);
       if ((int)(si % (size_t)n_threads) != t) continue;
       const st_plan* plan = plans[L % n_plans];
-      const int e = launch_conv(plan->d_tenants, plan->d_items_fused, (int64_t)plan->items_fused.size(), (void*)streams[si], nullptr);
+      const int e = launch_conv(plan->kernel_needs, plan->d_tenants, plan->d_items_fused, (int64_t)plan->items_fused.size(), (void*)streams[si], nullptr);
       if (e != (int)hipSuccess) { status[(size_t)t] = e; return; }
     }
   };

@@ -1559,45 +1559,6 @@ __device__ __forceinline__ void conv_tile_rows(ConstOp& T, const st_work_item it
   }
 }
 
-template <int CFG, int DT, class POL = PlainActs>
-__device__ __forceinline__ void run_cfg(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
-  constexpr TileShape s = kTileShapes[CFG];
-  if constexpr (DT != ST_DT_F32 && kPatchStages[CFG] > 0) {
-    if (T.k_order == kOrderPatch) {
-      conv_tile_patch<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, kPatchStages[CFG], DT, POL>(T, it, smem, prof);
-      return;
-    }
-  }
-  conv_tile<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, s.D, DT, POL>(T, it, smem, prof);
-}
-template <int CFG, int DT, class POL = PlainActs>
-__device__ __forceinline__ void run_gather(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
-  constexpr TileShape s = kTileShapes[CFG];
-  conv_tile_gather<s.MT, s.NT, s.WPX, s.WCH, s.MF, 128, CFG == 1 ? 2 : 4, DT, POL>(T, it, smem, prof);
-}
-
-template <int DT, class POL = PlainActs>
-__device__ __forceinline__ void run_dtype(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
-  if (T.vec_ok) {
-    switch (T.cfg) {
-      case 0: run_cfg<0, DT, POL>(T, it, smem, prof); break;
-      case 1: run_cfg<1, DT, POL>(T, it, smem, prof); break;
-      case 2: run_cfg<2, DT, POL>(T, it, smem, prof); break;
-      case 3: run_cfg<3, DT, POL>(T, it, smem, prof); break;
-      case 4: run_cfg<4, DT, POL>(T, it, smem, prof); break;
-      default: run_cfg<5, DT, POL>(T, it, smem, prof); break;
-    }
-  } else {
-    // the row tile for few-channel layers that the planner found eligible, else the any-channel tile (which exists for
-    // the two tile shapes marked in kGenericCfg)
-    if constexpr (DT != ST_DT_F32) {
-      if (T.cfg == kRowCfg) { conv_tile_rows<DT, POL>(T, it, smem, prof); return; }
-    }
-    if (T.cfg == 1) run_gather<1, DT, POL>(T, it, smem, prof);
-    else run_gather<3, DT, POL>(T, it, smem, prof);
-  }
-}
-
 // ---- max-pool of one output vector (chain kernel) ---------------------------------------------------
 // NHWC max-pool, one 16-byte vector of channels of one output pixel: idx counts (n, p, q, channel vector) with the
 // channel vector fastest.  Padding never wins; the result is a copy of the winning input's bits.
@@ -1669,23 +1630,64 @@ __device__ __forceinline__ void pool_item(ConstOp& T, const st_work_item it) {
   __builtin_amdgcn_raw_buffer_store_b128(v, make_rsrc(T.y, T.y_bytes), (int)((uint32_t)idx * 16u), 0, kAuxDeviceCoherent);
 }
 
-// One work item of a plan or chain: a tile of a convolution, or (chains only) a max-pool item.
-template <class POL>
-__device__ __forceinline__ void run_item(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
-  if (T.cfg == kChainPoolCfg) {
-    if (prof && threadIdx.x == 0) stamp_start(prof);
-    switch (T.in_dtype) {
-      case ST_DT_BF16: pool_item<ST_DT_BF16, POL::kActAux>(T, it); break;
-      case ST_DT_F16: pool_item<ST_DT_F16, POL::kActAux>(T, it); break;
-      default: pool_item<ST_DT_F32, POL::kActAux>(T, it); break;
-    }
-    if (prof && threadIdx.x == 0) stamp_end(prof);
-    return;
+template <int CFG, int DT, class POL>
+__device__ __forceinline__ void vector_tile(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
+  constexpr TileShape s = kTileShapes[CFG];
+  conv_tile<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, s.D, DT, POL>(T, it, smem, prof);
+}
+template <int CFG, int DT, class POL>
+__device__ __forceinline__ void patch_tile(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
+  constexpr TileShape s = kTileShapes[CFG];
+  if constexpr (DT != ST_DT_F32) conv_tile_patch<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, kPatchStages[CFG], DT, POL>(T, it, smem, prof);
+}
+template <int CFG, int DT, class POL>
+__device__ __forceinline__ void gather_tile(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
+  constexpr TileShape s = kTileShapes[CFG];
+  conv_tile_gather<s.MT, s.NT, s.WPX, s.WCH, s.MF, 128, CFG == 1 ? 2 : 4, DT, POL>(T, it, smem, prof);
+}
+
+template <uint32_t HAS, int DT, class POL>
+__device__ __forceinline__ void run_form(uint32_t form, ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
+  constexpr bool rows = (HAS & kHasRows) != 0u && DT != ST_DT_F32, gather = (HAS & kHasGather) != 0u, patch = DT != ST_DT_F32;
+  switch (form) {
+    case kFormVector + 0: vector_tile<0, DT, POL>(T, it, smem, prof); break;
+    case kFormVector + 1: vector_tile<1, DT, POL>(T, it, smem, prof); break;
+    case kFormVector + 2: vector_tile<2, DT, POL>(T, it, smem, prof); break;
+    case kFormVector + 3: vector_tile<3, DT, POL>(T, it, smem, prof); break;
+    case kFormVector + 4: vector_tile<4, DT, POL>(T, it, smem, prof); break;
+    case kFormVector + 5: vector_tile<5, DT, POL>(T, it, smem, prof); break;
+    case kFormPatch + 1: if constexpr (patch) patch_tile<1, DT, POL>(T, it, smem, prof); break;
+    case kFormPatch + 2: if constexpr (patch) patch_tile<2, DT, POL>(T, it, smem, prof); break;
+    case kFormPatch + 3: if constexpr (patch) patch_tile<3, DT, POL>(T, it, smem, prof); break;
+    case kFormPatch + 4: if constexpr (patch) patch_tile<4, DT, POL>(T, it, smem, prof); break;
+    case kFormGather + 1: if constexpr (gather) gather_tile<1, DT, POL>(T, it, smem, prof); break;
+    case kFormGather + 3: if constexpr (gather) gather_tile<3, DT, POL>(T, it, smem, prof); break;
+    case kFormRows: if constexpr (rows) conv_tile_rows<DT, POL>(T, it, smem, prof); break;
+    case kFormPool:
+      if constexpr ((HAS & kHasPools) != 0u) {
+        if (prof && threadIdx.x == 0) stamp_start(prof);
+        pool_item<DT, POL::kActAux>(T, it);
+        if (prof && threadIdx.x == 0) stamp_end(prof);
+      }
+      break;
+    default: break;
   }
-  switch (T.in_dtype) {
-    case ST_DT_BF16: run_dtype<ST_DT_BF16, POL>(T, it, smem, prof); break;
-    case ST_DT_F16: run_dtype<ST_DT_F16, POL>(T, it, smem, prof); break;
-    default: run_dtype<ST_DT_F32, POL>(T, it, smem, prof); break;
+}
+
+// One work item of a plan or chain: a tile of a convolution, or (chains only) a max-pool item.  it.reserved is its code word.
+template <uint32_t HAS, class POL>
+__device__ __forceinline__ void run_item(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
+  constexpr uint32_t types = HAS & 7u;
+  const uint32_t form = it.reserved & kFormMask;
+  if constexpr (types == 1u << ST_DT_BF16) run_form<HAS, ST_DT_BF16, POL>(form, T, it, smem, prof);
+  else if constexpr (types == 1u << ST_DT_F16) run_form<HAS, ST_DT_F16, POL>(form, T, it, smem, prof);
+  else if constexpr (types == 1u << ST_DT_F32) run_form<HAS, ST_DT_F32, POL>(form, T, it, smem, prof);
+  else {
+    switch (it.reserved >> kFormTypeShift) {
+      case ST_DT_BF16: run_form<HAS, ST_DT_BF16, POL>(form, T, it, smem, prof); break;
+      case ST_DT_F16: run_form<HAS, ST_DT_F16, POL>(form, T, it, smem, prof); break;
+      default: run_form<HAS, ST_DT_F32, POL>(form, T, it, smem, prof); break;
+    }
   }
 }
 
