@@ -261,14 +261,15 @@ void st_pipeline_destroy(st_pipeline* pipeline);
  * The space-time policy of Section 4 applied across layers as well as across tenants: the work items of every
  * op (a convolution layer, or a max-pool) of every tenant go into one queue, and one persistent launch works
  * through it (or, with few sequences, a launch per stage: see below).  Ops are grouped into SEQUENCES (one per tenant network: Section 4's disjoint graphs) and, within a
- * sequence, ordered by STAGE: an op's work items start once every work item of its sequence's ops with a smaller
- * stage is complete; ops of one sequence with equal stage are independent of each other (a block's projection
+ * sequence, ordered by STAGE: an op's work items start as if every work item of its sequence's ops with a smaller
+ * stage were complete (laid out per XCD, see below, an op that reads exactly what one op of the stage before writes, and touches
+ * nothing else of that stage, waits for the tiles it reads and for the stages before; nothing else starts early); ops of one sequence with equal stage are independent of each other (a block's projection
  * convolution and its first 1x1 convolution, say); different sequences never wait for each other inside a persistent
  * launch, and are in lock-step where a pass is a launch per stage.  The caller guarantees that this order covers every read-after-write, write-after-read and write-after-write between the
  * ops of a sequence, and that sequences share no written tensor.
  *
  * Tiles are chosen per stage (all ops of that stage, over all sequences, planned together as st_conv_plan would).
- * Within a stage the longest work items come first.  There is either one queue for the whole chip, worked through one
+ * Within a stage the longest work items come first, or, where they wait tile by tile, those that come first in the output.  There is either one queue for the whole chip, worked through one
  * launch per stage by default (with chain_queues = 1 as one persistent launch whose resident workgroups claim the entries
  * one by one in stage order), or (the default from 8 sequences on, on a whole 8-XCD device) the work is laid out per XCD, sequence s on XCD s mod 8, served only by the workgroups that run on that
  * XCD: a sequence's activations then stay in one XCD's L2, and a finished work item is announced through that L2 (a
@@ -276,7 +277,7 @@ void st_pipeline_destroy(st_pipeline* pipeline);
  * stage order that ONE workgroup works through (it draws its column when it starts; nothing is claimed per entry):
  * 32 "exclusive" columns, drawn by the first workgroup to arrive on each compute unit, and 32 "shared" ones for later
  * arrivals; a stage's entries go to the exclusive columns first and to the shared ones only beyond one per compute
- * unit (two tiles sharing a compute unit each run markedly slower than one that has it to itself).  Activations
+ * unit, or, where they wait tile by tile, to the column where a model of the pass has them end first (two tiles sharing a compute unit each run markedly slower than one that has it to itself).  Activations
  * written during the launch are read with device-scope loads, so no cache is invalidated between stages.
  * The one-queue form completes with any number of resident workgroups; the column form needs a workgroup for every
  * column in use to become resident eventually (on a GPU the launch has to itself all are at once; a caller that shares
@@ -358,6 +359,11 @@ st_status st_chain_worklist(const st_chain* chain, const st_work_item** items, i
  * queue); column j of XCD x (exclusive: j < columns; shared: columns <= j < 2 * columns) is entries
  * [begins[x * 2 * columns + j], begins[x * 2 * columns + j + 1]) of the work list. */
 st_status st_chain_columns(const st_chain* chain, const uint32_t** begins, int64_t* n);
+/* What every entry of a chain laid out per XCD waits for, valid until the chain is destroyed (*n = 0 with one queue).  Every
+ * work item has a number of its own, `flag`; a sequence's work items of one stage have consecutive numbers.  An entry starts
+ * once the work items [gate_begin, gate_begin + gate_count) and [tiles_begin, tiles_begin + tiles_count) are complete. */
+typedef struct st_chain_dep { uint32_t flag, gate_begin, gate_count, tiles_begin, tiles_count; } st_chain_dep;
+st_status st_chain_dependencies(const st_chain* chain, const st_chain_dep** deps, int64_t* n);
 void st_chain_destroy(st_chain* chain);
 
 /* Introspection (used by the bit-exact work-list tests and by reports). */

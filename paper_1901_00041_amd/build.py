@@ -16,8 +16,9 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJDIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libst_conv.so")
-SOURCES = ["st_conv_all.hip", "st_chain_all.hip", "st_conv_bf16_rows.hip", "st_chain_bf16.hip", "st_conv_bf16.hip", "st_conv_f16.hip", "st_conv_f32.hip",
-           "st_kernels.hip", "st_chain.hip", "st_plan.cpp", "st_chain.cpp"]
+SOURCES = ["st_conv_all.hip", "st_chain_all.hip", "st_chain_all_queue.hip", "st_conv_bf16_rows.hip", "st_chain_bf16.hip",
+           "st_chain_bf16_queue.hip", "st_conv_bf16.hip", "st_conv_f16.hip", "st_conv_f32.hip",
+           "st_kernels.hip", "st_chain.hip", "st_plan.cpp", "st_chain.cpp", "st_chain_deps.cpp"]
 # the benchmark's achievable-roof probe: its own small library, not part of the convolution library's ABI
 PROBE_LIB = os.path.join(PKG, "libst_bench_probe.so")
 PROBE_SOURCES = ["st_bench_probe.hip"]

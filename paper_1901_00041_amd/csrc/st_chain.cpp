@@ -8,6 +8,7 @@
 #include <new>
 #include <vector>
 
+#include "st_chain_deps.h"
 #include "st_host.h"
 #include "st_internal.h"
 
@@ -36,6 +37,8 @@ struct st_chain {
   std::vector<ChainPrefetch> prefetch;       // queues per XCD: XCD x's filters in stage order, [prefetch_begin[x], prefetch_begin[x + 1])
   uint32_t prefetch_begin[kNumXCDs + 1] = {};
   ChainPrefetch* d_prefetch = nullptr;
+  std::vector<st_chain_dep> deps;            // queues per XCD: beside every entry of items
+  ChainDep* d_deps = nullptr;
   int workgroups = 0;                        // planned size of the persistent launch (what it would be, with a launch per stage)
   int launch_workgroups = 0;                 // 0 = workgroups; else a smaller size asked for by the caller
   unsigned run_parity = 0;                   // control block the next run uses
@@ -72,6 +75,104 @@ static st_status validate_pool(const st_conv_desc& d, int i) {
   if ((int64_t)d.N * d.H * d.W * d.C * es >= ((int64_t)1 << 31) || (int64_t)d.N * P * Q * d.C * es >= ((int64_t)1 << 31))
     return fail(ST_ERR_UNSUPPORTED, "op %d (max-pool): tensors must stay below 2^31 bytes", i);
   return ST_OK;
+}
+
+static constexpr double kPoolItemClocks = 8000.0;      // a max-pool work item, 3.4 us in place
+static constexpr double kBoundaryClocks = 3000.0;      // last store of a tile to the first load of one that waited for it
+
+static uint32_t flag_of(const TenantDev& T, const st_work_item& it) {
+  return T.chain_flag_base + (it.tile_m * (uint32_t)T.tiles_n + it.tile_n) * (uint32_t)T.split_k + it.k_split_idx;
+}
+
+// Ops that wait tile by tile rely on "a stage complete" meaning "the stage before it complete" (st_chain_deps.cpp): a
+// sequence's ops of a stage keep their local ranges (by tile index; none: the op waits for all of the previous stage) if one
+// of them waits for the whole previous stage anyway or the ranges together hold every flag of it.
+typedef std::vector<std::vector<ChainDep>> LocalRanges;
+static void require_coverage(const std::vector<int>& stage_ops, const st_chain_op* ops, const std::vector<int64_t>& prev_begin,
+                             const std::vector<int64_t>& prev_count, LocalRanges* local) {
+  std::map<int, std::vector<int>> by_seq;
+  for (int i : stage_ops) by_seq[ops[i].sequence].push_back(i);
+  for (const auto& kv : by_seq) {
+    const int q = kv.first;
+    if (std::any_of(kv.second.begin(), kv.second.end(), [&](int i) { return (*local)[i].empty(); })) continue;
+    std::vector<int> steps((size_t)prev_count[q] + 1, 0);       // +1 where a range begins, -1 behind its end
+    for (int i : kv.second)
+      for (const ChainDep& d : (*local)[i]) {
+        ++steps[(size_t)(d.begin - prev_begin[q])];
+        --steps[(size_t)(d.begin - prev_begin[q]) + d.count];
+      }
+    bool all = true;
+    int depth = 0;
+    for (int64_t k = 0; k < prev_count[q]; ++k) {
+      depth += steps[(size_t)k];
+      all = all && depth > 0;
+    }
+    if (!all)
+      for (int i : kv.second) (*local)[i].clear();
+  }
+}
+
+static void prev_ops_next(const std::vector<int>& stage_ops, const st_chain_op* ops, int q, int64_t items, std::vector<int>* prev) {
+  if (items == 0) return;
+  prev->clear();
+  for (int i : stage_ops)
+    if (ops[i].sequence == q) prev->push_back(i);
+}
+
+// Deals one XCD's entries of a stage (of the ops mine) to its columns.  A stage that starts when the one before has ended:
+// longest entries first, to the columns in turn, exclusive ones first and shared ones only beyond one per compute unit, so that
+// a stage of no more entries than compute units never shares one.  A stage whose entries wait tile by tile: in the order of
+// their place in the output, each to the column where the model has it end first, so that what the next stage reads comes
+// in order and a compute unit that the stage before left idle goes on at once.
+static void deal(const std::vector<TenantDev>& table, const std::vector<int>& mine, const LocalRanges& local, const std::vector<double>& cost,
+                 const std::vector<st_work_item>& longest_first, std::vector<double>* flag_end, ChainDealer* dealer, std::vector<st_work_item>* columns) {
+  const bool by_tile = std::all_of(mine.begin(), mine.end(), [&](int i) { return !local[i].empty(); });
+  auto last_end = [&](uint32_t begin, uint32_t count) {
+    double t = 0.0;
+    for (uint32_t f = begin; f < begin + count; ++f) t = std::max(t, (*flag_end)[f]);
+    return t;
+  };
+  std::vector<double> gate_open(mine.size());
+  for (size_t o = 0; o < mine.size(); ++o) gate_open[o] = last_end(table[mine[o]].chain_dep_begin, table[mine[o]].chain_dep_count) + kBoundaryClocks;
+  size_t k = 0;
+  auto put = [&](const st_work_item& it, double ready) {
+    const double c = cost[it.tenant];
+    const size_t col = by_tile ? dealer->earliest(ready, c) : k % dealer->columns();
+    dealer->place(col, ready, c);
+    (*flag_end)[flag_of(table[it.tenant], it)] = dealer->ends(col);
+    columns[col].push_back(it);
+    ++k;
+  };
+  if (!by_tile && mine.size() != 1) {
+    std::map<int, double> open;
+    for (size_t o = 0; o < mine.size(); ++o) open[mine[o]] = gate_open[o];
+    for (const st_work_item& it : longest_first) put(it, open[it.tenant]);
+    return;
+  }
+  std::vector<int> next(mine.size(), 0);       // next tile index of every op; the op that is furthest behind goes on
+  for (;;) {
+    size_t o = mine.size();
+    double least = 2.0;
+    for (size_t j = 0; j < mine.size(); ++j) {
+      const double at = (double)next[j] / table[mine[j]].tiles_m;
+      if (next[j] < table[mine[j]].tiles_m && at < least) { least = at; o = j; }
+    }
+    if (o == mine.size()) break;
+    const TenantDev& T = table[mine[o]];
+    const int m = next[o]++;
+    double ready = gate_open[o];
+    if (by_tile) ready = std::max(ready, last_end(local[mine[o]][m].begin, local[mine[o]][m].count) + kBoundaryClocks);
+    for (int n = 0; n < T.tiles_n; ++n)
+      for (int slice = 0; slice < T.split_k; ++slice) {
+        st_work_item it;
+        it.tenant = (uint16_t)mine[o];
+        it.k_split_idx = (uint16_t)slice;
+        it.tile_m = (uint32_t)m;
+        it.tile_n = (uint32_t)n;
+        it.reserved = 0;
+        put(it, ready);
+      }
+  }
 }
 
 static void destroy_chain(st_chain* c) {
@@ -150,6 +251,12 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
     // ... and of the stage before that one: what a stage's filters wait for before they are prefetched
     std::vector<int64_t> prev2_begin((size_t)c->n_sequences, 0), prev2_count((size_t)c->n_sequences, 0);
     std::vector<ChainPrefetch> ahead[kNumXCDs];
+    // queues per XCD: the ops of the sequence's previous stage, what of it every tile of an op reads, the modelled
+    // clocks of an op's items, and when every work item of the stages so far ends (by flag) and every column
+    std::vector<std::vector<int>> prev_ops((size_t)c->n_sequences);
+    LocalRanges local((size_t)n_ops);
+    std::vector<double> cost((size_t)n_ops, kPoolItemClocks), flag_end;
+    std::vector<ChainDealer> dealers((size_t)kNumXCDs, ChainDealer(two_per_cu));
     // split-K workspace of a sequence: the largest need of any of its stages (its stages never overlap in time)
     std::vector<int64_t> seq_ws((size_t)c->n_sequences, 0), seq_ct((size_t)c->n_sequences, 0);
     struct Use { int op; int64_t ws_off, ct_off; };
@@ -177,6 +284,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
         T.chain_seq = q;
         T.chain_need = (uint32_t)done[q];
         c->table[i] = T;
+        cost[i] = sp->item_time[j];
         if (sp->info[j].split_k > 1) {
           const st_tenant_info& ti = sp->info[j];
           uses.push_back({i, stage_ws[q], stage_ct[q]});
@@ -232,15 +340,6 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
       c->kernel_needs |= needs;
       c->stage_needs.push_back(needs);
       if (c->n_queues == 1) c->stage_begin.push_back((int64_t)queues[0].size());
-      // one queue: as is.  Queues per XCD: the stage's entries (longest first) are dealt to the XCD's columns, to the
-      // exclusive ones first, to the shared ones only beyond one per compute unit, then round again; so a stage with
-      // no more entries than compute units never shares one, and every column is in stage order
-      for (int x = 0; x < c->n_queues; ++x) {
-        const std::vector<st_work_item>& sq = stage_q[(size_t)x];
-        const size_t ncol = two_per_cu ? 2 * (size_t)kChainColumns : (size_t)kChainColumns;
-        for (size_t k = 0; k < sq.size(); ++k)
-          queues[c->n_queues > 1 ? (size_t)x * 2 * kChainColumns + k % ncol : 0].push_back(sq[k]);
-      }
       std::vector<int64_t> cursor((size_t)c->n_sequences, 0), stage_begin((size_t)c->n_sequences, 0);
       for (int q = 0; q < c->n_sequences; ++q) {
         cursor[q] = stage_begin[q] = flag_total;
@@ -253,9 +352,42 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
         cursor[q] += c->info[i].item_count;
         T.chain_dep_begin = (uint32_t)prev_begin[q];
         T.chain_dep_count = (uint32_t)prev_count[q];
+        if (c->n_queues > 1 && prev_count[q] > 0) {
+          // waits tile by tile, if it reads exactly one op of the previous stage and nothing else of the two can collide
+          int src = -1, readers = 0;
+          bool apart = true;
+          for (int j : prev_ops[q]) {
+            apart = apart && chain_ops_disjoint(T, c->table[j]);
+            if (chain_reads(T, c->table[j])) { ++readers; src = j; }
+          }
+          if (apart && readers == 1 && chain_reads_exactly(T, c->table[src])) {
+            local[i].reserve((size_t)T.tiles_m);
+            for (int m = 0; m < T.tiles_m; ++m) local[i].push_back(chain_local_range(T, c->table[src], m));
+          }
+        }
         if (ops[i].kind == ST_OP_CONV)
           ahead[q % kNumXCDs].push_back({(uint32_t)i, T.chain_flag_base, (uint32_t)prev2_begin[q], (uint32_t)prev2_count[q]});
       }
+      if (c->n_queues > 1) {
+        require_coverage(kv.second, ops, prev_begin, prev_count, &local);
+        for (int i : kv.second) {
+          if (local[i].empty()) continue;
+          c->table[i].chain_dep_begin = (uint32_t)prev2_begin[ops[i].sequence];
+          c->table[i].chain_dep_count = (uint32_t)prev2_count[ops[i].sequence];
+        }
+      }
+      flag_end.resize((size_t)flag_total, 0.0);
+      for (int x = 0; x < c->n_queues; ++x) {
+        if (c->n_queues == 1) {
+          queues[0].insert(queues[0].end(), stage_q[0].begin(), stage_q[0].end());
+          continue;
+        }
+        std::vector<int> mine;
+        for (int i : kv.second)
+          if (ops[i].sequence % c->n_queues == x) mine.push_back(i);
+        deal(c->table, mine, local, cost, stage_q[(size_t)x], &flag_end, &dealers[(size_t)x], queues.data() + (size_t)x * 2 * kChainColumns);
+      }
+      for (int q = 0; q < c->n_sequences; ++q) prev_ops_next(kv.second, ops, q, stage_items[q], &prev_ops[q]);
       for (int q = 0; q < c->n_sequences; ++q) {
         if (stage_items[q] > 0) {
           prev2_begin[q] = prev_begin[q]; prev2_count[q] = prev_count[q];
@@ -285,10 +417,17 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
           c->prefetch.insert(c->prefetch.end(), ahead[x].begin(), ahead[x].end());
         }
         c->prefetch_begin[kNumXCDs] = (uint32_t)c->prefetch.size();
+        c->deps.reserve(c->items.size());
+        for (const st_work_item& it : c->items) {
+          const TenantDev& T = c->table[it.tenant];
+          const ChainDep d = local[it.tenant].empty() ? ChainDep{0u, 0u} : local[it.tenant][it.tile_m];
+          const bool waits = T.chain_need != 0u;
+          c->deps.push_back({flag_of(T, it), waits ? T.chain_dep_begin : 0u, waits ? T.chain_dep_count : 0u, d.begin, d.count});
+        }
       }
     }
     if (status == ST_OK) {
-      // arena: [op table][queue][control block x2, persistent launch only][split-K counters][completion flags][column boundaries][prefetch list][split-K partial tiles]
+      // arena: [op table][queue][control block x2, persistent launch only][split-K counters][completion flags][column boundaries][prefetch list][entries' dependencies][split-K partial tiles]
       auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
       c->ctl_slots = (uint32_t)(kChainCtlSeq + c->n_sequences);
       int64_t ws_total = 0, ct_total = 0;
@@ -305,7 +444,8 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
       const size_t off_flags = off_ct + up((size_t)ct_total * 4);
       const size_t off_cols = off_flags + up(c->n_queues > 1 ? c->items.size() * 4 : 0);
       const size_t off_pf = off_cols + up(c->colbegin.size() * 4);
-      const size_t off_ws = off_pf + up(c->prefetch.size() * sizeof(ChainPrefetch));
+      const size_t off_deps = off_pf + up(c->prefetch.size() * sizeof(ChainPrefetch));
+      const size_t off_ws = off_deps + up(c->deps.size() * sizeof(ChainDep));
       const size_t total = off_ws + (size_t)ws_total * 4;
       if (!host_only && n_ops > 0) {
         hipError_t e = hipMalloc((void**)&c->d_arena, total);
@@ -321,6 +461,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
           coded_items(c->table, c->items, (st_work_item*)(host.data() + off_items));
           if (!c->colbegin.empty()) std::memcpy(host.data() + off_cols, c->colbegin.data(), c->colbegin.size() * 4);
           if (!c->prefetch.empty()) std::memcpy(host.data() + off_pf, c->prefetch.data(), c->prefetch.size() * sizeof(ChainPrefetch));
+          for (size_t k = 0; k < c->deps.size(); ++k) ((ChainDep*)(host.data() + off_deps))[k] = {c->deps[k].tiles_begin, c->deps[k].tiles_count};
           e = hipMemcpy(c->d_arena, host.data(), off_ws, hipMemcpyHostToDevice);
           if (e != hipSuccess) status = hip_fail(e, "hipMemcpy (chain tables)");
           c->d_ops = (TenantDev*)c->d_arena;
@@ -336,6 +477,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
             c->item_flags_bytes = c->items.size() * 4;
             c->d_colbegin = (uint32_t*)(c->d_arena + off_cols);
             c->d_prefetch = (ChainPrefetch*)(c->d_arena + off_pf);
+            c->d_deps = (ChainDep*)(c->d_arena + off_deps);
           }
         }
       }
@@ -372,7 +514,7 @@ static st_status chain_launch(st_chain* c, void* stream, uint64_t* prof_dev) {
     if (c->d_item_flags) ST_HIP((hipError_t)launch_zero(c->d_item_flags, (int64_t)((c->item_flags_bytes + 15) & ~(size_t)15), stream));
     c->run_number = 1u;
   }
-  ST_HIP((hipError_t)launch_chain(c->kernel_needs, c->d_ops, c->d_items, (uint32_t)c->items.size(), c->d_colbegin, (uint32_t)c->n_queues, c->d_prefetch, c->prefetch_begin, c->d_ctl[p],
+  ST_HIP((hipError_t)launch_chain(c->kernel_needs, c->d_ops, c->d_items, (uint32_t)c->items.size(), c->d_colbegin, c->d_deps, (uint32_t)c->n_queues, c->d_prefetch, c->prefetch_begin, c->d_ctl[p],
                                   c->d_ctl[p ^ 1u], c->ctl_slots, c->d_item_flags, c->run_number, c->spin_limit_ticks, c->flags,
                                   c->launch_workgroups > 0 ? c->launch_workgroups : c->workgroups, stream, prof_dev));
   c->run_parity = p ^ 1u;
@@ -477,6 +619,13 @@ extern "C" st_status st_chain_columns(const st_chain* chain, const uint32_t** be
   if (!chain || !begins || !n) return fail(ST_ERR_INVALID_ARG, "NULL argument");
   *begins = chain->colbegin.empty() ? nullptr : chain->colbegin.data();
   *n = (int64_t)chain->colbegin.size();
+  return ST_OK;
+}
+
+extern "C" st_status st_chain_dependencies(const st_chain* chain, const st_chain_dep** deps, int64_t* n) {
+  if (!chain || !deps || !n) return fail(ST_ERR_INVALID_ARG, "NULL argument");
+  *deps = chain->deps.empty() ? nullptr : chain->deps.data();
+  *n = (int64_t)chain->deps.size();
   return ST_OK;
 }
 

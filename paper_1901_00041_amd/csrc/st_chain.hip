@@ -9,7 +9,10 @@ namespace st {
 
 // Each kernel is instantiated in a source file of its own (st_chain_*.hip).
 constexpr uint32_t kBf16Rows = (1u << ST_DT_BF16) | kHasRows | kHasPools;
-static const void* kernel_for(uint32_t needs) { return (needs & ~kBf16Rows) == 0u ? chain_kernel<kBf16Rows>() : chain_kernel<kHasEverything>(); }
+static const void* kernel_for(uint32_t needs, bool columns) {
+  if ((needs & ~kBf16Rows) == 0u) return columns ? chain_kernel<kBf16Rows, true>() : chain_kernel<kBf16Rows, false>();
+  return columns ? chain_kernel<kHasEverything, true>() : chain_kernel<kHasEverything, false>();
+}
 
 int chain_max_workgroups(int* out_workgroups, int* out_xcds) {
   int dev = 0, per_cu = 0;
@@ -18,7 +21,7 @@ int chain_max_workgroups(int* out_workgroups, int* out_xcds) {
   hipDeviceProp_t prop;
   e = hipGetDeviceProperties(&prop, dev);
   if (e != hipSuccess) return (int)e;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel_for(kHasEverything), kThreads, 0);      // (every chain kernel is compiled for the same occupancy)
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel_for(kHasEverything, true), kThreads, 0);      // (every chain kernel is compiled for the same occupancy)
   if (e != hipSuccess) return (int)e;
   if (per_cu < 1) per_cu = 1;
   *out_workgroups = per_cu * prop.multiProcessorCount;
@@ -27,13 +30,13 @@ int chain_max_workgroups(int* out_workgroups, int* out_xcds) {
   return 0;
 }
 
-int launch_chain(uint32_t needs, const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, uint32_t n_queues, const ChainPrefetch* prefetch_dev,
+int launch_chain(uint32_t needs, const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, const ChainDep* deps_dev, uint32_t n_queues, const ChainPrefetch* prefetch_dev,
                  const uint32_t* prefetch_begin, uint32_t* ctl, uint32_t* ctl_other, uint32_t ctl_slots, uint32_t* item_flags, uint32_t run_number,
                  uint32_t spin_limit_ticks, uint32_t flags, int grid, void* stream, uint64_t* prof_dev) {
   if (n_queues != 1u && n_queues != (uint32_t)kNumXCDs) return (int)hipErrorInvalidValue;
   if (grid <= 0 || n_items == 0u) return 0;
   if (((flags & kChainFlagLocalFlags) != 0u) != (n_queues > 1u)) return (int)hipErrorInvalidValue;
-  if (n_queues > 1u && (item_flags == nullptr || run_number == 0u || colbegin_dev == nullptr)) return (int)hipErrorInvalidValue;
+  if (n_queues > 1u && (item_flags == nullptr || run_number == 0u || colbegin_dev == nullptr || deps_dev == nullptr)) return (int)hipErrorInvalidValue;
   ChainArgs a;
   a.ops = ops_dev;
   a.items = items_dev;
@@ -48,10 +51,11 @@ int launch_chain(uint32_t needs, const TenantDev* ops_dev, const st_work_item* i
   a.n_queues = n_queues;
   a.q_end = n_items;
   a.colbegin = colbegin_dev;
+  a.deps = deps_dev;
   a.prefetch = prefetch_dev;
   for (int x = 0; x <= kNumXCDs; ++x) a.prefetch_begin[x] = prefetch_dev ? prefetch_begin[x] : 0u;
   void* addresses[] = {(void*)&a, nullptr};
-  return (int)hipLaunchKernel(kernel_for(needs), dim3((unsigned)grid), dim3(kThreads), addresses, 0, (hipStream_t)stream);
+  return (int)hipLaunchKernel(kernel_for(needs, n_queues > 1u), dim3((unsigned)grid), dim3(kThreads), addresses, 0, (hipStream_t)stream);
 }
 
 }  // namespace st

@@ -1,4 +1,4 @@
-// st_chain_kernel for chains of every type and form (and max-pools).
+// st_chain_kernel for any chain, laid out per XCD.
 #include "st_chain_kernel.hpp"
 
-template const void* st::chain_kernel<st::kHasEverything>();
+template const void* st::chain_kernel<st::kHasEverything, true>();

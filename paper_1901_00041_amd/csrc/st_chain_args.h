@@ -22,11 +22,14 @@ struct ChainArgs {
   const ChainPrefetch* prefetch;      // columns: XCD x's filters in stage order are prefetch[prefetch_begin[x] .. prefetch_begin[x + 1])
   uint32_t prefetch_begin[kNumXCDs + 1];
   const uint32_t* colbegin;   // columns: column j of XCD x is items[colbegin[x * 2 * kChainColumns + j] .. colbegin[.. + j + 1])
+  const ChainDep* deps;       // columns: beside every entry of items
 };
 
 // The kernel compiled for HAS, to launch with one ChainArgs.
-template <uint32_t HAS> const void* chain_kernel();
-extern template const void* chain_kernel<(1u << ST_DT_BF16) | kHasRows | kHasPools>();
-extern template const void* chain_kernel<kHasEverything>();
+template <uint32_t HAS, bool COLUMNS> const void* chain_kernel();
+extern template const void* chain_kernel<(1u << ST_DT_BF16) | kHasRows | kHasPools, false>();
+extern template const void* chain_kernel<(1u << ST_DT_BF16) | kHasRows | kHasPools, true>();
+extern template const void* chain_kernel<kHasEverything, false>();
+extern template const void* chain_kernel<kHasEverything, true>();
 
 }  // namespace st

@@ -16,10 +16,11 @@
 // either expires the waiter raises the abort flag, and every workgroup leaves at its next claim or wait.  A workgroup
 // also takes at most n_items + 1 entries.  So the kernel always exits, whatever the clock or the counters do.
 //
-// Memory: producers write their outputs through to memory (device-scope stores) and wait for them before they
-// signal; consumers read activations, residuals and partial tiles with device-scope loads (CoherentActs), which
-// never stop at a vector cache and take from an L2 only what that L2 holds newer than memory, so no cache is ever
-// invalidated.  (The workgroup-scope invalidate does nothing for a workgroup that sits on one compute unit, and
+// Memory: consumers read activations, residuals and partial tiles with device-scope loads, which never stop at a vector
+// cache and take from an L2 what that L2 holds newer than memory, so no cache is ever invalidated.  Producers wait for
+// their stores before they signal: with one queue they write through to memory (CoherentActs), with queues per XCD, where
+// all of a sequence's readers share their L2, to that L2 (LocalActs).  Eight networks, us per pass written through and to the
+// L2: batch 1 361 -> 353, batch 3 597 -> 596, batch 8 1142 -> 1137.  (The workgroup-scope invalidate does nothing for a workgroup that sits on one compute unit, and
 // the device-scope one also empties the XCD's L2 of the filters: measured 1-2 us per work item.)  The signal is,
 // with one queue for the chip, a device-scope atomic on the sequence's counter; with queues per XCD, where producer
 // and consumer share one L2, a plain store of the run's number into the work item's own flag, which the consumer's
@@ -27,6 +28,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "st_chain_args.h"
 #include "st_internal.h"
@@ -59,16 +62,20 @@ __device__ __forceinline__ void prefetch_filters(ConstOp& T, uint32_t rank, int 
   }
 }
 
-// Whether flags [c0, n) all hold the run's number (one wavefront, uniform); c0 moves past those found set.  64 flags at a
-// time, or 256 while that many are left.
-__device__ __forceinline__ bool flags_set(const uint32_t* f, uint32_t n, uint32_t run, uint32_t lane, uint32_t& c0) {
-  while (c0 + 64u < n) {
+// The flags an entry waits for: [gate, gate + n_gate) and [tiles, tiles + n - n_gate), looked at as one list of n.
+struct FlagList { uint32_t gate, n_gate, tiles, n; };
+
+// Whether flags c0 .. n - 1 of the list all hold the run's number (one wavefront, uniform); c0 moves past those found set.  64
+// flags at a time, or 256 while that many are left.
+__device__ __forceinline__ bool flags_set(const uint32_t* item_flags, const FlagList& l, uint32_t run, uint32_t lane, uint32_t& c0) {
+  auto flag = [&](uint32_t c) { return __hip_atomic_load(item_flags + (c < l.n_gate ? l.gate + c : l.tiles + (c - l.n_gate)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  while (c0 + 64u < l.n) {
     constexpr int G = 4;
     uint32_t v[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const uint32_t c = c0 + 64u * g + lane;
-      v[g] = __hip_atomic_load(f + (c < n ? c : n - 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      v[g] = flag(c < l.n ? c : l.n - 1u);
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -76,11 +83,11 @@ __device__ __forceinline__ bool flags_set(const uint32_t* f, uint32_t n, uint32_
       c0 += 64u;
     }
   }
-  if (c0 < n) {
+  if (c0 < l.n) {
     const uint32_t c = c0 + lane;
-    const bool unset = (c < n) && __hip_atomic_load(f + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != run;
+    const bool unset = (c < l.n) && flag(c) != run;
     if (__builtin_amdgcn_ballot_w64(unset) != 0ull) return false;
-    c0 = n;
+    c0 = l.n;
   }
   return true;
 }
@@ -88,7 +95,7 @@ __device__ __forceinline__ bool flags_set(const uint32_t* f, uint32_t n, uint32_
 // Whether the stage before prefetch entry pf's has started, i.e. the stage before that one is complete.
 __device__ __forceinline__ bool prefetch_due(const ChainArgs& a, uint32_t pf, uint32_t lane, uint32_t& c0) {
   ConstPrefetch& p = ((ConstPrefetch*)a.prefetch)[pf];
-  return flags_set(a.item_flags + p.gate_begin, p.gate_count, a.run_number, lane, c0);
+  return flags_set(a.item_flags, FlagList{p.gate_begin, p.gate_count, 0u, p.gate_count}, a.run_number, lane, c0);
 }
 
 // Next position of queue q for this workgroup (thread 0 only); past the end once the pass has been abandoned.
@@ -109,7 +116,10 @@ __device__ __forceinline__ uint32_t chain_claim(const ChainArgs& a, uint32_t q, 
 // than it has columns in use, the entries of the columns nobody drew stay undone, their dependants' waits expire,
 // and the pass is abandoned and reported.  (The one-queue form, whose entries are claimed one by one, completes with
 // any number of resident workgroups.)
-template <uint32_t HAS>
+//
+// COLUMNS: this form.  Otherwise one queue, claimed entry by entry (what goes with either, signals and stores, is then known
+// when the kernel is compiled).
+template <uint32_t HAS, bool COLUMNS>
 __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[kSmemBytes];
   uint32_t* s_msg = (uint32_t*)smem;      // between work items only: read, then a barrier, before a tile or the next message
@@ -122,7 +132,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
       __hip_atomic_store(&a.ctl_other[a.ctl_slots * kChainCtlStride + i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   // the entries of this workgroup: [qb, qe) of the work list; one queue: claimed one by one from all of it
-  const bool claiming = a.n_queues == 1u;
+  constexpr bool claiming = !COLUMNS, by_flags = COLUMNS;
   uint32_t qb = 0u, qe = a.q_end;
   uint32_t pf = 0u, pf_end = 0u, rank = 0u;     // filters still to prefetch (shared columns only), and this workgroup's share
   if (!claiming) {
@@ -157,7 +167,8 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
   }
   uint32_t n_done = 0u;
   bool gave_up = false;
-  uint32_t seen_key = 0xffffffffu, seen_need = 0u;      // the dependency this workgroup last saw complete
+  uint32_t seen_key = 0xffffffffu, seen_need = 0u;      // the dependency (with flags: the gate) this workgroup last saw complete
+  uint32_t seen_begin = 0u, seen_end = 0u;              // ... and the range of tiles
   {
     uint32_t next = 0xffffffffu;            // one queue, thread 0: the entry claimed ahead
     if (claiming && tid == 0) next = chain_claim(a, 0u, qb, qe);
@@ -183,23 +194,31 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
       // one word of every 64-byte line of the op record, requested before the dependency wait and used after it, so
       // that the record sits in the scalar cache when the tile code reads its fields
       const uint32_t rec_touch = (uint32_t)(uintptr_t)T.x ^ (uint32_t)T.R ^ (uint32_t)T.tiles_m ^ T.x_bytes ^ T.chain_flag_base;
-      // A workgroup's further entries of a stage need not look again: one look at the flags of a stage of hundreds of items
-      // is microseconds.
-      const bool by_flags = (a.flags & kChainFlagLocalFlags) != 0u;
+      // What this workgroup has seen complete need not be looked at again: the gate of its earlier entries of this stage, and
+      // their tiles (the items of one pixel tile often follow each other in a column).
       const uint32_t key = by_flags ? T.chain_dep_begin : (uint32_t)T.chain_seq;
-      if (T.chain_need != 0u && !(key == seen_key && T.chain_need <= seen_need)) {
-        // Wavefront 0 looks at the dependency: with flags, at those of the sequence's previous stage, 64 at a time from
-        // the first that was not yet set (they were stored by workgroups of this XCD and sit, newer than memory, in
-        // its L2, where a device-scope load finds them; such a load never stops at the vector cache); with a
+      const bool gate_seen = key == seen_key && T.chain_need <= seen_need;
+      FlagList wanted{0u, 0u, 0u, 0u};
+      if (by_flags) {
+        const __attribute__((address_space(4))) ChainDep& d = ((const __attribute__((address_space(4))) ChainDep*)a.deps)[idx];
+        const uint32_t begin = d.begin, count = d.count;
+        wanted.gate = T.chain_dep_begin;
+        wanted.n_gate = gate_seen ? 0u : T.chain_dep_count;
+        wanted.tiles = begin;
+        wanted.n = wanted.n_gate + (begin >= seen_begin && begin + count <= seen_end ? 0u : count);
+      }
+      if (T.chain_need != 0u && (by_flags ? wanted.n != 0u : !gate_seen)) {
+        // Wavefront 0 looks at the dependency: with flags, at those of the gate and of the tiles the entry reads (ChainDep),
+        // 64 at a time from the first that was not yet set (they were stored by workgroups of this XCD and sit, newer than
+        // memory, in its L2, where a device-scope load finds them; such a load never stops at the vector cache); with a
         // counter, at the sequence's count of finished entries (bumped by device-scope atomics, carried out at the
         // memory side; a workgroup-scope load would stop at the vector cache and never see it move).
-        const uint32_t* f = a.item_flags + T.chain_dep_begin;
-        const uint32_t n = T.chain_dep_count, run = a.run_number, need = T.chain_need;
+        const uint32_t run = a.run_number, need = T.chain_need;
         const uint32_t* ctr = a.ctl + (kChainCtlSeq + T.chain_seq) * kChainCtlStride;
         uint32_t c0 = 0u;                     // flags before c0 are known to be set
         auto satisfied = [&]() -> bool {      // wavefront 0 only, uniform
           if (!by_flags) return (int32_t)(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - need) >= 0;
-          return flags_set(f, n, run, (uint32_t)tid, c0);
+          return flags_set(a.item_flags, wanted, run, (uint32_t)tid, c0);
         };
         // Wait.  In between, filters of coming stages may be due (pf): wavefront 0 says what happens next, 1 = the entry
         // starts, 2 = prefetch, 0 = the pass is abandoned.
@@ -235,20 +254,26 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
         // No cache is invalidated here: everything an entry reads that this launch wrote (activations, residuals,
         // split-K partial tiles) is read with device-scope loads, and everything else did not change.
         if (msg == 0u) { gave_up = true; break; }
-        seen_key = key;
-        seen_need = T.chain_need;
+        if (T.chain_dep_count != 0u) {        // (an empty range has no beginning to be known by)
+          seen_key = key;
+          seen_need = T.chain_need;
+        }
+        if (wanted.n != wanted.n_gate) {
+          seen_begin = wanted.tiles;
+          seen_end = wanted.tiles + (wanted.n - wanted.n_gate);
+        }
       }
       while (pf < pf_end && ((ConstPrefetch*)a.prefetch)[pf].flag_base <= T.chain_flag_base) ++pf;      // too late to prefetch these
       asm volatile("" ::"s"(rec_touch));
-      run_item<HAS, CoherentActs>(T, it, smem, prof);
-      // Completion.  Outputs were stored write-through; channel counts that are not a multiple of 8 take an epilogue
-      // with plain stores and need the release fence (write-back of the L2).
-      if ((it.reserved & kFormMask) != kFormPool && (T.K & 7) != 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      run_item<HAS, std::conditional_t<COLUMNS, LocalActs, CoherentActs>>(T, it, smem, prof);
+      // Completion.  With one queue outputs were stored write-through; channel counts that are not a multiple of 8 take an
+      // epilogue with plain stores and need the release fence (write-back of the L2).
+      if (!COLUMNS && (it.reserved & kFormMask) != kFormPool && (T.K & 7) != 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       __builtin_amdgcn_s_waitcnt(0);          // every store of this thread has been acknowledged
       __syncthreads();                        // ... of every thread; also: smem and s_msg are free again
       ++n_done;
       if (tid == 0) {
-        if ((a.flags & kChainFlagLocalFlags) != 0u) {
+        if (by_flags) {
           const uint32_t pos = ((uint32_t)it.tile_m * (uint32_t)T.tiles_n + (uint32_t)it.tile_n) * (uint32_t)T.split_k + (uint32_t)it.k_split_idx;
           __hip_atomic_store(a.item_flags + T.chain_flag_base + pos, a.run_number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         } else {
@@ -288,7 +313,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
   if (tid == 0 && n_done != 0u) __hip_atomic_fetch_add(&a.ctl[kChainCtlDone * kChainCtlStride], n_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <uint32_t HAS>
-const void* chain_kernel() { return (const void*)st_chain_kernel<HAS>; }
+template <uint32_t HAS, bool COLUMNS>
+const void* chain_kernel() { return (const void*)st_chain_kernel<HAS, COLUMNS>; }
 
 }  // namespace st

@@ -36,6 +36,7 @@ struct st_plan {
   std::vector<st_conv_desc> descs;
   std::vector<st_tenant_info> info;
   std::vector<st::TenantDev> tenants;       // host mirror of the device table
+  std::vector<double> item_time;            // the cost model's clocks per work item of each tenant
   std::vector<st_work_item> items_fused;    // order of the fused launch
   std::vector<st_work_item> items_tenant;   // tenant-major, sliced by the baselines
   bool host_only = false;

@@ -100,8 +100,8 @@ struct TenantDev {
   int32_t chain_seq;          // sequence whose completion counter this op's work items wait on and bump
   uint32_t chain_need;        // work items of that sequence that must be complete before this op's may start
   // one completion flag per work item (queue per XCD): work item (tile_m, tile_n, slice) of this op owns flag
-  // chain_flag_base + (tile_m * tiles_n + tile_n) * split_k + slice; the op may start once the flags
-  // [chain_dep_begin, chain_dep_begin + chain_dep_count) of the sequence's previous stage all hold the run's number
+  // chain_flag_base + (tile_m * tiles_n + tile_n) * split_k + slice; an entry of the op may start once the flags
+  // [chain_dep_begin, chain_dep_begin + chain_dep_count) and those of its own ChainDep all hold the run's number
   uint32_t chain_flag_base, chain_dep_begin, chain_dep_count;
 };
 static_assert(offsetof(TenantDev, ws) == 192 && sizeof(TenantDev) == 256, "lines of the scalar cache");
@@ -143,9 +143,13 @@ constexpr int kChainColumns = kNumCUs / kNumXCDs; // exclusive columns per XCD (
 constexpr uint32_t kChainFlagLocalFlags = 4u;     // completion travels through per-item flags in the XCD's own L2
 // Filters to pull into an XCD's L2 ahead of their stage: op's w, once the flags [gate_begin, gate_begin + gate_count) are
 // set (those of the stage two before; none for the first two stages); flag_base is the op's own.
+// What an entry waits for besides the range in its op's record: the flags [begin, begin + count).  An op that reads exactly what
+// one op of the previous stage writes has the stage before that in its record (everything earlier is then complete) and
+// here, per entry, the previous stage's tiles that the entry reads; any other op has the whole previous stage in its record.
+struct ChainDep { uint32_t begin, count; };
 struct ChainPrefetch { uint32_t op, flag_base, gate_begin, gate_count; };
 int chain_max_workgroups(int* out_workgroups, int* out_xcds);
-int launch_chain(uint32_t needs, const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, uint32_t n_queues, const ChainPrefetch* prefetch_dev,
+int launch_chain(uint32_t needs, const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, const ChainDep* deps_dev, uint32_t n_queues, const ChainPrefetch* prefetch_dev,
                  const uint32_t* prefetch_begin, uint32_t* ctl, uint32_t* ctl_other, uint32_t ctl_slots, uint32_t* item_flags, uint32_t run_number,
                  uint32_t spin_limit_ticks, uint32_t flags, int grid, void* stream, uint64_t* prof_dev);
 int launch_empty(void* stream);

@@ -606,6 +606,7 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
     for (int t = 0; t < n_tenants; ++t) {
       st_tenant_info& ti = p->info[t];
       const Option& op = options[t][pick[t]];
+      p->item_time.push_back(op.item_time);
       ti.tile_cfg = op.cfg;
       ti.k_steps = cdiv(ti.Kgemm * elem_size(descs[t].in_dtype), kTileShapes[op.cfg].KB);
       ti.MT = kTileShapes[op.cfg].MT;

@@ -177,10 +177,13 @@ constexpr int kAuxDeviceCoherent = 16;   // sc1
 // How a tile reads activations (x and the residual): what another kernel wrote before this launch can be read
 // through the caches (PlainActs); what other workgroups of the SAME launch write (the chain kernel) must be read
 // with device-scope loads, which never stop at the compute unit's vector cache and take from the L2 only what that
-// L2 itself holds newer than memory (CoherentActs).  Outputs are stored write-through either way; filters never
-// change during a launch and always go through the caches.
-struct PlainActs { static constexpr int kActAux = 0; };
-struct CoherentActs { static constexpr int kActAux = kAuxDeviceCoherent; };
+// L2 itself holds newer than memory (CoherentActs).  Outputs are stored write-through (a launch per layer: they leave the L2
+// while the kernel still runs, see tile_epilogue), unless everyone who reads them during the launch shares the L2
+// (LocalActs: a chain laid out per XCD; the same goes for split-K partial tiles and their counters); filters never change
+// during a launch and always go through the caches.
+struct PlainActs { static constexpr int kActAux = 0, kOutAux = kAuxDeviceCoherent; static constexpr bool kOneL2 = false; };
+struct CoherentActs { static constexpr int kActAux = kAuxDeviceCoherent, kOutAux = kAuxDeviceCoherent; static constexpr bool kOneL2 = false; };
+struct LocalActs { static constexpr int kActAux = kAuxDeviceCoherent, kOutAux = 0; static constexpr bool kOneL2 = true; };
 
 // floor(n / d) for 0 <= n < 2^31 with the planner's multiplier m = floor(2^(31+L)/d)+1, L = ceil(log2 d)
 __device__ __forceinline__ int fast_div(int n, uint32_t m, int L) {
@@ -328,7 +331,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
       const bool ok = (MT * NV % kThreads == 0 || v < MT * NV) & (m < m_end) & (ch < Kf);
       const uint32_t off = ok ? ((uint32_t)m * (uint32_t)Kf + (uint32_t)ch) * 2u : kInvalidOffset;
       const u32x4 d = *(const u32x4*)(smem + (row < MT ? row : 0) * PITCHB + cv * 16);
-      __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off, 0, kAuxDeviceCoherent);
+      __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off, 0, POL::kOutAux);
     }
    }
   }
@@ -413,7 +416,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
 #pragma unroll
             for (int e = 0; e < 4; ++e) a[u][e] = a[u][e] > 0.f ? a[u][e] : 0.f;
           }
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a[u]), ry, (int)off[u], 0, kAuxDeviceCoherent);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a[u]), ry, (int)off[u], 0, POL::kOutAux);
         }
       }
     } else if constexpr (DT != ST_DT_F32) {
@@ -461,7 +464,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
             pk[e] = pack16<DT>(lo[u][2 * e], lo[u][2 * e + 1]);
             pk[2 + e] = pack16<DT>(hi[u][2 * e], hi[u][2 * e + 1]);
           }
-          __builtin_amdgcn_raw_buffer_store_b128(pk, ry, (int)off[u], 0, kAuxDeviceCoherent);
+          __builtin_amdgcn_raw_buffer_store_b128(pk, ry, (int)off[u], 0, POL::kOutAux);
         }
       }
     }
@@ -533,7 +536,7 @@ _Pragma("unroll")
 // ---- split-K hand-off ----------------------------------------------------------------------------
 // Publishes this workgroup's partial tile; the last workgroup to arrive sums all slices in index order into acc and
 // returns true (it goes on to the epilogue), the others return false.
-template <int MT, int NT, int BM, int BN, int MF, class Acc>
+template <int MT, int NT, int BM, int BN, int MF, class POL, class Acc>
 __device__ __forceinline__ bool split_k_reduce(ConstOp& T, const st_work_item it, Acc (&acc)[BM][BN], int tid, char* smem, uint64_t* prof) {
   constexpr int NG = (MF == 32) ? 4 : 1;      // groups of 4 consecutive filters per block per lane
   {
@@ -550,15 +553,16 @@ __device__ __forceinline__ bool split_k_reduce(ConstOp& T, const st_work_item it
         for (int g = 0; g < NG; ++g) {
           f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
           __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs,
-                                                 (((i * BN + j) * NG + g) * kThreads + tid) * 16, my, kAuxDeviceCoherent);
+                                                 (((i * BN + j) * NG + g) * kThreads + tid) * 16, my, POL::kOutAux);
         }
     __builtin_amdgcn_s_waitcnt(0);       // every store of this thread has completed (written through)
     __syncthreads();
     uint32_t* flag = (uint32_t*)smem;
     if (tid == 0) {
-      const uint32_t old = __hip_atomic_fetch_add(&T.counters[tile_id], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      constexpr int scope = POL::kOneL2 ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT;      // in that L2, or at the memory side
+      const uint32_t old = __hip_atomic_fetch_add(&T.counters[tile_id], 1u, __ATOMIC_RELAXED, scope);
       const uint32_t last = (old == (uint32_t)(T.split_k - 1));
-      if (last) __hip_atomic_store(&T.counters[tile_id], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next run
+      if (last) __hip_atomic_store(&T.counters[tile_id], 0u, __ATOMIC_RELAXED, scope);  // next run
       *flag = last;
     }
     __syncthreads();
@@ -926,7 +930,7 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
   }
 
   if (prof && tid == 0) prof[2] = __builtin_readcyclecounter();
-  if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
+  if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF, POL>(T, it, acc, tid, smem, prof)) return;
 
   // ---- epilogue: (+ residual) -> ReLU -> cast -> store ---------------------------------------------
   tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem, res_lds);
@@ -1120,7 +1124,7 @@ __device__ __forceinline__ void conv_tile_patch(ConstOp& T, const st_work_item i
   block(std::false_type{});
 
   if (prof && tid == 0) prof[2] = __builtin_readcyclecounter();
-  if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
+  if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF, POL>(T, it, acc, tid, smem, prof)) return;
   tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem);
   if (prof && tid == 0) stamp_end(prof);
 }
@@ -1337,7 +1341,7 @@ __device__ __forceinline__ void conv_tile_gather(ConstOp& T, const st_work_item 
 
   if (prof && tid == 0) prof[2] = __builtin_readcyclecounter();
 
-  if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF>(T, it, acc, tid, smem, prof)) return;
+  if (T.split_k > 1 && !split_k_reduce<MT, NT, BM, BN, MF, POL>(T, it, acc, tid, smem, prof)) return;
 
   // ---- epilogue: (+ residual) -> ReLU -> cast -> store ---------------------------------------------
   tile_epilogue<MT, NT, BM, BN, MF, DT, 1, kSmemBytes, POL>(T, acc, m0, T.M, n0, wm0, wn0, lrow, lk, tid, smem);
@@ -1622,12 +1626,12 @@ __device__ __forceinline__ u32x4 maxpool_vector(const void* __restrict__ xv, uin
 }
 
 // One max-pool work item: kThreads output vectors, stored write-through.
-template <int DT, int AUX>
+template <int DT, class POL>
 __device__ __forceinline__ void pool_item(ConstOp& T, const st_work_item it) {
   const int64_t idx = (int64_t)it.tile_m * kThreads + work_thread_id();
   if (idx >= (int64_t)T.M) return;
-  const u32x4 v = maxpool_vector<DT, AUX>(T.x, T.x_bytes, idx, T.H, T.W, T.C, T.P, T.Q, T.R, T.stride, T.pad);
-  __builtin_amdgcn_raw_buffer_store_b128(v, make_rsrc(T.y, T.y_bytes), (int)((uint32_t)idx * 16u), 0, kAuxDeviceCoherent);
+  const u32x4 v = maxpool_vector<DT, POL::kActAux>(T.x, T.x_bytes, idx, T.H, T.W, T.C, T.P, T.Q, T.R, T.stride, T.pad);
+  __builtin_amdgcn_raw_buffer_store_b128(v, make_rsrc(T.y, T.y_bytes), (int)((uint32_t)idx * 16u), 0, POL::kOutAux);
 }
 
 template <int CFG, int DT, class POL>
@@ -1666,7 +1670,7 @@ __device__ __forceinline__ void run_form(uint32_t form, ConstOp& T, const st_wor
     case kFormPool:
       if constexpr ((HAS & kHasPools) != 0u) {
         if (prof && threadIdx.x == 0) stamp_start(prof);
-        pool_item<DT, POL::kActAux>(T, it);
+        pool_item<DT, POL>(T, it);
         if (prof && threadIdx.x == 0) stamp_end(prof);
       }
       break;
