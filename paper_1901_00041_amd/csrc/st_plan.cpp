@@ -94,13 +94,13 @@ struct ItemCosts { double first[kNumTileCfgs], step[kNumTileCfgs], epi[kNumTileC
 enum { kCosts16 = 0, kCosts32 = 1, kCostsPatch = 2 };
 // [kCosts*][alone on the compute unit]
 static const ItemCosts kCosts[3][2] = {
-    {{{4800, 4500, 4500, 3800, 4200, 3250, 3000}, {1250, 740, 740, 430, 650, 560, 520}, {4700, 2500, 2600, 1800, 1400, 1230, 2800}},
-     {{2700, 2500, 2500, 2300, 2600, 2200, 3000}, {820, 470, 470, 305, 450, 375, 520}, {3900, 2070, 2080, 1500, 1240, 1120, 2800}}},
+    {{{4800, 4500, 4500, 3800, 4200, 3250, 3000}, {1250, 740, 740, 430, 650, 560, 310}, {4700, 2500, 2600, 1800, 1400, 1230, 2300}},
+     {{2700, 2500, 2500, 2300, 2600, 2200, 3000}, {820, 470, 470, 305, 450, 375, 310}, {3900, 2070, 2080, 1500, 1240, 1120, 2300}}},
     {{{5200, 5500, 5500, 4300, 4300, 3250, 0}, {7200, 3600, 3600, 1850, 1850, 1060, 0}, {8000, 4500, 4000, 3000, 1800, 1330, 0}},
      {{3500, 3000, 3000, 2500, 2700, 2300, 0}, {4350, 2260, 2240, 1200, 1300, 740, 0}, {4300, 2200, 2200, 1670, 1430, 1180, 0}}},
     {{{4800, 2300, 2400, 2000, 2300, 3250, 0}, {1250, 620, 680, 380, 590, 560, 0}, {4700, 2400, 2500, 1700, 1400, 1230, 0}},
      {{2700, 1500, 1550, 1300, 1600, 2200, 0}, {820, 465, 445, 310, 410, 375, 0}, {3900, 2060, 2030, 1500, 1240, 1120, 0}}}};
-static const double kRowStageCost = 6500.0;     // row tile: copying image rows and filters into LDS
+static const double kRowStageCost = 4300.0;     // row tile: copying image rows and filters into LDS
 // any channel count (conv_tile_gather) [fp32 operands]: bound by the texture addresser, which takes unaligned vectors apart
 static const double kGatherStepCost[2][kNumTileCfgs] = {{0, 2600.0, 0, 1550.0, 0, 0, 0}, {0, 3600.0, 0, 2000.0, 0, 0, 0}};
 static const double kGatherPartCost[kNumTileCfgs] = {0, 4000.0, 0, 1900.0, 0, 0, 0};   // more if the step crosses a filter row
@@ -284,7 +284,7 @@ static Option make_row_option(const st_conv_desc& d, int rows_per_tile, bool alo
   o.steps_per_split = d.R;
   o.items = (int64_t)d.N * cdiv(P, rows_per_tile) * cdiv(Q, kTileShapes[kRowCfg].MT) * cdiv(d.K, kTileShapes[kRowCfg].NT);
   const ItemCosts& c = kCosts[0][alone ? 1 : 0];
-  o.item_time = c.first[kRowCfg] + kRowStageCost + 500.0 * rows_per_tile + rows_per_tile * (d.R * c.step[kRowCfg] + c.epi[kRowCfg]);
+  o.item_time = c.first[kRowCfg] + kRowStageCost + 300.0 * rows_per_tile + rows_per_tile * (d.R * c.step[kRowCfg] + c.epi[kRowCfg]);
   o.area = o.item_time * (double)o.items;
   return o;
 }

@@ -1382,6 +1382,7 @@ __device__ __forceinline__ void conv_tile_rows(ConstOp& T, const st_work_item it
   static_assert(kStageBytes >= (MT / EPI_PASSES) * (NT + 4) * 4 && kStageBytes >= MT * (NT * 2 + 16), "row tile stage buffer");
   typedef Mma<DT, MF> MMA;
   typedef typename MMA::Acc Acc;
+  constexpr bool HOLD = POL::kActAux == 0;           // (see rows_held)
   const int tid = work_thread_id();
   if (prof && tid == 0) stamp_start(prof);
   const int lane = tid & 63, wave = tid >> 6;
@@ -1513,11 +1514,11 @@ __device__ __forceinline__ void conv_tile_rows(ConstOp& T, const st_work_item it
   const char* wrow = sW + (wn0 + lrow) * R * (KR * 2) + lk * 16;
   const int q_end = (q0 + MT < Q) ? q0 + MT : Q;
   // operands of one (filter row, half): the filter vector and BM masked pixel vectors
-  struct Ops { u32x4 wf; u32x4 xf[BM]; };
+  struct Ops { u32x4 xf[BM]; };
+  auto fetch_w = [&](auto HALF, int r) -> u32x4 { return *(const u32x4*)(wrow + r * (KR * 2) + decltype(HALF)::value * 32); };
   auto fetch = [&](auto HALF, int rt, int r, Ops& o) {
     constexpr int half = decltype(HALF)::value;
     const char* xr = sX + (rt * T.stride + r) * pitch + half * 32;
-    o.wf = *(const u32x4*)(wrow + r * (KR * 2) + half * 32);
 #pragma unroll
     for (int i = 0; i < BM; ++i) {
       const uint32_t* src = (const uint32_t*)(xr + qa[i]);
@@ -1525,37 +1526,78 @@ __device__ __forceinline__ void conv_tile_rows(ConstOp& T, const st_work_item it
     }
   };
   // masking is left to the point of use, so that the LDS reads stay in flight behind the other half's MFMAs
-  auto mma = [&](auto HALF, const Ops& o, Acc (&acc)[BM][BN]) {
+  auto mma = [&](auto HALF, auto NH, const u32x4& wf, const Ops& o, Acc (&acc)[BM][BN]) {
     constexpr int half = decltype(HALF)::value;
+    constexpr bool LAST = half + 1 == decltype(NH)::value;       // (an earlier half is full)
 #pragma unroll
     for (int i = 0; i < BM; ++i) {
-      const u32x4 xf = {o.xf[i][0] & msk[half][0], o.xf[i][1] & msk[half][1], o.xf[i][2] & msk[half][2], o.xf[i][3] & msk[half][3]};
-      acc[i][0] = MMA::run(o.wf, xf, acc[i][0]);
+      u32x4 xf = o.xf[i];
+      if (LAST) xf = u32x4{xf[0] & msk[half][0], xf[1] & msk[half][1], xf[2] & msk[half][2], xf[3] & msk[half][3]};
+      acc[i][0] = MMA::run(wf, xf, acc[i][0]);
     }
   };
-  for (int rt = 0; rt < nrows_out; ++rt) {
-    Acc acc[BM][BN];
+  // One output row after another: row(rt, acc) adds up its pixels.
+  auto each_row = [&](auto row) {
+    for (int rt = 0; rt < nrows_out; ++rt) {
+      Acc acc[BM][BN];
 #pragma unroll
-    for (int i = 0; i < BM; ++i)
+      for (int i = 0; i < BM; ++i)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][0][v] = 0.f;
-    // the operands of the next half step are fetched from LDS while the MFMAs of the current one run; the
-    // loop exists once per number of halves so that its body is free of branches
-    auto k_loop = [&](auto NH) {
-      constexpr int halves = decltype(NH)::value;
+        for (int v = 0; v < 16; ++v) acc[i][0][v] = 0.f;
+      row(rt, acc);
+      const int mrow = (n * P + p0 + rt) * Q;
+      tile_epilogue<MT, NT, BM, BN, MF, DT, EPI_PASSES, kStageBytes, POL>(T, acc, mrow + q0, mrow + q_end, n0, wm0, wn0, lrow, lk, tid, smem);
+    }
+  };
+  // Seven filter rows of two halves, the usual stem: the filters stay in registers for all output rows of the item, and the
+  // pixels of the next filter row are fetched from LDS while the MFMAs of the current one run.  What bounds it is still the
+  // latency of those reads and of the epilogue's two barriers: an output row of 128 pixels x 64 filters beside a second
+  // workgroup 6270 clocks (filters read again for every row, a loop over the filter rows) -> 4750, of which the MFMAs are 900; eight
+  // stems of batch 8 60.8 us -> 51.6.  Not in a chain: its one kernel has no registers to spare for it (eight networks of
+  // batch 1 346 us -> 351).
+  auto rows_held = [&](auto RN, auto NH) {
+    constexpr int rows = decltype(RN)::value, halves = decltype(NH)::value;
+    u32x4 w[rows][halves];
+    static_for<rows>([&](auto RR) {
+      static_for<halves>([&](auto HALF) { w[decltype(RR)::value][decltype(HALF)::value] = fetch_w(HALF, decltype(RR)::value); });
+    });
+    each_row([&](int rt, Acc (&acc)[BM][BN]) {
+      Ops o[2][halves];
+      static_for<halves>([&](auto HALF) { fetch(HALF, rt, 0, o[0][decltype(HALF)::value]); });
+      static_for<rows>([&](auto RR) {
+        constexpr int r = decltype(RR)::value;
+        if constexpr (r + 1 < rows) static_for<halves>([&](auto HALF) { fetch(HALF, rt, r + 1, o[(r + 1) & 1][decltype(HALF)::value]); });
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<halves>([&](auto HALF) { mma(HALF, NH, w[r][decltype(HALF)::value], o[r & 1][decltype(HALF)::value], acc); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+  };
+  // Any number of filter rows: operands of the next half step are fetched while the MFMAs of the current one run; the loop
+  // exists once per number of halves so that its body is free of branches.
+  auto rows_streamed = [&](auto NH) {
+    constexpr int halves = decltype(NH)::value;
+    each_row([&](int rt, Acc (&acc)[BM][BN]) {
       Ops o0, o1;
-      fetch(std::integral_constant<int, 0>{}, rt, 0, o0);
+      u32x4 w0, w1;
+      auto first = [&](int r) { w0 = fetch_w(std::integral_constant<int, 0>{}, r); fetch(std::integral_constant<int, 0>{}, rt, r, o0); };
+      first(0);
       for (int r = 0; r < R; ++r) {
-        if constexpr (halves > 1) fetch(std::integral_constant<int, 1>{}, rt, r, o1);
-        mma(std::integral_constant<int, 0>{}, o0, acc);
-        // the last iteration fetches filter row R - 1 again instead of branching around the reads
-        fetch(std::integral_constant<int, 0>{}, rt, (r + 1 < R) ? r + 1 : r, o0);
-        if constexpr (halves > 1) mma(std::integral_constant<int, 1>{}, o1, acc);
+        if constexpr (halves > 1) { w1 = fetch_w(std::integral_constant<int, 1>{}, r); fetch(std::integral_constant<int, 1>{}, rt, r, o1); }
+        mma(std::integral_constant<int, 0>{}, NH, w0, o0, acc);
+        first((r + 1 < R) ? r + 1 : r);      // the last time filter row R - 1 again instead of a branch around the reads
+        if constexpr (halves > 1) mma(std::integral_constant<int, 1>{}, NH, w1, o1, acc);
       }
-    };
-    if (nh > 1) k_loop(std::integral_constant<int, 2>{}); else k_loop(std::integral_constant<int, 1>{});
-    const int mrow = (n * P + p0 + rt) * Q;
-    tile_epilogue<MT, NT, BM, BN, MF, DT, EPI_PASSES, kStageBytes, POL>(T, acc, mrow + q0, mrow + q_end, n0, wm0, wn0, lrow, lk, tid, smem);
+    });
+  };
+  const std::integral_constant<int, 1> one{};
+  const std::integral_constant<int, 2> two{};
+  if (HOLD && R == 7 && nh > 1) {
+    if constexpr (HOLD) rows_held(std::integral_constant<int, 7>{}, two);
+  } else if (nh > 1) {
+    rows_streamed(two);
+  } else {
+    rows_streamed(one);
   }
   if (prof && tid == 0) {
     prof[2] = __builtin_readcyclecounter();
