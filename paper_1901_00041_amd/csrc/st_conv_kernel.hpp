@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "st_internal.h"
 #include "st_launch.h"
 #include "st_tiles.hpp"
@@ -25,7 +27,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_conv_kernel(const TenantDev* _
   it.reserved = ip->reserved;
   ConstOp& T = *(ConstOp*)(tenants + it.tenant);
   uint64_t* prof = prof_base ? prof_base + (size_t)blockIdx.x * kProfSlots : nullptr;
-  run_item<HAS, PlainActs>(T, it, smem, prof);
+  run_item<HAS, std::conditional_t<(HAS & kHasGather) != 0u, RaggedActs, PlainActs>>(T, it, smem, prof);
 }
 
 template <uint32_t HAS>

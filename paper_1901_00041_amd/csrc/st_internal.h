@@ -35,14 +35,16 @@ constexpr TileShape kTileShapes[kNumTileCfgs] = {
 };
 constexpr int kSmemBytes = 81920;  // LDS per workgroup: half a compute unit's 160 KiB
 constexpr int kRowStageBytes = 18432;   // row tile: LDS set aside for the epilogue's transposition buffer
-// tile shapes that also exist for any channel count (conv_tile_gather: not a multiple of the 16-byte vector
-// width); the planner maps such tenants onto one of them
+// tile shapes that exist for any channel count through conv_tile_gather; the planner maps tenants whose channels are not
+// a multiple of the 16-byte vector onto one of them
 constexpr bool kGenericCfg[kNumTileCfgs] = {false, true, false, true, false, false, false};
+// ... and those that exist for whole vectors and channels left over (kOrderPieces)
+constexpr bool kPiecesCfg[kNumTileCfgs] = {false, true, false, true, true, true, false};
 
 // What a workgroup runs, in the `reserved` word of the device's copy of a work item: a tile form (vector and any-channel forms
 // of a shape, its form with the input patch resident, the row tile, a chain's max-pool) and the operands' type.  A workgroup
 // then needs nothing but its work item to find its code, and the tenant's record is fetched once, by the tile that runs.
-constexpr uint32_t kFormVector = 0, kFormPatch = 8, kFormGather = 16, kFormRows = 24, kFormPool = 25;     // + the tile shape for the first three
+constexpr uint32_t kFormVector = 0, kFormPatch = 8, kFormGather = 16, kFormRows = 24, kFormPool = 25, kFormPieces = 32;     // + the tile shape for all but rows and pool
 constexpr uint32_t kFormTypeShift = 8, kFormMask = (1u << kFormTypeShift) - 1u;
 // What a kernel was compiled for: bit `type` for every operand type, and the forms beyond vector and patch tiles.  All tile
 // code in one kernel costs every launch: a tile is reached over several far jumps through instructions that no other
@@ -54,6 +56,7 @@ constexpr uint32_t kHasRows = 8u, kHasGather = 16u, kHasPools = 32u, kHasEveryth
 
 constexpr int kOrderTaps = 0, kOrderChannels = 1, kOrderLinear = 2;   // see conv_tile
 constexpr int kOrderPatch = 3;     // see conv_tile_patch
+constexpr int kOrderPieces = 4;    // any channel count of more than a vector: whole vectors first, then the channels left over (conv_tile)
 // filter steps resident in LDS when a tile shape keeps its input patch there (0: the shape has no such form; two patches and
 // two 16 KiB steps of a 128x128 tile would leave no room for a third).  Filters from beyond the L2 need the fourth step
 // where a step is short: eight tenants of 3x3 on 64x64 tiles 11.1 us with three, 9.1 with four.
@@ -72,9 +75,10 @@ struct TenantDev {
   int32_t Q, PQ, M, Kg;
   int32_t in_dtype, out_dtype, epilogue;
   int32_t cfg, split_k, k_steps, k_steps_per_split;
-  int32_t vec_ok;        // 1: C is a multiple of the 16-byte vector width (conv_tile), 0: any channel count or row tile
+  int32_t vec_ok;        // 1: C is a multiple of the 16-byte vector width, 2: kOrderPieces (both conv_tile), 0: any channel count or row tile
   int32_t step_dk, step_dr;   // one K step in the reduction index (r*S + s)*C + c: KT elements = step_dr filter rows of
-                              //    S*C elements and step_dk elements more
+                              //    S*C elements and step_dk elements more; kOrderPieces: a tap's channels in whole vectors, and
+                              //    the steps that all taps' whole vectors take (k_steps counts those of the channels left over, too)
   int32_t k_order;            // kOrder*: how conv_tile walks the reduction index
   uint32_t tap_rows;          // kOrderChannels: bit r*S for every filter row r
   int32_t patch_rows;         // kOrderPatch: most input pixels a tile's taps touch
@@ -85,7 +89,7 @@ struct TenantDev {
   uint32_t magic_pq, magic_q;
   uint32_t x_bytes, w_bytes;  // buffer sizes for bounds-checked loads
   uint32_t y_bytes;           // size of y (and of the residual) in bytes
-  int32_t shift_c, shift_s;   // the same division for d = C and d = S
+  int32_t shift_c, shift_s;   // the same division for d = C (kOrderPieces: step_dk) and d = S
   uint32_t magic_c, magic_s;
   int32_t P;
   // read by some
@@ -110,6 +114,7 @@ static_assert(sizeof(TenantDev) % 8 == 0, "TenantDev must keep pointer alignment
 // The work item's code word for an op, and what its kernel must have been compiled for.
 inline uint32_t tile_code(const TenantDev& T) {
   const uint32_t form = T.cfg == kChainPoolCfg ? kFormPool
+                        : T.vec_ok == 2        ? kFormPieces + (uint32_t)T.cfg
                         : T.vec_ok             ? (T.k_order == kOrderPatch ? kFormPatch : kFormVector) + (uint32_t)T.cfg
                         : T.cfg == kRowCfg     ? kFormRows
                                                : kFormGather + (T.cfg == 1 ? 1u : 3u);

@@ -181,9 +181,11 @@ constexpr int kAuxDeviceCoherent = 16;   // sc1
 // while the kernel still runs, see tile_epilogue), unless everyone who reads them during the launch shares the L2
 // (LocalActs: a chain laid out per XCD; the same goes for split-K partial tiles and their counters); filters never change
 // during a launch and always go through the caches.
-struct PlainActs { static constexpr int kActAux = 0, kOutAux = kAuxDeviceCoherent; static constexpr bool kOneL2 = false; };
-struct CoherentActs { static constexpr int kActAux = kAuxDeviceCoherent, kOutAux = kAuxDeviceCoherent; static constexpr bool kOneL2 = false; };
-struct LocalActs { static constexpr int kActAux = kAuxDeviceCoherent, kOutAux = 0; static constexpr bool kOneL2 = true; };
+// kAnyFilters: whole vectors are stored for filter counts off the vector width, too (see tile_epilogue).
+struct PlainActs { static constexpr int kActAux = 0, kOutAux = kAuxDeviceCoherent; static constexpr bool kOneL2 = false, kAnyFilters = false; };
+struct RaggedActs : PlainActs { static constexpr bool kAnyFilters = true; };
+struct CoherentActs { static constexpr int kActAux = kAuxDeviceCoherent, kOutAux = kAuxDeviceCoherent; static constexpr bool kOneL2 = false, kAnyFilters = false; };
+struct LocalActs { static constexpr int kActAux = kAuxDeviceCoherent, kOutAux = 0; static constexpr bool kOneL2 = true, kAnyFilters = false; };
 
 // floor(n / d) for 0 <= n < 2^31 with the planner's multiplier m = floor(2^(31+L)/d)+1, L = ceil(log2 d)
 __device__ __forceinline__ int fast_div(int n, uint32_t m, int L) {
@@ -271,10 +273,17 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
   const bool relu = (T.epilogue & ST_EPI_RELU) != 0u;
   const bool has_res = (T.epilogue & ST_EPI_RESIDUAL) != 0u;
   const int Kf = T.K;
-  const bool vec4 = (Kf & 3) == 0;
+  const bool vec4 = (Kf & 3) == 0, whole = (Kf & 7) == 0;
+  // Any number of filters: a row of the output is still mostly whole vectors (at element-aligned addresses); what is left of
+  // it is stored element by element, by the lanes that hold it.  (With stores per lane and element instead, four of 2 bytes for
+  // every four filters of a pixel, a 128x64 tile of 201 filters spent 9900 clocks after its last MFMA.)  Not with a
+  // residual, not in row tiles, and only in the kernel for everything: the second way out costs other launches 2-3 % (16
+  // unlike tenants 40.1 -> 41.2 us).
+  constexpr bool kAnyFilters = POL::kAnyFilters && PASSES == 1;
+  const bool rest = kAnyFilters && !whole && n0 + NT > Kf;       // this tile holds the end of the rows
   bool done16 = false;
   if constexpr (DT != ST_DT_F32) {
-   if ((Kf & 7) == 0 && T.out_dtype != ST_DT_F32 && (!has_res || res_lds >= 0)) {
+   if (T.out_dtype != ST_DT_F32 && (has_res ? (Kf & 7) == 0 && res_lds >= 0 : whole || kAnyFilters)) {
     // 16-bit output: the residual (if any, staged in LDS) is added to the accumulators, ReLU and the rounding are applied
     // to them, and the transposition buffer holds the finished 16-bit values, [pixel][filter], the whole tile at once.
     // Every lane then moves 16 bytes of one output row from LDS to memory.
@@ -323,6 +332,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
     __syncthreads();
     constexpr int NV = NT / 8;
     constexpr int IT = (MT * NV + kThreads - 1) / kThreads;
+    auto store_rows = [&](auto REST) {       // REST: with the end of the rows
 #pragma unroll
     for (int u = 0; u < IT; ++u) {
       const int v = u * kThreads + tid;
@@ -331,12 +341,29 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
       const bool ok = (MT * NV % kThreads == 0 || v < MT * NV) & (m < m_end) & (ch < Kf);
       const uint32_t off = ok ? ((uint32_t)m * (uint32_t)Kf + (uint32_t)ch) * 2u : kInvalidOffset;
       const u32x4 d = *(const u32x4*)(smem + (row < MT ? row : 0) * PITCHB + cv * 16);
-      __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off, 0, POL::kOutAux);
+      if constexpr (!decltype(REST)::value) {
+        __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off, 0, POL::kOutAux);
+      } else if (ok) {
+        if (ch + 8 <= Kf) {
+          __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off, 0, POL::kOutAux);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 7; ++e)
+            if (ch + e < Kf) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(d[e >> 1] >> (16 * (e & 1))), ry, (int)(off + 2u * e), 0, POL::kOutAux);
+        }
+      }
+    }
+    };
+    if constexpr (kAnyFilters) {
+      if (rest) store_rows(std::true_type{});
+      else store_rows(std::false_type{});
+    } else {
+      store_rows(std::false_type{});
     }
    }
   }
   if (done16) return;
-  if ((Kf & 7) == 0) {
+  if (whole || (kAnyFilters && !has_res && T.out_dtype == ST_DT_F32)) {
     // Transpose through LDS: accumulators go to an fp32 [pixel][filter] tile, then every lane handles 16
     // bytes of one output row, so residual loads and output stores are whole contiguous rows.
     constexpr int PITCH = NT + 4;   // floats; the pad keeps the 16-byte writes of 16 pixels on distinct banks
@@ -392,6 +419,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
       constexpr int NV = NT / 4;
       constexpr int IT = (MP * NV + kThreads - 1) / kThreads;
       constexpr int UB = IT < 4 ? IT : 4;        // vectors in flight per thread (bounds register use)
+      auto store_rows = [&](auto REST) {
 #pragma unroll
       for (int u0 = 0; u0 < IT; u0 += UB) {
         f32x4 a[UB];
@@ -416,8 +444,27 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
 #pragma unroll
             for (int e = 0; e < 4; ++e) a[u][e] = a[u][e] > 0.f ? a[u][e] : 0.f;
           }
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a[u]), ry, (int)off[u], 0, POL::kOutAux);
+          const u32x4 d = __builtin_bit_cast(u32x4, a[u]);
+          const int ch = n0 + ((u0 + u) * kThreads + tid) % NV * 4;
+          if constexpr (!decltype(REST)::value) {
+            __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off[u], 0, POL::kOutAux);
+          } else if (off[u] != kInvalidOffset) {
+            if (ch + 4 <= Kf) {
+              __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off[u], 0, POL::kOutAux);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 3; ++e)
+                if (ch + e < Kf) __builtin_amdgcn_raw_buffer_store_b32(d[e], ry, (int)(off[u] + 4u * e), 0, POL::kOutAux);
+            }
+          }
         }
+      }
+      };
+      if constexpr (kAnyFilters) {
+        if (rest) store_rows(std::true_type{});
+        else store_rows(std::false_type{});
+      } else {
+        store_rows(std::false_type{});
       }
     } else if constexpr (DT != ST_DT_F32) {
       constexpr int NV = NT / 8;
@@ -617,7 +664,13 @@ __device__ __forceinline__ bool split_k_reduce(ConstOp& T, const st_work_item it
 // LDS rows are KB bytes without padding: 16-byte chunk c of row r sits at position c ^ swz(r), so that the 16 rows an
 // MFMA operand read touches at a time fall into 16 different 16-byte bank groups; the swizzle is applied by choosing
 // which chunk each lane fetches (a lane's LDS position is fixed).
-template <int MT, int NT, int WPX, int WCH, int MF, int KB, int ST, int DT, class POL = PlainActs>
+//
+// PIECES: layers whose channel count is no multiple of the vector.  The reduction index is then walked in two parts: the whole
+// vectors of every tap's channels, which go straight to LDS like any others (an element-aligned address costs nothing where it is a
+// multiple of four bytes, and twice the step where it is not), and at the end the few channels left over, a vector per tap
+// through registers.  A 64x64 step of 3x3, 240 channels or so, alone: fp32 1295 clocks
+// where conv_tile_gather takes 1780, bf16 462 (odd channel counts 961) for 1074 (1187).
+template <int MT, int NT, int WPX, int WCH, int MF, int KB, int ST, int DT, bool PIECES, class POL = PlainActs>
 __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr int ES = ElemOf<DT>::ES;
   constexpr int VEC = 16 / ES;          // elements per 16-byte vector
@@ -653,7 +706,8 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
   const int ks_begin = (int)it.k_split_idx * T.k_steps_per_split;
   int ks_end = ks_begin + T.k_steps_per_split;
   if (ks_end > T.k_steps) ks_end = T.k_steps;
-  const int nsteps = ks_end - ks_begin;
+  const int main_steps = PIECES ? step_dr : ks_end;      // steps of whole vectors (of the layer), before those of left-over channels
+  const int nsteps = (PIECES && main_steps < ks_end ? main_steps : ks_end) - ks_begin;
 
   // staging: which row of an instruction's block of RPI rows, and which 16-byte chunk of it, this lane fetches
   const int lr = lane / CH;
@@ -662,7 +716,7 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
   // per-thread patch rows: first image row and column, and element offset of the patch (a 1x1 layer of stride 1 without
   // padding needs no position in the image: output pixel m is input pixel m)
   int a_h0[AW], a_w0[AW], a_base[AW];
-  const bool same_pixels = T.k_order == kOrderLinear && T.stride == 1;
+  const bool same_pixels = !PIECES && T.k_order == kOrderLinear && T.stride == 1;
   if (!same_pixels) {
 #pragma unroll
     for (int i = 0; i < AW; ++i) {
@@ -703,13 +757,19 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
     b_lds[u] = (uint32_t)((rbase ^ (u * SUBB)) + MT * KB + wn0 * KB);
   }
 
-  Acc acc[BM][BN];
+  // PIECES: two sums of each block, one over even and one over odd sub-steps.  Layers of this form are often split less than
+  // with gathered tiles, and a longer chain of fp32 additions errs more (43 such layers against 64 bits, mean relative error
+  // 2.79e-7 gathered, 3.12e-7 with one sum, 2.65e-7 with two).
+  Acc acc[BM][BN], odd[PIECES ? BM : 1][PIECES ? BN : 1];
 #pragma unroll
   for (int i = 0; i < BM; ++i)
 #pragma unroll
     for (int j = 0; j < BN; ++j)
 #pragma unroll
-      for (int v = 0; v < (int)(sizeof(Acc) / 4); ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < (int)(sizeof(Acc) / 4); ++v) {
+        acc[i][j][v] = 0.f;
+        if constexpr (PIECES) odd[i][j][v] = 0.f;
+      }
   struct Frags { u32x4 w[NSUB][BN], x[NSUB][BM]; };
   auto read_one = [&](auto I, auto stage_off, Frags& f) {     // operand fragment I of the step: per sub-step filters, then pixels
     constexpr int u = decltype(I)::value / (BN + BM), q = decltype(I)::value % (BN + BM);
@@ -720,14 +780,15 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
   constexpr int NMMA = NSUB * BM * BN;
   auto mma_one = [&](auto I, const Frags& f) {
     constexpr int u = decltype(I)::value / (BM * BN), i = decltype(I)::value / BN % BM, j = decltype(I)::value % BN;
-    acc[i][j] = MMA::run(f.w[u][j], f.x[u][i], acc[i][j]);
+    if constexpr (PIECES && u % 2 == 1) odd[i][j] = MMA::run(f.w[u][j], f.x[u][i], odd[i][j]);
+    else acc[i][j] = MMA::run(f.w[u][j], f.x[u][i], acc[i][j]);
   };
   auto mma = [&](const Frags& f) { static_for<NMMA>([&](auto I) { mma_one(I, f); }); };
 
   // A 16-bit residual tile is loaded into the stage of the last step but one as soon as that is free (no later loads
   // are waited for by count), and added in the epilogue.
   int res_lds = -1;
-  if constexpr (DT != ST_DT_F32) {
+  if constexpr (DT != ST_DT_F32 && !PIECES) {
     if ((T.epilogue & ST_EPI_RESIDUAL) != 0u && T.out_dtype != ST_DT_F32 && (T.K & 7) == 0 && T.split_k == 1)
       res_lds = (nsteps == 1 ? 1 : (nsteps - 2) % ST) * kStage;
   }
@@ -737,6 +798,7 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
   //   kOrderChannels  C a multiple of the step, at most 32 taps: channel blocks outermost, the R*S taps of a block one
   //                   after another.  Tap and block are uniform, a row's valid taps are bits of one register.
   //   kOrderLinear    1x1 layers without padding: nothing changes from step to step but the scalar offset.
+  //   kOrderPieces    ascending over the whole vectors of every tap (PIECES); the lane works its tap out afresh every step.
   // What bounds a step: 16 clocks of the vector-memory unit per load instruction (a 64x64 step is 256), MFMA time, and,
   // for a wavefront that has its SIMD to itself, four clocks or so per instruction of any kind.  Hence tap masks, immediate
   // LDS offsets and as little scalar arithmetic as possible.  Clocks per 64x64 step alone on a compute unit, 3x3 layers:
@@ -753,7 +815,10 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
     uint32_t bad[AW], bad0[AW];            // kOrderChannels: bit 31 - t: tap t of this row lies outside; bad: shifted to the next tap
     const uint32_t c_bytes = (uint32_t)(C * ES), wrap_row = (uint32_t)((WC - SC) * ES);
     const uint32_t wrap_a = (uint32_t)(KB - R * WC * ES), wrap_b = (uint32_t)(KB - R * SC * ES);
-    if constexpr (order == kOrderTaps) {
+    if constexpr (order == kOrderPieces) {
+      kk = ks_begin * KT + chunk * VEC;       // position among the whole vectors
+      b_soff = 0u;
+    } else if constexpr (order == kOrderTaps) {
       const int k = ks_begin * KT + chunk * VEC;
       kr = fast_div(fast_div(k, T.magic_c, T.shift_c), T.magic_s, T.shift_s);
       kk = k - kr * SC;
@@ -794,12 +859,25 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
 #pragma unroll
     for (int i = 0; i < BW; ++i) {
       const int row = n0 + (i * 4 + wave) * RPI + lr;
-      vb[i] = b_off[i] = row < T.K ? (uint32_t)(row * T.Kg + chunk * VEC) * ES : kInvalidOffset;
+      vb[i] = b_off[i] = row < T.K ? (uint32_t)(row * T.Kg + (order == kOrderPieces ? 0 : chunk * VEC)) * ES : kInvalidOffset;
     }
     auto addresses = [&]() {
       if constexpr (order == kOrderChannels) {
 #pragma unroll
         for (int i = 0; i < AW; ++i) va[i] = (bad[i] & kTop) | ((uint32_t)a_base[i] + a_soff);
+      } else if constexpr (order == kOrderPieces) {
+        const int tap = fast_div(kk, T.magic_c, T.shift_c), c = kk - tap * step_dk;
+        const int r = fast_div(tap, T.magic_s, T.shift_s), sx = tap - r * S;
+        const bool kin = r < R;         // past the end nothing is loaded
+        const int off = r * WC + sx * C + c;
+#pragma unroll
+        for (int i = 0; i < AW; ++i) {
+          const bool ok = kin & ((unsigned)(a_h0[i] + r) < (unsigned)H) & ((unsigned)(a_w0[i] + sx) < (unsigned)W);
+          va[i] = ok ? (uint32_t)(a_base[i] + off) * ES : kInvalidOffset;
+        }
+        const uint32_t b = kin ? (uint32_t)(tap * C + c) * ES : 0u, kmask = kin ? 0u : kInvalidOffset;
+#pragma unroll
+        for (int i = 0; i < BW; ++i) vb[i] = (b_off[i] + b) | kmask;
       } else if constexpr (order == kOrderTaps) {
         const bool kin = kr < R;        // past the end of the reduction index nothing is loaded
         const int hr = kin ? kr : (1 << 28);
@@ -835,6 +913,8 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
             for (int i = 0; i < AW; ++i) bad[i] = bad0[i];
           }
         }
+      } else if constexpr (order == kOrderPieces) {
+        kk += KT;
       } else {
         const bool wrap = kk + step_dk >= SC;
         kk += step_dk - (wrap ? SC : 0);
@@ -923,10 +1003,59 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
       cur = n2;
     }
   };
+  if constexpr (PIECES) {
+    if (nsteps > 0) k_loop(std::integral_constant<int, kOrderPieces>{});
+    else if (prof && tid == 0) prof[1] = __builtin_readcyclecounter();
+    // The channels left over: a vector per tap, the last one inside its channels, of which those that the whole vectors have are
+    // cleared in both operands; 16 bytes at a time to where load_to_lds would have put them.
+    const int left = C - step_dk, taps = R * S;
+    uint32_t keep[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+      keep[d] = ES == 4 ? (d >= VEC - left ? 0xffffffffu : 0u) : (2 * d >= VEC - left ? 0x0000ffffu : 0u) | (2 * d + 1 >= VEC - left ? 0xffff0000u : 0u);
+    const __amdgpu_buffer_rsrc_t bx = make_rsrc(T.x, T.x_bytes), bw = make_rsrc(T.w, T.w_bytes);
+    u32x4 qa[AW], qb[BW];
+    auto fetch_left = [&](int ts) {
+      const int tap = (ts - main_steps) * CH + chunk;
+      const int r = fast_div(tap, T.magic_s, T.shift_s), sx = tap - r * S;
+      const bool kin = tap < taps;
+#pragma unroll
+      for (int i = 0; i < AW; ++i) {
+        const bool ok = kin & ((unsigned)(a_h0[i] + r) < (unsigned)H) & ((unsigned)(a_w0[i] + sx) < (unsigned)W);
+        qa[i] = __builtin_amdgcn_raw_buffer_load_b128(bx, (int)(ok ? (uint32_t)(a_base[i] + r * WC + sx * C + C - VEC) * ES : kInvalidOffset), 0, POL::kActAux);
+      }
+#pragma unroll
+      for (int i = 0; i < BW; ++i) {
+        const int row = n0 + (i * 4 + wave) * RPI + lr;
+        qb[i] = __builtin_amdgcn_raw_buffer_load_b128(bw, (int)((kin & (row < T.K)) ? (uint32_t)(row * T.Kg + tap * C + C - VEC) * ES : kInvalidOffset), 0, 0);
+      }
+    };
+    int ts = ks_begin > main_steps ? ks_begin : main_steps;
+    if (ts < ks_end) fetch_left(ts);
+    for (; ts < ks_end; ++ts) {
+      __syncthreads();                // the stage is no longer read
+#pragma unroll
+      for (int i = 0; i < AW; ++i) *(u32x4*)(smem + wave * 1024 + i * 4096 + lane * 16) = u32x4{qa[i][0] & keep[0], qa[i][1] & keep[1], qa[i][2] & keep[2], qa[i][3] & keep[3]};
+#pragma unroll
+      for (int i = 0; i < BW; ++i) *(u32x4*)(smem + wave * 1024 + MT * KB + i * 4096 + lane * 16) = u32x4{qb[i][0] & keep[0], qb[i][1] & keep[1], qb[i][2] & keep[2], qb[i][3] & keep[3]};
+      __syncthreads();
+      if (ts + 1 < ks_end) fetch_left(ts + 1);
+      Frags f;
+      read_frags(0, f);
+      mma(f);
+    }
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+#pragma unroll
+      for (int j = 0; j < BN; ++j)
+#pragma unroll
+        for (int v = 0; v < (int)(sizeof(Acc) / 4); ++v) acc[i][j][v] += odd[i][j][v];
+  } else {
   switch (T.k_order) {
     case kOrderLinear: k_loop(std::integral_constant<int, kOrderLinear>{}); break;
     case kOrderChannels: k_loop(std::integral_constant<int, kOrderChannels>{}); break;
     default: k_loop(std::integral_constant<int, kOrderTaps>{}); break;
+  }
   }
 
   if (prof && tid == 0) prof[2] = __builtin_readcyclecounter();
@@ -1129,7 +1258,7 @@ __device__ __forceinline__ void conv_tile_patch(ConstOp& T, const st_work_item i
   if (prof && tid == 0) stamp_end(prof);
 }
 
-// ---- gather tile for channel counts that are not a multiple of the 16-byte vector -------------------
+// ---- gather tile: channel counts that hold no whole 16-byte vector (and any other, where the planner finds it shorter) -------
 // The same implicit GEMM for any C, D steps of loads kept in flight in registers ahead of an LDS double buffer with rows
 // padded by 16 bytes.  A vector of the reduction index is contiguous in memory as long as it stays inside one filter row,
 // and is then one 16-byte load from an element-aligned address; only vectors that cross into the next filter row, into the
@@ -1679,12 +1808,17 @@ __device__ __forceinline__ void pool_item(ConstOp& T, const st_work_item it) {
 template <int CFG, int DT, class POL>
 __device__ __forceinline__ void vector_tile(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr TileShape s = kTileShapes[CFG];
-  conv_tile<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, s.D, DT, POL>(T, it, smem, prof);
+  conv_tile<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, s.D, DT, false, POL>(T, it, smem, prof);
 }
 template <int CFG, int DT, class POL>
 __device__ __forceinline__ void patch_tile(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
   constexpr TileShape s = kTileShapes[CFG];
   if constexpr (DT != ST_DT_F32) conv_tile_patch<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, kPatchStages[CFG], DT, POL>(T, it, smem, prof);
+}
+template <int CFG, int DT, class POL>
+__device__ __forceinline__ void pieces_tile(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
+  constexpr TileShape s = kTileShapes[CFG];
+  conv_tile<s.MT, s.NT, s.WPX, s.WCH, s.MF, s.KB, s.D, DT, true, POL>(T, it, smem, prof);
 }
 template <int CFG, int DT, class POL>
 __device__ __forceinline__ void gather_tile(ConstOp& T, const st_work_item it, char* smem, uint64_t* prof) {
@@ -1708,6 +1842,10 @@ __device__ __forceinline__ void run_form(uint32_t form, ConstOp& T, const st_wor
     case kFormPatch + 4: if constexpr (patch) patch_tile<4, DT, POL>(T, it, smem, prof); break;
     case kFormGather + 1: if constexpr (gather) gather_tile<1, DT, POL>(T, it, smem, prof); break;
     case kFormGather + 3: if constexpr (gather) gather_tile<3, DT, POL>(T, it, smem, prof); break;
+    case kFormPieces + 1: if constexpr (gather) pieces_tile<1, DT, POL>(T, it, smem, prof); break;
+    case kFormPieces + 3: if constexpr (gather) pieces_tile<3, DT, POL>(T, it, smem, prof); break;
+    case kFormPieces + 4: if constexpr (gather) pieces_tile<4, DT, POL>(T, it, smem, prof); break;
+    case kFormPieces + 5: if constexpr (gather) pieces_tile<5, DT, POL>(T, it, smem, prof); break;
     case kFormRows: if constexpr (rows) conv_tile_rows<DT, POL>(T, it, smem, prof); break;
     case kFormPool:
       if constexpr ((HAS & kHasPools) != 0u) {

@@ -1,0 +1,69 @@
+"""Channel counts that are no multiple of the 16-byte vector but hold one: whole vectors of every tap, then the channels left over.
+Every tile shape, split and unsplit, channel counts around the vector and the K step, windows that leave the image, filter counts
+off the vector width with and without a residual, and slices that hold only whole vectors, only left-over channels, or nothing."""
+import pytest
+
+from paper_1901_00041_amd import st_conv as sc
+
+pytestmark = pytest.mark.gpu
+
+# C, H, W, K, R, S, stride, pad
+LAYERS = [(9, 9, 11, 24, 3, 3, 1, 1), (15, 13, 7, 65, 5, 5, 2, 2), (17, 8, 8, 7, 1, 1, 1, 0), (65, 10, 9, 70, 3, 3, 1, 1), (63, 12, 5, 131, 1, 7, 1, 3),
+          (70, 9, 9, 64, 2, 3, 3, 0), (131, 21, 10, 201, 1, 1, 1, 0), (239, 6, 7, 33, 3, 3, 2, 1), (129, 5, 5, 8, 5, 5, 1, 2), (11, 5, 70, 9, 7, 1, 1, 3),
+          (31, 4, 4, 16, 4, 4, 1, 3)]
+
+
+@pytest.mark.parametrize("dtype,out", [("bf16", "bf16"), ("bf16", "f32"), ("f16", "f16"), ("f32", "f32")])
+@pytest.mark.parametrize("tile_cfg,split", [(0, 0), (2, 1), (2, 3), (4, 1), (4, 4), (5, 1), (5, 2), (6, 1), (6, 3), (4, 64)])
+def test_layers(tile_cfg, split, dtype, out):
+    import torch
+    import torch.nn.functional as F
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}
+    gen = torch.Generator().manual_seed(tile_cfg * 100 + split)
+    descs, made = [], []
+    for i, (C, H, W, K, R, S, stride, pad) in enumerate(LAYERS):
+        N = 1 + i % 3
+        x = (torch.rand((N, H, W, C), generator=gen) * 2 - 1).to(dt[dtype])
+        w = (torch.randn((K, R, S, C), generator=gen) * (1.0 / (R * S * C)) ** 0.5).to(dt[dtype])
+        ref = F.conv2d(x.double().permute(0, 3, 1, 2), w.double().permute(0, 3, 1, 2), stride=stride, padding=pad).permute(0, 2, 3, 1)
+        res = (torch.rand(ref.shape, generator=gen) * 2 - 1).to(dt[out]) if i % 2 else None
+        if res is not None:
+            ref = ref + res.double()
+        big = torch.full((ref.numel() + 64,), 7.0, dtype=dt[out], device="cuda")       # nothing around the output is touched
+        y = big[32:32 + ref.numel()].view(ref.shape)
+        y.fill_(float("nan"))
+        epi = (sc.ST_EPI_RELU if i % 3 == 0 else 0) | (sc.ST_EPI_RESIDUAL if res is not None else 0)
+        ref = ref.clamp(min=0) if i % 3 == 0 else ref
+        dx, dw, dr = x.cuda(), w.cuda(), None if res is None else res.cuda()
+        descs.append(sc.make_desc(N, C, H, W, K, R, S, stride, pad, dtype, out, dx, dw, y, dr, epi))
+        made.append((dx, dw, dr, y, big, ref, R * S * C))
+    plan = sc.st_conv_plan(descs, sc.plan_opts(tile_cfg=tile_cfg, split_k=split), keep=made)
+    for rep in range(2):
+        sc.st_conv_run(plan)
+    torch.cuda.synchronize()
+    for i, (_, _, _, y, big, ref, k) in enumerate(made):
+        got = y.cpu().double()
+        # the output's rounding and fp32 sums of k products of a few hundredths (for fp32 operands their rounding, too)
+        tol = ref.abs() * {"bf16": 2.0 ** -8, "f16": 2.0 ** -10, "f32": 2.0 ** -20}[out] + k ** 0.5 * 2.0 ** -21 + 2.0 ** -20
+        assert ((got - ref).abs() <= tol).all(), (LAYERS[i], float((got - ref).abs().max()))
+        assert (big[:32] == 7).all() and (big[-32:] == 7).all(), LAYERS[i]
+
+
+def test_no_left_over_reads_past_the_tensors():
+    """Inputs and filters at the very end of an allocation, NaN right behind them and in front of them."""
+    import torch
+    for dtype in (torch.bfloat16, torch.float32):
+        name = "bf16" if dtype == torch.bfloat16 else "f32"
+        N, C, H, W, K = 1, 67, 5, 6, 20
+        nx, nw = N * H * W * C, K * 9 * C
+        bx = torch.full((nx + 64,), float("nan"), dtype=dtype, device="cuda")
+        bw = torch.full((nw + 64,), float("nan"), dtype=dtype, device="cuda")
+        x, w = bx[32:32 + nx].view(N, H, W, C), bw[32:32 + nw].view(K, 3, 3, C)
+        x.uniform_(-1, 1)
+        w.uniform_(-0.1, 0.1)
+        y = torch.empty((N, H, W, K), dtype=torch.float32, device="cuda")
+        for tile_cfg in (2, 4, 5, 6):
+            y.fill_(float("nan"))
+            sc.st_conv_run(sc.st_conv_plan([sc.make_desc(N, C, H, W, K, 3, 3, 1, 1, name, "f32", x, w, y)], sc.plan_opts(tile_cfg=tile_cfg, split_k=1), keep=[bx, bw, y]))
+            torch.cuda.synchronize()
+            assert torch.isfinite(y).all()
