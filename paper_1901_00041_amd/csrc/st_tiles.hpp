@@ -1734,22 +1734,18 @@ __device__ __forceinline__ void conv_tile_rows(ConstOp& T, const st_work_item it
   }
 }
 
-// ---- max-pool of one output vector (chain kernel) ---------------------------------------------------
+// ---- max-pool of one output vector -----------------------------------------------------------------
 // NHWC max-pool, one 16-byte vector of channels of one output pixel: idx counts (n, p, q, channel vector) with the
 // channel vector fastest.  Padding never wins; the result is a copy of the winning input's bits.
 // AUX: cache policy of the input loads (0: through the caches; kAuxDeviceCoherent: device-scope loads, for an input
-// that other workgroups of the same launch wrote); x_bytes < 2^31 is the size of the input.
+// that other workgroups of the same launch wrote); x_bytes is the size of the input; it and the output's are below 2^31, so
+// 32 bits are enough for everything (64-bit divisions are hundreds of instructions).
 template <int DT, int AUX = 0>
-__device__ __forceinline__ u32x4 maxpool_vector(const void* __restrict__ xv, uint32_t x_bytes, int64_t idx, int H, int W, int C, int P,
+__device__ __forceinline__ u32x4 maxpool_vector(const void* __restrict__ xv, uint32_t x_bytes, uint32_t idx, int H, int W, int C, int P,
                                                 int Q, int win, int stride, int pad) {
   constexpr int ES = ElemOf<DT>::ES, VEC = 16 / ES;
-  const int CV = C / VEC;
-  const int cv = (int)(idx % CV);
-  int64_t t = idx / CV;
-  const int q = (int)(t % Q);
-  t /= Q;
-  const int p = (int)(t % P);
-  const int n = (int)(t / P);
+  const uint32_t CV = (uint32_t)C / VEC, cv = idx % CV, pixel = idx / CV, pq = pixel / (uint32_t)Q;
+  const int q = (int)(pixel - pq * (uint32_t)Q), n = (int)(pq / (uint32_t)P), p = (int)(pq - (uint32_t)n * (uint32_t)P);
   float best[VEC];
   uint32_t bits[VEC];
 #pragma unroll
@@ -1761,17 +1757,17 @@ __device__ __forceinline__ u32x4 maxpool_vector(const void* __restrict__ xv, uin
   constexpr int B = 9;
   const __amdgpu_buffer_rsrc_t rx = make_rsrc(xv, x_bytes);
   const int taps = win * win;
+  int r = 0, sx = 0;
   for (int t0 = 0; t0 < taps; t0 += B) {
     u32x4 raw[B];
     bool ok[B];
 #pragma unroll
     for (int u = 0; u < B; ++u) {
-      const int tp = t0 + u;
-      const int r = tp / win, sx = tp - r * win;
       const int h = p * stride - pad + r, w = q * stride - pad + sx;
-      ok[u] = (tp < taps) & ((unsigned)h < (unsigned)H) & ((unsigned)w < (unsigned)W);
-      const int64_t xoff = ((((int64_t)n * H + h) * W + w) * C + (int64_t)cv * VEC) * ES;
-      raw[u] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(ok[u] ? (uint32_t)xoff : kInvalidOffset), 0, AUX);
+      ok[u] = (t0 + u < taps) & ((unsigned)h < (unsigned)H) & ((unsigned)w < (unsigned)W);
+      const uint32_t xoff = ((uint32_t)((n * H + h) * W + w) * (uint32_t)C + cv * VEC) * ES;
+      raw[u] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(ok[u] ? xoff : kInvalidOffset), 0, AUX);
+      if (++sx == win) { sx = 0; ++r; }
     }
 #pragma unroll
     for (int u = 0; u < B; ++u) {
@@ -1799,10 +1795,10 @@ __device__ __forceinline__ u32x4 maxpool_vector(const void* __restrict__ xv, uin
 // One max-pool work item: kThreads output vectors, stored write-through.
 template <int DT, class POL>
 __device__ __forceinline__ void pool_item(ConstOp& T, const st_work_item it) {
-  const int64_t idx = (int64_t)it.tile_m * kThreads + work_thread_id();
-  if (idx >= (int64_t)T.M) return;
+  const uint32_t idx = it.tile_m * (uint32_t)kThreads + (uint32_t)work_thread_id();
+  if (idx >= (uint32_t)T.M) return;
   const u32x4 v = maxpool_vector<DT, POL::kActAux>(T.x, T.x_bytes, idx, T.H, T.W, T.C, T.P, T.Q, T.R, T.stride, T.pad);
-  __builtin_amdgcn_raw_buffer_store_b128(v, make_rsrc(T.y, T.y_bytes), (int)((uint32_t)idx * 16u), 0, POL::kOutAux);
+  __builtin_amdgcn_raw_buffer_store_b128(v, make_rsrc(T.y, T.y_bytes), (int)(idx * 16u), 0, POL::kOutAux);
 }
 
 template <int CFG, int DT, class POL>
