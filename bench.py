@@ -280,7 +280,7 @@ def launch_floor_us(n: int = 2000) -> float:
 # ----------------------------------------------------------------------------------------------------------------
 # roofline
 # ----------------------------------------------------------------------------------------------------------------
-KERNEL_SOURCES = ("st_internal.h", "st_tiles.hpp", "st_conv_kernel.hpp", "st_kernels.hip", "st_chain_kernel.hpp", "st_chain.hip", "st_plan.cpp", "st_chain.cpp")
+KERNEL_SOURCES = ("st_internal.h", "st_tiles.hpp", "st_conv_kernel.hpp", "st_kernels.hip", "st_chain_kernel.hpp", "st_chain.hip", "st_plan.cpp", "st_chain.cpp", "st_chain_deps.cpp")
 
 
 def kernel_sources_id() -> str:
