@@ -365,7 +365,8 @@ static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int6
     if (o.tile_cfg > 0) {
       int forced = o.tile_cfg - 1;
       if (forced == kRowCfg) forced = 1;                 // row tile requested but not eligible
-      if (!vec_ok && !kGenericCfg[forced]) forced = (kTileShapes[forced].MT >= 128) ? 1 : 3;  // nearest gather kernel
+      if (!vec_ok && !kGenericCfg[forced] && !(pieces_ok(d) && kPiecesCfg[forced]))
+        forced = (kTileShapes[forced].MT >= 128) ? 1 : 3;                    // the nearest shape this layer has
       if (c != forced) continue;
     }
     if (o.split_k >= 1) {
