@@ -369,6 +369,16 @@ void st_chain_destroy(st_chain* chain);
 /* Introspection (used by the bit-exact work-list tests and by reports). */
 st_status st_conv_plan_info(const st_plan* plan, st_plan_info* out);
 st_status st_conv_plan_tenant_info(const st_plan* plan, int32_t tenant, st_tenant_info* out);
+/* How a tenant's operands reach its tiles.  With the tile shape and the split-K factor this fixes the order of an output's fp32
+ * sum; it follows from the layer, the shape and the split alone, so equal choices give equal bits in any company. */
+typedef enum st_tile_form {
+  ST_FORM_GATHERED = 0,  /* any channel count, through registers                                           */
+  ST_FORM_VECTORS = 1,   /* channels a multiple of the 16-byte vector, straight to LDS                     */
+  ST_FORM_PATCH = 2,     /* ... with the input pixels under the tile's taps resident (3x3 stride 1)        */
+  ST_FORM_PIECES = 3,    /* any channel count above a vector: whole vectors, then the channels left over   */
+  ST_FORM_ROWS = 4       /* few channels: rows of the image resident                                       */
+} st_tile_form;
+st_status st_conv_plan_tenant_form(const st_plan* plan, int32_t tenant, int32_t* out_form);
 /* Host copies of the work lists, valid until the plan is destroyed.  which: 0 = order used by the
  * fused launch, 1 = tenant-major order used by the two baselines. */
 st_status st_conv_plan_worklist(const st_plan* plan, int32_t which, const st_work_item** items,

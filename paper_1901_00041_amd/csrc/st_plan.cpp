@@ -166,6 +166,23 @@ static bool pieces_ok(const st_conv_desc& d) {
   return d.C % vec != 0 && d.C > vec && ((int64_t)d.W + 2 * (int64_t)d.pad) * d.C < ((int64_t)1 << 31);
 }
 
+// Which form a layer takes on a tile shape (-1: it has none there).  Nothing but the layer and the shape decides: a layer's fp32 sums
+// then run in one order whatever company it is planned in.  Where a shape has both forms for any channel count, the one of whole
+// vectors and channels left over is the faster one at every channel count for 16-bit types (64x64 and 128x64 tiles, 1x1 to 5x5,
+// 9 to 243 channels, alone and beside a second workgroup: 1.3 to 4.1 times) and for fp32 but where its vector of left-over
+// channels per tap makes the reduction more than half as long again.  fp32, 64x64 beside a second workgroup, clocks of an item gathered
+// and in pieces: five channels 3x3 13500 14750, 5x5 22300 25400; seven 3x3 14000 14800, 5x5 28400 25500; nine 17100 17400, 37300
+// 31500; 13 to 122 channels 1.05 to 1.3 times as fast in pieces, alone on the unit up to 1.5.
+static int form_on(const st_conv_desc& d, int cfg) {
+  if (cfg == kRowCfg) return -1;
+  if (vector_ok(d)) return kVectors;
+  if (pieces_ok(d) && kPiecesCfg[cfg]) {
+    const int vec = 16 / elem_size(d.in_dtype), padded = d.C / vec * vec + vec;
+    if (!kGenericCfg[cfg] || d.in_dtype != ST_DT_F32 || 2 * padded <= 3 * d.C) return kPieces;
+  }
+  return kGenericCfg[cfg] ? kGathered : -1;
+}
+
 // Whether a tile shape can keep the layer's input patch in LDS (see conv_tile_patch), and the patch's size: 16-bit types,
 // 3x3, stride 1, no more output columns and rows than input ones (then the input pixels under a tile's pixels ascend),
 // channels a multiple of the step, and LDS room for the patch (twice when there is more than one channel block) beside
@@ -357,18 +374,14 @@ static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int6
       if (o.rows_per_tile == 0 || o.rows_per_tile == rt) out.push_back(make_row_option(d, rt, alone));
     if (o.tile_cfg - 1 == kRowCfg) return out;
   }
-  const bool vec_ok = vector_ok(d);
-  for (int choice = 0; choice < 3 * kNumTileCfgs; ++choice) {
-    const int form = choice / kNumTileCfgs == 0 ? kVectors : choice / kNumTileCfgs == 1 ? kPieces : kGathered, c = choice % kNumTileCfgs;
-    if (c == kRowCfg) continue;
-    if (form == kVectors ? !vec_ok : form == kPieces ? !pieces_ok(d) || !kPiecesCfg[c] : vec_ok || !kGenericCfg[c]) continue;
-    if (o.tile_cfg > 0) {
-      int forced = o.tile_cfg - 1;
-      if (forced == kRowCfg) forced = 1;                 // row tile requested but not eligible
-      if (!vec_ok && !kGenericCfg[forced] && !(pieces_ok(d) && kPiecesCfg[forced]))
-        forced = (kTileShapes[forced].MT >= 128) ? 1 : 3;                    // the nearest shape this layer has
-      if (c != forced) continue;
-    }
+  int forced = o.tile_cfg - 1;
+  if (o.tile_cfg > 0) {
+    if (forced == kRowCfg) forced = 1;                                              // row tile requested but not eligible
+    if (form_on(d, forced) < 0) forced = (kTileShapes[forced].MT >= 128) ? 1 : 3;   // the nearest shape this layer has
+  }
+  for (int c = 0; c < kNumTileCfgs; ++c) {
+    const int form = form_on(d, c);
+    if (form < 0 || (o.tile_cfg > 0 && c != forced)) continue;
     if (o.split_k >= 1) {
       out.push_back(make_option(d, M, Ng, kbytes, form, alone, c, o.split_k));
       continue;
@@ -1438,6 +1451,14 @@ extern "C" st_status st_conv_plan_tenant_info(const st_plan* plan, int32_t tenan
   if (!plan || !out) return fail(ST_ERR_INVALID_ARG, "NULL argument");
   if (tenant < 0 || (size_t)tenant >= plan->info.size()) return fail(ST_ERR_INVALID_ARG, "tenant index out of range");
   *out = plan->info[tenant];
+  return ST_OK;
+}
+
+extern "C" st_status st_conv_plan_tenant_form(const st_plan* plan, int32_t tenant, int32_t* out_form) {
+  if (!plan || !out_form) return fail(ST_ERR_INVALID_ARG, "NULL argument");
+  if (tenant < 0 || tenant >= (int32_t)plan->tenants.size()) return fail(ST_ERR_INVALID_ARG, "tenant index out of range");
+  const uint32_t form = tile_code(plan->tenants[tenant]) & kFormMask;
+  *out_form = form == kFormRows ? ST_FORM_ROWS : form >= kFormPieces ? ST_FORM_PIECES : form >= kFormGather ? ST_FORM_GATHERED : form >= kFormPatch ? ST_FORM_PATCH : ST_FORM_VECTORS;
   return ST_OK;
 }
 

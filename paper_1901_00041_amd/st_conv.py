@@ -17,12 +17,13 @@ ST_DT_F32, ST_DT_BF16, ST_DT_F16 = 0, 1, 2
 ST_LAYOUT_NHWC_KRSC, ST_LAYOUT_NCHW_KCRS = 0, 1
 ST_EPI_RELU, ST_EPI_RESIDUAL = 1, 2
 ST_OP_CONV, ST_OP_MAXPOOL = 0, 1
+ST_FORM_GATHERED, ST_FORM_VECTORS, ST_FORM_PATCH, ST_FORM_PIECES, ST_FORM_ROWS = range(5)
 DTYPE_CODE = {"f32": ST_DT_F32, "bf16": ST_DT_BF16, "f16": ST_DT_F16}
 
 EXPORTS = ["st_conv_plan", "st_conv_run", "st_conv_run_noalloc", "st_conv_noalloc_max_bytes", "st_conv_run_profiled", "st_conv_run_tenant_times", "st_conv_run_time_only", "st_conv_run_space_only",
            "st_conv_run_plans_time_only", "st_conv_run_plans_space_only", "st_conv_run_plans_on_streams", "st_conv_run_plans_on_streams_many", "st_conv_plan_rebind", "st_conv_plan_rebind_all",
            "st_pipeline_create", "st_pipeline_slots", "st_pipeline_next", "st_pipeline_run", "st_pipeline_run_many", "st_pipeline_sync", "st_pipeline_destroy",
-           "st_plan_cache_create", "st_plan_cache_get", "st_plan_cache_get_stats", "st_plan_cache_destroy", "st_conv_plan_info", "st_conv_plan_tenant_info", "st_conv_plan_worklist",
+           "st_plan_cache_create", "st_plan_cache_get", "st_plan_cache_get_stats", "st_plan_cache_destroy", "st_conv_plan_info", "st_conv_plan_tenant_info", "st_conv_plan_tenant_form", "st_conv_plan_worklist",
            "st_conv_plan_destroy", "st_chain_plan", "st_chain_run", "st_chain_run_profiled", "st_chain_aborted", "st_chain_set_wait_limit_us",
            "st_chain_get_info", "st_chain_get_op_info", "st_chain_worklist", "st_chain_columns", "st_chain_dependencies", "st_chain_set_workgroups", "st_chain_destroy", "st_tile_shape", "st_tile_count", "st_maxpool_nhwc",
            "st_launch_empty", "st_launch_copy", "st_status_string", "st_last_error_message"]
@@ -149,6 +150,7 @@ def lib() -> ctypes.CDLL:
         L.st_conv_run_plans_on_streams_many.restype = i32
         L.st_conv_plan_info.argtypes = [vp, P(st_plan_info)]
         L.st_conv_plan_tenant_info.argtypes = [vp, i32, P(st_tenant_info)]
+        L.st_conv_plan_tenant_form.argtypes = [vp, i32, P(i32)]
         L.st_conv_plan_worklist.argtypes = [vp, i32, P(P(st_work_item)), P(i64)]
         L.st_conv_plan_destroy.argtypes = [vp]
         L.st_conv_plan_destroy.restype = None
@@ -180,7 +182,7 @@ def lib() -> ctypes.CDLL:
         for name in ("st_conv_plan", "st_conv_run", "st_conv_run_profiled", "st_conv_run_plans_time_only",
                      "st_conv_run_plans_space_only", "st_conv_run_time_only", "st_conv_run_space_only",
                      "st_conv_plan_rebind", "st_conv_plan_rebind_all", "st_plan_cache_create", "st_plan_cache_get",
-                     "st_plan_cache_get_stats", "st_conv_plan_info", "st_conv_plan_tenant_info",
+                     "st_plan_cache_get_stats", "st_conv_plan_info", "st_conv_plan_tenant_info", "st_conv_plan_tenant_form",
                      "st_conv_plan_worklist", "st_tile_shape", "st_tile_count",
                      "st_maxpool_nhwc", "st_launch_empty", "st_launch_copy"):
             getattr(L, name).restype = i32
@@ -527,6 +529,13 @@ def st_conv_plan_tenant_info(plan: Plan, tenant: int) -> st_tenant_info:
     out = st_tenant_info()
     _check(lib().st_conv_plan_tenant_info(plan.handle, tenant, ctypes.byref(out)), "st_conv_plan_tenant_info")
     return out
+
+
+def st_conv_plan_tenant_form(plan: Plan, tenant: int) -> int:
+    """One of ST_FORM_*: how the tenant's operands reach its tiles."""
+    out = ctypes.c_int32()
+    _check(lib().st_conv_plan_tenant_form(plan.handle, tenant, ctypes.byref(out)), "st_conv_plan_tenant_form")
+    return out.value
 
 
 def st_conv_plan_worklist(plan: Plan, which: int = 0) -> np.ndarray:

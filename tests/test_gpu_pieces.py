@@ -67,3 +67,32 @@ def test_no_left_over_reads_past_the_tensors():
             sc.st_conv_run(sc.st_conv_plan([sc.make_desc(N, C, H, W, K, 3, 3, 1, 1, name, "f32", x, w, y)], sc.plan_opts(tile_cfg=tile_cfg, split_k=1), keep=[bx, bw, y]))
             torch.cuda.synchronize()
             assert torch.isfinite(y).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_bits_do_not_depend_on_company(dtype):
+    """A layer alone on the tile and split that it has in a launch of many: the same form, the same order of its sums, the same bits."""
+    import torch
+    dt = {"bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    gen = torch.Generator().manual_seed(5)
+    layers = LAYERS + [(5, 16, 16, 64, 5, 5, 1, 2), (6, 9, 9, 40, 3, 3, 1, 1), (3, 10, 12, 20, 3, 3, 1, 1), (200, 30, 30, 128, 1, 1, 1, 0)]
+    tensors = []
+    for C, H, W, K, R, S, stride, pad in layers:
+        x = (torch.rand((1, H, W, C), generator=gen) * 2 - 1).to(dt).cuda()
+        w = (torch.randn((K, R, S, C), generator=gen) * 0.05).to(dt).cuda()
+        P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+        tensors.append((x, w, [torch.full((1, P, Q, K), float("nan"), device="cuda") for _ in range(2)]))
+
+    def desc(i, which):
+        C, H, W, K, R, S, stride, pad = layers[i]
+        x, w, ys = tensors[i]
+        return sc.make_desc(1, C, H, W, K, R, S, stride, pad, dtype, "f32", x, w, ys[which])
+    many = sc.st_conv_plan([desc(i, 0) for i in range(len(layers))], keep=tensors)
+    sc.st_conv_run(many)
+    for i in range(len(layers)):
+        ti = sc.st_conv_plan_tenant_info(many, i)
+        alone = sc.st_conv_plan([desc(i, 1)], sc.plan_opts(tile_cfg=ti.tile_cfg + 1, split_k=ti.split_k, rows_per_tile=ti.rows_per_tile), keep=tensors)
+        assert sc.st_conv_plan_tenant_form(alone, 0) == sc.st_conv_plan_tenant_form(many, i)
+        sc.st_conv_run(alone)
+        torch.cuda.synchronize()
+        assert torch.equal(tensors[i][2][0], tensors[i][2][1]), layers[i]

@@ -1,4 +1,6 @@
 """Planning of layers whose channel count is no multiple of the 16-byte vector (no GPU)."""
+import random
+
 import pytest
 
 from paper_1901_00041_amd import st_conv as sc
@@ -34,3 +36,47 @@ def test_a_forced_shape_that_such_layers_do_not_have_is_the_nearest_one(dtype, c
     for tile_cfg, want in [(1, 1), (3, 3), (7, 1)] + ([(5, 3), (6, 3)] if narrow else []):
         _, (ti,) = _plan([(2, channels, 14, 13, 70, 3, 3, 1, 1, dtype)], tile_cfg=tile_cfg)
         assert ti.tile_cfg == want, tile_cfg
+
+
+def _random_layers(rng, n):
+    out = []
+    for _ in range(n):
+        dtype = rng.choice(("bf16", "f16", "f32"))
+        r, s = rng.choice(((1, 1), (3, 3), (5, 5), (1, 7), (2, 3)))
+        epi = rng.choice((0, sc.ST_EPI_RELU, sc.ST_EPI_RESIDUAL))
+        out.append((rng.randint(1, 4), rng.randint(1, 260), rng.randint(7, 40), rng.randint(7, 40), rng.randint(1, 260), r, s, rng.choice((1, 1, 2)), rng.randint(0, max(r, s) // 2),
+                    dtype, rng.choice((dtype, "f32")), epi))
+    return out
+
+
+def _choice(plan, i, ti):
+    return ti.tile_cfg, ti.split_k, ti.rows_per_tile, sc.st_conv_plan_tenant_form(plan, i), ti.k_steps, ti.k_steps_per_split
+
+
+@pytest.mark.parametrize("seed", range(12))
+def test_a_layer_planned_alone_on_its_tile_and_split_takes_the_same_form(seed):
+    rng = random.Random(seed)
+    layers = _random_layers(rng, rng.randint(2, 40))
+    plan, infos = _plan(layers)
+    for i, (layer, ti) in enumerate(zip(layers, infos)):
+        alone, (ta,) = _plan([layer], tile_cfg=ti.tile_cfg + 1, split_k=ti.split_k, rows_per_tile=ti.rows_per_tile)
+        assert _choice(plan, i, ti) == _choice(alone, 0, ta), layer
+
+
+@pytest.mark.parametrize("layer", [(1, 5, 16, 16, 64, 5, 5, 1, 2, "f32"), (1, 6, 16, 16, 64, 3, 3, 1, 1, "f32"), (1, 9, 16, 16, 64, 3, 3, 1, 1, "bf16"),
+                                   (1, 243, 16, 16, 64, 1, 1, 1, 0, "f16")])
+@pytest.mark.parametrize("tile_cfg", [2, 4, 5, 6])
+def test_company_does_not_change_the_form(layer, tile_cfg):
+    alone, (ta,) = _plan([layer], tile_cfg=tile_cfg, split_k=1)
+    many, infos = _plan([layer] * 200, tile_cfg=tile_cfg, split_k=1)
+    assert _choice(alone, 0, ta) == _choice(many, 0, infos[0])
+
+
+def test_forms_are_reported():
+    plan, _ = _plan([(1, 64, 14, 14, 64, 1, 1, 1, 0, "bf16"), (1, 64, 14, 14, 64, 3, 3, 1, 1, "bf16"), (1, 67, 14, 14, 64, 3, 3, 1, 1, "bf16"),
+                     (1, 7, 14, 14, 64, 3, 3, 1, 1, "bf16"), (1, 5, 14, 14, 64, 3, 3, 1, 1, "f32")], tile_cfg=4, split_k=1)
+    assert [sc.st_conv_plan_tenant_form(plan, i) for i in range(5)] == [sc.ST_FORM_VECTORS, sc.ST_FORM_PATCH, sc.ST_FORM_PIECES, sc.ST_FORM_GATHERED, sc.ST_FORM_GATHERED]
+    plan, _ = _plan([(1, 3, 224, 224, 64, 7, 7, 2, 3, "bf16")])
+    assert sc.st_conv_plan_tenant_form(plan, 0) == sc.ST_FORM_ROWS
+    with pytest.raises(sc.StError):
+        sc.st_conv_plan_tenant_form(plan, 1)
