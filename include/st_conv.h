@@ -103,7 +103,8 @@ typedef struct st_tenant_info {
   int32_t MT, NT;              /* pixels and filters per tile                               */
   int32_t tiles_m, tiles_n;    /* tiles_m = ceil(M/MT), or N*ceil(P/rows_per_tile)*ceil(Q/MT) when row_tiled */
   int32_t split_k;             /* slices of Kgemm per output tile                           */
-  int32_t k_steps;             /* K steps (of the tile shape's k_step_bytes per row) over Kgemm */
+  int32_t k_steps;             /* K steps (of the tile shape's k_step_bytes per row) over Kgemm; ST_FORM_PIECES: */
+                               /* over all taps' whole vectors, then over the channels left over */
   int32_t k_steps_per_split;   /* ceil(k_steps / split_k); the last slice may be shorter    */
   int64_t item_begin;          /* slice [item_begin, item_begin+item_count) of the          */
   int64_t item_count;          /*   tenant-major work list belongs to this tenant           */

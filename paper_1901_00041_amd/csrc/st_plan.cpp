@@ -126,18 +126,25 @@ enum Form { kGathered = 0, kVectors = 1, kPieces = 2 };       // (TenantDev.vec_
 static const double kLeftStepCost = 1200.0;
 static const double kOddStepFactor = 2.0;
 
-// A tap's channels in whole vectors, the steps that the taps' vectors take and those of the channels left over.
-struct PieceSteps { int vectors, main, left; };
-static PieceSteps piece_steps(const st_conv_desc& d, int cfg) {
-  const int es = elem_size(d.in_dtype), vec = 16 / es, c = d.C / vec * vec;
+// The K steps of a layer on a tile shape: those of the reduction index, or in pieces those of all taps' whole vectors (`vectors`
+// channels of each tap), then those of the channels left over, a vector per tap.
+struct KSteps { int main, left, vectors; };
+static KSteps k_steps_of(const st_conv_desc& d, int form, int cfg) {
+  const int es = elem_size(d.in_dtype), vec = 16 / es, c = form == kPieces ? d.C / vec * vec : d.C;
   const int64_t taps = (int64_t)d.R * d.S;
-  return {c, cdiv(taps * c * es, kTileShapes[cfg].KB), cdiv(taps * 16, kTileShapes[cfg].KB)};
+  return {cdiv(taps * c * es, kTileShapes[cfg].KB), form == kPieces ? cdiv(taps * 16, kTileShapes[cfg].KB) : 0, c};
 }
 
 // Clocks of one K step of a form (of the whole vectors, for kPieces).
 static double step_cost(const st_conv_desc& d, int form, int cfg, const ItemCosts& c) {
   if (form == kGathered) return gather_step_cost(d, cfg);
   return c.step[cfg] * (form == kPieces && elem_size(d.in_dtype) == 2 && d.C % 2 != 0 ? kOddStepFactor : 1.0);
+}
+
+// Clocks that steps [begin, end) of a layer take.
+static double steps_cost(const st_conv_desc& d, int form, int cfg, const ItemCosts& c, const KSteps& k, int begin, int end) {
+  const int main = std::min(end, k.main) - std::min(begin, k.main), left = end - begin - main;
+  return main * step_cost(d, form, cfg, c) + left * (c.step[cfg] + kLeftStepCost);
 }
 
 struct Option {
@@ -336,11 +343,12 @@ static Option make_row_option(const st_conv_desc& d, int rows_per_tile, bool alo
   return o;
 }
 
-static Option make_option(const st_conv_desc& d, int64_t M, int64_t Ng, int64_t kbytes, int form, bool alone, int cfg, int split) {
+static Option make_option(const st_conv_desc& d, int64_t M, int64_t Ng, int form, bool alone, int cfg, int split) {
   Option o;
   o.form = form;
   o.rows_per_tile = 0;
-  const int k_steps = cdiv(kbytes, kTileShapes[cfg].KB);
+  const KSteps k = k_steps_of(d, form, cfg);
+  const int k_steps = k.main + k.left;
   split = std::max(1, std::min(split, std::min(k_steps, 65535)));
   const int per = cdiv(k_steps, split);
   split = cdiv(k_steps, per);          // no empty slice
@@ -353,19 +361,19 @@ static Option make_option(const st_conv_desc& d, int64_t M, int64_t Ng, int64_t 
   const ItemCosts& c = kCosts[d.in_dtype == ST_DT_F32 ? kCosts32 : patch ? kCostsPatch : kCosts16][alone ? 1 : 0];
   const double elems = (double)kTileShapes[cfg].MT * kTileShapes[cfg].NT;
   const int batch = elems > 4096 ? 4 : 8;      // slices read back at a time
-  double steps_time = per * step_cost(d, form, cfg, c);
-  if (form == kPieces) {
-    const PieceSteps ps = piece_steps(d, cfg);
-    const int mine = cdiv(ps.main + ps.left, split), left = std::min(mine, ps.left);      // of the last slice, the longest
-    steps_time = (mine - left) * step_cost(d, form, cfg, c) + left * (c.step[cfg] + kLeftStepCost);
-  }
-  o.item_time = (form == kGathered ? kGatherFirstCost : c.first[cfg]) + steps_time + c.epi[cfg] +
-                (split > 1 ? kSplitCost + kSplitPerElem * elems + (kSplitRoundCost + kSplitRoundPerElem * elems) * ((split - 1) / batch) : 0.0);
+  // the longest slice: the first one, or where channels left over are dearer the last whole one or the last one
+  double steps_time = 0.0;
+  for (int i : {0, split - 2, split - 1})
+    if (i >= 0) steps_time = std::max(steps_time, steps_cost(d, form, cfg, c, k, i * per, std::min(k_steps, (i + 1) * per)));
+  const double around = (form == kGathered ? kGatherFirstCost : c.first[cfg]) + c.epi[cfg] +
+                        (split > 1 ? kSplitCost + kSplitPerElem * elems + (kSplitRoundCost + kSplitRoundPerElem * elems) * ((split - 1) / batch) : 0.0);
+  o.item_time = around + steps_time;
   o.area = o.item_time * (double)o.items;
+  if (form == kPieces) o.area = (double)o.items * (around + steps_cost(d, form, cfg, c, k, 0, k_steps) / split);    // slices may differ a lot
   return o;
 }
 
-static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int64_t Ng, int64_t kbytes, bool alone,
+static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int64_t Ng, bool alone,
                                           const st_plan_opts& o) {
   std::vector<Option> out;
   const bool row_ok = row_tile_ok(d);
@@ -383,12 +391,12 @@ static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int6
     const int form = form_on(d, c);
     if (form < 0 || (o.tile_cfg > 0 && c != forced)) continue;
     if (o.split_k >= 1) {
-      out.push_back(make_option(d, M, Ng, kbytes, form, alone, c, o.split_k));
+      out.push_back(make_option(d, M, Ng, form, alone, c, o.split_k));
       continue;
     }
     int last_split = 0;
     for (int sp : kSplitChoices) {
-      Option op = make_option(d, M, Ng, kbytes, form, alone, c, sp);
+      Option op = make_option(d, M, Ng, form, alone, c, sp);
       if (op.split == last_split) continue;             // clamped to the same factor as before
       if (op.split > 1 && op.steps_per_split < 2) continue;
       last_split = op.split;
@@ -652,7 +660,7 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       std::vector<std::vector<Option>> options(n_tenants);
       for (int t = 0; t < n_tenants; ++t) {
         const st_tenant_info& ti = p->info[t];
-        options[t] = tenant_options(descs[t], ti.M, ti.Ngemm, ti.Kgemm * elem_size(descs[t].in_dtype), alone, o);
+        options[t] = tenant_options(descs[t], ti.M, ti.Ngemm, alone, o);
       }
       return options;
     };
@@ -688,7 +696,8 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       p->item_time.push_back(op.item_time);
       form.push_back(op.form);
       ti.tile_cfg = op.cfg;
-      ti.k_steps = cdiv(ti.Kgemm * elem_size(descs[t].in_dtype), kTileShapes[op.cfg].KB);
+      const KSteps k = k_steps_of(descs[t], op.form, op.cfg);
+      ti.k_steps = k.main + k.left;
       ti.MT = kTileShapes[op.cfg].MT;
       ti.NT = kTileShapes[op.cfg].NT;
       ti.tiles_m = cdiv(ti.M, ti.MT);
@@ -752,23 +761,30 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       }
     }
     if (o.order == 0) {
-      // All items of a tenant cost the same except those of a shorter last K slice, so sorting the items by cost
-      // (stably, from the nested tenant-major order) is sorting at most two runs per tenant.
-      struct Run { int tenant; int which; int64_t cost, count; };     // which: -1 all items, 0 full slices, 1 the last slice
+      // A tenant's items differ by their K slice only (the last one is shorter; in pieces the steps of the channels left over, which
+      // lie at the end, are longer), so sorting the items by cost (stably, from the nested tenant-major order) is sorting
+      // runs of slices that cost the same, few per tenant.
+      struct Run { int tenant, begin, end; int64_t cost, count; };      // K slices [begin, end) of every tile
       std::vector<Run> runs;
       runs.reserve((size_t)n_tenants * 2);
       for (int t = 0; t < n_tenants; ++t) {
         const st_tenant_info& ti = p->info[t];
-        const int last_steps = ti.k_steps - (ti.split_k - 1) * ti.k_steps_per_split;
         const ItemCosts& c = kCosts[descs[t].in_dtype == ST_DT_F32 ? 1 : 0][0];
-        const double step = ti.row_tiled ? c.step[ti.tile_cfg] : step_cost(descs[t], form[t], ti.tile_cfg, c);
-        auto cost = [&](int steps) { return (int64_t)(steps * step + c.epi[ti.tile_cfg]) * std::max(1, ti.rows_per_tile); };
-        if (ti.split_k == 1 || last_steps == ti.k_steps_per_split) {
-          runs.push_back({t, -1, cost(ti.split_k == 1 ? ti.k_steps : ti.k_steps_per_split), ti.item_count});
-        } else {
-          const int64_t tiles = ti.item_count / ti.split_k;
-          runs.push_back({t, 0, cost(ti.k_steps_per_split), ti.item_count - tiles});
-          runs.push_back({t, 1, cost(last_steps), tiles});
+        const KSteps k = k_steps_of(descs[t], form[t], ti.tile_cfg);
+        const int64_t tiles = ti.item_count / ti.split_k;
+        auto cost = [&](int slice) {
+          const int begin = slice * ti.k_steps_per_split, end = std::min(ti.k_steps, begin + ti.k_steps_per_split);
+          const double steps = ti.row_tiled ? (end - begin) * c.step[ti.tile_cfg] : steps_cost(descs[t], form[t], ti.tile_cfg, c, k, begin, end);
+          return (int64_t)(steps + c.epi[ti.tile_cfg]) * std::max(1, ti.rows_per_tile);
+        };
+        for (int i = 0; i < ti.split_k; ++i) {
+          const int64_t mine = cost(i);
+          if (i > 0 && runs.back().cost == mine) {
+            ++runs.back().end;
+            runs.back().count += tiles;
+          } else {
+            runs.push_back({t, i, i + 1, mine, tiles});
+          }
         }
       }
       std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.cost > b.cost; });
@@ -777,8 +793,7 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
         const st_tenant_info& ti = p->info[r.tenant];
         for (int tm = 0; tm < ti.tiles_m; ++tm)
           for (int tn = 0; tn < ti.tiles_n; ++tn)
-            for (int s = 0; s < ti.split_k; ++s) {
-              if (r.which >= 0 && (s == ti.split_k - 1) != (r.which == 1)) continue;
+            for (int s = r.begin; s < r.end; ++s) {
               st_work_item it;
               it.tenant = (uint16_t)r.tenant;
               it.k_split_idx = (uint16_t)s;
@@ -836,13 +851,11 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       T.row_pitch = row_tile_pitch(d);
       magic_for(T.row_pitch / 16, &T.magic_nvp, &T.shift_nvp);
       if (form[t] == kPieces) {
-        const PieceSteps ps = piece_steps(d, ti.tile_cfg);
+        const KSteps k = k_steps_of(d, kPieces, ti.tile_cfg);
         T.k_order = kOrderPieces;
-        T.step_dk = ps.vectors;
-        T.step_dr = ps.main;
-        T.k_steps = ps.main + ps.left;            // (the plan's own count goes by Kgemm: not more)
-        T.k_steps_per_split = cdiv(T.k_steps, ti.split_k);
-        magic_for(ps.vectors, &T.magic_c, &T.shift_c);
+        T.step_dk = k.vectors;
+        T.step_dr = k.main;
+        magic_for(k.vectors, &T.magic_c, &T.shift_c);
       }
       magic_for(d.R, &T.magic_r, &T.shift_r);
       magic_for(T.PQ, &T.magic_pq, &T.shift_pq);

@@ -80,3 +80,36 @@ def test_forms_are_reported():
     assert sc.st_conv_plan_tenant_form(plan, 0) == sc.ST_FORM_ROWS
     with pytest.raises(sc.StError):
         sc.st_conv_plan_tenant_form(plan, 1)
+
+
+def _steps(c, window, dtype, kb):
+    """K steps of whole vectors and of left-over channels, from the layout of the reduction index."""
+    es = 4 if dtype == "f32" else 2
+    vec = 16 // es
+    taps = window[0] * window[1]
+    return -(-taps * (c // vec * vec) * es // kb), -(-taps * 16 // kb)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("c,window", [(9, (5, 5)), (61, (1, 1)), (125, (1, 1)), (67, (3, 3)), (243, (3, 3)), (13, (7, 7))])
+@pytest.mark.parametrize("tile_cfg", [2, 4, 5, 6])
+@pytest.mark.parametrize("split", [1, 2, 3, 5])
+def test_steps_and_slices_are_the_kernels_own(dtype, c, window, tile_cfg, split):
+    plan, (ti,) = _plan([(1, c, 16, 16, 64, window[0], window[1], 1, window[0] // 2, dtype)], tile_cfg=tile_cfg, split_k=split)
+    assert sc.st_conv_plan_tenant_form(plan, 0) == sc.ST_FORM_PIECES
+    main, left = _steps(c, window, dtype, sc.st_tile_shape(ti.tile_cfg)[2])
+    assert ti.k_steps == main + left
+    assert ti.k_steps_per_split == -(-ti.k_steps // ti.split_k) and (ti.split_k - 1) * ti.k_steps_per_split < ti.k_steps
+    assert ti.split_k <= split
+
+
+def test_slices_of_left_over_channels_start_first():
+    """Nine channels, 5x5: four steps of whole vectors, then four of the channel left over, which take longer."""
+    layer = (1, 9, 32, 32, 64, 5, 5, 1, 2, "bf16")
+    plan, (ti,) = _plan([layer], tile_cfg=4, split_k=2)
+    assert (ti.k_steps, ti.k_steps_per_split) == (8, 4)
+    slices = sc.st_conv_plan_worklist(plan, 0)["k_split_idx"].tolist()
+    assert slices == sorted(slices, reverse=True)
+    plan, (ti,) = _plan([layer], tile_cfg=4, split_k=4)         # two of each
+    slices = sc.st_conv_plan_worklist(plan, 0)["k_split_idx"].tolist()
+    assert sorted(slices[:len(slices) // 2]) == [2] * ti.tiles_m + [3] * ti.tiles_m
