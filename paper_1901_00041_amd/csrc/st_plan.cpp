@@ -83,23 +83,28 @@ static void magic_for(int d, uint32_t* m, int32_t* L) {
 //   first operands staged | one K step | epilogue | split-K hand-off (write-through, counter, read back).
 // A workgroup that has its compute unit to itself and two that share one behave differently (the shared step is bound by
 // the compute unit's 64 bytes per clock from the L2, the lone one by latency and instruction issue), and fp32 MFMAs take
-// eight times as long as 16-bit ones, so there are four tables, and two more for 16-bit 3x3 layers whose input patch stays
-// in LDS (a shape without that form costs there what it costs in the first table).
+// eight times as long as 16-bit ones, so there are four tables; two more for 16-bit 3x3 layers whose input patch stays
+// in LDS (a shape without that form costs there what it costs in the first table); and two for 16-bit layers whose channels are no
+// multiple of the step (kOrderTaps), whose rows straddle cache lines and whose lanes keep a position each: a shared step
+// of 64x64 takes 850 clocks (16 to 240 channels, 3x3 and 5x5) where one of 64 or 128 channels takes 430.  fp32 layers of that order are bound by their MFMAs and
+// cost what the others do.
 // The launch is modelled as list scheduling of the items on workgroup slots: its duration is about max(longest item, sum
 // of item times / slots).  The planner picks, per tenant, the (tile, split) option that minimises that maximum over
 // the whole launch: once for kSlots slots of shared compute units and, if the caller names no number of slots, once for
 // one workgroup on each.  (So a plan with target_items, which every stack and chain has, is priced by the shared tables
 // throughout; and the order of the fused list goes by the shared tables without the patch form, whatever was planned.)
 struct ItemCosts { double first[kNumTileCfgs], step[kNumTileCfgs], epi[kNumTileCfgs]; };
-enum { kCosts16 = 0, kCosts32 = 1, kCostsPatch = 2 };
+enum { kCosts16 = 0, kCosts32 = 1, kCostsPatch = 2, kCostsTaps = 3 };
 // [kCosts*][alone on the compute unit]
-static const ItemCosts kCosts[3][2] = {
+static const ItemCosts kCosts[4][2] = {
     {{{4800, 4500, 4500, 3800, 4200, 3250, 3000}, {1250, 740, 740, 430, 650, 560, 310}, {4700, 2500, 2600, 1800, 1400, 1230, 2300}},
      {{2700, 2500, 2500, 2300, 2600, 2200, 3000}, {820, 470, 470, 305, 450, 375, 310}, {3900, 2070, 2080, 1500, 1240, 1120, 2300}}},
     {{{5200, 5500, 5500, 4300, 4300, 3250, 0}, {7200, 3600, 3600, 1850, 1850, 1060, 0}, {8000, 4500, 4000, 3000, 1800, 1330, 0}},
      {{3500, 3000, 3000, 2500, 2700, 2300, 0}, {4350, 2260, 2240, 1200, 1300, 740, 0}, {4300, 2200, 2200, 1670, 1430, 1180, 0}}},
     {{{4800, 2300, 2400, 2000, 2300, 3250, 0}, {1250, 620, 680, 380, 590, 560, 0}, {4700, 2400, 2500, 1700, 1400, 1230, 0}},
-     {{2700, 1500, 1550, 1300, 1600, 2200, 0}, {820, 465, 445, 310, 410, 375, 0}, {3900, 2060, 2030, 1500, 1240, 1120, 0}}}};
+     {{2700, 1500, 1550, 1300, 1600, 2200, 0}, {820, 465, 445, 310, 410, 375, 0}, {3900, 2060, 2030, 1500, 1240, 1120, 0}}},
+    {{{1200, 2250, 2300, 2650, 2400, 1850, 0}, {2210, 1300, 1370, 850, 1060, 840, 0}, {4700, 2500, 2600, 1800, 1400, 1230, 0}},
+     {{2050, 3350, 3000, 3550, 2950, 2300, 0}, {1490, 745, 785, 475, 605, 475, 0}, {3900, 2070, 2080, 1500, 1240, 1120, 0}}}};
 static const double kRowStageCost = 4300.0;     // row tile: copying image rows and filters into LDS
 // any channel count (conv_tile_gather) [fp32 operands]: bound by the texture addresser, which takes unaligned vectors apart
 static const double kGatherStepCost[2][kNumTileCfgs] = {{0, 2600.0, 0, 1550.0, 0, 0, 0}, {0, 3600.0, 0, 2000.0, 0, 0, 0}};
@@ -119,12 +124,29 @@ static double gather_step_cost(const st_conv_desc& d, int cfg) {
 
 enum Form { kGathered = 0, kVectors = 1, kPieces = 2 };       // (TenantDev.vec_ok)
 
-// kOrderPieces: what a step of left-over channels costs more than another, and by how much vectors at addresses that are no
-// multiple of four bytes slow a step down (64x64, 3x3 of 240 channels alone: 462 clocks and 961).  A launch of 24 layers off every
-// round number: 31.7 us with gathered tiles for all of them, 26.6 with the form that costs less; 28 such launches of 3 to 40 layers:
-// 0.97 to 2.0 times as fast, 1.24 in the geometric mean (with 4000 here 1.21).
-static const double kLeftStepCost = 1200.0;
-static const double kOddStepFactor = 2.0;
+// Pieces: until the first operands are staged | a step of whole vectors | a step of channels left over | more for every tap in it;
+// [16-bit types and an even channel count, 16-bit types and an odd one (vectors at odd multiples of two bytes), fp32][alone on the
+// compute unit][tile shape].  Least relative squares over the stamps of 1x1, 3x3 and 5x5 layers of 5 to 243 channels, 24 layers or so
+// to a table: the items are within 15 % of it, 2 to 7 % in the root mean square.  120 random launches of 3 to 40 layers off every round
+// number, with all three epilogues: 0.97 (one launch of 17.7 us; the next 1.00) to 2.7 times as fast as with gathered tiles for all of
+// them, 1.37 in the geometric mean; where pieces went by the vector tiles' prices, and epilogues by one price each, 0.76 to 1.7, 1.22.
+struct PieceCosts { double first[kNumTileCfgs], step[kNumTileCfgs], left[kNumTileCfgs], tap[kNumTileCfgs]; };
+static const PieceCosts kPieceCosts[3][2] = {
+    {{{0, 3000, 0, 2400, 1850, 1700, 0}, {0, 1490, 0, 970, 1220, 1030, 0}, {0, 690, 0, 560, 1340, 1180, 0}, {0, 34, 0, 27, 0, 0, 0}},
+     {{0, 3000, 0, 2350, 2450, 2000, 0}, {0, 850, 0, 510, 690, 590, 0}, {0, 1010, 0, 950, 990, 920, 0}, {0, 36, 0, 27, 26, 18, 0}}},
+    {{{0, 1750, 0, 1500, 1400, 1400, 0}, {0, 1790, 0, 1200, 1720, 1470, 0}, {0, 1580, 0, 1100, 1340, 1200, 0}, {0, 400, 0, 250, 180, 140, 0}},
+     {{0, 2050, 0, 1600, 2250, 1700, 0}, {0, 1100, 0, 720, 1120, 950, 0}, {0, 1800, 0, 1410, 810, 920, 0}, {0, 150, 0, 100, 115, 80, 0}}},
+    {{{0, 3900, 0, 2200, 1600, 1950, 0}, {0, 4000, 0, 2200, 2380, 1440, 0}, {0, 3440, 0, 1930, 3180, 1820, 0}, {0, 185, 0, 130, 17, 21, 0}},
+     {{0, 2900, 0, 2050, 2200, 1900, 0}, {0, 2600, 0, 1410, 1540, 975, 0}, {0, 2550, 0, 1800, 2030, 1370, 0}, {0, 82, 0, 25, 20, 12, 0}}}};
+static const PieceCosts& piece_costs(const st_conv_desc& d, bool alone) {
+  return kPieceCosts[d.in_dtype == ST_DT_F32 ? 2 : d.C % 2][alone ? 1 : 0];
+}
+
+// Epilogues whose rows are no whole vectors, by elements: filter counts off four, [alone][tile shape] (3x3 layers of 62 and 64
+// channels, every shape and type, 250 to 252 filters).  With a residual twice that, or that for multiples of four; without, those store whole vectors.
+static const double kElementEpi[2][kNumTileCfgs] = {{45000, 16000, 15000, 7300, 2200, 1100, 0}, {24500, 11500, 11500, 5000, 1650, 1000, 0}};
+// A residual of whole vectors that no K step hides (every form for any channel count), more than the same epilogue without.
+static const double kOpenResidualEpi[kNumTileCfgs] = {0, 700, 0, 350, 400, 400, 0};
 
 // The K steps of a layer on a tile shape: those of the reduction index, or in pieces those of all taps' whole vectors (`vectors`
 // channels of each tap), then those of the channels left over, a vector per tap.
@@ -135,16 +157,27 @@ static KSteps k_steps_of(const st_conv_desc& d, int form, int cfg) {
   return {cdiv(taps * c * es, kTileShapes[cfg].KB), form == kPieces ? cdiv(taps * 16, kTileShapes[cfg].KB) : 0, c};
 }
 
-// Clocks of one K step of a form (of the whole vectors, for kPieces).
-static double step_cost(const st_conv_desc& d, int form, int cfg, const ItemCosts& c) {
-  if (form == kGathered) return gather_step_cost(d, cfg);
-  return c.step[cfg] * (form == kPieces && elem_size(d.in_dtype) == 2 && d.C % 2 != 0 ? kOddStepFactor : 1.0);
+static const ItemCosts& item_costs(const st_conv_desc& d, int cfg, bool patch, bool alone) {
+  const bool taps = cfg != kRowCfg && d.C % (kTileShapes[cfg].KB / 2) != 0;
+  return kCosts[d.in_dtype == ST_DT_F32 ? kCosts32 : patch ? kCostsPatch : taps ? kCostsTaps : kCosts16][alone ? 1 : 0];
 }
 
 // Clocks that steps [begin, end) of a layer take.
-static double steps_cost(const st_conv_desc& d, int form, int cfg, const ItemCosts& c, const KSteps& k, int begin, int end) {
-  const int main = std::min(end, k.main) - std::min(begin, k.main), left = end - begin - main;
-  return main * step_cost(d, form, cfg, c) + left * (c.step[cfg] + kLeftStepCost);
+static double steps_cost(const st_conv_desc& d, int form, int cfg, const ItemCosts& c, bool alone, const KSteps& k, int begin, int end) {
+  if (form == kGathered) return (end - begin) * gather_step_cost(d, cfg);
+  if (form == kVectors) return (end - begin) * c.step[cfg];
+  const PieceCosts& p = piece_costs(d, alone);
+  const int main = std::min(end, k.main) - std::min(begin, k.main);
+  return main * p.step[cfg] + (end - begin - main) * (p.left[cfg] + p.tap[cfg] * d.R * d.S / k.left);
+}
+
+// Clocks from the last MFMA to the end of the item.  any_filters: the launch's kernel stores whole vectors for any filter count
+// (kHasEverything; see tile_epilogue).
+static double epilogue_cost(const st_conv_desc& d, int form, int cfg, const ItemCosts& c, bool alone, bool any_filters) {
+  const bool residual = (d.epilogue & ST_EPI_RESIDUAL) != 0u;
+  if (d.K % 8 == 0) return c.epi[cfg] + (residual && form != kVectors ? kOpenResidualEpi[cfg] : 0.0);
+  if (!residual && (any_filters || d.K % 4 == 0)) return c.epi[cfg];
+  return std::max(c.epi[cfg], kElementEpi[alone ? 1 : 0][cfg] * (residual && d.K % 4 != 0 ? 2.0 : 1.0));
 }
 
 struct Option {
@@ -343,7 +376,7 @@ static Option make_row_option(const st_conv_desc& d, int rows_per_tile, bool alo
   return o;
 }
 
-static Option make_option(const st_conv_desc& d, int64_t M, int64_t Ng, int form, bool alone, int cfg, int split) {
+static Option make_option(const st_conv_desc& d, int64_t M, int64_t Ng, int form, bool alone, bool any_filters, int cfg, int split) {
   Option o;
   o.form = form;
   o.rows_per_tile = 0;
@@ -358,22 +391,23 @@ static Option make_option(const st_conv_desc& d, int64_t M, int64_t Ng, int form
   o.items = (int64_t)cdiv(M, kTileShapes[cfg].MT) * cdiv(Ng, kTileShapes[cfg].NT) * split;
   int32_t rows, loads;
   const bool patch = per % kPatchTaps == 0 && patch_geometry(d, cfg, &rows, &loads);
-  const ItemCosts& c = kCosts[d.in_dtype == ST_DT_F32 ? kCosts32 : patch ? kCostsPatch : kCosts16][alone ? 1 : 0];
+  const ItemCosts& c = item_costs(d, cfg, patch, alone);
   const double elems = (double)kTileShapes[cfg].MT * kTileShapes[cfg].NT;
   const int batch = elems > 4096 ? 4 : 8;      // slices read back at a time
   // the longest slice: the first one, or where channels left over are dearer the last whole one or the last one
   double steps_time = 0.0;
   for (int i : {0, split - 2, split - 1})
-    if (i >= 0) steps_time = std::max(steps_time, steps_cost(d, form, cfg, c, k, i * per, std::min(k_steps, (i + 1) * per)));
-  const double around = (form == kGathered ? kGatherFirstCost : c.first[cfg]) + c.epi[cfg] +
+    if (i >= 0) steps_time = std::max(steps_time, steps_cost(d, form, cfg, c, alone, k, i * per, std::min(k_steps, (i + 1) * per)));
+  const double around = (form == kGathered ? kGatherFirstCost : form == kPieces ? piece_costs(d, alone).first[cfg] : c.first[cfg]) +
+                        epilogue_cost(d, form, cfg, c, alone, any_filters) +
                         (split > 1 ? kSplitCost + kSplitPerElem * elems + (kSplitRoundCost + kSplitRoundPerElem * elems) * ((split - 1) / batch) : 0.0);
   o.item_time = around + steps_time;
   o.area = o.item_time * (double)o.items;
-  if (form == kPieces) o.area = (double)o.items * (around + steps_cost(d, form, cfg, c, k, 0, k_steps) / split);    // slices may differ a lot
+  if (form == kPieces) o.area = (double)o.items * (around + steps_cost(d, form, cfg, c, alone, k, 0, k_steps) / split);    // slices may differ a lot
   return o;
 }
 
-static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int64_t Ng, bool alone,
+static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int64_t Ng, bool alone, bool any_filters,
                                           const st_plan_opts& o) {
   std::vector<Option> out;
   const bool row_ok = row_tile_ok(d);
@@ -391,12 +425,12 @@ static std::vector<Option> tenant_options(const st_conv_desc& d, int64_t M, int6
     const int form = form_on(d, c);
     if (form < 0 || (o.tile_cfg > 0 && c != forced)) continue;
     if (o.split_k >= 1) {
-      out.push_back(make_option(d, M, Ng, form, alone, c, o.split_k));
+      out.push_back(make_option(d, M, Ng, form, alone, any_filters, c, o.split_k));
       continue;
     }
     int last_split = 0;
     for (int sp : kSplitChoices) {
-      Option op = make_option(d, M, Ng, form, alone, c, sp);
+      Option op = make_option(d, M, Ng, form, alone, any_filters, c, sp);
       if (op.split == last_split) continue;             // clamped to the same factor as before
       if (op.split > 1 && op.steps_per_split < 2) continue;
       last_split = op.split;
@@ -656,11 +690,13 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       p->bytes += ti.bytes;
     }
     // tile shape and split-K per tenant, chosen jointly from the cost model
+    bool any_filters = false;       // several types, or a form for any channel count (launch_conv)
+    for (int t = 0; t < n_tenants; ++t) any_filters |= descs[t].in_dtype != descs[0].in_dtype || (!vector_ok(descs[t]) && !row_tile_ok(descs[t]));
     auto all_options = [&](bool alone) {
       std::vector<std::vector<Option>> options(n_tenants);
       for (int t = 0; t < n_tenants; ++t) {
         const st_tenant_info& ti = p->info[t];
-        options[t] = tenant_options(descs[t], ti.M, ti.Ngemm, alone, o);
+        options[t] = tenant_options(descs[t], ti.M, ti.Ngemm, alone, any_filters, o);
       }
       return options;
     };
@@ -769,13 +805,13 @@ extern "C" st_status st_conv_plan(const st_conv_desc* descs, int32_t n_tenants, 
       runs.reserve((size_t)n_tenants * 2);
       for (int t = 0; t < n_tenants; ++t) {
         const st_tenant_info& ti = p->info[t];
-        const ItemCosts& c = kCosts[descs[t].in_dtype == ST_DT_F32 ? 1 : 0][0];
+        const ItemCosts& c = item_costs(descs[t], ti.tile_cfg, false, false);
         const KSteps k = k_steps_of(descs[t], form[t], ti.tile_cfg);
         const int64_t tiles = ti.item_count / ti.split_k;
         auto cost = [&](int slice) {
           const int begin = slice * ti.k_steps_per_split, end = std::min(ti.k_steps, begin + ti.k_steps_per_split);
-          const double steps = ti.row_tiled ? (end - begin) * c.step[ti.tile_cfg] : steps_cost(descs[t], form[t], ti.tile_cfg, c, k, begin, end);
-          return (int64_t)(steps + c.epi[ti.tile_cfg]) * std::max(1, ti.rows_per_tile);
+          if (ti.row_tiled) return (int64_t)((end - begin) * c.step[ti.tile_cfg] + c.epi[ti.tile_cfg]) * ti.rows_per_tile;
+          return (int64_t)(steps_cost(descs[t], form[t], ti.tile_cfg, c, false, k, begin, end) + epilogue_cost(descs[t], form[t], ti.tile_cfg, c, false, any_filters));
         };
         for (int i = 0; i < ti.split_k; ++i) {
           const int64_t mine = cost(i);

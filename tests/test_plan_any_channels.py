@@ -113,3 +113,25 @@ def test_slices_of_left_over_channels_start_first():
     plan, (ti,) = _plan([layer], tile_cfg=4, split_k=4)         # two of each
     slices = sc.st_conv_plan_worklist(plan, 0)["k_split_idx"].tolist()
     assert sorted(slices[:len(slices) // 2]) == [2] * ti.tiles_m + [3] * ti.tiles_m
+
+
+def test_stores_by_element_are_priced():
+    """Among small layers, 1x1 with 251 filters and a residual: its rows are no whole vectors, and a 128x128 tile spends 27500 clocks
+    storing them, twice what any other work item of the launch takes in all."""
+    R = sc.ST_EPI_RESIDUAL
+    layers = [(2, 145, 20, 35, 32, 3, 3, 1, 1, "bf16", "bf16", R), (4, 120, 5, 40, 251, 1, 1, 3, 0, "f16", "f16", R), (1, 91, 7, 30, 25, 1, 7, 1, 3, "f32", "f32", R),
+              (4, 8, 5, 34, 96, 3, 3, 1, 1, "bf16", "bf16", R), (3, 92, 32, 13, 109, 5, 5, 1, 1, "f16", "f32", R), (1, 160, 23, 18, 214, 1, 1, 3, 0, "f32", "f32", R)]
+    _, infos = _plan(layers)
+    assert infos[1].MT * infos[1].NT <= 64 * 64
+    assert infos[5].MT * infos[5].NT <= 32 * 64
+
+
+def test_steps_of_pieces_are_priced():
+    """226 channels, 3x3: beside a second workgroup a 128x64 step takes twice what it takes with a multiple of 64 channels.  Unsplit on
+    that tile this layer ran 83000 clocks, half as long again as anything else in its launch."""
+    layers = [(1, 128, 31, 26, 45, 3, 3, 3, 0, "bf16", "f32"), (4, 226, 11, 39, 72, 3, 3, 3, 1, "f16", "f16"), (4, 120, 16, 17, 222, 3, 3, 1, 1, "f32", "f32"),
+              (2, 152, 23, 37, 50, 5, 5, 1, 1, "f32", "f32"), (4, 199, 28, 11, 1, 3, 3, 1, 0, "f32", "f32"), (2, 112, 9, 25, 56, 5, 5, 2, 2, "f32", "f32"),
+              (4, 184, 36, 40, 32, 3, 3, 1, 0, "f16", "f32"), (3, 72, 28, 10, 197, 3, 3, 1, 0, "f16", "f32")]
+    plan, infos = _plan(layers)
+    assert sc.st_conv_plan_tenant_form(plan, 1) == sc.ST_FORM_PIECES
+    assert infos[1].MT * infos[1].NT // infos[1].split_k <= 64 * 64
