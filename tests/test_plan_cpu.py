@@ -436,3 +436,15 @@ def test_default_plan_prefers_one_workgroup_per_compute_unit_when_the_model_says
     a4 = sc.st_conv_plan_info(sc.st_conv_plan([_desc(s) for s in shapes4], sc.plan_opts(host_only=1)))
     f4 = sc.st_conv_plan_info(sc.st_conv_plan([_desc(s) for s in shapes4], sc.plan_opts(host_only=1, target_items=400)))
     assert a4.n_items == f4.n_items > 256
+
+
+def test_row_tiles_start_with_items_as_long_as_they_are():
+    """A stem's items of two rows copy image rows and filters before anything else: with that they take longer than four steps of a
+    128x128 tile (16800 clocks by the planner's costs, and 14500), and start first."""
+    descs = [sc.make_desc(*s, "bf16", "f32", 0x10000 * (3 * i + 1), 0x10000 * (3 * i + 2), 0x10000 * (3 * i + 3))
+             for i, s in enumerate([(1, 256, 56, 56, 512, 1, 1, 1, 0)] * 2 + [(4, 3, 224, 224, 64, 7, 7, 2, 3)])]
+    plan = sc.st_conv_plan(descs, sc.plan_opts(host_only=1, rows_per_tile=2))
+    stem = sc.st_conv_plan_tenant_info(plan, 2)
+    assert stem.row_tiled and stem.rows_per_tile == 2 and sc.st_conv_plan_tenant_info(plan, 0).tile_cfg == 0
+    order = sc.st_conv_plan_worklist(plan, 0)["tenant"].tolist()
+    assert order[:stem.item_count] == [2] * stem.item_count
