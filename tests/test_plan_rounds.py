@@ -1,0 +1,30 @@
+"""Launches of unlike layers are planned in whole rounds of workgroup slots (no GPU)."""
+import pytest
+
+from paper_1901_00041_amd import st_conv as sc
+
+FAKE = 1 << 32
+# Eight layers of batch up to four, one of them a stem.
+STEM = [(4, 512, 14, 14, 512, 1, 1, 1, 0, "bf16", "f32"), (3, 64, 56, 56, 64, 3, 3, 1, 1, "bf16", "f32"), (3, 64, 7, 7, 1024, 1, 1, 1, 0, "bf16", "f32"),
+        (1, 128, 56, 56, 128, 3, 3, 1, 1, "bf16", "f32"), (1, 1024, 56, 56, 128, 1, 1, 1, 0, "bf16", "f32"), (3, 256, 28, 28, 256, 3, 3, 1, 1, "bf16", "f32"),
+        (3, 512, 7, 7, 1024, 1, 1, 1, 0, "bf16", "f32"), (4, 3, 224, 224, 64, 7, 7, 2, 3, "bf16", "f32")]
+# Layers off every round number, in every type.
+RAGGED = [(3, 168, 24, 34, 112, 1, 7, 1, 3, "bf16", "bf16"), (3, 18, 34, 10, 179, 3, 3, 1, 0, "f16", "f32"), (4, 32, 23, 31, 141, 3, 3, 1, 0, "f32", "f32"),
+          (1, 32, 12, 31, 168, 5, 5, 1, 1, "bf16", "f32"), (2, 64, 33, 11, 88, 7, 1, 3, 2, "f16", "f16"), (2, 8, 3, 29, 153, 7, 1, 1, 2, "f32", "f32"),
+          (1, 250, 8, 38, 164, 5, 5, 2, 1, "bf16", "f32"), (4, 56, 29, 17, 137, 1, 1, 2, 0, "f16", "f16"), (1, 176, 17, 14, 136, 1, 1, 1, 0, "f32", "f32"),
+          (4, 16, 37, 11, 256, 1, 1, 2, 0, "bf16", "bf16"), (2, 32, 4, 11, 256, 2, 3, 3, 0, "f16", "f16")]
+
+
+def _items(layers, epilogue=0, **opts):
+    descs = [sc.make_desc(*s, FAKE * (3 * i + 1), FAKE * (3 * i + 2), FAKE * (3 * i + 3), None, epilogue) for i, s in enumerate(layers)]
+    return int(sc.st_conv_plan_info(sc.st_conv_plan(descs, sc.plan_opts(host_only=1, **opts))).n_items)
+
+
+@pytest.mark.parametrize("layers", [STEM, RAGGED])
+def test_no_few_items_beyond_the_slots(layers):
+    """With 604 and 528 items on 512 slots these took a second round, for half as long again as with one."""
+    assert _items(layers, sc.ST_EPI_RELU) <= 512
+
+
+def test_a_callers_share_is_planned_as_before():
+    assert [_items(STEM, target_items=n) for n in (200, 300, 512)] == [372, 420, 653]
