@@ -143,9 +143,13 @@ static const PieceCosts& piece_costs(const st_conv_desc& d, bool alone) {
   return kPieceCosts[d.in_dtype == ST_DT_F32 ? 2 : d.C % 2][alone ? 1 : 0];
 }
 
-// Epilogues whose rows are no whole vectors, by elements: filter counts off four, [alone][tile shape] (3x3 layers of 62 and 64
-// channels, every shape and type, 250 to 252 filters).  With a residual twice that, or that for multiples of four; without, those store whole vectors.
-static const double kElementEpi[2][kNumTileCfgs] = {{45000, 16000, 15000, 7300, 2200, 1100, 0}, {24500, 11500, 11500, 5000, 1650, 1000, 0}};
+// Epilogues whose rows are no whole vectors, by elements, of a tile full of filters, [with a residual][filter count off four][fp32
+// output][alone on the compute unit][tile shape]: stamps of 3x3 layers of 64 and 67 channels with 241 to 252 filters, every type.
+static const double kElementEpi[2][2][2][2][kNumTileCfgs] = {
+    {{{{11000, 3500, 3500, 1900, 1400, 850, 0}, {7000, 2800, 2800, 1900, 1350, 850, 0}}, {{12000, 4300, 4400, 2200, 1250, 750, 0}, {6500, 2800, 2900, 1700, 1200, 750, 0}}},
+     {{{41000, 12400, 12200, 6450, 2170, 1080, 0}, {21000, 9800, 9500, 4400, 1650, 1000, 0}}, {{45000, 15500, 16000, 8000, 2700, 1150, 0}, {23000, 10700, 10700, 4800, 1600, 925, 0}}}},
+    {{{{36000, 14300, 17500, 6750, 3030, 1710, 0}, {20500, 10300, 10500, 5400, 2830, 1650, 0}}, {{46500, 18600, 22200, 8700, 3500, 2100, 0}, {24000, 10500, 11500, 5500, 2800, 1620, 0}}},
+     {{{60000, 26500, 30000, 12400, 4150, 2000, 0}, {32000, 16500, 16800, 8600, 3660, 1860, 0}}, {{79000, 32500, 39000, 15200, 5400, 2450, 0}, {43000, 18200, 20000, 9500, 4000, 1880, 0}}}}};
 // A residual of whole vectors that no K step hides (every form for any channel count), more than the same epilogue without.
 static const double kOpenResidualEpi[kNumTileCfgs] = {0, 700, 0, 350, 400, 400, 0};
 
@@ -177,8 +181,9 @@ static double steps_cost(const st_conv_desc& d, int form, int cfg, const ItemCos
 static double epilogue_cost(const st_conv_desc& d, int form, int cfg, const ItemCosts& c, bool alone, bool any_filters) {
   const bool residual = (d.epilogue & ST_EPI_RESIDUAL) != 0u;
   if (d.K % 8 == 0) return c.epi[cfg] + (residual && form != kVectors ? kOpenResidualEpi[cfg] : 0.0);
-  if (!residual && (any_filters || d.K % 4 == 0)) return c.epi[cfg];
-  return std::max(c.epi[cfg], kElementEpi[alone ? 1 : 0][cfg] * (residual && d.K % 4 != 0 ? 2.0 : 1.0));
+  if (!residual && any_filters) return c.epi[cfg];
+  const double full = std::min(1.0, (double)d.K / kTileShapes[cfg].NT);
+  return std::max(c.epi[cfg], full * kElementEpi[residual][d.K % 4 != 0][d.out_dtype == ST_DT_F32][alone ? 1 : 0][cfg]);
 }
 
 struct Option {

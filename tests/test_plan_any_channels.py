@@ -135,3 +135,12 @@ def test_steps_of_pieces_are_priced():
     plan, infos = _plan(layers)
     assert sc.st_conv_plan_tenant_form(plan, 1) == sc.ST_FORM_PIECES
     assert infos[1].MT * infos[1].NT // infos[1].split_k <= 64 * 64
+
+
+def test_stores_by_element_are_priced_by_what_is_stored():
+    """67 filters fill half of a 128-filter tile: 2156 items of 32x64 ran a fifth longer than 539 of 128x64.  And fp32 results with a
+    residual cost more on 64x128 tiles than on 128x64 (39000 clocks, 32500): 227 us and 182."""
+    _, infos = _plan([(4, 208, 28, 28, 67, 1, 1, 1, 0, "bf16", "bf16", sc.ST_EPI_RELU)] * 11)
+    assert infos[0].MT * infos[0].NT >= 128 * 64
+    _, infos = _plan([(3, 64, 56, 56, 469, 3, 3, 1, 1, "bf16", "f32", sc.ST_EPI_RELU | sc.ST_EPI_RESIDUAL)] * 7)
+    assert (infos[0].MT, infos[0].NT) == (128, 64)
