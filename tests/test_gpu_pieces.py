@@ -1,6 +1,6 @@
 """Channel counts that are no multiple of the 16-byte vector but hold one: whole vectors of every tap, then the channels left over.
-Every tile shape, split and unsplit, channel counts around the vector and the K step, windows that leave the image, filter counts
-off the vector width with and without a residual, and slices that hold only whole vectors, only left-over channels, or nothing."""
+Every tile shape that has this form, split and unsplit, channel counts around the vector and the K step, windows that leave the image,
+filter counts off the vector width with and without a residual, and slices that hold only whole vectors or only left-over channels."""
 import pytest
 
 from paper_1901_00041_amd import st_conv as sc
@@ -11,6 +11,11 @@ pytestmark = pytest.mark.gpu
 LAYERS = [(9, 9, 11, 24, 3, 3, 1, 1), (15, 13, 7, 65, 5, 5, 2, 2), (17, 8, 8, 7, 1, 1, 1, 0), (65, 10, 9, 70, 3, 3, 1, 1), (63, 12, 5, 131, 1, 7, 1, 3),
           (70, 9, 9, 64, 2, 3, 3, 0), (131, 21, 10, 201, 1, 1, 1, 0), (239, 6, 7, 33, 3, 3, 2, 1), (129, 5, 5, 8, 5, 5, 1, 2), (11, 5, 70, 9, 7, 1, 1, 3),
           (31, 4, 4, 16, 4, 4, 1, 3)]
+
+
+def _check_form(plan, i, tile_cfg):
+    assert sc.st_conv_plan_tenant_form(plan, i) == sc.ST_FORM_PIECES
+    assert tile_cfg == 0 or sc.st_conv_plan_tenant_info(plan, i).tile_cfg == tile_cfg - 1
 
 
 @pytest.mark.parametrize("dtype,out", [("bf16", "bf16"), ("bf16", "f32"), ("f16", "f16"), ("f32", "f32")])
@@ -38,6 +43,8 @@ def test_layers(tile_cfg, split, dtype, out):
         descs.append(sc.make_desc(N, C, H, W, K, R, S, stride, pad, dtype, out, dx, dw, y, dr, epi))
         made.append((dx, dw, dr, y, big, ref, R * S * C))
     plan = sc.st_conv_plan(descs, sc.plan_opts(tile_cfg=tile_cfg, split_k=split), keep=made)
+    for i in range(len(made)):
+        _check_form(plan, i, tile_cfg)
     for rep in range(2):
         sc.st_conv_run(plan)
     torch.cuda.synchronize()
@@ -64,7 +71,9 @@ def test_no_left_over_reads_past_the_tensors():
         y = torch.empty((N, H, W, K), dtype=torch.float32, device="cuda")
         for tile_cfg in (2, 4, 5, 6):
             y.fill_(float("nan"))
-            sc.st_conv_run(sc.st_conv_plan([sc.make_desc(N, C, H, W, K, 3, 3, 1, 1, name, "f32", x, w, y)], sc.plan_opts(tile_cfg=tile_cfg, split_k=1), keep=[bx, bw, y]))
+            plan = sc.st_conv_plan([sc.make_desc(N, C, H, W, K, 3, 3, 1, 1, name, "f32", x, w, y)], sc.plan_opts(tile_cfg=tile_cfg, split_k=1), keep=[bx, bw, y])
+            _check_form(plan, 0, tile_cfg)
+            sc.st_conv_run(plan)
             torch.cuda.synchronize()
             assert torch.isfinite(y).all()
 
