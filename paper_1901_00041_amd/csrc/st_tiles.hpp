@@ -1258,7 +1258,7 @@ __device__ __forceinline__ void conv_tile_patch(ConstOp& T, const st_work_item i
   if (prof && tid == 0) stamp_end(prof);
 }
 
-// ---- gather tile: channel counts that hold no whole 16-byte vector (and any other, where the planner finds it shorter) -------
+// ---- gather tile: channel counts that hold no whole 16-byte vector, and those where its walk is much the shorter one (form_on) -------
 // The same implicit GEMM for any C, D steps of loads kept in flight in registers ahead of an LDS double buffer with rows
 // padded by 16 bytes.  A vector of the reduction index is contiguous in memory as long as it stays inside one filter row,
 // and is then one 16-byte load from an element-aligned address; only vectors that cross into the next filter row, into the
