@@ -13,8 +13,9 @@
 // lowest unfinished entry is always held by a running workgroup whose dependencies are complete; no co-residency of
 // all workgroups is needed.  Columns: each is worked through in stage order, and every column in use needs its
 // workgroup.  Every wait is bounded twice over: by a wall-clock limit and by a count of polls; when
-// either expires the waiter raises the abort flag, and every workgroup leaves at its next claim or wait.  A workgroup
-// also takes at most n_items + 1 entries.  So the kernel always exits, whatever the clock or the counters do.
+// either expires the waiter raises the abort flag; a workgroup that sees it claims no further entry, and works through the
+// rest of its column with waits of a few looks.  A workgroup also takes at most n_items + 1 entries.  So the kernel always exits,
+// whatever the clock or the counters do.
 //
 // Memory: consumers read activations, residuals and partial tiles with device-scope loads, which never stop at a vector
 // cache and take from an L2 what that L2 holds newer than memory, so no cache is ever invalidated.  Producers wait for
@@ -51,12 +52,11 @@ typedef __attribute__((address_space(4))) const ChainPrefetch ConstPrefetch;
 // spread out on purpose, one line per lane and round trip: in one burst they delay the running stage's own loads.
 // Eight networks of batch 1, us per pass: no prefetch 411, 256 threads with four lines each in flight 394, with one line
 // 388, 128 threads 378, 64 threads 380; batch 8: 1333, 1255, 1249, 1246, 1273.
-__device__ __forceinline__ void prefetch_filters(ConstOp& T, uint32_t rank, int tid) {
-  constexpr uint32_t kLanes = 128u;
-  if ((uint32_t)tid >= kLanes) return;
+constexpr uint32_t kPrefetchLanes = 128u;
+__device__ __forceinline__ void prefetch_filters(ConstOp& T, uint32_t rank, int tid) {      // threads below kPrefetchLanes
   const __amdgpu_buffer_rsrc_t rw = make_rsrc(T.w, T.w_bytes);
   const uint32_t w_bytes = T.w_bytes;
-  for (uint32_t off = (rank * kLanes + (uint32_t)tid) * 128u; off < w_bytes; off += (uint32_t)kChainColumns * kLanes * 128u) {
+  for (uint32_t off = (rank * kPrefetchLanes + (uint32_t)tid) * 128u; off < w_bytes; off += (uint32_t)kChainColumns * kPrefetchLanes * 128u) {
     const uint32_t v = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rw, (int)off, 0, 0);
     asm volatile("" ::"v"(v));
   }
@@ -90,6 +90,11 @@ __device__ __forceinline__ bool flags_set(const uint32_t* item_flags, const Flag
     c0 = l.n;
   }
   return true;
+}
+
+// Whether the pass has been abandoned (uniform in a wavefront).
+__device__ __forceinline__ bool abandoned(const ChainArgs& a) {
+  return __builtin_amdgcn_readfirstlane(__hip_atomic_load(&a.ctl[kChainCtlAbort * kChainCtlStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0u;
 }
 
 // Whether the stage before prefetch entry pf's has started, i.e. the stage before that one is complete.
@@ -162,11 +167,11 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
     if (in_xcd >= (uint32_t)kChainColumns) {
       rank = in_xcd - (uint32_t)kChainColumns;
       pf = a.prefetch_begin[xcc];
-      pf_end = a.prefetch_begin[xcc + 1u];
+      if (__builtin_amdgcn_readfirstlane((uint32_t)tid) < kPrefetchLanes) pf_end = a.prefetch_begin[xcc + 1u];
     }
   }
   uint32_t n_done = 0u;
-  bool gave_up = false;
+  bool gave_up = false;                         // per wavefront
   uint32_t seen_key = 0xffffffffu, seen_need = 0u;      // the dependency (with flags: the gate) this workgroup last saw complete
   uint32_t seen_begin = 0u, seen_end = 0u;              // ... and the range of tiles
   {
@@ -208,52 +213,50 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
         wanted.n = wanted.n_gate + (begin >= seen_begin && begin + count <= seen_end ? 0u : count);
       }
       if (T.chain_need != 0u && (by_flags ? wanted.n != 0u : !gate_seen)) {
-        // Wavefront 0 looks at the dependency: with flags, at those of the gate and of the tiles the entry reads (ChainDep),
+        // Look at the dependency: with flags, at those of the gate and of the tiles the entry reads (ChainDep),
         // 64 at a time from the first that was not yet set (they were stored by workgroups of this XCD and sit, newer than
         // memory, in its L2, where a device-scope load finds them; such a load never stops at the vector cache); with a
         // counter, at the sequence's count of finished entries (bumped by device-scope atomics, carried out at the
         // memory side; a workgroup-scope load would stop at the vector cache and never see it move).
         const uint32_t run = a.run_number, need = T.chain_need;
         const uint32_t* ctr = a.ctl + (kChainCtlSeq + T.chain_seq) * kChainCtlStride;
+        const uint32_t lane = (uint32_t)work_thread_id() & 63u;
         uint32_t c0 = 0u;                     // flags before c0 are known to be set
-        auto satisfied = [&]() -> bool {      // wavefront 0 only, uniform
-          if (!by_flags) return (int32_t)(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - need) >= 0;
-          return flags_set(a.item_flags, wanted, run, (uint32_t)tid, c0);
+        auto satisfied = [&]() -> bool {      // uniform in a wavefront
+          if (!by_flags) return (int32_t)(__builtin_amdgcn_readfirstlane(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) - need) >= 0;
+          return flags_set(a.item_flags, wanted, run, lane, c0);
         };
-        // Wait.  In between, filters of coming stages may be due (pf): wavefront 0 says what happens next, 1 = the entry
-        // starts, 2 = prefetch, 0 = the pass is abandoned.
+        // Columns: every wavefront looks for itself, so that neither a message through LDS nor a barrier stands between the flag that ends
+        // the wait and the tile (one wavefront looking for all: eight networks of batch 1 346 us, of batch 8 1107; each for
+        // itself 335 and 1095).  In between, filters of coming stages may be due (pf).  A wavefront that gives up goes on as if
+        // the wait had ended, so that the barriers of all four stay in step: every access is checked against the tensors' sizes,
+        // and what is computed is lost with the pass, which the abort flag reports; later waits see that flag and end at once.
+        // One queue: wavefront 0 looks for all; four looking at a counter at the memory side slow each other down (670 us -> 719).
         const uint64_t t0 = wall_clock64();
-        uint32_t polls = 0u, p0 = 0u, msg;
-        do {
-          if (tid < 64) {
-            msg = 1u;
-            while (!satisfied()) {
-              if (pf < pf_end && prefetch_due(a, pf, (uint32_t)tid, p0)) { msg = 2u; break; }
-              // the abort flag and the clock are looked at on every 16th poll (every few microseconds) after the first looks
-              if ((++polls & 15u) != 0u || polls <= (uint32_t)kChainGraceLooks) { __builtin_amdgcn_s_sleep(2); continue; }
-              if (__hip_atomic_load(&a.ctl[kChainCtlAbort * kChainCtlStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) { msg = 0u; break; }
-              if (wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls) {
-                if (tid == 0) __hip_atomic_store(&a.ctl[kChainCtlAbort * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                msg = 0u;
-                break;
-              }
-              __builtin_amdgcn_s_sleep(2);
+        uint32_t polls = 0u, p0 = 0u;
+        if (COLUMNS || tid < 64) {
+          while (!satisfied()) {
+            if (pf < pf_end && prefetch_due(a, pf, lane, p0)) {
+              prefetch_filters(*(ConstOp*)(a.ops + ((ConstPrefetch*)a.prefetch)[pf].op), rank, tid);
+              ++pf;
+              p0 = 0u;
+              continue;
             }
-            if (tid == 0) s_msg[1] = msg;
+            // the abort flag and the clock are looked at on every 16th poll (every few microseconds) after the first looks
+            if ((++polls & 15u) != 0u || polls <= (uint32_t)kChainGraceLooks) { __builtin_amdgcn_s_sleep(1); continue; }
+            if (abandoned(a)) { gave_up = true; break; }
+            if (wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls) {
+              if (lane == 0u) __hip_atomic_store(&a.ctl[kChainCtlAbort * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              gave_up = true;
+              break;
+            }
+            __builtin_amdgcn_s_sleep(1);
           }
-          __syncthreads();
-          msg = __builtin_amdgcn_readfirstlane(s_msg[1]);
-          __syncthreads();                    // s_msg[1] has been read by everyone
-          if (msg == 2u) {
-            prefetch_filters(*(ConstOp*)(a.ops + ((ConstPrefetch*)a.prefetch)[pf].op), rank, tid);
-            ++pf;
-            p0 = 0u;
-          }
-        } while (msg == 2u);
+        }
+        if (!COLUMNS) __syncthreads();
         waited = wall_clock64() - t0;
         // No cache is invalidated here: everything an entry reads that this launch wrote (activations, residuals,
         // split-K partial tiles) is read with device-scope loads, and everything else did not change.
-        if (msg == 0u) { gave_up = true; break; }
         if (T.chain_dep_count != 0u) {        // (an empty range has no beginning to be known by)
           seen_key = key;
           seen_need = T.chain_need;
@@ -271,44 +274,37 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
       if (!COLUMNS && (it.reserved & kFormMask) != kFormPool && (T.K & 7) != 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       __builtin_amdgcn_s_waitcnt(0);          // every store of this thread has been acknowledged
       __syncthreads();                        // ... of every thread; also: smem and s_msg are free again
-      ++n_done;
-      if (tid == 0) {
+      if (!gave_up) ++n_done;
+      if (tid == 0 && !gave_up) {
         if (by_flags) {
           const uint32_t pos = ((uint32_t)it.tile_m * (uint32_t)T.tiles_n + (uint32_t)it.tile_n) * (uint32_t)T.split_k + (uint32_t)it.k_split_idx;
           __hip_atomic_store(a.item_flags + T.chain_flag_base + pos, a.run_number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         } else {
           __hip_atomic_fetch_add(a.ctl + (kChainCtlSeq + T.chain_seq) * kChainCtlStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        // One queue: the following entry is claimed only now.  The claim is a round trip to memory: issued before the
-        // entry's work it sits in front of the first operand loads in the in-order memory counter; issued before the
-        // completion signal (even as early as the end of the K loop: measured) it delays every dependant.
-        if (claiming) next = chain_claim(a, 0u, qb, qe);
         if (prof) prof[7] = waited;
       }
+      // One queue: the following entry is claimed only now.  The claim is a round trip to memory: issued before the
+      // entry's work it sits in front of the first operand loads in the in-order memory counter; issued before the
+      // completion signal (even as early as the end of the K loop: measured) it delays every dependant.
+      if (claiming && tid == 0) next = chain_claim(a, 0u, qb, qe);
     }
   }
-  // a shared column is often done long before the pass is: go on prefetching
-  if (pf < pf_end && !gave_up) {
-    const uint64_t t0 = wall_clock64();
-    uint32_t polls = 0u;
-    while (pf < pf_end) {
-      if (tid < 64) {
-        uint32_t p0 = 0u, msg = 2u;
-        while (!prefetch_due(a, pf, (uint32_t)tid, p0)) {
-          __builtin_amdgcn_s_sleep(8);
-          if ((++polls & 15u) != 0u) continue;
-          if (wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls ||
-              __hip_atomic_load(&a.ctl[kChainCtlAbort * kChainCtlStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) { msg = 0u; break; }
-        }
-        if (tid == 0) s_msg[1] = msg;
-      }
-      __syncthreads();
-      const uint32_t msg = __builtin_amdgcn_readfirstlane(s_msg[1]);
-      __syncthreads();
-      if (msg == 0u) break;                   // a prefetch is only a favour: nothing to report
+  // a shared column is often done long before the pass is: go on prefetching (a favour: nothing to report if it cannot)
+  const uint64_t t0 = wall_clock64();
+  const uint32_t lane = (uint32_t)work_thread_id() & 63u;
+  uint32_t polls = 0u, p0 = 0u;
+  while (pf < pf_end && !gave_up) {
+    if (prefetch_due(a, pf, lane, p0)) {
       prefetch_filters(*(ConstOp*)(a.ops + ((ConstPrefetch*)a.prefetch)[pf].op), rank, tid);
       ++pf;
+      p0 = 0u;
+      continue;
     }
+    __builtin_amdgcn_s_sleep(8);
+    if ((++polls & 15u) == 0u)
+      gave_up = wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls ||
+                abandoned(a);
   }
   if (tid == 0 && n_done != 0u) __hip_atomic_fetch_add(&a.ctl[kChainCtlDone * kChainCtlStride], n_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
