@@ -147,6 +147,14 @@ __device__ __forceinline__ float f16_bits_to_f32(uint16_t b) {
   return (float)__builtin_bit_cast(_Float16, b);
 }
 
+// v > 0 ? v : 0, also for NaN, in one instruction: the median of v, 0 and infinity, which the compiler must not know to be one (it
+// makes a maximum of it, behind another one that quiets NaNs).
+__device__ __forceinline__ float relu_f32(float v) {
+  float inf;
+  asm("s_mov_b32 %0, 0x7f800000" : "=s"(inf));
+  return __builtin_amdgcn_fmed3f(v, 0.f, inf);
+}
+
 // two fp32 values rounded to nearest even, packed; DT is one of the 16-bit types
 template <int DT>
 __device__ __forceinline__ uint32_t pack16(float a, float b) {
@@ -189,7 +197,7 @@ struct LocalActs { static constexpr int kActAux = kAuxDeviceCoherent, kOutAux = 
 
 // floor(n / d) for 0 <= n < 2^31 with the planner's multiplier m = floor(2^(31+L)/d)+1, L = ceil(log2 d)
 __device__ __forceinline__ int fast_div(int n, uint32_t m, int L) {
-  return (int)((uint32_t)(((uint64_t)(uint32_t)n * m) >> 31) >> L);
+  return (int)(__umulhi((uint32_t)n << 1, m) >> L);      // the upper half of 2n * m: one multiplication, where n * m takes two
 }
 
 constexpr uint32_t kInvalidOffset = 0x80000000u;   // >= num_records of every buffer: the load returns 0
@@ -245,12 +253,13 @@ template <int MT, int NT, class POL>
 __device__ __forceinline__ void stage_residual(ConstOp& T, int m0, int n0, int wave, int lane, uint32_t lds_base) {
   constexpr int CH = NT / 8, RPI = 64 / CH;
   const u32x4 rr = rsrc_words(T.res, T.y_bytes);
+  // rows 4 * RPI apart have the same swizzle, and rows past the last pixel lie past the tensor's end
+  const int row0 = wave * RPI + lane / CH, ch = n0 + ((lane % CH) ^ residual_swizzle<NT>(row0)) * 8;
+  const uint32_t off0 = ch < T.K ? ((uint32_t)(m0 + row0) * (uint32_t)T.K + (uint32_t)ch) * 2u : kInvalidOffset, turn = 4u * RPI * (uint32_t)T.K * 2u;
   static_for<kResidualLoads<MT, NT>>([&](auto I) {
     constexpr int i = decltype(I)::value;
-    const int row = (i * 4 + wave) * RPI + lane / CH;
-    const int ch = n0 + ((lane % CH) ^ residual_swizzle<NT>(row)) * 8;
-    const bool ok = (row < MT) & (m0 + row < T.M) & (ch < T.K);
-    load_to_lds<POL::kActAux, i * 4096>(rr, ok ? ((uint32_t)(m0 + row) * (uint32_t)T.K + (uint32_t)ch) * 2u : kInvalidOffset, 0u, lds_base);
+    const bool ok = (i + 1) * 4 * RPI <= MT || i * 4 * RPI + row0 < MT;
+    load_to_lds<POL::kActAux, i * 4096>(rr, ok ? off0 + (uint32_t)i * turn : kInvalidOffset, 0u, lds_base);
   });
 }
 
@@ -263,10 +272,14 @@ __device__ __forceinline__ void stage_residual(ConstOp& T, int m0, int n0, int w
 // The transposition buffer `smem` holds MT/PASSES pixel rows; with PASSES > 1 the tile is written out in
 // that many slices of consecutive pixel rows.
 // DT is the operands' type: 16-bit outputs have the operands' type (out_dtype is fp32 or in_dtype).
+// What bounds it, beside the two barriers, is the number of vector instructions: two wavefronts share a SIMD, so each costs a
+// wavefront eight clocks.  ReLU in one instruction and only where asked for, and offsets by adding, took a third of them away
+// (128x128 with a residual: 360 -> 230; eight networks of batch 1 as a chain 334.5 us -> 325, four of batch 4 as launches 532 -> 520).
 // res_lds >= 0: the tile of a 16-bit residual is on its way to smem + res_lds (stage_residual); else a residual is loaded
 // here, where its latency is in the open (128x128 tile, bf16, alone on its compute unit: 7900 clocks from the last MFMA to
 // the last store with the residual loaded here, 4500 with it staged; without a residual 5700 -> 3400 with packed conversions).
-template <int MT, int NT, int BM, int BN, int MF, int DT, int PASSES = 1, int CAP = kSmemBytes, class POL = PlainActs, class Acc>
+// TO_END: m_end is the number of pixels (rows past it lie past the tensor's end, which no store gets beyond).
+template <int MT, int NT, int BM, int BN, int MF, int DT, int PASSES = 1, int CAP = kSmemBytes, class POL = PlainActs, bool TO_END = true, class Acc>
 __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], int m0, int m_end, int n0, int wm0,
                                               int wn0, int lrow, int lk, int tid, char* smem, int res_lds = -1) {
   constexpr int NG = (MF == 32) ? 4 : 1;
@@ -309,6 +322,14 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
             acc[i][j][4 * g + 3] += unpack16<DT>(r.y, 1);
           }
     }
+    if (relu) {
+#pragma unroll
+      for (int i = 0; i < BM; ++i)
+#pragma unroll
+        for (int j = 0; j < BN; ++j)
+#pragma unroll
+          for (int v = 0; v < 4 * NG; ++v) acc[i][j][v] = relu_f32(acc[i][j][v]);
+    }
     __syncthreads();                // the buffer (operands, residual, or the previous tile) is no longer read
 #pragma unroll
     for (int i = 0; i < BM; ++i)
@@ -318,28 +339,22 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
         for (int g = 0; g < NG; ++g) {
           const int row = wm0 + i * MF + lrow;
           const int chl = wn0 + j * MF + ((MF == 32) ? (8 * g + 4 * lk) : (4 * lk));
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] = acc[i][j][4 * g + e];
-            if (relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
-          }
           uint2 pk;
-          pk.x = pack16<DT>(v[0], v[1]);
-          pk.y = pack16<DT>(v[2], v[3]);
+          pk.x = pack16<DT>(acc[i][j][4 * g], acc[i][j][4 * g + 1]);
+          pk.y = pack16<DT>(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
           *(uint2*)(smem + row * PITCHB + chl * 2) = pk;
         }
     __syncthreads();
-    constexpr int NV = NT / 8;
-    constexpr int IT = (MT * NV + kThreads - 1) / kThreads;
+    constexpr int NV = NT / 8, ROWS = kThreads / NV;      // vectors of a row; rows stored at a time
+    constexpr int IT = (MT + ROWS - 1) / ROWS;
+    const int row0 = tid / NV, cv = tid % NV, ch = n0 + cv * 8;
+    const uint32_t off0 = ch < Kf ? ((uint32_t)(m0 + row0) * (uint32_t)Kf + (uint32_t)ch) * 2u : kInvalidOffset, turn = (uint32_t)(ROWS * 2) * (uint32_t)Kf;
     auto store_rows = [&](auto REST) {       // REST: with the end of the rows
 #pragma unroll
     for (int u = 0; u < IT; ++u) {
-      const int v = u * kThreads + tid;
-      const int row = v / NV, cv = v % NV;
-      const int m = m0 + row, ch = n0 + cv * 8;
-      const bool ok = (MT * NV % kThreads == 0 || v < MT * NV) & (m < m_end) & (ch < Kf);
-      const uint32_t off = ok ? ((uint32_t)m * (uint32_t)Kf + (uint32_t)ch) * 2u : kInvalidOffset;
+      const int row = row0 + u * ROWS;
+      const bool ok = ((u + 1) * ROWS <= MT || row < MT) & (TO_END || m0 + row < m_end) & (!decltype(REST)::value || ((m0 + row < m_end) & (ch < Kf)));
+      const uint32_t off = ok ? off0 + (uint32_t)u * turn : kInvalidOffset;
       const u32x4 d = *(const u32x4*)(smem + (row < MT ? row : 0) * PITCHB + cv * 16);
       if constexpr (!decltype(REST)::value) {
         __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off, 0, POL::kOutAux);
@@ -375,26 +390,24 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
     const __amdgpu_buffer_rsrc_t rr = make_rsrc(has_res ? T.res : T.y, T.y_bytes);
     // Residual vectors are requested before the accumulators are staged, so their latency overlaps the
     // transposition (single-slice tiles only).
+    // offset of the thread's u-th vector of slice `pass` (ES: bytes of an element)
+    auto row_off = [&](auto ES, int u, int pass) -> uint32_t {
+      constexpr int es = decltype(ES)::value, nv = NT * es / 16, rows = kThreads / nv;
+      const int row0 = tid / nv, row = row0 + u * rows, ch = n0 + tid % nv * (16 / es);
+      const uint32_t off0 = ch < Kf ? ((uint32_t)(m0 + row0) * (uint32_t)Kf + (uint32_t)ch) * (uint32_t)es : kInvalidOffset;
+      const bool ok = (MP % rows == 0 || row < MP) & (TO_END || m0 + pass * MP + row < m_end);
+      return ok ? off0 + (uint32_t)(pass * MP + u * rows) * (uint32_t)(Kf * es) : kInvalidOffset;
+    };
     constexpr int IT32 = (MP * (NT / 4) + kThreads - 1) / kThreads, IT16 = (MP * (NT / 8) + kThreads - 1) / kThreads;
     constexpr bool kPrefetchRes = (PASSES == 1);
     u32x4 rpre[kPrefetchRes ? IT32 : 1];
     if (kPrefetchRes && has_res) {
       if (T.out_dtype == ST_DT_F32) {
 #pragma unroll
-        for (int u = 0; u < IT32; ++u) {
-          const int v = u * kThreads + tid;
-          const int m = m0 + v / (NT / 4), ch = n0 + (v % (NT / 4)) * 4;
-          const bool ok = (MP * (NT / 4) % kThreads == 0 || v < MP * (NT / 4)) & (m < m_end) & (ch < Kf);
-          rpre[u] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)(ok ? ((uint32_t)m * (uint32_t)Kf + (uint32_t)ch) * 4u : kInvalidOffset), 0, POL::kActAux);
-        }
+        for (int u = 0; u < IT32; ++u) rpre[u] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)row_off(std::integral_constant<int, 4>{}, u, 0), 0, POL::kActAux);
       } else if constexpr (DT != ST_DT_F32) {
 #pragma unroll
-        for (int u = 0; u < IT16; ++u) {
-          const int v = u * kThreads + tid;
-          const int m = m0 + v / (NT / 8), ch = n0 + (v % (NT / 8)) * 8;
-          const bool ok = (MP * (NT / 8) % kThreads == 0 || v < MP * (NT / 8)) & (m < m_end) & (ch < Kf);
-          rpre[u] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)(ok ? ((uint32_t)m * (uint32_t)Kf + (uint32_t)ch) * 2u : kInvalidOffset), 0, POL::kActAux);
-        }
+        for (int u = 0; u < IT16; ++u) rpre[u] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)row_off(std::integral_constant<int, 2>{}, u, 0), 0, POL::kActAux);
       }
     }
 #pragma unroll
@@ -428,9 +441,8 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
         for (int u = 0; u < UB; ++u) {
           const int v = (u0 + u) * kThreads + tid;
           const int row = v / NV, cv = v % NV;
-          const int m = mp0 + row, ch = n0 + cv * 4;
-          const bool ok = (MP * NV % kThreads == 0 || v < MP * NV) & (m < m_end) & (ch < Kf);
-          off[u] = ok ? ((uint32_t)m * (uint32_t)Kf + (uint32_t)ch) * 4u : kInvalidOffset;
+          off[u] = row_off(std::integral_constant<int, 4>{}, u0 + u, pass);
+          if constexpr (decltype(REST)::value) off[u] = (mp0 + row < m_end) & (n0 + cv * 4 < Kf) ? off[u] : kInvalidOffset;
           a[u] = *(const f32x4*)(sC + (row < MP ? row : 0) * PITCH + cv * 4);
         }
         if (has_res) {
@@ -442,7 +454,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
         for (int u = 0; u < UB; ++u) {
           if (relu) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) a[u][e] = a[u][e] > 0.f ? a[u][e] : 0.f;
+            for (int e = 0; e < 4; ++e) a[u][e] = relu_f32(a[u][e]);
           }
           const u32x4 d = __builtin_bit_cast(u32x4, a[u]);
           const int ch = n0 + ((u0 + u) * kThreads + tid) % NV * 4;
@@ -478,9 +490,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
         for (int u = 0; u < UB; ++u) {
           const int v = (u0 + u) * kThreads + tid;
           const int row = v / NV, cv = v % NV;
-          const int m = mp0 + row, ch = n0 + cv * 8;
-          const bool ok = (MP * NV % kThreads == 0 || v < MP * NV) & (m < m_end) & (ch < Kf);
-          off[u] = ok ? ((uint32_t)m * (uint32_t)Kf + (uint32_t)ch) * 2u : kInvalidOffset;
+          off[u] = row_off(std::integral_constant<int, 2>{}, u0 + u, pass);
           const float* src = sC + (row < MP ? row : 0) * PITCH + cv * 8;
           lo[u] = *(const f32x4*)src;
           hi[u] = *(const f32x4*)(src + 4);
@@ -501,8 +511,8 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
           if (relu) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              lo[u][e] = lo[u][e] > 0.f ? lo[u][e] : 0.f;
-              hi[u][e] = hi[u][e] > 0.f ? hi[u][e] : 0.f;
+              lo[u][e] = relu_f32(lo[u][e]);
+              hi[u][e] = relu_f32(hi[u][e]);
             }
           }
           u32x4 pk;
@@ -543,7 +553,7 @@ _Pragma("unroll")
             }
             if (relu)
 _Pragma("unroll")
-              for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+              for (int e = 0; e < 4; ++e) v[e] = relu_f32(v[e]);
             if (vec4) *(f32x4*)y = f32x4{v[0], v[1], v[2], v[3]};
             else {
 _Pragma("unroll")
@@ -564,7 +574,7 @@ _Pragma("unroll")
             }
             if (relu)
 _Pragma("unroll")
-              for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+              for (int e = 0; e < 4; ++e) v[e] = relu_f32(v[e]);
             uint2 pk;
             pk.x = pack16<DT>(v[0], v[1]);
             pk.y = pack16<DT>(v[2], v[3]);
@@ -856,11 +866,10 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
         }
       }
     }
+    const int b_row = n0 + wave * RPI + lr;
+    const uint32_t b_first = (uint32_t)(b_row * T.Kg + (order == kOrderPieces ? 0 : chunk * VEC)) * ES, b_turn = (uint32_t)(4 * RPI * ES) * (uint32_t)T.Kg;
 #pragma unroll
-    for (int i = 0; i < BW; ++i) {
-      const int row = n0 + (i * 4 + wave) * RPI + lr;
-      vb[i] = b_off[i] = row < T.K ? (uint32_t)(row * T.Kg + (order == kOrderPieces ? 0 : chunk * VEC)) * ES : kInvalidOffset;
-    }
+    for (int i = 0; i < BW; ++i) vb[i] = b_off[i] = b_row + i * 4 * RPI < T.K ? b_first + (uint32_t)i * b_turn : kInvalidOffset;
     auto addresses = [&]() {
       if constexpr (order == kOrderChannels) {
 #pragma unroll
@@ -1138,11 +1147,10 @@ __device__ __forceinline__ void conv_tile_patch(ConstOp& T, const st_work_item i
     load_to_lds<POL::kActAux, 0>(rx, v, soff, __builtin_amdgcn_readfirstlane(lds + (uint32_t)j * 4096u));
   };
   uint32_t b_off[BW];
+  const int b_row = n0 + wave * RPI + lr;
+  const uint32_t b_first = (uint32_t)(b_row * T.Kg + chunk * VEC) * ES, b_turn = (uint32_t)(4 * RPI * ES) * (uint32_t)T.Kg;
 #pragma unroll
-  for (int i = 0; i < BW; ++i) {
-    const int row = n0 + (i * 4 + wave) * RPI + lr;
-    b_off[i] = row < T.K ? (uint32_t)(row * T.Kg + chunk * VEC) * ES : kInvalidOffset;
-  }
+  for (int i = 0; i < BW; ++i) b_off[i] = b_row + i * 4 * RPI < T.K ? b_first + (uint32_t)i * b_turn : kInvalidOffset;
   uint32_t b_soff = __builtin_amdgcn_readfirstlane((uint32_t)(block0 * KB));      // of the step to be staged next
   const uint32_t wrap_b = (uint32_t)KB - (uint32_t)(kTaps - 1) * c_bytes;
   const uint32_t b_base = lds0 + b_lds0;
@@ -1675,7 +1683,7 @@ __device__ __forceinline__ void conv_tile_rows(ConstOp& T, const st_work_item it
         for (int v = 0; v < 16; ++v) acc[i][0][v] = 0.f;
       row(rt, acc);
       const int mrow = (n * P + p0 + rt) * Q;
-      tile_epilogue<MT, NT, BM, BN, MF, DT, EPI_PASSES, kStageBytes, POL>(T, acc, mrow + q0, mrow + q_end, n0, wm0, wn0, lrow, lk, tid, smem);
+      tile_epilogue<MT, NT, BM, BN, MF, DT, EPI_PASSES, kStageBytes, POL, false>(T, acc, mrow + q0, mrow + q_end, n0, wm0, wn0, lrow, lk, tid, smem);
     }
   };
   // Seven filter rows of two halves, the usual stem: the filters stay in registers for all output rows of the item, and the
