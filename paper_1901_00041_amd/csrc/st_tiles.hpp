@@ -201,6 +201,9 @@ __device__ __forceinline__ int fast_div(int n, uint32_t m, int L) {
 }
 
 constexpr uint32_t kInvalidOffset = 0x80000000u;   // >= num_records of every buffer: the load returns 0
+// Output rows of this many filters or more are stored by element: the offset of a tile's last row (at most 127 rows of 4-byte
+// elements past an offset below 2^31) must not pass 2^32, where it would come round into the tensor.
+constexpr int kWideFilters = 1 << 22;
 
 // ---- memory to LDS without registers -------------------------------------------------------------
 // One instruction moves 16 bytes per lane from a buffer straight into LDS: lane l's bytes land at lds_base + 16 * l
@@ -286,7 +289,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
   const bool relu = (T.epilogue & ST_EPI_RELU) != 0u;
   const bool has_res = (T.epilogue & ST_EPI_RESIDUAL) != 0u;
   const int Kf = T.K;
-  const bool vec4 = (Kf & 3) == 0, whole = (Kf & 7) == 0;
+  const bool vec4 = (Kf & 3) == 0, narrow = Kf < kWideFilters, whole = (Kf & 7) == 0 && narrow;
   // Any number of filters: a row of the output is still mostly whole vectors (at element-aligned addresses); what is left of
   // it is stored element by element, by the lanes that hold it.  (With stores per lane and element instead, four of 2 bytes for
   // every four filters of a pixel, a 128x64 tile of 201 filters spent 9900 clocks after its last MFMA.)  Not with a
@@ -296,7 +299,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
   const bool rest = kAnyFilters && !whole && n0 + NT > Kf;       // this tile holds the end of the rows
   bool done16 = false;
   if constexpr (DT != ST_DT_F32) {
-   if (T.out_dtype != ST_DT_F32 && (has_res ? (Kf & 7) == 0 && res_lds >= 0 : whole || kAnyFilters)) {
+   if (T.out_dtype != ST_DT_F32 && (has_res ? whole && res_lds >= 0 : whole || (kAnyFilters && narrow))) {
     // 16-bit output: the residual (if any, staged in LDS) is added to the accumulators, ReLU and the rounding are applied
     // to them, and the transposition buffer holds the finished 16-bit values, [pixel][filter], the whole tile at once.
     // Every lane then moves 16 bytes of one output row from LDS to memory.
@@ -378,7 +381,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
    }
   }
   if (done16) return;
-  if (whole || (kAnyFilters && !has_res && T.out_dtype == ST_DT_F32)) {
+  if (whole || (kAnyFilters && narrow && !has_res && T.out_dtype == ST_DT_F32)) {
     // Transpose through LDS: accumulators go to an fp32 [pixel][filter] tile, then every lane handles 16
     // bytes of one output row, so residual loads and output stores are whole contiguous rows.
     constexpr int PITCH = NT + 4;   // floats; the pad keeps the 16-byte writes of 16 pixels on distinct banks
