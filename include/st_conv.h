@@ -339,8 +339,9 @@ st_status st_chain_run(st_chain* chain, void* hip_stream);
  * a max-pool entry leaves [1] and [2] at 0; slot [7] = ticks of the 100 MHz clock the entry waited for its dependency,
  * 0 where a launch holds one stage).  Synchronous diagnostic. */
 st_status st_chain_run_profiled(st_chain* chain, void* hip_stream, uint64_t* stamps, int64_t capacity);
-/* Waits for the device, then *aborted = 1 if any run since the last call gave up on a dependency wait, or if the
- * last run did not complete every work item (an XCD that received no workgroups); the chain is reset. */
+/* Waits for the device, then *aborted = 1 if any run since the last call gave up on a dependency wait or did not
+ * complete every work item (an XCD that received no workgroups); the chain is reset.  The outputs of that run and of
+ * the runs after it are then not to be relied on (later runs start from what it left of the split-K counters). */
 st_status st_chain_aborted(st_chain* chain, int32_t* aborted);
 /* The wall-clock limit of a dependency wait in microseconds (0 = give up at once unless already satisfied: a test
  * hook that makes every kernel still exit normally).  No effect where a pass is a launch per stage: nothing waits

@@ -42,7 +42,6 @@ struct st_chain {
   int workgroups = 0;                        // planned size of the persistent launch (what it would be, with a launch per stage)
   int launch_workgroups = 0;                 // 0 = workgroups; else a smaller size asked for by the caller
   unsigned run_parity = 0;                   // control block the next run uses
-  int64_t runs = 0;
   uint32_t run_number = 0;                   // number of the most recent run (per-item completion flags hold it)
   // device
   char* d_arena = nullptr;
@@ -518,7 +517,6 @@ static st_status chain_launch(st_chain* c, void* stream, uint64_t* prof_dev) {
                                   c->d_ctl[p ^ 1u], c->ctl_slots, c->d_item_flags, c->run_number, c->spin_limit_ticks, c->flags,
                                   c->launch_workgroups > 0 ? c->launch_workgroups : c->workgroups, stream, prof_dev));
   c->run_parity = p ^ 1u;
-  ++c->runs;
   return ST_OK;
 }
 
@@ -549,17 +547,19 @@ extern "C" st_status st_chain_aborted(st_chain* chain, int32_t* aborted) {
   if (chain->host_only || chain->items.empty()) return ST_OK;
   ST_HIP(hipDeviceSynchronize());
   if (chain->stage_launches) return ST_OK;           // nothing waits inside a launch, nothing can give up
-  uint32_t flag[2] = {0u, 0u}, done = 0u;
-  for (int b = 0; b < 2; ++b) ST_HIP(hipMemcpy(&flag[b], chain->d_ctl[b] + kChainCtlAbort * kChainCtlStride, 4, hipMemcpyDeviceToHost));
-  // the block of the most recent run still holds its count of completed work items (the other one was cleared by it)
-  const unsigned last = chain->run_parity ^ 1u;
-  ST_HIP(hipMemcpy(&done, chain->d_ctl[last] + kChainCtlDone * kChainCtlStride, 4, hipMemcpyDeviceToHost));
-  const bool incomplete = chain->runs > 0 && done != (uint32_t)chain->items.size();
-  if (flag[0] | flag[1] | (incomplete ? 1u : 0u)) {
+  bool lost = false;
+  for (const uint32_t* ctl : chain->d_ctl) {
+    uint32_t words[kChainCtlHead * kChainCtlStride];
+    ST_HIP(hipMemcpy(words, ctl, sizeof(words), hipMemcpyDeviceToHost));
+    // (the counts wrap at 2^32, all alike)
+    lost = lost || words[kChainCtlLost * kChainCtlStride] != 0u ||
+           words[kChainCtlDone * kChainCtlStride] != words[kChainCtlStarted * kChainCtlStride] * (uint32_t)chain->items.size();
+  }
+  if (lost) {
     // an abandoned pass has left its queue head, its sequence counters and some split-K arrival counters anywhere
     ST_HIP(hipMemset(chain->d_ctl[0], 0, ((size_t)chain->ctl_slots * kChainCtlStride + kChainRankWords) * 4 * 2));
     if (chain->counters_bytes) ST_HIP(hipMemset(chain->d_counters, 0, chain->counters_bytes));
-    chain->runs = 0;
+    ST_HIP(hipDeviceSynchronize());                  // before a run on a stream that does not wait for this one
     *aborted = 1;
   }
   return ST_OK;

@@ -97,6 +97,12 @@ __device__ __forceinline__ bool abandoned(const ChainArgs& a) {
   return __builtin_amdgcn_readfirstlane(__hip_atomic_load(&a.ctl[kChainCtlAbort * kChainCtlStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0u;
 }
 
+// Abandons the pass: the flag that its workgroups look at, and the one that outlives it.
+__device__ __forceinline__ void abandon(const ChainArgs& a) {
+  __hip_atomic_store(&a.ctl[kChainCtlLost * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(&a.ctl[kChainCtlAbort * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Whether the stage before prefetch entry pf's has started, i.e. the stage before that one is complete.
 __device__ __forceinline__ bool prefetch_due(const ChainArgs& a, uint32_t pf, uint32_t lane, uint32_t& c0) {
   ConstPrefetch& p = ((ConstPrefetch*)a.prefetch)[pf];
@@ -130,9 +136,11 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
   uint32_t* s_msg = (uint32_t*)smem;      // between work items only: read, then a barrier, before a tile or the next message
   const int tid = threadIdx.x;
   if (blockIdx.x == 0) {
-    // the control block of the NEXT run (runs alternate between two blocks; the stream orders them)
+    // the control block of the NEXT run (runs alternate between two blocks; the stream orders them), but for the slots that are
+    // st_chain_aborted's to clear
     for (uint32_t i = (uint32_t)tid; i < a.ctl_slots; i += kThreads)
-      __hip_atomic_store(&a.ctl_other[i * kChainCtlStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (i == (uint32_t)kChainCtlAbort || i >= (uint32_t)kChainCtlHead) __hip_atomic_store(&a.ctl_other[i * kChainCtlStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 64) __hip_atomic_fetch_add(&a.ctl[kChainCtlStarted * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (uint32_t i = (uint32_t)tid; i < (uint32_t)kChainRankWords; i += kThreads)
       __hip_atomic_store(&a.ctl_other[a.ctl_slots * kChainCtlStride + i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -145,7 +153,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
     if (xcc >= a.n_queues) {
       // an XCD this launch was not planned for: its workgroups must not touch any entry (completion flags are only
       // valid inside one XCD); the pass is reported as abandoned
-      if (tid == 0) __hip_atomic_store(&a.ctl[kChainCtlAbort * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid == 0) abandon(a);
       return;
     }
     if (tid == 0) {
@@ -246,7 +254,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
             if ((++polls & 15u) != 0u || polls <= (uint32_t)kChainGraceLooks) { __builtin_amdgcn_s_sleep(1); continue; }
             if (abandoned(a)) { gave_up = true; break; }
             if (wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls) {
-              if (lane == 0u) __hip_atomic_store(&a.ctl[kChainCtlAbort * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              if (lane == 0u) abandon(a);
               gave_up = true;
               break;
             }

@@ -134,7 +134,9 @@ int launch_conv_kernel(const TenantDev* tenants_dev, const st_work_item* items_d
 // Persistent chain launch (st_chain.hip).  ctl / ctl_other: this run's and the next run's control block.  A block is
 // ctl_slots slots of kChainCtlStride 32-bit words (256 bytes) with one live word each, so that the words hundreds of
 // workgroups poll and bump sit in different cache lines and memory channels: slot kChainCtlAbort the abort flag,
-// kChainCtlDone the count of completed work items, kChainCtlHead the head of the one queue, or with queues per XCD
+// kChainCtlLost whether any run on the block was abandoned, kChainCtlDone the completed work items of all runs on it and
+// kChainCtlStarted the number of these runs (a run clears the other block for the next one, all but these three, which only
+// st_chain_aborted clears), kChainCtlHead the head of the one queue, or with queues per XCD
 // kChainCtlHead + 2x + k the number of exclusive (k = 0) / shared (k = 1) columns of XCD x drawn so far,
 // kChainCtlSeq + s the completion counter of sequence s; kChainRankWords dense words follow the slots (how many
 // workgroups have arrived on each compute unit).  n_queues is 1 (entries [0, n_items) claimed one by one) or
@@ -142,7 +144,7 @@ int launch_conv_kernel(const TenantDev* tenants_dev, const st_work_item* items_d
 // columns are x * 2 * kChainColumns + [0, kChainColumns), its shared ones follow).  item_flags / run_number: the
 // per-item completion flags and this run's number (queues per XCD only; else nullptr / anything).
 constexpr int kChainCtlStride = 64;
-constexpr int kChainCtlAbort = 1, kChainCtlDone = 2, kChainCtlHead = 4, kChainCtlSeq = 4 + 2 * kNumXCDs;
+constexpr int kChainCtlLost = 0, kChainCtlAbort = 1, kChainCtlDone = 2, kChainCtlStarted = 3, kChainCtlHead = 4, kChainCtlSeq = 4 + 2 * kNumXCDs;
 constexpr int kChainRankWords = kNumXCDs * 256;   // arrival counts per (XCD, compute unit key), dense, after the slots
 constexpr int kChainColumns = kNumCUs / kNumXCDs; // exclusive columns per XCD (one per compute unit), and as many shared
 constexpr uint32_t kChainFlagLocalFlags = 4u;     // completion travels through per-item flags in the XCD's own L2
