@@ -97,10 +97,12 @@ __device__ __forceinline__ bool abandoned(const ChainArgs& a) {
   return __builtin_amdgcn_readfirstlane(__hip_atomic_load(&a.ctl[kChainCtlAbort * kChainCtlStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0u;
 }
 
-// Abandons the pass: the flag that its workgroups look at, and the one that outlives it.
+// A wavefront gives the pass up: the flag that the pass's workgroups look at, the one that outlives it, and one off the count of
+// completed items, since wavefront 0 of the workgroup may call the item complete all the same (it can see the last flag just then).
 __device__ __forceinline__ void abandon(const ChainArgs& a) {
   __hip_atomic_store(&a.ctl[kChainCtlLost * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(&a.ctl[kChainCtlAbort * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_fetch_sub(&a.ctl[kChainCtlDone * kChainCtlStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Whether the stage before prefetch entry pf's has started, i.e. the stage before that one is complete.
@@ -238,7 +240,8 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
         // the wait and the tile (one wavefront looking for all: eight networks of batch 1 346 us, of batch 8 1107; each for
         // itself 335 and 1095).  In between, filters of coming stages may be due (pf).  A wavefront that gives up goes on as if
         // the wait had ended, so that the barriers of all four stay in step: every access is checked against the tensors' sizes,
-        // and what is computed is lost with the pass, which the abort flag reports; later waits see that flag and end at once.
+        // and what is computed is lost with the pass, which the abort flag reports; a later wait of its that is not over at once ends
+        // when the flag is next looked at, after a few looks (knowing that it gave up costs every wait: 325 us -> 333).
         // One queue: wavefront 0 looks for all; four looking at a counter at the memory side slow each other down (670 us -> 719).
         const uint64_t t0 = wall_clock64();
         uint32_t polls = 0u, p0 = 0u;
@@ -252,8 +255,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
             }
             // the abort flag and the clock are looked at on every 16th poll (every few microseconds) after the first looks
             if ((++polls & 15u) != 0u || polls <= (uint32_t)kChainGraceLooks) { __builtin_amdgcn_s_sleep(1); continue; }
-            if (abandoned(a)) { gave_up = true; break; }
-            if (wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls) {
+            if (__builtin_expect(abandoned(a) || wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls, 0)) {
               if (lane == 0u) abandon(a);
               gave_up = true;
               break;
