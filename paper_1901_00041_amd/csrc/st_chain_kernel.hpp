@@ -264,6 +264,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
           }
         }
         if (!COLUMNS) __syncthreads();
+        else asm volatile("" ::: "memory");   // no barrier, but the compiler may not move a load of the tile's before the looks either
         waited = wall_clock64() - t0;
         // No cache is invalidated here: everything an entry reads that this launch wrote (activations, residuals,
         // split-K partial tiles) is read with device-scope loads, and everything else did not change.
