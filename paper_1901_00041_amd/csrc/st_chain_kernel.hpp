@@ -39,7 +39,9 @@
 namespace st {
 
 constexpr int kChainGraceLooks = 24;             // looks at a dependency (0.3 us each) before the abort flag and the clock are looked at
-constexpr uint32_t kChainMaxPolls = 1u << 22;   // a poll takes a microsecond or so: seconds, far beyond any real wait
+// Looks after which a wait of at most `limit` ticks of 10 ns ends whatever the clock says.  A look takes 0.2 us at the least (a load
+// from the L2 and the pause), so one per 80 ns of the limit cannot end it early.
+__device__ __forceinline__ uint32_t max_polls(uint32_t limit) { return (limit >> 3) + 64u; }
 
 // Nothing counts as invariant inside the loop over work items, which has stores, atomics and barriers in it: what never
 // changes while a launch runs is read through the constant address space.
@@ -255,7 +257,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
             }
             // the abort flag and the clock are looked at on every 16th poll (every few microseconds) after the first looks
             if ((++polls & 15u) != 0u || polls <= (uint32_t)kChainGraceLooks) { __builtin_amdgcn_s_sleep(1); continue; }
-            if (__builtin_expect(abandoned(a) || wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls, 0)) {
+            if (__builtin_expect(abandoned(a) || wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > max_polls(a.spin_limit), 0)) {
               if (lane == 0u) abandon(a);
               gave_up = true;
               break;
@@ -314,7 +316,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
     }
     __builtin_amdgcn_s_sleep(8);
     if ((++polls & 15u) == 0u)
-      gave_up = wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > kChainMaxPolls ||
+      gave_up = wall_clock64() - t0 > (uint64_t)a.spin_limit || polls > max_polls(a.spin_limit) ||
                 abandoned(a);
   }
   if (tid == 0 && n_done != 0u) __hip_atomic_fetch_add(&a.ctl[kChainCtlDone * kChainCtlStride], n_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

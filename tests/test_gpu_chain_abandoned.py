@@ -71,3 +71,24 @@ def test_an_incomplete_pass_without_waits_is_reported_after_later_passes(later):
     for i, t in enumerate(tenants):
         helpers.check_tenant(t, f"tenant {i}")
     assert not chain.aborted()
+
+
+def test_a_wait_lasts_as_long_as_its_limit():
+    """The count of looks that also bounds a wait is far above what fits into the limit: with one workgroup per compute unit nobody
+    draws the shared columns, and their dependants wait for the whole limit."""
+    import time
+    import torch
+    stack, want = _stack(0)
+    chain = stack.chain
+    assert chain.info().workgroups == 512
+    chain.set_workgroups(256)
+    chain.set_wait_limit_us(2_000_000)
+    torch.cuda.synchronize()
+    t0 = time.monotonic()
+    stack.run("fused_chain")
+    torch.cuda.synchronize()
+    assert 2.0 <= time.monotonic() - t0 < 10.0
+    assert chain.aborted()
+    chain.set_workgroups(0)
+    chain.set_wait_limit_us(100000)
+    _right_again(stack, want)
