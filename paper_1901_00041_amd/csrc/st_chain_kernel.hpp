@@ -284,7 +284,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
       run_item<HAS, std::conditional_t<COLUMNS, LocalActs, CoherentActs>>(T, it, smem, prof);
       // Completion.  With one queue outputs were stored write-through; channel counts that are not a multiple of 8 take an
       // epilogue with plain stores and need the release fence (write-back of the L2).
-      if (!COLUMNS && (it.reserved & kFormMask) != kFormPool && ((T.K & 7) != 0 || T.K >= kWideFilters)) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if (!COLUMNS && (it.reserved & kFormMask) != kFormPool && (T.K & 7) != 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       __builtin_amdgcn_s_waitcnt(0);          // every store of this thread has been acknowledged
       __syncthreads();                        // ... of every thread; also: smem and s_msg are free again
       if (!gave_up) ++n_done;

@@ -201,9 +201,13 @@ __device__ __forceinline__ int fast_div(int n, uint32_t m, int L) {
 }
 
 constexpr uint32_t kInvalidOffset = 0x80000000u;   // >= num_records of every buffer: the load returns 0
-// Output rows of this many filters or more are stored by element: the offset of a tile's last row (at most 127 rows of 4-byte
-// elements past an offset below 2^31) must not pass 2^32, where it would come round into the tensor.
-constexpr int kWideFilters = 1 << 22;
+// Offsets of a tile's output and residual rows, each the one before plus a launch constant.  Rows past the last pixel are not compared
+// with it but left to the tensor's end, so the sum stops at kPastEnd (a tensor is shorter than 2^31 bytes) instead of coming
+// round into the tensor, however long the rows; the addition that saturates is one instruction like the other.
+constexpr int kPastEnd = 0x7fffffff;
+__device__ __forceinline__ int next_row(int off, int turn) { return __builtin_elementwise_add_sat(off, turn); }
+template <int BYTES>                                             // BYTES times the number of filters (uniform)
+__device__ __forceinline__ int row_turn(int filters) { return filters <= kPastEnd / BYTES ? filters * BYTES : kPastEnd; }
 
 // ---- memory to LDS without registers -------------------------------------------------------------
 // One instruction moves 16 bytes per lane from a buffer straight into LDS: lane l's bytes land at lds_base + 16 * l
@@ -256,13 +260,14 @@ template <int MT, int NT, class POL>
 __device__ __forceinline__ void stage_residual(ConstOp& T, int m0, int n0, int wave, int lane, uint32_t lds_base) {
   constexpr int CH = NT / 8, RPI = 64 / CH;
   const u32x4 rr = rsrc_words(T.res, T.y_bytes);
-  // rows 4 * RPI apart have the same swizzle, and rows past the last pixel lie past the tensor's end
-  const int row0 = wave * RPI + lane / CH, ch = n0 + ((lane % CH) ^ residual_swizzle<NT>(row0)) * 8;
-  const uint32_t off0 = ch < T.K ? ((uint32_t)(m0 + row0) * (uint32_t)T.K + (uint32_t)ch) * 2u : kInvalidOffset, turn = 4u * RPI * (uint32_t)T.K * 2u;
+  // rows 4 * RPI apart have the same swizzle
+  const int row0 = wave * RPI + lane / CH, ch = n0 + ((lane % CH) ^ residual_swizzle<NT>(row0)) * 8, turn = row_turn<4 * RPI * 2>(T.K);
+  int off = (ch < T.K) & (m0 + row0 < T.M) ? (int)(((uint32_t)(m0 + row0) * (uint32_t)T.K + (uint32_t)ch) * 2u) : kPastEnd;
   static_for<kResidualLoads<MT, NT>>([&](auto I) {
     constexpr int i = decltype(I)::value;
     const bool ok = (i + 1) * 4 * RPI <= MT || i * 4 * RPI + row0 < MT;
-    load_to_lds<POL::kActAux, i * 4096>(rr, ok ? off0 + (uint32_t)i * turn : kInvalidOffset, 0u, lds_base);
+    load_to_lds<POL::kActAux, i * 4096>(rr, (uint32_t)(ok ? off : kPastEnd), 0u, lds_base);
+    off = next_row(off, turn);
   });
 }
 
@@ -289,7 +294,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
   const bool relu = (T.epilogue & ST_EPI_RELU) != 0u;
   const bool has_res = (T.epilogue & ST_EPI_RESIDUAL) != 0u;
   const int Kf = T.K;
-  const bool vec4 = (Kf & 3) == 0, narrow = Kf < kWideFilters, whole = (Kf & 7) == 0 && narrow;
+  const bool vec4 = (Kf & 3) == 0, whole = (Kf & 7) == 0;
   // Any number of filters: a row of the output is still mostly whole vectors (at element-aligned addresses); what is left of
   // it is stored element by element, by the lanes that hold it.  (With stores per lane and element instead, four of 2 bytes for
   // every four filters of a pixel, a 128x64 tile of 201 filters spent 9900 clocks after its last MFMA.)  Not with a
@@ -299,7 +304,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
   const bool rest = kAnyFilters && !whole && n0 + NT > Kf;       // this tile holds the end of the rows
   bool done16 = false;
   if constexpr (DT != ST_DT_F32) {
-   if (T.out_dtype != ST_DT_F32 && (has_res ? whole && res_lds >= 0 : whole || (kAnyFilters && narrow))) {
+   if (T.out_dtype != ST_DT_F32 && (has_res ? whole && res_lds >= 0 : whole || kAnyFilters)) {
     // 16-bit output: the residual (if any, staged in LDS) is added to the accumulators, ReLU and the rounding are applied
     // to them, and the transposition buffer holds the finished 16-bit values, [pixel][filter], the whole tile at once.
     // Every lane then moves 16 bytes of one output row from LDS to memory.
@@ -350,24 +355,24 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
     __syncthreads();
     constexpr int NV = NT / 8, ROWS = kThreads / NV;      // vectors of a row; rows stored at a time
     constexpr int IT = (MT + ROWS - 1) / ROWS;
-    const int row0 = tid / NV, cv = tid % NV, ch = n0 + cv * 8;
-    const uint32_t off0 = ch < Kf ? ((uint32_t)(m0 + row0) * (uint32_t)Kf + (uint32_t)ch) * 2u : kInvalidOffset, turn = (uint32_t)(ROWS * 2) * (uint32_t)Kf;
+    const int row0 = tid / NV, cv = tid % NV, ch = n0 + cv * 8, turn = row_turn<ROWS * 2>(Kf);
     auto store_rows = [&](auto REST) {       // REST: with the end of the rows
+    int at = (ch < Kf) & (m0 + row0 < m_end) ? (int)(((uint32_t)(m0 + row0) * (uint32_t)Kf + (uint32_t)ch) * 2u) : kPastEnd;
 #pragma unroll
-    for (int u = 0; u < IT; ++u) {
+    for (int u = 0; u < IT; ++u, at = next_row(at, turn)) {
       const int row = row0 + u * ROWS;
       const bool ok = ((u + 1) * ROWS <= MT || row < MT) & (TO_END || m0 + row < m_end) & (!decltype(REST)::value || ((m0 + row < m_end) & (ch < Kf)));
-      const uint32_t off = ok ? off0 + (uint32_t)u * turn : kInvalidOffset;
+      const int off = ok ? at : kPastEnd;
       const u32x4 d = *(const u32x4*)(smem + (row < MT ? row : 0) * PITCHB + cv * 16);
       if constexpr (!decltype(REST)::value) {
-        __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off, 0, POL::kOutAux);
+        __builtin_amdgcn_raw_buffer_store_b128(d, ry, off, 0, POL::kOutAux);
       } else if (ok) {
         if (ch + 8 <= Kf) {
-          __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off, 0, POL::kOutAux);
+          __builtin_amdgcn_raw_buffer_store_b128(d, ry, off, 0, POL::kOutAux);
         } else {
 #pragma unroll
           for (int e = 0; e < 7; ++e)
-            if (ch + e < Kf) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(d[e >> 1] >> (16 * (e & 1))), ry, (int)(off + 2u * e), 0, POL::kOutAux);
+            if (ch + e < Kf) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(d[e >> 1] >> (16 * (e & 1))), ry, off + 2 * e, 0, POL::kOutAux);
         }
       }
     }
@@ -381,7 +386,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
    }
   }
   if (done16) return;
-  if (whole || (kAnyFilters && narrow && !has_res && T.out_dtype == ST_DT_F32)) {
+  if (whole || (kAnyFilters && !has_res && T.out_dtype == ST_DT_F32)) {
     // Transpose through LDS: accumulators go to an fp32 [pixel][filter] tile, then every lane handles 16
     // bytes of one output row, so residual loads and output stores are whole contiguous rows.
     constexpr int PITCH = NT + 4;   // floats; the pad keeps the 16-byte writes of 16 pixels on distinct banks
@@ -393,24 +398,36 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
     const __amdgpu_buffer_rsrc_t rr = make_rsrc(has_res ? T.res : T.y, T.y_bytes);
     // Residual vectors are requested before the accumulators are staged, so their latency overlaps the
     // transposition (single-slice tiles only).
-    // offset of the thread's u-th vector of slice `pass` (ES: bytes of an element)
-    auto row_off = [&](auto ES, int u, int pass) -> uint32_t {
-      constexpr int es = decltype(ES)::value, nv = NT * es / 16, rows = kThreads / nv;
-      const int row0 = tid / nv, row = row0 + u * rows, ch = n0 + tid % nv * (16 / es);
-      const uint32_t off0 = ch < Kf ? ((uint32_t)(m0 + row0) * (uint32_t)Kf + (uint32_t)ch) * (uint32_t)es : kInvalidOffset;
-      const bool ok = (MP % rows == 0 || row < MP) & (TO_END || m0 + pass * MP + row < m_end);
-      return ok ? off0 + (uint32_t)(pass * MP + u * rows) * (uint32_t)(Kf * es) : kInvalidOffset;
+    // Offset of the thread's first vector of slice `pass`, and from one of its rows to the next (ES: bytes of an element).
+    auto first_row = [&](auto ES, int pass) -> int {
+      constexpr int es = decltype(ES)::value, nv = NT * es / 16;
+      const int m = m0 + tid / nv, ch = n0 + tid % nv * (16 / es);
+      const uint32_t off0 = ((uint32_t)m * (uint32_t)Kf + (uint32_t)ch) * (uint32_t)es;
+      return (ch < Kf) & (m + pass * MP < m_end) ? (int)(off0 + (uint32_t)(pass * MP) * (uint32_t)(Kf * es)) : kPastEnd;
     };
+    auto turn_of = [&](auto ES) { return row_turn<kThreads / (NT * decltype(ES)::value / 16) * decltype(ES)::value>(Kf); };
+    // ... of its u-th row, which `at` has come to
+    auto row_off = [&](auto ES, int u, int pass, int at) -> int {
+      constexpr int nv = NT * decltype(ES)::value / 16, rows = kThreads / nv;
+      const int row = tid / nv + u * rows;
+      return (MP % rows == 0 || row < MP) & (TO_END || m0 + pass * MP + row < m_end) ? at : kPastEnd;
+    };
+    constexpr std::integral_constant<int, 4> k4{};
+    constexpr std::integral_constant<int, 2> k2{};
     constexpr int IT32 = (MP * (NT / 4) + kThreads - 1) / kThreads, IT16 = (MP * (NT / 8) + kThreads - 1) / kThreads;
     constexpr bool kPrefetchRes = (PASSES == 1);
     u32x4 rpre[kPrefetchRes ? IT32 : 1];
     if (kPrefetchRes && has_res) {
       if (T.out_dtype == ST_DT_F32) {
+        const int turn = turn_of(k4);
+        int at = first_row(k4, 0);
 #pragma unroll
-        for (int u = 0; u < IT32; ++u) rpre[u] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)row_off(std::integral_constant<int, 4>{}, u, 0), 0, POL::kActAux);
+        for (int u = 0; u < IT32; ++u, at = next_row(at, turn)) rpre[u] = __builtin_amdgcn_raw_buffer_load_b128(rr, row_off(k4, u, 0, at), 0, POL::kActAux);
       } else if constexpr (DT != ST_DT_F32) {
+        const int turn = turn_of(k2);
+        int at = first_row(k2, 0);
 #pragma unroll
-        for (int u = 0; u < IT16; ++u) rpre[u] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)row_off(std::integral_constant<int, 2>{}, u, 0), 0, POL::kActAux);
+        for (int u = 0; u < IT16; ++u, at = next_row(at, turn)) rpre[u] = __builtin_amdgcn_raw_buffer_load_b128(rr, row_off(k2, u, 0, at), 0, POL::kActAux);
       }
     }
 #pragma unroll
@@ -435,23 +452,25 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
       constexpr int NV = NT / 4;
       constexpr int IT = (MP * NV + kThreads - 1) / kThreads;
       constexpr int UB = IT < 4 ? IT : 4;        // vectors in flight per thread (bounds register use)
+      const int turn = turn_of(k4);
       auto store_rows = [&](auto REST) {
+      int at = first_row(k4, pass);
 #pragma unroll
       for (int u0 = 0; u0 < IT; u0 += UB) {
         f32x4 a[UB];
-        uint32_t off[UB];
+        int off[UB];
 #pragma unroll
-        for (int u = 0; u < UB; ++u) {
+        for (int u = 0; u < UB; ++u, at = next_row(at, turn)) {
           const int v = (u0 + u) * kThreads + tid;
           const int row = v / NV, cv = v % NV;
-          off[u] = row_off(std::integral_constant<int, 4>{}, u0 + u, pass);
-          if constexpr (decltype(REST)::value) off[u] = (mp0 + row < m_end) & (n0 + cv * 4 < Kf) ? off[u] : kInvalidOffset;
+          off[u] = row_off(k4, u0 + u, pass, at);
+          if constexpr (decltype(REST)::value) off[u] = (mp0 + row < m_end) & (n0 + cv * 4 < Kf) ? off[u] : kPastEnd;
           a[u] = *(const f32x4*)(sC + (row < MP ? row : 0) * PITCH + cv * 4);
         }
         if (has_res) {
 #pragma unroll
           for (int u = 0; u < UB; ++u)
-            a[u] += __builtin_bit_cast(f32x4, kPrefetchRes ? rpre[u0 + u] : __builtin_amdgcn_raw_buffer_load_b128(rr, (int)off[u], 0, POL::kActAux));
+            a[u] += __builtin_bit_cast(f32x4, kPrefetchRes ? rpre[u0 + u] : __builtin_amdgcn_raw_buffer_load_b128(rr, off[u], 0, POL::kActAux));
         }
 #pragma unroll
         for (int u = 0; u < UB; ++u) {
@@ -462,14 +481,14 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
           const u32x4 d = __builtin_bit_cast(u32x4, a[u]);
           const int ch = n0 + ((u0 + u) * kThreads + tid) % NV * 4;
           if constexpr (!decltype(REST)::value) {
-            __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off[u], 0, POL::kOutAux);
-          } else if (off[u] != kInvalidOffset) {
+            __builtin_amdgcn_raw_buffer_store_b128(d, ry, off[u], 0, POL::kOutAux);
+          } else if (off[u] != kPastEnd) {
             if (ch + 4 <= Kf) {
-              __builtin_amdgcn_raw_buffer_store_b128(d, ry, (int)off[u], 0, POL::kOutAux);
+              __builtin_amdgcn_raw_buffer_store_b128(d, ry, off[u], 0, POL::kOutAux);
             } else {
 #pragma unroll
               for (int e = 0; e < 3; ++e)
-                if (ch + e < Kf) __builtin_amdgcn_raw_buffer_store_b32(d[e], ry, (int)(off[u] + 4u * e), 0, POL::kOutAux);
+                if (ch + e < Kf) __builtin_amdgcn_raw_buffer_store_b32(d[e], ry, off[u] + 4 * e, 0, POL::kOutAux);
             }
           }
         }
@@ -485,15 +504,17 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
       constexpr int NV = NT / 8;
       constexpr int IT = (MP * NV + kThreads - 1) / kThreads;
       constexpr int UB = IT < 4 ? IT : 4;
+      const int turn = turn_of(k2);
+      int at = first_row(k2, pass);
 #pragma unroll
       for (int u0 = 0; u0 < IT; u0 += UB) {
         f32x4 lo[UB], hi[UB];
-        uint32_t off[UB];
+        int off[UB];
 #pragma unroll
-        for (int u = 0; u < UB; ++u) {
+        for (int u = 0; u < UB; ++u, at = next_row(at, turn)) {
           const int v = (u0 + u) * kThreads + tid;
           const int row = v / NV, cv = v % NV;
-          off[u] = row_off(std::integral_constant<int, 2>{}, u0 + u, pass);
+          off[u] = row_off(k2, u0 + u, pass, at);
           const float* src = sC + (row < MP ? row : 0) * PITCH + cv * 8;
           lo[u] = *(const f32x4*)src;
           hi[u] = *(const f32x4*)(src + 4);
@@ -501,7 +522,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
         if (has_res) {
 #pragma unroll
           for (int u = 0; u < UB; ++u) {
-            const u32x4 r = kPrefetchRes ? rpre[u0 + u] : __builtin_amdgcn_raw_buffer_load_b128(rr, (int)off[u], 0, POL::kActAux);
+            const u32x4 r = kPrefetchRes ? rpre[u0 + u] : __builtin_amdgcn_raw_buffer_load_b128(rr, off[u], 0, POL::kActAux);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               lo[u][e] += unpack16<DT>(r[e >> 1], e & 1);
@@ -524,7 +545,7 @@ __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], in
             pk[e] = pack16<DT>(lo[u][2 * e], lo[u][2 * e + 1]);
             pk[2 + e] = pack16<DT>(hi[u][2 * e], hi[u][2 * e + 1]);
           }
-          __builtin_amdgcn_raw_buffer_store_b128(pk, ry, (int)off[u], 0, POL::kOutAux);
+          __builtin_amdgcn_raw_buffer_store_b128(pk, ry, off[u], 0, POL::kOutAux);
         }
       }
     }
