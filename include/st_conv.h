@@ -284,8 +284,8 @@ void st_pipeline_destroy(st_pipeline* pipeline);
  * column in use to become resident eventually (on a GPU the launch has to itself all are at once; a caller that shares
  * the GPU with long-running kernels of its own and sees passes abandoned should plan with chain_queues = 1).  Every
  * dependency wait
- * is bounded by a wall-clock limit (default 100 ms) and a poll count, after which the launch abandons the pass:
- * every workgroup leaves, outputs are incomplete, and st_chain_aborted reports it.  Same ops + same inputs =>
+ * is bounded by a wall-clock limit (default 100 ms) and a count of looks that is never reached before it, after which the launch abandons
+ * the pass: it ends without further waits of that length, outputs are incomplete or wrong, and st_chain_aborted reports it.  Same ops + same inputs =>
  * outputs bitwise identical from run to run, and bitwise identical to running the stages one st_conv_run at a
  * time with the same tiles. */
 typedef enum { ST_OP_CONV = 0, ST_OP_MAXPOOL = 1 } st_op_kind;

@@ -240,7 +240,7 @@ __global__ __launch_bounds__(kThreads, 2) void st_chain_kernel(const ChainArgs a
         };
         // Columns: every wavefront looks for itself, so that neither a message through LDS nor a barrier stands between the flag that ends
         // the wait and the tile (one wavefront looking for all: eight networks of batch 1 346 us, of batch 8 1107; each for
-        // itself 335 and 1095).  In between, filters of coming stages may be due (pf).  A wavefront that gives up goes on as if
+        // itself 335 and 1095; how long a wavefront pauses between looks, 64 or 128 clocks, changes neither).  In between, filters of coming stages may be due (pf).  A wavefront that gives up goes on as if
         // the wait had ended, so that the barriers of all four stay in step: every access is checked against the tensors' sizes,
         // and what is computed is lost with the pass, which the abort flag reports; a later wait of its that is not over at once ends
         // when the flag is next looked at, after a few looks (knowing that it gave up costs every wait: 325 us -> 333).

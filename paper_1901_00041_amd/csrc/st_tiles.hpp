@@ -284,8 +284,9 @@ __device__ __forceinline__ void stage_residual(ConstOp& T, int m0, int n0, int w
 // wavefront eight clocks.  ReLU in one instruction and only where asked for, and offsets by adding, took a third of them away
 // (128x128 with a residual: 360 -> 230; eight networks of batch 1 as a chain 334.5 us -> 325, four of batch 4 as launches 532 -> 520).
 // res_lds >= 0: the tile of a 16-bit residual is on its way to smem + res_lds (stage_residual); else a residual is loaded
-// here, where its latency is in the open (128x128 tile, bf16, alone on its compute unit: 7900 clocks from the last MFMA to
-// the last store with the residual loaded here, 4500 with it staged; without a residual 5700 -> 3400 with packed conversions).
+// here, where its latency is in the open (128x128 tile, bf16, alone on its compute unit, clocks from the last MFMA to the last store:
+// 7900 with the residual loaded here, 4500 with it staged, 3070 since a third of the instructions went; without a residual 5700,
+// 3400 with packed conversions, now 1840; ReLU 240 more).
 // TO_END: m_end is the number of pixels (rows past it lie past the tensor's end, which no store gets beyond).
 template <int MT, int NT, int BM, int BN, int MF, int DT, int PASSES = 1, int CAP = kSmemBytes, class POL = PlainActs, bool TO_END = true, class Acc>
 __device__ __forceinline__ void tile_epilogue(ConstOp& T, Acc (&acc)[BM][BN], int m0, int m_end, int n0, int wm0,
