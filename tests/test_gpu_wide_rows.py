@@ -59,7 +59,7 @@ def test_other_operand_types(dtype, out, residual, K):
     _run_plan(desc, dict(tile_cfg=2), y, want, keep)
 
 
-@pytest.mark.parametrize("K", [1 << 24, (1 << 24) + 3])              # whole vectors, and the end of the rows by element behind them
+@pytest.mark.parametrize("K", [1 << 25, (1 << 25) + 3])              # whole vectors, and the end of the rows by element behind them
 @pytest.mark.parametrize("C", [9, 3])                                # in pieces, and gathered: the kernel for everything
 @pytest.mark.parametrize("out", ["bf16", "f32"])
 def test_any_channel_count(K, C, out):
@@ -73,7 +73,7 @@ def test_any_channel_count(K, C, out):
 @pytest.mark.parametrize("residual", [False, True])
 def test_row_tile(out, residual):
     """Several output rows and slices of a row: a row of outputs ends inside the tensor, where only the comparison keeps stores out."""
-    K = 1 << 22
+    K = 1 << 23
     print(f"wide rows: row tile, out={out} residual={residual}", flush=True)
     desc, y, want, keep = _layer(K, 3, 5, 40, 3, 2, 1, "bf16", out, residual)
     plan = _run_plan(desc, dict(tile_cfg=7), y, want, keep)
@@ -89,7 +89,7 @@ def test_split_reduction():
 
 
 @pytest.mark.parametrize("chain_queues", [1, 2])
-@pytest.mark.parametrize("K", [1 << 22, (1 << 22) + 4])              # rows stored as vectors, and by element (one queue: behind a release fence)
+@pytest.mark.parametrize("K", [1 << 25, (1 << 25) + 4])              # rows stored as vectors, and by element (one queue: behind a release fence)
 @pytest.mark.parametrize("out", ["bf16", "f32"])
 def test_a_chain_reads_them_back(out, K, chain_queues):
     """Two layers in one launch, the second with the long rows that the first has written as its residual: read on other compute units,
@@ -101,7 +101,8 @@ def test_a_chain_reads_them_back(out, K, chain_queues):
     want2 = want2 + want
     second = sc.make_desc(1, 16, 1, 3, K, 1, 1, 1, 0, "bf16", out, x2, w2, z, y, sc.ST_EPI_RESIDUAL)
     chain = sc.Chain([sc.make_chain_op(sc.ST_OP_CONV, 0, 0, desc), sc.make_chain_op(sc.ST_OP_CONV, 0, 1, second)],
-                     sc.plan_opts(chain_queues=chain_queues, tile_cfg=4), keep=[keep, x2, w2, y, z])
+                     sc.plan_opts(chain_queues=chain_queues, tile_cfg=1), keep=[keep, x2, w2, y, z])
+    chain.set_wait_limit_us(2_000_000)                              # 262144 tiles on one XCD before the second layer's last may start
     for _ in range(3):
         y.fill_(77.0)
         z.fill_(55.0)
