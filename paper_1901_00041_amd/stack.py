@@ -14,6 +14,7 @@ builds the descriptors and issues the run calls.
 """
 from __future__ import annotations
 
+import dataclasses
 import time
 from typing import List
 
@@ -32,6 +33,30 @@ from . import synth
 STACK_SLOTS = 300
 
 
+def _reuse_buffers(steps: List[synth.Step]) -> List[synth.Step]:
+    """The steps on as few bytes as they can do with: a block adds to its shortcut in place, the stages' block outputs
+    alternate between two buffers, one of them the stem's.  The network's output has a buffer of its own, exactly as large
+    as it.
+    Fewer bytes stay in the caches longer.  us per pass with two buffers for the blocks of a stage and one for the projections, and so:
+    8 tenants of batch 1 as a chain 327 -> 322, of batch 8 1074 -> 1048 (a buffer for every step, which the chain's tests use:
+    346 and 1098); 4 of batch 4 as layer launches 526 -> 522, or 522 -> 475 where passes over the same tensors follow each other
+    and find what the memory-side cache kept (492 in place alone)."""
+    at, out = {0: 0}, []
+    for st in steps:
+        src, res = at[st.src], at[st.res] if st.res is not None else None
+        dst = st.dst
+        if res is not None:
+            dst = res
+        elif st.name.endswith(".proj"):
+            dst = 1 if src == 6 else 6
+        at[st.dst] = dst
+        if st.pool_after:
+            at[st.pool_dst] = st.pool_dst
+        out.append(dataclasses.replace(st, src=src, dst=dst, res=res))
+    out[-1] = dataclasses.replace(out[-1], dst=max(at.values()) + 1)
+    return out
+
+
 class ResNetStack:
     def __init__(self, n_tenants: int = 8, cfg: int = 5, batch: int = 1, image: int = 224, seeded_weights: bool = True,
                  plan_opts=None, co_schedule: bool = True, unique_buffers: bool = False):
@@ -44,7 +69,6 @@ class ResNetStack:
         if unique_buffers:
             # every step writes a buffer of its own (nothing is overwritten within a pass), so that after ONE launch
             # over the whole network every layer's inputs and outputs can still be read back
-            import dataclasses
             latest, fresh, steps = {0: 0}, 100, []
             for st in self.steps:
                 src, res = latest[st.src], (latest[st.res] if st.res is not None else None)
@@ -57,6 +81,8 @@ class ResNetStack:
                 if st.pool_after:
                     latest[st.pool_dst] = pool_dst
             self.steps = steps
+        else:
+            self.steps = _reuse_buffers(self.steps)
         dev = "cuda"
         # activation buffers: one tensor per buffer id holding every tenant (tenant-major), sized for the
         # largest use of that id
