@@ -16,7 +16,7 @@ from __future__ import annotations
 
 import dataclasses
 import time
-from typing import List
+from typing import List, Optional
 
 import numpy as np
 
@@ -33,10 +33,45 @@ from . import synth
 STACK_SLOTS = 300
 
 
+XCDS = 8
+# A chain is laid out per XCD, as one launch, from as many sequences on as there are XCDs; fewer run as a launch per stage, in
+# lock-step.  So fewer tenants than that have their batches divided, each part a sequence of its own.  us per pass at
+# 224x224, whole and divided: 4 tenants of batch 2 370 -> 303, of batch 4 524 -> 413, of batch 8 775 -> 607; 1 of batch 8 344 -> 293;
+# 2 of batch 8 447 -> 385; 6 of batch 4 735 -> 597; at 128x128 4 of batch 4 331 -> 264.  Eight tenants gain nothing (of batch
+# 2, 4, 8: 422, 628, 1077 whole, 437, 641, 1060 in two parts each): they stay whole.
+# How many parts: an XCD works through its sequences' images in a time that grows with the images and, since every sequence reads
+# the filters for itself and pays its own dependencies, with the sequences, by about what 0.85 images of 224x224 cost (6 tenants of
+# batch 4 in 2 or 4 parts, at most 4 or 3 images and 2 or 3 sequences on an XCD: 625 or 597 us at 224x224, 364 or 422 at 128x128).
+# Where the XCD with the most images has over one and a half times the average, lock-step is no slower (2 tenants of batch
+# 5 363 us whole, 386 divided; 3 of batch 3 374 and 401; but 3 of batch 4, at 1.33 times, 442 and 417).
+SEQUENCE_COST = 0.85
+
+
+def chain_parts(n_tenants: int, batch: int, image: int = 224) -> int:
+    """Sequences that build_chain divides a tenant's batch into."""
+    if n_tenants >= XCDS or n_tenants * batch < XCDS:
+        return 1
+    best, parts = None, 1
+    for k in range(-(-XCDS // n_tenants), min(batch, 4 * XCDS // n_tenants) + 1):
+        load = [0] * XCDS
+        for seq in range(n_tenants * k):
+            load[seq % XCDS] += _share(batch, k)[seq // n_tenants]
+        cost = max(load) * (image / 224.0) ** 2 + SEQUENCE_COST * -(-n_tenants * k // XCDS)
+        if max(load) * XCDS <= 1.5 * n_tenants * batch and (best is None or cost < best):
+            best, parts = cost, k
+    return parts
+
+
+def _share(batch: int, parts: int) -> List[int]:
+    """Images of each part."""
+    return [batch // parts + (j < batch % parts) for j in range(parts)]
+
+
 def _reuse_buffers(steps: List[synth.Step]) -> List[synth.Step]:
     """The steps on as few bytes as they can do with: a block adds to its shortcut in place, the stages' block outputs
     alternate between two buffers, one of them the stem's.  The network's output has a buffer of its own, exactly as large
-    as it.
+    as it: one tensor over the batch, also where parts of the batch run as sequences of their own (build_chain) and keep apart in every
+    other buffer.
     Fewer bytes stay in the caches longer.  us per pass with two buffers for the blocks of a stage and one for the projections, and so:
     8 tenants of batch 1 as a chain 327 -> 322, of batch 8 1074 -> 1048 (a buffer for every step, which the chain's tests use:
     346 and 1098); 4 of batch 4 as layer launches 526 -> 522, or 522 -> 475 where passes over the same tensors follow each other
@@ -64,7 +99,7 @@ class ResNetStack:
         self.torch = torch
         if plan_opts is None:
             plan_opts = sc.plan_opts(target_items=STACK_SLOTS)
-        self.n_tenants, self.cfg = n_tenants, cfg
+        self.n_tenants, self.cfg, self.batch = n_tenants, cfg, batch
         self.steps: List[synth.Step] = synth.resnet50_steps(batch, image)
         if unique_buffers:
             # every step writes a buffer of its own (nothing is overwritten within a pass), so that after ONE launch
@@ -312,11 +347,19 @@ class ResNetStack:
             anchor.wait_event(done)
 
     # ---- the whole pass as one persistent launch --------------------------------------------------------
-    def build_chain(self, chain_queues: int = 0) -> None:
-        """One chain over every tenant's whole network: tenant t is sequence t; a layer group is a stage (the
-        projection conv and the block's first 1x1 conv share one), the max-pool after the stem a stage of its own.
-        Planned with the stack's own options, so every stage gets the tiles of the layer-by-layer plans."""
+    def build_chain(self, chain_queues: int = 0, parts: Optional[int] = None) -> None:
+        """One chain over every tenant's whole network: a layer group is a stage (the projection conv and the block's first
+        1x1 conv share one), the max-pool after the stem a stage of its own.  Planned with the stack's own options.
+        A tenant is one sequence, or `parts` of them, each with its share of the batch (default: chain_parts).  Undivided,
+        every stage gets the tiles of the layer-by-layer plans.  A part's images keep to their own share of every activation
+        buffer, so that parts may be at different depths; between network input and output the buffers of a divided chain
+        then hold a tenant's images at equal distances, not one behind the other."""
         po = self._plan_opts
+        if parts is None:
+            whole_gpu = self.torch.cuda.get_device_properties(self.buf[0].device).multi_processor_count >= 32 * XCDS
+            parts = chain_parts(self.n_tenants, self.batch, self.steps[0].shape.H) if chain_queues == 0 and whole_gpu else 1
+        share = _share(self.batch, parts)
+        self.chain_parts = parts
         opts = sc.plan_opts(tile_cfg=po.tile_cfg, split_k=po.split_k, target_items=po.target_items,
                             rows_per_tile=po.rows_per_tile, chain_queues=chain_queues)
         ops = []
@@ -325,11 +368,23 @@ class ResNetStack:
                 st = self.steps[i]
                 s = st.shape
                 for t in range(self.n_tenants):
-                    ops.append(sc.make_chain_op(sc.ST_OP_CONV, t, 2 * gi, self._step_descs[i][t]))
-                    if st.pool_after:
-                        p = (s.P + 2 - 3) // 2 + 1
-                        d = sc.make_desc(s.N, s.K, s.P, s.Q, s.K, 3, 3, 2, 1, "bf16", "bf16", self.buf[st.dst][t], None, self.buf[st.pool_dst][t])
-                        ops.append(sc.make_chain_op(sc.ST_OP_MAXPOOL, t, 2 * gi + 1, d))
+                    whole = self._step_descs[i][t]
+                    for j, n in enumerate(share):
+                        seq, first = j * self.n_tenants + t, sum(share[:j])
+
+                        def at(buf_id):          # address of the part's first image in a tenant's buffer
+                            b = self.buf[buf_id]
+                            return b.data_ptr() + (t * self.batch + first) * (b.shape[1] // self.batch) * b.element_size()
+                        d = whole
+                        if parts > 1:
+                            d = sc.st_conv_desc.from_buffer_copy(whole)
+                            d.N, d.x, d.y = n, at(st.src), at(st.dst)
+                            if st.res is not None:
+                                d.residual = at(st.res)
+                        ops.append(sc.make_chain_op(sc.ST_OP_CONV, seq, 2 * gi, d))
+                        if st.pool_after:
+                            d = sc.make_desc(n, s.K, s.P, s.Q, s.K, 3, 3, 2, 1, "bf16", "bf16", at(st.dst), None, at(st.pool_dst))
+                            ops.append(sc.make_chain_op(sc.ST_OP_MAXPOOL, seq, 2 * gi + 1, d))
         self.chain = sc.Chain(ops, opts, keep=[self.buf, self.weights])
         self.chain_ops = ops
 
@@ -337,6 +392,11 @@ class ResNetStack:
         if policy == "fused_chain":
             if getattr(self, "chain", None) is None:
                 self.build_chain()
+            if self.chain_parts > 1 and self.torch.cuda.is_current_stream_capturing():
+                # a graph replays launches with the arguments they were captured with; a persistent launch needs a new run number
+                # each time, launches per layer do not
+                self.run("fused", stream)
+                return
             self.chain.run(stream)
             return
         if policy.startswith("fused_groups"):
