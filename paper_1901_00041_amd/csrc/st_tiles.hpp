@@ -652,31 +652,46 @@ __device__ __forceinline__ bool split_k_reduce(ConstOp& T, const st_work_item it
       if (prof && tid == 0) prof[6] = wall_clock64();
       return false;
     }
-    // Sum the slices in index order.  Loads are issued in batches (GB groups x SB slices) so that the
-    // device-coherent reads, each a trip to memory, overlap; slices past split_k read as zero.
+    // Sum the slices in index order.  Loads are issued in batches (GB groups x SB slices) so that the device-coherent reads, each
+    // a trip to memory, overlap.  Tiles of 32x32 blocks load only the slices there are, and take the own one from the registers
+    // it is still in: a load that is out of range still costs the compute unit's 16 clocks, and 64x64 in three slices had 24 of
+    // 32 to spare (20 fp32 layers 18.37 us -> 18.15).  The small tiles have few loads, and the branches cost more than they
+    // do where the slices come from memory (four 3x3 layers of batch 1, 16x64 in four: 7.21 us, 7.36 with branches), not where
+    // they come from the L2 (eight networks of batch 1 as a chain 321.3 -> 319.6).
     constexpr int NGRP = BM * BN * NG;
     constexpr int GB = NGRP < 4 ? NGRP : 4;
     constexpr int SB = (NGRP > 4) ? 4 : 8;   // at most 32 partial vectors (128 registers) in flight
     static_assert(NGRP % GB == 0, "group batching");
-    const int split = T.split_k;
+    constexpr bool kPick = MF == 32 || POL::kOneL2;
+    const int split = T.split_k, mine = (int)it.k_split_idx;
 #pragma unroll
     for (int g0 = 0; g0 < NGRP; g0 += GB) {
       f32x4 sum[GB];
 #pragma unroll
       for (int gg = 0; gg < GB; ++gg) sum[gg] = f32x4{0.f, 0.f, 0.f, 0.f};
       for (int s0 = 0; s0 < split; s0 += SB) {
-        u32x4 part[SB][GB];
+        f32x4 part[SB][GB];
 #pragma unroll
-        for (int ss = 0; ss < SB; ++ss)
+        for (int ss = 0; ss < SB; ++ss) {
+          if (!kPick || (s0 + ss < split && s0 + ss != mine)) {
 #pragma unroll
-          for (int gg = 0; gg < GB; ++gg) {
-            const uint32_t voff = (s0 + ss < split) ? (uint32_t)(((g0 + gg) * kThreads + tid) * 16) : kInvalidOffset;
-            part[ss][gg] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (s0 + ss) * (int)kTileBytes, kAuxDeviceCoherent);
+            for (int gg = 0; gg < GB; ++gg) {
+              const uint32_t voff = kPick || s0 + ss < split ? (uint32_t)(((g0 + gg) * kThreads + tid) * 16) : kInvalidOffset;
+              part[ss][gg] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (s0 + ss) * (int)kTileBytes, kAuxDeviceCoherent));
+            }
+          } else {
+#pragma unroll
+            for (int gg = 0; gg < GB; ++gg) {
+              const int grp = g0 + gg, i = grp / (BN * NG), j = (grp / NG) % BN, g = grp % NG;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) part[ss][gg][e] = s0 + ss == mine ? acc[i][j][4 * g + e] : 0.f;
+            }
           }
+        }
 #pragma unroll
         for (int ss = 0; ss < SB; ++ss)
 #pragma unroll
-          for (int gg = 0; gg < GB; ++gg) sum[gg] += __builtin_bit_cast(f32x4, part[ss][gg]);
+          for (int gg = 0; gg < GB; ++gg) sum[gg] += part[ss][gg];
       }
 #pragma unroll
       for (int gg = 0; gg < GB; ++gg) {
