@@ -657,12 +657,13 @@ __device__ __forceinline__ bool split_k_reduce(ConstOp& T, const st_work_item it
     // it is still in: a load that is out of range still costs the compute unit's 16 clocks, and 64x64 in three slices had 24 of
     // 32 to spare (20 fp32 layers 18.37 us -> 18.15).  The small tiles have few loads, and the branches cost more than they
     // do where the slices come from memory (four 3x3 layers of batch 1, 16x64 in four: 7.21 us, 7.36 with branches), not where
-    // they come from the L2 (eight networks of batch 1 as a chain 321.3 -> 319.6).
+    // they come from the L2 (eight networks of batch 1 as a chain 321.3 -> 319.6).  Nor in the kernel for everything, which is short of
+    // scalar registers (24 layers off every round number 26.35 us -> 26.55).
     constexpr int NGRP = BM * BN * NG;
     constexpr int GB = NGRP < 4 ? NGRP : 4;
     constexpr int SB = (NGRP > 4) ? 4 : 8;   // at most 32 partial vectors (128 registers) in flight
     static_assert(NGRP % GB == 0, "group batching");
-    constexpr bool kPick = MF == 32 || POL::kOneL2;
+    constexpr bool kPick = (MF == 32 && !POL::kAnyFilters) || POL::kOneL2;
     const int split = T.split_k, mine = (int)it.k_split_idx;
 #pragma unroll
     for (int g0 = 0; g0 < NGRP; g0 += GB) {
@@ -1155,7 +1156,6 @@ __device__ __forceinline__ void conv_tile_patch(ConstOp& T, const st_work_item i
   typedef typename MMA::Acc Acc;
   static_assert(ES == 2 && (KB == 128 || KB == 256) && NT % (4 * RPI) == 0 && kTaps == 9 && ST < kTaps, "patch tile shape");
 
-  asm volatile("" ::"s"(T.patch_rows), "s"(T.patch_loads), "s"(T.patch_blocks));      // with the fields of every tile
   tile_fields_loaded(T);
   const int tid = work_thread_id();
   if (prof && tid == 0) stamp_start(prof);
