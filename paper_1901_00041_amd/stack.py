@@ -35,10 +35,10 @@ STACK_SLOTS = 300
 
 XCDS = 8
 # A chain is laid out per XCD, as one launch, from as many sequences on as there are XCDs; fewer run as a launch per stage, in
-# lock-step.  So fewer tenants than that have their batches divided, each part a sequence of its own.  us per pass at
-# 224x224, whole and divided: 4 tenants of batch 2 370 -> 303, of batch 4 524 -> 413, of batch 8 775 -> 607; 1 of batch 8 344 -> 293;
-# 2 of batch 8 447 -> 385; 6 of batch 4 735 -> 597; at 128x128 4 of batch 4 331 -> 264.  Eight tenants gain nothing (of batch
-# 2, 4, 8: 422, 628, 1077 whole, 437, 641, 1060 in two parts each): they stay whole.
+# lock-step.  Where a caller allows it (build_chain), fewer tenants than that have their batches divided, each part a sequence of
+# its own.  us per pass at 224x224, whole and divided: 4 tenants of batch 2 370 -> 303, of batch 4 524 -> 413, of batch 8 775 -> 607;
+# 1 of batch 8 344 -> 293; 2 of batch 8 447 -> 385; 6 of batch 4 735 -> 597; at 128x128 4 of batch 4 331 -> 264.  Eight tenants stay
+# whole: batches of 2 and 4 lose (422 and 628 whole, 437 and 641 in two parts each), of 8 gain 2 % (1077, 1060).
 # How many parts: an XCD works through its sequences' images in a time that grows with the images and, since every sequence reads
 # the filters for itself and pays its own dependencies, with the sequences, by about what 0.85 images of 224x224 cost (6 tenants of
 # batch 4 in 2 or 4 parts, at most 4 or 3 images and 2 or 3 sequences on an XCD: 625 or 597 us at 224x224, 364 or 422 at 128x128).
@@ -48,7 +48,8 @@ SEQUENCE_COST = 0.85
 
 
 def chain_parts(n_tenants: int, batch: int, image: int = 224) -> int:
-    """Sequences that build_chain divides a tenant's batch into."""
+    """Sequences into which build_chain divides a tenant's batch where the choice is left to it.  Measured for batches up to 8;
+    larger ones follow the same rule."""
     if n_tenants >= XCDS or n_tenants * batch < XCDS:
         return 1
     best, parts = None, 1
@@ -347,19 +348,32 @@ class ResNetStack:
             anchor.wait_event(done)
 
     # ---- the whole pass as one persistent launch --------------------------------------------------------
-    def build_chain(self, chain_queues: int = 0, parts: Optional[int] = None) -> None:
+    def build_chain(self, chain_queues: int = 0, parts: Optional[int] = 1) -> None:
         """One chain over every tenant's whole network: a layer group is a stage (the projection conv and the block's first
-        1x1 conv share one), the max-pool after the stem a stage of its own.  Planned with the stack's own options.
-        A tenant is one sequence, or `parts` of them, each with its share of the batch (default: chain_parts).  Undivided,
-        every stage gets the tiles of the layer-by-layer plans.  A part's images keep to their own share of every activation
-        buffer, so that parts may be at different depths; between network input and output the buffers of a divided chain
-        then hold a tenant's images at equal distances, not one behind the other."""
-        po = self._plan_opts
+        1x1 conv share one), the max-pool after the stem a stage of its own.  Planned with the stack's own options, so every stage
+        of an undivided chain gets the tiles, and the bits, of the layer-by-layer plans.
+
+        A tenant is one sequence, or `parts` of them, each with its share of the batch; None leaves the number to chain_parts.
+        Eight sequences or more are ONE persistent launch, which needs the GPU to itself: its workgroups wait for each other, and
+        a pass whose workgroups do not all become resident (beside another such launch or a long kernel, on a stream with a
+        compute-unit mask) is given up after 100 ms with outputs that are incomplete, which only chain.aborted() tells.  Fewer are a
+        launch per stage, which asks for nothing and is never given up.  So dividing fewer than eight tenants is the
+        caller's choice.  It also changes tiles and splits, hence the order of an output's fp32 sum.
+
+        In a divided chain each part keeps to its own share of every activation buffer, so that parts may be at different depths:
+        a part's images lie one behind the other from the start of its share on, the shares at distances that
+        follow the buffer's size and not the layer's (network input and output are whole tensors all the same)."""
         if parts is None:
-            whole_gpu = self.torch.cuda.get_device_properties(self.buf[0].device).multi_processor_count >= 32 * XCDS
-            parts = chain_parts(self.n_tenants, self.batch, self.steps[0].shape.H) if chain_queues == 0 and whole_gpu else 1
+            parts = chain_parts(self.n_tenants, self.batch, self.steps[0].shape.H) if chain_queues == 0 else 1
+            self._build_chain(chain_queues, parts)
+            if parts == 1 or self.chain.info().n_queues > 1:
+                return
+            parts = 1          # not a whole device: as a launch per stage, parts are only more and smaller layers
+        self._build_chain(chain_queues, parts)
+
+    def _build_chain(self, chain_queues: int, parts: int) -> None:
+        po = self._plan_opts
         share = _share(self.batch, parts)
-        self.chain_parts = parts
         opts = sc.plan_opts(tile_cfg=po.tile_cfg, split_k=po.split_k, target_items=po.target_items,
                             rows_per_tile=po.rows_per_tile, chain_queues=chain_queues)
         ops = []
@@ -386,7 +400,7 @@ class ResNetStack:
                             d = sc.make_desc(n, s.K, s.P, s.Q, s.K, 3, 3, 2, 1, "bf16", "bf16", at(st.dst), None, at(st.pool_dst))
                             ops.append(sc.make_chain_op(sc.ST_OP_MAXPOOL, seq, 2 * gi + 1, d))
         self.chain = sc.Chain(ops, opts, keep=[self.buf, self.weights])
-        self.chain_ops = ops
+        self.chain_ops, self.chain_parts = ops, parts
 
     def run(self, policy: str = "fused", stream=None) -> None:
         if policy == "fused_chain":
