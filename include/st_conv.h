@@ -333,7 +333,9 @@ typedef struct st_chain st_chain; /* opaque */
 st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const st_plan_opts* opts, st_chain** out_chain);
 /* One pass: one launch on hip_stream, or one per stage (chain_queues = 0 with fewer than 8 sequences, or on a device that
  * is not a whole 8-XCD one).  Asynchronous, allocation-free.  Two runs of one chain must not overlap in time (queue them
- * on one stream). */
+ * on one stream).  While hip_stream is being captured, the pass goes into the graph, with the wait limit and the workgroups of
+ * that moment, as one launch and a small one ahead of it (or as the launches per stage): it can be replayed any number
+ * of times, with other runs of the chain in between, and a replay is a run like any other, to st_chain_aborted too. */
 st_status st_chain_run(st_chain* chain, void* hip_stream);
 /* The same with in-kernel time stamps per queue entry (HOST buffer of 8 uint64 per entry, as st_conv_run_profiled;
  * a max-pool entry leaves [1] and [2] at 0; slot [7] = ticks of the 100 MHz clock the entry waited for its dependency,

@@ -42,12 +42,14 @@ struct st_chain {
   int workgroups = 0;                        // planned size of the persistent launch (what it would be, with a launch per stage)
   int launch_workgroups = 0;                 // 0 = workgroups; else a smaller size asked for by the caller
   unsigned run_parity = 0;                   // control block the next run uses
-  uint32_t run_number = 0;                   // number of the most recent run (per-item completion flags hold it)
+  uint32_t run_number = 0;                   // number of the most recent run that was not captured (per-item completion flags hold it)
   // device
   char* d_arena = nullptr;
   TenantDev* d_ops = nullptr;
   st_work_item* d_items = nullptr;
-  uint32_t* d_ctl[2] = {nullptr, nullptr};
+  // Control blocks: [0] and [1] for ordinary runs in turn, [2] for captured ones; [3] nobody reads (what a captured run clears
+  // in place of the next run's).
+  uint32_t* d_ctl[kChainCtlBlocks] = {};
   char* d_counters = nullptr;                // split-K arrival counters of all sequences
   size_t counters_bytes = 0;
   uint32_t* d_item_flags = nullptr;          // one completion flag per work item (queue per XCD only)
@@ -426,7 +428,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
       }
     }
     if (status == ST_OK) {
-      // arena: [op table][queue][control block x2, persistent launch only][split-K counters][completion flags][column boundaries][prefetch list][entries' dependencies][split-K partial tiles]
+      // arena: [op table][queue][control blocks, persistent launch only][split-K counters][completion flags][column boundaries][prefetch list][entries' dependencies][split-K partial tiles]
       auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
       c->ctl_slots = (uint32_t)(kChainCtlSeq + c->n_sequences);
       int64_t ws_total = 0, ct_total = 0;
@@ -439,7 +441,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
       const size_t off_items = up((size_t)n_ops * sizeof(TenantDev));
       const size_t off_ctl = off_items + up(c->items.size() * sizeof(st_work_item));
       const size_t ctl_words = c->stage_launches ? 0 : (size_t)c->ctl_slots * kChainCtlStride + kChainRankWords;   // one control block
-      const size_t off_ct = off_ctl + up(ctl_words * 4 * 2);
+      const size_t off_ct = off_ctl + up(ctl_words * 4 * kChainCtlBlocks);
       const size_t off_flags = off_ct + up((size_t)ct_total * 4);
       const size_t off_cols = off_flags + up(c->n_queues > 1 ? c->items.size() * 4 : 0);
       const size_t off_pf = off_cols + up(c->colbegin.size() * 4);
@@ -466,8 +468,7 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
           c->d_ops = (TenantDev*)c->d_arena;
           c->d_items = (st_work_item*)(c->d_arena + off_items);
           if (!c->stage_launches) {
-            c->d_ctl[0] = (uint32_t*)(c->d_arena + off_ctl);
-            c->d_ctl[1] = c->d_ctl[0] + ctl_words;
+            for (int b = 0; b < kChainCtlBlocks; ++b) c->d_ctl[b] = (uint32_t*)(c->d_arena + off_ctl) + (size_t)b * ctl_words;
           }
           c->d_counters = c->d_arena + off_ct;
           c->counters_bytes = (size_t)ct_total * 4;
@@ -496,6 +497,18 @@ extern "C" st_status st_chain_plan(const st_chain_op* ops, int32_t n_ops, const 
   return ST_OK;
 }
 
+// Whether what is queued on the stream goes into a graph.  (The default stream cannot be captured; asking about it fails while
+// another one is.)
+static bool capturing(void* stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (!stream) return false;
+  if (hipStreamIsCapturing((hipStream_t)stream, &status) != hipSuccess) {
+    (void)hipGetLastError();          // the launch says what is wrong with the stream
+    return false;
+  }
+  return status != hipStreamCaptureStatusNone;
+}
+
 static st_status chain_launch(st_chain* c, void* stream, uint64_t* prof_dev) {
   if (!c) return fail(ST_ERR_INVALID_ARG, "chain is NULL");
   if (c->host_only) return fail(ST_ERR_UNSUPPORTED, "chain was built host-only and cannot run");
@@ -507,15 +520,25 @@ static st_status chain_launch(st_chain* c, void* stream, uint64_t* prof_dev) {
     }
     return ST_OK;
   }
+  auto launch = [&](uint32_t* ctl, uint32_t* ctl_other, uint32_t run_number) {
+    return (hipError_t)launch_chain(c->kernel_needs, c->d_ops, c->d_items, (uint32_t)c->items.size(), c->d_colbegin, c->d_deps, (uint32_t)c->n_queues, c->d_prefetch, c->prefetch_begin, ctl,
+                                    ctl_other, c->ctl_slots, c->d_item_flags, run_number, c->spin_limit_ticks, c->flags,
+                                    c->launch_workgroups > 0 ? c->launch_workgroups : c->workgroups, stream, prof_dev);
+  };
+  if (capturing(stream)) {
+    // A graph replays the launch with these arguments, any number of times and between other runs: a control block and a run
+    // number that no other run uses, made new by a launch ahead of it, and nothing of the host's numbering moves.
+    ST_HIP((hipError_t)launch_chain_reset(c->d_ctl[2], c->ctl_slots, c->d_item_flags, (uint32_t)(c->item_flags_bytes / 4), stream));
+    ST_HIP(launch(c->d_ctl[2], c->d_ctl[3], kChainCapturedRun));
+    return ST_OK;
+  }
   const unsigned p = c->run_parity;
-  if (++c->run_number == 0u) {
-    // the run numbers have wrapped: forget every flag of the old numbering (a fill kernel, so a capture may hold it)
+  if (++c->run_number == kChainCapturedRun) {
+    // the run numbers have wrapped: forget every flag of the old numbering
     if (c->d_item_flags) ST_HIP((hipError_t)launch_zero(c->d_item_flags, (int64_t)((c->item_flags_bytes + 15) & ~(size_t)15), stream));
     c->run_number = 1u;
   }
-  ST_HIP((hipError_t)launch_chain(c->kernel_needs, c->d_ops, c->d_items, (uint32_t)c->items.size(), c->d_colbegin, c->d_deps, (uint32_t)c->n_queues, c->d_prefetch, c->prefetch_begin, c->d_ctl[p],
-                                  c->d_ctl[p ^ 1u], c->ctl_slots, c->d_item_flags, c->run_number, c->spin_limit_ticks, c->flags,
-                                  c->launch_workgroups > 0 ? c->launch_workgroups : c->workgroups, stream, prof_dev));
+  ST_HIP(launch(c->d_ctl[p], c->d_ctl[p ^ 1u], c->run_number));
   c->run_parity = p ^ 1u;
   return ST_OK;
 }
@@ -548,7 +571,8 @@ extern "C" st_status st_chain_aborted(st_chain* chain, int32_t* aborted) {
   ST_HIP(hipDeviceSynchronize());
   if (chain->stage_launches) return ST_OK;           // nothing waits inside a launch, nothing can give up
   bool lost = false;
-  for (const uint32_t* ctl : chain->d_ctl) {
+  for (int b = 0; b < 3; ++b) {
+    const uint32_t* ctl = chain->d_ctl[b];
     uint32_t words[kChainCtlHead * kChainCtlStride];
     ST_HIP(hipMemcpy(words, ctl, sizeof(words), hipMemcpyDeviceToHost));
     // (the counts wrap at 2^32, all alike)
@@ -557,7 +581,7 @@ extern "C" st_status st_chain_aborted(st_chain* chain, int32_t* aborted) {
   }
   if (lost) {
     // an abandoned pass has left its queue head, its sequence counters and some split-K arrival counters anywhere
-    ST_HIP(hipMemset(chain->d_ctl[0], 0, ((size_t)chain->ctl_slots * kChainCtlStride + kChainRankWords) * 4 * 2));
+    ST_HIP(hipMemset(chain->d_ctl[0], 0, ((size_t)chain->ctl_slots * kChainCtlStride + kChainRankWords) * 4 * kChainCtlBlocks));
     if (chain->counters_bytes) ST_HIP(hipMemset(chain->d_counters, 0, chain->counters_bytes));
     ST_HIP(hipDeviceSynchronize());                  // before a run on a stream that does not wait for this one
     *aborted = 1;

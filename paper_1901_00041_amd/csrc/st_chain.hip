@@ -4,6 +4,7 @@
 
 #include "st_chain_args.h"
 #include "st_internal.h"
+#include "st_launch.h"
 
 namespace st {
 
@@ -56,6 +57,21 @@ int launch_chain(uint32_t needs, const TenantDev* ops_dev, const st_work_item* i
   for (int x = 0; x <= kNumXCDs; ++x) a.prefetch_begin[x] = prefetch_dev ? prefetch_begin[x] : 0u;
   void* addresses[] = {(void*)&a, nullptr};
   return (int)hipLaunchKernel(kernel_for(needs, n_queues > 1u), dim3((unsigned)grid), dim3(kThreads), addresses, 0, (hipStream_t)stream);
+}
+
+// What a captured run needs to start from: its control block as the run before would have left it, and no flag set.
+__global__ __launch_bounds__(256) void st_chain_reset_kernel(uint32_t* ctl, uint32_t ctl_slots, uint32_t* item_flags, uint32_t n_flags) {
+  const uint32_t first = blockIdx.x * 256u + threadIdx.x, step = gridDim.x * 256u;
+  for (uint32_t i = first; i < ctl_slots; i += step)
+    if (i == (uint32_t)kChainCtlAbort || i >= (uint32_t)kChainCtlHead) ctl[i * kChainCtlStride] = 0u;
+  for (uint32_t i = first; i < (uint32_t)kChainRankWords; i += step) ctl[ctl_slots * kChainCtlStride + i] = 0u;
+  for (uint32_t i = first; i < n_flags; i += step) item_flags[i] = 0u;
+}
+
+int launch_chain_reset(uint32_t* ctl, uint32_t ctl_slots, uint32_t* item_flags, uint32_t n_flags, void* stream) {
+  const uint32_t n = n_flags > (uint32_t)kChainRankWords ? n_flags : (uint32_t)kChainRankWords;      // (at most 4116 slots)
+  const unsigned blocks = (n + 255u) / 256u < 256u ? (n + 255u) / 256u : 256u;
+  return (int)launch(st_chain_reset_kernel, blocks, 256, stream, ctl, ctl_slots, item_flags, n_flags);
 }
 
 }  // namespace st

@@ -143,6 +143,10 @@ int launch_conv_kernel(const TenantDev* tenants_dev, const st_work_item* items_d
 // kNumXCDs (colbegin_dev: kNumXCDs * 2 * kChainColumns + 1 column boundaries in device memory; XCD x's exclusive
 // columns are x * 2 * kChainColumns + [0, kChainColumns), its shared ones follow).  item_flags / run_number: the
 // per-item completion flags and this run's number (queues per XCD only; else nullptr / anything).
+// A run that is captured into a graph has a block and a number of its own (kChainCapturedRun, which no other run gets);
+// launch_chain_reset goes ahead of it and clears what the run before would have, and every flag.
+constexpr int kChainCtlBlocks = 4;
+constexpr uint32_t kChainCapturedRun = 0xffffffffu;
 constexpr int kChainCtlStride = 64;
 constexpr int kChainCtlLost = 0, kChainCtlAbort = 1, kChainCtlDone = 2, kChainCtlStarted = 3, kChainCtlHead = 4, kChainCtlSeq = 4 + 2 * kNumXCDs;
 constexpr int kChainRankWords = kNumXCDs * 256;   // arrival counts per (XCD, compute unit key), dense, after the slots
@@ -159,6 +163,7 @@ int chain_max_workgroups(int* out_workgroups, int* out_xcds);
 int launch_chain(uint32_t needs, const TenantDev* ops_dev, const st_work_item* items_dev, uint32_t n_items, const uint32_t* colbegin_dev, const ChainDep* deps_dev, uint32_t n_queues, const ChainPrefetch* prefetch_dev,
                  const uint32_t* prefetch_begin, uint32_t* ctl, uint32_t* ctl_other, uint32_t ctl_slots, uint32_t* item_flags, uint32_t run_number,
                  uint32_t spin_limit_ticks, uint32_t flags, int grid, void* stream, uint64_t* prof_dev);
+int launch_chain_reset(uint32_t* ctl, uint32_t ctl_slots, uint32_t* item_flags, uint32_t n_flags, void* stream);
 int launch_empty(void* stream);
 // Allocation-free path: device address of the current GPU's fixed scratch array (looked up on first use per device),
 // host bytes -> device through kernel arguments (sizes rounded up to 16 bytes; dst 16-byte aligned), and a zero fill.

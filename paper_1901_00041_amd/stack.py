@@ -406,11 +406,6 @@ class ResNetStack:
         if policy == "fused_chain":
             if getattr(self, "chain", None) is None:
                 self.build_chain()
-            if self.chain_parts > 1 and self.torch.cuda.is_current_stream_capturing():
-                # a graph replays launches with the arguments they were captured with; a persistent launch needs a new run number
-                # each time, launches per layer do not
-                self.run("fused", stream)
-                return
             self.chain.run(stream)
             return
         if policy.startswith("fused_groups"):

@@ -61,7 +61,7 @@ def test_nothing_is_divided_unasked(n_tenants, batch):
 
 
 def test_divided_chain_in_a_graph():
-    """A captured pass of a divided chain can be replayed: launches per layer are what the graph holds."""
+    """A captured pass of a divided chain can be replayed."""
     import torch
     from paper_1901_00041_amd.stack import ResNetStack
     stack = ResNetStack(n_tenants=4, batch=2, image=64, seeded_weights=False, plan_opts=sc.plan_opts(tile_cfg=4, split_k=1))
