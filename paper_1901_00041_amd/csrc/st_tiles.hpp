@@ -653,55 +653,75 @@ __device__ __forceinline__ bool split_k_reduce(ConstOp& T, const st_work_item it
       return false;
     }
     // Sum the slices in index order.  Loads are issued in batches (GB groups x SB slices) so that the device-coherent reads, each
-    // a trip to memory, overlap.  Tiles of 32x32 blocks load only the slices there are, and take the own one from the registers
-    // it is still in: a load that is out of range still costs the compute unit's 16 clocks, and 64x64 in three slices had 24 of
-    // 32 to spare (20 fp32 layers 18.37 us -> 18.15).  The small tiles have few loads, and the branches cost more than they
-    // do where the slices come from memory (four 3x3 layers of batch 1, 16x64 in four: 7.21 us, 7.36 with branches), not where
-    // they come from the L2 (eight networks of batch 1 as a chain 321.3 -> 319.6).  Nor in the kernel for everything, which is short of
-    // scalar registers (24 layers off every round number 26.35 us -> 26.55).
+    // a trip to memory, overlap.  A load that is out of range still costs the compute unit's 16 clocks, so tiles of 32x32 blocks
+    // with fewer slices than a batch holds load those there are (`pick`), and take the own one from the registers it is still in.
+    // us, without and with, three 3x3 layers 256 -> 256 at 14x14: bf16 64x64 in 2, 4, 6, 7 slices 8.1, 7.7, 9.95, 9.9 -> 7.6, 7.3,
+    // 9.35, 9.4; 64x128 in 2, 3 10.9, 10.65 -> 10.3, 10.05; fp32 1 to 2 %; 20 fp32 layers in 3 18.65 -> 17.95.  A full batch has one
+    // load to spare and a branch for each (four batches in flight, their 7x7 layer 64x64 in 8 slices, 25.5 -> 25.8; 64x128 in 5 to 7, only
+    // the rest picked from, 11.05 -> 11.25), so more slices are loaded in whole batches.  The small tiles have few loads, and the branches cost more than they
+    // do where the slices come from memory (four 3x3 layers of batch 1, 16x64 in four: 7.21 us, 7.36 with branches), not where they
+    // come from the L2 (eight networks of batch 1 as a chain 321.3 -> 319.6).  Chains pick in every batch: a second loop makes them spill
+    // (320 -> 338).  Nor in the kernel for everything, which is short of scalar registers (24 layers off every round number 26.35 -> 26.55).
     constexpr int NGRP = BM * BN * NG;
     constexpr int GB = NGRP < 4 ? NGRP : 4;
     constexpr int SB = (NGRP > 4) ? 4 : 8;   // at most 32 partial vectors (128 registers) in flight
     static_assert(NGRP % GB == 0, "group batching");
-    constexpr bool kPick = (MF == 32 && !POL::kAnyFilters) || POL::kOneL2;
     const int split = T.split_k, mine = (int)it.k_split_idx;
+    auto sum_slices = [&](auto PICK, auto ONE_BATCH) {
+      constexpr bool pick = decltype(PICK)::value, one = decltype(ONE_BATCH)::value;       // one: split < SB
+      constexpr int SL = one ? SB - 1 : SB;
 #pragma unroll
-    for (int g0 = 0; g0 < NGRP; g0 += GB) {
-      f32x4 sum[GB];
+      for (int g0 = 0; g0 < NGRP; g0 += GB) {
+        f32x4 sum[GB];
 #pragma unroll
-      for (int gg = 0; gg < GB; ++gg) sum[gg] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int s0 = 0; s0 < split; s0 += SB) {
-        f32x4 part[SB][GB];
+        for (int gg = 0; gg < GB; ++gg) sum[gg] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < (one ? 1 : split); s0 += SB) {
+          f32x4 part[SB][GB];
 #pragma unroll
-        for (int ss = 0; ss < SB; ++ss) {
-          if (!kPick || (s0 + ss < split && s0 + ss != mine)) {
+          for (int ss = 0; ss < SL; ++ss) {
+            if (!pick || (s0 + ss < split && s0 + ss != mine)) {
 #pragma unroll
-            for (int gg = 0; gg < GB; ++gg) {
-              const uint32_t voff = kPick || s0 + ss < split ? (uint32_t)(((g0 + gg) * kThreads + tid) * 16) : kInvalidOffset;
-              part[ss][gg] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (s0 + ss) * (int)kTileBytes, kAuxDeviceCoherent));
-            }
-          } else {
+              for (int gg = 0; gg < GB; ++gg) {
+                const uint32_t voff = pick || s0 + ss < split ? (uint32_t)(((g0 + gg) * kThreads + tid) * 16) : kInvalidOffset;
+                part[ss][gg] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (s0 + ss) * (int)kTileBytes, kAuxDeviceCoherent));
+              }
+            } else {
 #pragma unroll
-            for (int gg = 0; gg < GB; ++gg) {
-              const int grp = g0 + gg, i = grp / (BN * NG), j = (grp / NG) % BN, g = grp % NG;
+              for (int gg = 0; gg < GB; ++gg) {
+                const int grp = g0 + gg, i = grp / (BN * NG), j = (grp / NG) % BN, g = grp % NG;
 #pragma unroll
-              for (int e = 0; e < 4; ++e) part[ss][gg][e] = s0 + ss == mine ? acc[i][j][4 * g + e] : 0.f;
+                for (int e = 0; e < 4; ++e) part[ss][gg][e] = s0 + ss == mine ? acc[i][j][4 * g + e] : 0.f;
+              }
             }
           }
+#pragma unroll
+          for (int ss = 0; ss < SL; ++ss)
+#pragma unroll
+            for (int gg = 0; gg < GB; ++gg) sum[gg] += part[ss][gg];
         }
 #pragma unroll
-        for (int ss = 0; ss < SB; ++ss)
+        for (int gg = 0; gg < GB; ++gg) {
+          const int grp = g0 + gg;
+          const int i = grp / (BN * NG), j = (grp / NG) % BN, g = grp % NG;
 #pragma unroll
-          for (int gg = 0; gg < GB; ++gg) sum[gg] += part[ss][gg];
+          for (int e = 0; e < 4; ++e) acc[i][j][4 * g + e] = sum[gg][e];
+        }
       }
-#pragma unroll
-      for (int gg = 0; gg < GB; ++gg) {
-        const int grp = g0 + gg;
-        const int i = grp / (BN * NG), j = (grp / NG) % BN, g = grp % NG;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[i][j][4 * g + e] = sum[gg][e];
+    };
+    constexpr std::true_type yes;
+    constexpr std::false_type no;
+    constexpr bool in_chain = POL::kActAux == kAuxDeviceCoherent;
+    if constexpr (POL::kOneL2 || (in_chain && MF == 32)) {
+      sum_slices(yes, no);
+      return true;
+    }
+    if constexpr (MF == 32 && !POL::kAnyFilters) {
+      if (split < SB) {
+        sum_slices(yes, yes);
+        return true;
       }
     }
+    sum_slices(no, no);
   }
   return true;
 }
