@@ -64,7 +64,8 @@ typedef struct st_conv_desc {
   const void* x;         /* device, N*H*W*C elements of in_dtype                         */
   const void* w;         /* device, K*R*S*C elements of in_dtype                         */
   void* y;               /* device, N*P*Q*K elements of out_dtype, written               */
-  const void* residual;  /* device, same shape and dtype as y; required iff ST_EPI_RESIDUAL */
+  const void* residual;  /* device, same shape and dtype as y; required iff ST_EPI_RESIDUAL.  May be y itself (the */
+                         /* layer is then added to y in place, anew on every run), but not overlap it otherwise */
 } st_conv_desc;
 
 /* Planner knobs; pass NULL for defaults.  Zero-initialise, then set what you need. */

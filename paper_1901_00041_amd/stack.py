@@ -70,13 +70,16 @@ def _share(batch: int, parts: int) -> List[int]:
 
 def _reuse_buffers(steps: List[synth.Step]) -> List[synth.Step]:
     """The steps on as few bytes as they can do with: a block adds to its shortcut in place, the stages' block outputs
-    alternate between two buffers, one of them the stem's.  The network's output has a buffer of its own, exactly as large
-    as it: one tensor over the batch, also where parts of the batch run as sequences of their own (build_chain) and keep apart in every
-    other buffer.
+    alternate between two buffers, one of them the stem's.  (So a block's third step has dst == res: the shortcut is gone afterwards,
+    and the step repeated alone adds again; a pass is repeated whole.)  The network's output has a buffer of its own, exactly as
+    large as it: one tensor over the batch, also where parts of the batch run as sequences of their own (build_chain) and keep
+    apart in every other buffer.
     Fewer bytes stay in the caches longer.  us per pass with two buffers for the blocks of a stage and one for the projections, and so:
     8 tenants of batch 1 as a chain 327 -> 322, of batch 8 1074 -> 1048 (a buffer for every step, which the chain's tests use:
     346 and 1098); 4 of batch 4 as layer launches 526 -> 522, or 522 -> 475 where passes over the same tensors follow each other
-    and find what the memory-side cache kept (492 in place alone)."""
+    and find what the memory-side cache kept (492 in place alone).  Other stacks as layer launches, with what else changed
+    in the tiles meanwhile: 1 tenant of batch 8 399 -> 392, 8 of batch 1 427 -> 422, of batch 4 750 -> 747, 2 of batch 1 312 -> 307; 1 of batch 1 249
+    and 2 of batch 2 350 as before; 5 of batch 1 394 -> 396, 4 of batch 2 at 160x160 359 -> 361."""
     at, out = {0: 0}, []
     for st in steps:
         src, res = at[st.src], at[st.res] if st.res is not None else None
@@ -204,7 +207,8 @@ class ResNetStack:
 
     # ---- execution -----------------------------------------------------------------------------------
     def run_group(self, gi: int, stream=None) -> None:
-        """One fused launch over every tenant's descriptors of every step of group gi."""
+        """One fused launch over every tenant's descriptors of every step of group gi.  A step with a residual adds to its
+        shortcut in place (_reuse_buffers): run again without the steps before it, it adds once more."""
         sc.st_conv_run(self.group_plans[gi], stream)
         for i in self.groups[gi]:
             st = self.steps[i]
@@ -220,6 +224,7 @@ class ResNetStack:
         return self._solo[i]
 
     def run_step(self, i: int, policy: str = "fused", stream=None) -> None:
+        """Step i of every tenant; a step with a residual adds in place, as in run_group."""
         st = self.steps[i]
         if policy == "fused":
             sc.st_conv_run(self.plans[i], stream)
