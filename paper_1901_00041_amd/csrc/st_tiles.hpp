@@ -769,15 +769,20 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = (int)it.tile_m * MT;
   const int n0 = (int)it.tile_n * NT;
+  // Launches of fp32 layers alone: what the first loads do not need is read and worked out behind them.  us: 20 3x3 layers
+  // 128 -> 128 at 16x16 18.10 -> 17.85, 30 1x1 layers 256 -> 256 11.46 -> 11.14, 13 of 136 -> 512 at 8x8 with a residual 6.97 -> 6.76, four 3x3
+  // of 512 at 7x7 17.40 -> 17.08.  Others lose by it or gain nothing: 24 layers off every round number 26.05 -> 26.25, 32 unlike tenants
+  // 78.6 -> 79.0, four networks of batch 4 as layer launches 511.5 -> 514.4, eight of batch 8 as a chain 1036 -> 1038.
+  constexpr bool late = DT == ST_DT_F32 && std::is_same_v<POL, PlainActs>;
   // everything the K loop needs of the record, read once (the loads to LDS count as writes to any memory)
-  const int C = T.C, W = T.W, WC = W * C, H = T.H, R = T.R, S = T.S, SC = S * C;
+  const int C = T.C, W = T.W, WC = W * C, H = T.H, R = T.R, S = T.S, SC = S * C, step_dk0 = late ? 0 : T.step_dk, step_dr0 = late ? 0 : T.step_dr;
   const u32x4 rx = rsrc_words(T.x, T.x_bytes), rw = rsrc_words(T.w, T.w_bytes);
 
   // K-step range of this work item
   const int ks_begin = (int)it.k_split_idx * T.k_steps_per_split;
   int ks_end = ks_begin + T.k_steps_per_split;
   if (ks_end > T.k_steps) ks_end = T.k_steps;
-  const int main_steps = PIECES ? T.step_dr : ks_end;      // steps of whole vectors (of the layer), before those of left-over channels
+  const int main_steps = PIECES ? (late ? T.step_dr : step_dr0) : ks_end;      // steps of whole vectors (of the layer), before those of left-over channels
   const int nsteps = (PIECES && main_steps < ks_end ? main_steps : ks_end) - ks_begin;
 
   // staging: which row of an instruction's block of RPI rows, and which 16-byte chunk of it, this lane fetches
@@ -829,6 +834,7 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
       b_lds[u] = (uint32_t)((rbase ^ (u * SUBB)) + MT * KB + wn0 * KB);
     }
   };
+  if constexpr (!late) operand_addresses();
 
   // PIECES: two sums of each block, one over even and one over odd sub-steps.  Layers of this form are often split less than
   // with gathered tiles, and a longer chain of fp32 additions errs more (43 such layers against 64 bits, mean relative error
@@ -861,12 +867,10 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
   // A 16-bit residual tile is loaded into the stage of the last step but one as soon as that is free (no later loads
   // are waited for by count), and added in the epilogue.
   int res_lds = -1;
-  auto place_residual = [&]() {
-    if constexpr (DT != ST_DT_F32 && !PIECES) {
-      if ((T.epilogue & ST_EPI_RESIDUAL) != 0u && T.out_dtype != ST_DT_F32 && (T.K & 7) == 0 && T.split_k == 1)
-        res_lds = (nsteps == 1 ? 1 : (nsteps - 2) % ST) * kStage;
-    }
-  };
+  if constexpr (DT != ST_DT_F32 && !PIECES) {
+    if ((T.epilogue & ST_EPI_RESIDUAL) != 0u && T.out_dtype != ST_DT_F32 && (T.K & 7) == 0 && T.split_k == 1)
+      res_lds = (nsteps == 1 ? 1 : (nsteps - 2) % ST) * kStage;
+  }
   // The reduction index k = (r*S + s)*C + c is walked in one of three orders (planner's k_order):
   //   kOrderTaps      ascending k; any C.  Every lane keeps the position of its own vector: filter row kr and element
   //                   kk = s*C + c inside it, which is also the element offset inside the image row, from the patch.
@@ -883,7 +887,8 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
   auto k_loop = [&](auto ORDER) {
     constexpr int order = decltype(ORDER)::value;
     constexpr uint32_t kTop = 0x80000000u;
-    const int step_dk = order == kOrderTaps || order == kOrderPieces ? T.step_dk : 0, step_dr = order == kOrderTaps ? T.step_dr : 0;
+    const int step_dk = !late ? step_dk0 : order == kOrderTaps || order == kOrderPieces ? T.step_dk : 0;
+    const int step_dr = !late ? step_dr0 : order == kOrderTaps ? T.step_dr : 0;
     int kr = 0, kk = 0, koff = 0;          // kOrderTaps: per lane
     int s_left = 0, r_left = 0;            // kOrderChannels: taps left in this filter row, rows left after it
     uint32_t a_soff = 0u, b_soff;          // byte offsets of the step; kOrderChannels: a_soff is added per lane (it may be negative)
@@ -1011,10 +1016,7 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
       static_for<AW + BW>([&](auto I) { issue_one(I, s * kStage); });
       advance();
     }
-    // What the loads do not need is worked out behind them (20 fp32 layers 18.70 us -> 18.43, four 3x3 layers of batch 1 7.26 ->
-    // 7.22, 24 layers off every round number 26.3 -> 26.15, four networks of batch 4 as layer launches 517.4 -> 515.6).
-    operand_addresses();
-    place_residual();
+    if constexpr (late) operand_addresses();
     if (res_lds >= 0 && nsteps == 1) {          // a one-step K loop: the residual follows the operands at once
       stage_residual<MT, NT, POL>(T, m0, n0, wave, lane, lds0 + (uint32_t)res_lds);
       wait_loads_barrier<kResidualLoads<MT, NT>>();
@@ -1085,12 +1087,12 @@ __device__ __forceinline__ void conv_tile(ConstOp& T, const st_work_item it, cha
   if constexpr (PIECES) {
     if (nsteps > 0) k_loop(std::integral_constant<int, kOrderPieces>{});
     else {
-      operand_addresses();
+      if constexpr (late) operand_addresses();
       if (prof && tid == 0) prof[1] = __builtin_readcyclecounter();
     }
     // The channels left over: a vector per tap, the last one inside its channels, of which those that the whole vectors have are
     // cleared in both operands; 16 bytes at a time to where load_to_lds would have put them.
-    const int left = C - T.step_dk, taps = R * S;
+    const int left = C - (late ? T.step_dk : step_dk0), taps = R * S;
     uint32_t keep[4];
 #pragma unroll
     for (int d = 0; d < 4; ++d)
